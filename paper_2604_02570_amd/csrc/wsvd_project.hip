@@ -25,7 +25,6 @@ struct ProjectParams {
   int* err_word;
   int Hkv, E, t_cap, n_tok, seq0;   // direct kernel: grid z = sequence - seq0
   int n_cg, tg_seq, n_tg;           // staged kernel: channel groups, token groups per sequence and in all
-  int i4;                           // int4 latents (rank 32): asymmetric codes, two rows per value byte
   // paged cache only (else null): codes / meta are pools of n_pages pages, a page = page_rows rows of every kv head in the
   // layout of a contiguous plane; block_table [B][max_pages]
   const int* block_table;
@@ -53,110 +52,119 @@ WSVD_DEV ProjRow project_row(const ProjectParams& p, int pl, int seq, int kv, in
   return r;
 }
 
-// per token and head: symmetric int8 (the latent quantiser's rule), then the stores.  acc[c][tt] = channel tile ct0 + c
-// x token tile tb * TT + tt of this wave, in the 32 x 32 accumulator order.
-template <int R, int CT, int TT>
+// One token's row of one head and plane: the 16 channels of every 32 that this lane holds in a[], the rest in its partner
+// half.  Symmetric int8 (the latent quantiser's rule), then the stores.
+template <int RT>
+WSVD_DEV void store_row_i8(const ProjectParams& p, const v16f (&a)[RT], int pl, int seq, int kv, int t, bool on) {
+  constexpr int R = 32 * RT;
+  const int g2 = (threadIdx.x & 63) >> 5;
+  float m = 0.f;
+#pragma unroll
+  for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+    for (int v = 0; v < 16; v++) m = fmaxf(m, fabsf(a[rt][v]));
+  m = fmaxf(m, __shfl_xor(m, 32));
+  uint16_t sh = 0x3C00u;
+  if (m != 0.f) sh = guard_scale_f16(m / 127.0f);
+  const float sc = f16_bits_to_f32(sh);
+  if (!on) return;
+  const ProjRow pr = project_row(p, pl, seq, kv, t, R);
+  if (!pr.ok) return;
+#pragma unroll
+  for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+    for (int m4 = 0; m4 < 4; m4++) {
+      uint32_t pk = 0;
+      int q[4];
+#pragma unroll
+      for (int jj = 0; jj < 4; jj++) {
+        q[jj] = (int)fminf(fmaxf(__builtin_rintf(a[rt][4 * m4 + jj] / sc), -127.f), 127.f);
+        pk |= ((uint32_t)q[jj] & 0xFFu) << (8 * jj);
+      }
+      const int j0 = 32 * rt + 8 * m4 + 4 * g2;                         // channels j0 .. j0 + 3
+      if (pl == 0) *(uint32_t*)(pr.plane + i8_k_offset(pr.t, j0, R)) = pk;
+      else {
+#pragma unroll
+        for (int jj = 0; jj < 4; jj++) pr.plane[i8_v_offset(pr.t, j0 + jj, R)] = (uint8_t)q[jj];
+      }
+    }
+  if (g2 == 0) p.meta[pl][pr.meta] = sh;
+}
+
+// The same for int4 (rank 32: one channel tile per head): the rule of quantize_row_i4; K bytes pair dims (2 adjacent
+// registers), V bytes pair rows t, t ^ 1 = this lane and its neighbour (the caller guarantees an even start row, so row
+// parity = lane parity).  next_on: the neighbour's row is stored too.
+WSVD_DEV void store_row_i4(const ProjectParams& p, const v16f& a, int pl, int seq, int kv, int t, bool on, bool next_on) {
+  const int lane = threadIdx.x & 63, g2 = lane >> 5;
+  float lo = 0.f, hi = 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; v++) { lo = fminf(lo, a[v]); hi = fmaxf(hi, a[v]); }
+  lo = fminf(lo, __shfl_xor(lo, 32)); hi = fmaxf(hi, __shfl_xor(hi, 32));
+  uint16_t sh = 0x3C00u;
+  float z = 0.f;
+  const bool flat = (hi == lo);
+  if (!flat) sh = guard_scale_f16((hi - lo) / 15.0f);
+  const float sc = f16_bits_to_f32(sh);
+  if (!flat) z = fminf(fmaxf(__builtin_rintf(-lo / sc), 0.f), 15.f);
+  const int zi = (int)z;
+  ProjRow pr = {nullptr, 0, t, false};
+  if (on) { pr = project_row(p, pl, seq, kv, t, 16); on = pr.ok; }
+#pragma unroll
+  for (int m4 = 0; m4 < 4; m4++) {
+    int q[4];
+#pragma unroll
+    for (int jj = 0; jj < 4; jj++) {
+      const float v = fminf(fmaxf(__builtin_rintf(a[4 * m4 + jj] / sc), -64.f), 64.f);
+      const int qq = (int)v + zi;
+      q[jj] = qq < 0 ? 0 : (qq > 15 ? 15 : qq);
+    }
+    const int j0 = 8 * m4 + 4 * g2;                                     // channels j0 .. j0 + 3
+    int nib;
+    if (pl == 0) {
+      if (on) *(uint16_t*)(pr.plane + i4_k_offset(pr.t, j0, &nib)) = (uint16_t)(q[0] | (q[1] << 4) | (q[2] << 8) | (q[3] << 12));
+    } else {
+#pragma unroll
+      for (int jj = 0; jj < 4; jj++) {
+        const int qn = __builtin_amdgcn_update_dpp(0, q[jj], kDppQuadSwap1, 0xF, 0xF, true);   // the neighbour row's code
+        if (on && (lane & 1) == 0) pr.plane[i4_v_offset(pr.t, j0 + jj, &nib)] = (uint8_t)(q[jj] | ((next_on ? qn : 0) << 4));
+      }
+    }
+  }
+  if (on && g2 == 0) *(uint32_t*)&p.meta[pl][pr.meta * 2] = (uint32_t)sh | ((uint32_t)f32_to_f16_bits_rne((float)zi) << 16);
+}
+
+// acc[c][tt] = channel tile ct0 + c x token tile tb * TT + tt of this wave, in the 32 x 32 accumulator order.  The format
+// is a template parameter and no loop leaves early: every index into acc has to be a constant after unrolling.  (With
+// both formats in one body the loops stayed rolled, acc was indexed at run time and all 256 accumulators of a lane lived
+// in scratch memory: 10.2 ms for 16 x 2048 tokens against 0.5 ms.)
+template <int R, int CT, int TT, bool I4>
 WSVD_DEV void project_store(const ProjectParams& p, v16f (&acc)[CT][TT], int ct0, int tb, int seq, int n0) {
   constexpr int RT = R / 32;
-  const int lane = threadIdx.x & 63, n = lane & 31, g2 = lane >> 5;
+  static_assert(!I4 || R == 32, "int4 latents have rank 32");
+  const int n = threadIdx.x & 31;
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
 #pragma unroll
   for (int h = 0; h < CT / RT; h++) {
     const int ct = ct0 + h * RT;
-    if (ct >= tiles) break;
-    const int pl = ct / tiles_plane, kv = (ct % tiles_plane) / RT;
-    const size_t ph = (size_t)seq * p.Hkv + kv;
-    uint8_t* plane = p.codes[pl] + ph * (size_t)p.t_cap * R;
+    const int pl = ct / tiles_plane, kv = (ct % tiles_plane) / RT;      // (wave-uniform)
 #pragma unroll
     for (int tt = 0; tt < TT; tt++) {
       const int tok = (tb * TT + tt) * 32 + n;                          // this lane's token of the prompt
       const int t = n0 + tok;                                           // and its cache row
-      if constexpr (R == 32) {
-        if (p.i4) {
-          // int4 (rank 32: one channel tile per head): the rule of quantize_row_i4 on the 16 channels this lane holds
-          // and the 16 of its partner half; K bytes pair dims (2 adjacent registers), V bytes pair rows t, t ^ 1 = this
-          // lane and its neighbour (the caller guarantees an even start row, so row parity = lane parity)
-          float lo = 0.f, hi = 0.f;
+      const bool on = ct < tiles && tok < p.n_tok && n0 >= 0 && t < p.t_cap;
+      if constexpr (I4) {
+        store_row_i4(p, acc[h][tt], pl, seq, kv, t, on && (n0 & 1) == 0, tok + 1 < p.n_tok && t + 1 < p.t_cap);
+      } else {
+        v16f a[RT];
 #pragma unroll
-          for (int v = 0; v < 16; v++) { lo = fminf(lo, acc[h][tt][v]); hi = fmaxf(hi, acc[h][tt][v]); }
-          lo = fminf(lo, __shfl_xor(lo, 32)); hi = fmaxf(hi, __shfl_xor(hi, 32));
-          uint16_t sh = 0x3C00u;
-          float z = 0.f;
-          const bool flat = (hi == lo);
-          if (!flat) sh = guard_scale_f16((hi - lo) / 15.0f);
-          const float sc = f16_bits_to_f32(sh);
-          if (!flat) z = fminf(fmaxf(__builtin_rintf(-lo / sc), 0.f), 15.f);
-          const int zi = (int)z;
-          bool on = tok < p.n_tok && n0 >= 0 && (n0 & 1) == 0 && t < p.t_cap;
-          ProjRow pr = {p.codes[pl] + ph * (size_t)p.t_cap * 16, ph * p.t_cap + t, t, true};
-          if (p.block_table && on) { pr = project_row(p, pl, seq, kv, t, 16); on = pr.ok; }
-          uint8_t* plane4 = pr.plane;
-          const int tr = pr.t;
-#pragma unroll
-          for (int m4 = 0; m4 < 4; m4++) {
-            int q[4];
-#pragma unroll
-            for (int jj = 0; jj < 4; jj++) {
-              const float v = fminf(fmaxf(__builtin_rintf(acc[h][tt][4 * m4 + jj] / sc), -64.f), 64.f);
-              const int qq = (int)v + zi;
-              q[jj] = qq < 0 ? 0 : (qq > 15 ? 15 : qq);
-            }
-            const int j0 = 8 * m4 + 4 * g2;                             // channels j0 .. j0 + 3
-            if (pl == 0) {
-              int nib;
-              if (on) *(uint16_t*)(plane4 + i4_k_offset(tr, j0, &nib)) = (uint16_t)(q[0] | (q[1] << 4) | (q[2] << 8) | (q[3] << 12));
-            } else {
-#pragma unroll
-              for (int jj = 0; jj < 4; jj++) {
-                const int qn = __builtin_amdgcn_update_dpp(0, q[jj], kDppQuadSwap1, 0xF, 0xF, true);   // the neighbour row's code
-                const bool nb_on = tok + 1 < p.n_tok && t + 1 < p.t_cap;
-                int nib;
-                if (on && (n & 1) == 0) plane4[i4_v_offset(tr, j0 + jj, &nib)] = (uint8_t)(q[jj] | ((nb_on ? qn : 0) << 4));
-              }
-            }
-          }
-          if (on && g2 == 0) *(uint32_t*)&p.meta[pl][pr.meta * 2] = (uint32_t)sh | ((uint32_t)f32_to_f16_bits_rne((float)zi) << 16);
-          continue;
-        }
+        for (int rt = 0; rt < RT; rt++) a[rt] = acc[h * RT + rt][tt];
+        store_row_i8<RT>(p, a, pl, seq, kv, t, on);
       }
-      float a = 0.f;
-#pragma unroll
-      for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-        for (int v = 0; v < 16; v++) a = fmaxf(a, fabsf(acc[h * RT + rt][tt][v]));
-      a = fmaxf(a, __shfl_xor(a, 32));
-      uint16_t sh = 0x3C00u;
-      if (a != 0.f) sh = guard_scale_f16(a / 127.0f);
-      const float sc = f16_bits_to_f32(sh);
-      if (tok >= p.n_tok || n0 < 0 || t >= p.t_cap) continue;
-      ProjRow pr = {plane, ph * p.t_cap + t, t, true};
-      if (p.block_table) { pr = project_row(p, pl, seq, kv, t, R); if (!pr.ok) continue; }
-      uint8_t* const pln = pr.plane;
-      const int tr = pr.t;
-#pragma unroll
-      for (int rt = 0; rt < RT; rt++)
-#pragma unroll
-        for (int m4 = 0; m4 < 4; m4++) {
-          uint32_t pk = 0;
-          int q[4];
-#pragma unroll
-          for (int jj = 0; jj < 4; jj++) {
-            q[jj] = (int)fminf(fmaxf(__builtin_rintf(acc[h * RT + rt][tt][4 * m4 + jj] / sc), -127.f), 127.f);
-            pk |= ((uint32_t)q[jj] & 0xFFu) << (8 * jj);
-          }
-          const int j0 = 32 * rt + 8 * m4 + 4 * g2;                     // channels j0 .. j0 + 3
-          if (pl == 0) *(uint32_t*)(pln + i8_k_offset(tr, j0, R)) = pk;
-          else {
-#pragma unroll
-            for (int jj = 0; jj < 4; jj++) pln[i8_v_offset(tr, j0 + jj, R)] = (uint8_t)q[jj];
-          }
-        }
-      if (g2 == 0) p.meta[pl][pr.meta] = sh;
     }
   }
 }
 
-template <int R, int CT, int TT, int WC, int ST = 3>
+template <int R, int CT, int TT, int WC, bool I4 = false, int ST = 3>
 __global__ __launch_bounds__(256) void k_prefill_project(ProjectParams p) {
   constexpr int RT = R / 32;
   static_assert(CT % RT == 0, "a head's channels stay in one wave");
@@ -209,7 +217,7 @@ __global__ __launch_bounds__(256) void k_prefill_project(ProjectParams p) {
       }
     }
   }
-  project_store<R, CT, TT>(p, acc, ct0, tb, seq, n0);
+  project_store<R, CT, TT, I4>(p, acc, ct0, tb, seq, n0);
 }
 
 // The same projection with both operands staged through LDS: a workgroup of 4 waves (2 x 2, each 4 x 4 tiles) owns
@@ -222,7 +230,7 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int kProjKC = 64, kProjXRow = 144;
 constexpr int kProjABytes = 8 * 4 * 1024, kProjXBytes = 256 * kProjXRow, kProjStage = kProjABytes + kProjXBytes;
 
-template <int R, int WAVES>
+template <int R, int WAVES, bool I4>
 __global__ __launch_bounds__(64 * WAVES) void k_prefill_project_lds(ProjectParams p) {
   extern __shared__ __align__(16) uint8_t proj_lds[];
   constexpr int RT = R / 32, CT = 4, TT = 16 / WAVES;                   // 2 x (WAVES / 2) waves, each 4 x TT tiles
@@ -325,7 +333,7 @@ __global__ __launch_bounds__(64 * WAVES) void k_prefill_project_lds(ProjectParam
   }
   const int ct0 = (cg * 2 + wc) * CT, tb = by * (8 / TT) + wt;
   if (ct0 >= tiles || tb * 32 * TT >= p.n_tok) return;
-  project_store<R, CT, TT>(p, acc, ct0, tb, seq, n0);
+  project_store<R, CT, TT, I4>(p, acc, ct0, tb, seq, n0);
 }
 
 // after the projection: the lengths move on by the rows that fitted (one thread per sequence)
@@ -341,11 +349,24 @@ __global__ void k_prefill_bump(int* seq_lens, int seq0, int n_seq, int n_tok, in
   if (n0 < 0 || n0 + n_tok > t_cap) atomicExch(err_word, (int)WSVD_E_CAPACITY);
 }
 
-template <int R, int CT, int TT, int WC, int ST = 3>
+template <int R, int CT, int TT, int WC, bool I4 = false>
 void launch_project(const ProjectParams& p, int n_seq, hipStream_t s) {
   const int tiles = 2 * p.Hkv * (R / 32), tok_wg = 32 * TT * (4 / WC);
   dim3 grid((unsigned)((tiles + WC * CT - 1) / (WC * CT)), (unsigned)((p.n_tok + tok_wg - 1) / tok_wg), (unsigned)n_seq);
-  hipLaunchKernelGGL((k_prefill_project<R, CT, TT, WC, ST>), grid, dim3(256), 0, s, p);
+  hipLaunchKernelGGL((k_prefill_project<R, CT, TT, WC, I4>), grid, dim3(256), 0, s, p);
+}
+
+template <int R, int WAVES, bool I4 = false>
+hipError_t launch_project_lds(const ProjectParams& p, hipStream_t s) {
+  static bool raised = false;             // the kernel's limit of dynamic LDS, raised once per instantiation
+  const size_t lds = 2 * (size_t)kProjStage;
+  if (!raised) {
+    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_lds<R, WAVES, I4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    raised = true;
+  }
+  hipLaunchKernelGGL((k_prefill_project_lds<R, WAVES, I4>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(64 * WAVES), lds, s, p);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -366,7 +387,6 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   p.seq_lens = cache.seq_lens; p.err_word = ctx->err_word;
   p.Hkv = d.n_kv_heads; p.E = d.d_model; p.t_cap = d.t_cap; p.n_tok = n_tok;
   p.n_cg = p.tg_seq = p.n_tg = 0;
-  p.i4 = i4 ? 1 : 0;
   p.block_table = nullptr; p.page_rows = p.max_pages = p.n_pages = 0;
   if (paged) { p.block_table = paged->block_table; p.page_rows = paged->page_rows; p.max_pages = paged->max_pages; p.n_pages = paged->n_pages; }
   const int n_seq = seq < 0 ? d.batch : 1;
@@ -377,7 +397,7 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   const bool staged_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
   int shape = ctx->opt.project_shape ? ctx->opt.project_shape : (work >= (1LL << 22) ? (staged_ok ? 1 : 44) : 21);
   if ((shape == 1 || shape == 2) && !staged_ok) shape = 44;
-  if (i4 && (shape == 1 || shape == 2)) shape = 44;      // int4: the direct kernels (the staged one stores int8 rows only)
+  hipError_t e = hipSuccess;
   if (d.rank > 64) {
     // ranks 96 / 128: a wave owns the 3 / 4 channel tiles of one head and 1 or 4 token tiles
     const bool big = work >= (1LL << 22);
@@ -386,22 +406,13 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   } else if (shape == 1 || shape == 2) {
     const int tiles = 2 * p.Hkv * (d.rank / 32);
     p.n_cg = (tiles + 7) / 8; p.tg_seq = (n_tok + 255) / 256; p.n_tg = p.tg_seq * n_seq;
-    dim3 grid((unsigned)(p.n_cg * p.n_tg));
-    const size_t lds = 2 * (size_t)kProjStage;
-    static bool raised[4] = {false, false, false, false};   // the kernels' limit of dynamic LDS, raised once
     const bool w8 = shape == 2;
-    const void* fn = d.rank == 32 ? (w8 ? (const void*)k_prefill_project_lds<32, 8> : (const void*)k_prefill_project_lds<32, 4>)
-                                  : (w8 ? (const void*)k_prefill_project_lds<64, 8> : (const void*)k_prefill_project_lds<64, 4>);
-    const int fi = (d.rank == 64) * 2 + w8;
-    if (!raised[fi]) {
-      hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-      if (e != hipSuccess) return e;
-      raised[fi] = true;
-    }
-    if (d.rank == 32 && !w8) hipLaunchKernelGGL((k_prefill_project_lds<32, 4>), grid, dim3(256), lds, s, p);
-    else if (d.rank == 32) hipLaunchKernelGGL((k_prefill_project_lds<32, 8>), grid, dim3(512), lds, s, p);
-    else if (!w8) hipLaunchKernelGGL((k_prefill_project_lds<64, 4>), grid, dim3(256), lds, s, p);
-    else hipLaunchKernelGGL((k_prefill_project_lds<64, 8>), grid, dim3(512), lds, s, p);
+    if (i4) e = launch_project_lds<32, 4, true>(p, s);
+    else if (d.rank == 32) e = w8 ? launch_project_lds<32, 8>(p, s) : launch_project_lds<32, 4>(p, s);
+    else e = w8 ? launch_project_lds<64, 8>(p, s) : launch_project_lds<64, 4>(p, s);
+  } else if (i4) {
+    if (shape == 44) launch_project<32, 4, 4, 4, true>(p, n_seq, s);
+    else launch_project<32, 2, 1, 4, true>(p, n_seq, s);
   } else if (d.rank == 32) {
     if (shape == 44) launch_project<32, 4, 4, 4>(p, n_seq, s);
     else if (shape == 42) launch_project<32, 4, 2, 4>(p, n_seq, s);
@@ -413,8 +424,8 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
     else if (shape == 24) launch_project<64, 2, 4, 4>(p, n_seq, s);
     else launch_project<64, 2, 1, 4>(p, n_seq, s);
   }
-  hipError_t e = hipGetLastError();
+  if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prefill_bump, dim3((n_seq + 63) / 64), dim3(64), 0, s, cache.seq_lens, p.seq0, n_seq, n_tok, d.t_cap, ctx->err_word, p.i4);
+  hipLaunchKernelGGL(k_prefill_bump, dim3((n_seq + 63) / 64), dim3(64), 0, s, cache.seq_lens, p.seq0, n_seq, n_tok, d.t_cap, ctx->err_word, i4 ? 1 : 0);
   return hipGetLastError();
 }
