@@ -5,16 +5,32 @@
 // whole score / softmax / value loop runs on latents of dimension r instead of keys and values of dimension d.
 //   prologue  Q~^T [r x 32 queries] = B_K q^T                       bf16 MFMA, operands straight from global memory
 //   loop      S^T [32 keys x 32 queries] = C_K Q~^T                 fp16 MFMA: codes are exact in fp16, Q~ is an fp16 pair
-//             online softmax down the columns (a lane owns one query column: running max and sum are per lane)
+//             online softmax down the columns (a lane owns one query column)
 //             U^T [r x 32 queries] += (diag(s_V) C_V)^T P           fp16 MFMA: code * scale and P rounded to fp16 (2^-12
-//                                                                   relative each), P through LDS
+//                                                                   relative each)
 //   epilogue  O^T [d x 32 queries] = B_V^T (U / l)                  bf16 MFMA, U an bf16 pair
-// The loop is bound by the vector ALU (the products are a few per cent of its time), so it is written to spend few
-// vector instructions per score: byte-permute code conversion, no masks on blocks every query sees whole, the
-// accumulator rescaled only when some running maximum moved, single-term fp16 operands for the value product.
-// One wavefront per (sequence, kv head, block of 32 query rows); a query row is a (token, head) pair, token-major, so
-// the G heads that share a kv head share the stream too.  The cache blocks are read in the layout the decode kernels
-// use (a 32-token block of the K plane is a ready-made operand with row = token, one of the V plane with row = dim).
+//
+// The loop is bound by the vector ALU (16 exponentials at half rate are a quarter of it; the products hide behind it only
+// in part, about 10 cycles each remain), so it is laid out to spend few vector instructions per score:
+//   * the QW waves of a key group convert the codes of QW cache blocks to fp16 operands once, one block each, through two
+//     LDS stages, and each attends its own 32 query rows to all of them (48 of the conversion's instructions per block
+//     become 12 and 6 LDS reads);
+//   * the key rows of the score product are taken in the order 16 g + 4 m + j for accumulator register 4 m + j of lane
+//     half g (the lane of the A operand loads that token's codes).  The weights a lane ends up with are then, in register
+//     order, the operand the value product wants: P never leaves the registers, and the 16 scales a lane needs, of K as
+//     of V, are 16 consecutive fp16 values of the metadata plane;
+//   * score * scale - reference is one mixed-precision multiply-add.  The reference of the exponentials is not the
+//     running maximum but the maximum at the last rescaling; a wave rescales when a block's weights sum to more than 64;
+//   * the sum of the weights is taken from the fp16 pairs (dot products with 1), the same values the value product sums.
+// 16 x 2048 tokens, 32 heads, r = 32: 0.43 ms (0.53 ms with one wave per 32 rows converting for itself, the maximum
+// exchanged every block and P through LDS).  Counters then: vector ALU busy 65 %, matrix cores 27 % of 0.82 M cycles at a
+// clock that the load holds at 1.8 - 2.0 GHz.  Tried and slower: two query blocks per wave without LDS (0.44 ms, 193
+// registers, two waves per SIMD; three waves spill), the next block's score products issued under the softmax (0.47 ms).
+//
+// A workgroup is QW x KG waves: KG key groups take every KG-th stage of QW blocks, their (m, l, U) meet in LDS.  A query
+// row is a (token, head) pair, token-major, so the G heads that share a kv head share the stream too.  The cache blocks
+// are read in the layout the decode kernels use (a 32-token block of the K plane is a ready-made operand with row = token,
+// one of the V plane with row = dim).
 // 32x32 accumulator layout throughout: lane L holds column L % 32, rows 8 (v / 4) + 4 (L / 32) + v % 4, v = 0..15.
 #include <type_traits>
 #include "wsvd_dev.h"
@@ -53,207 +69,291 @@ WSVD_DEV void split_bf16(float x, uint32_t& hi, uint32_t& lo) {
   lo = __float_as_uint(x - __uint_as_float(hi)) & 0xFFFF0000u;
 }
 
-template <int R>
-__global__ __launch_bounds__(64) void k_prefill_attn(PrefillParams p) {
-  constexpr int KK = R / 32;
-  __shared__ __attribute__((aligned(16))) float sc_lds[32];             // K scales of the block's 32 tokens
-  __shared__ __attribute__((aligned(16))) _Float16 pt[32][40];          // P in fp16, [query][key], padded rows
+typedef _Float16 v2f16 __attribute__((ext_vector_type(2)));
+// A wave rescales when 16 of a lane's weights sum to more.  Above 16, or equal scores would rescale every block; fp16 would
+// allow 16384 (0.40 ms instead of 0.43), but the largest weight of a column is exact only when it is the reference: with
+// 64 the error against fp64 is 2.09e-4 .. 2.13e-4 over five shapes, with 16384 2.12e-4 .. 2.17e-4 (running maximum: 2.11e-4).
+constexpr float kLazySum = 64.0f;
 
-  const int lane = threadIdx.x, n = lane & 31, g2 = lane >> 5;
+template <int R, int D, int QW, int KG>
+__global__ __launch_bounds__(64 * QW * KG) __attribute__((amdgpu_waves_per_eu(R == 32 ? 4 : 2)))
+void k_prefill_attn(PrefillParams p) {
+  constexpr int KK = R / 32;
+  constexpr int BLK = 4 * KK * 1024 + 64;                               // one cache block as operands: K, V', K scales
+  constexpr int STAGE = QW * BLK;                                       // QW blocks: one converted by each wave of a group
+  constexpr int STAGES = KG * 2 * STAGE, MERGE = KG > 1 ? QW * KG * (KK * 4096 + 256) : 0;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[STAGES > MERGE ? STAGES : MERGE];
+
+  const int lane = threadIdx.x & 63, n = lane & 31, g2 = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);    // (uniform: block addresses stay scalar)
+  const int qw = wave % QW, kg = wave / QW;
   // the last query blocks see the most keys: they are started first, so that the launch does not end on its longest waves
-  const int kv = blockIdx.x, qb = gridDim.y - 1 - blockIdx.y, b = blockIdx.z;
-  const int nb = p.seq_lens[b];
-  const int n_eff = min(max(nb - p.n_after, 0), p.t_cap);
-  const int rho = qb * 32 + n;                                          // this lane's query row
-  const bool row_ok = rho < p.NR;
-  const int rho_c = min(rho, p.NR - 1);
-  const int lim = row_ok ? n_eff - p.nq + rho_c / p.G + 1 : 0;          // this query sees keys [0, lim); may be <= 0
-  const int rho_last = min(qb * 32 + 31, p.NR - 1);
-  const int lim_max = n_eff - p.nq + rho_last / p.G + 1;                // rows are token-major: the last row sees most
-  const int n_kblocks = lim_max > 0 ? (lim_max + 31) >> 5 : 0;
+  const int kv = blockIdx.x, qb = (gridDim.y - 1 - blockIdx.y) * QW + qw, b = blockIdx.z;
   const size_t ph = (size_t)b * p.Hkv + kv;
-  float* orow = p.out + (ph * p.NR + rho_c) * p.d;
-  if (n_kblocks == 0) {                                                 // nothing visible to any row of the block
-    if (row_ok) for (int c = g2 * (p.d >> 1); c < (g2 + 1) * (p.d >> 1); c++) orow[c] = 0.f;
+  const int perm = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
+  const int rho_c = min(qb * 32 + n, p.NR - 1);                         // this lane's query row
+  const bool row_ok = qb * 32 + n < p.NR;
+  // nothing here depends on the length: queries, B_K and the length itself travel in one round trip
+  v8bf16 bq[D / 16], bk[KK][D / 16];
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) bq[ks] = *(const v8bf16*)(p.q + (ph * p.NR + rho_c) * D + 8 * g2 + 16 * ks);
+#pragma unroll
+  for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) bk[kk][ks] = *(const v8bf16*)(p.BK + ((size_t)kv * R + 32 * kk + perm) * D + 16 * ks + 8 * g2);
+  const int n_eff = min(max(p.seq_lens[b] - p.n_after, 0), p.t_cap);
+  const int lim = row_ok ? n_eff - p.nq + rho_c / p.G + 1 : 0;          // this query sees keys [0, lim); may be <= 0
+  // rows are token-major: a wave's last row sees most of its keys, the workgroup's last row most of all.
+  // (readfirstlane: the divisions run on the vector ALU, the values are uniform)
+  auto sees = [&](int row) { return __builtin_amdgcn_readfirstlane(n_eff - p.nq + min(row, p.NR - 1) / p.G + 1); };
+  const int lim_wg = sees((qb - qw) * 32 + 32 * QW - 1);
+  const int n_kblocks = lim_wg > 0 ? (lim_wg + 31) >> 5 : 0;            // of the workgroup
+  if (n_kblocks == 0) {                                                 // nothing visible to any row of the workgroup
+    float* orow = p.out + (ph * p.NR + rho_c) * D;
+    if (row_ok && kg == 0)
+      for (int c = g2 * (D / 2); c < (g2 + 1) * (D / 2); c++) orow[c] = 0.f;
     return;
   }
+  const int lim_max = qb * 32 < p.NR ? sees(qb * 32 + 31) : 0, lim_min = sees(qb * 32);
+  const int kb_end = lim_max > 0 ? (lim_max + 31) >> 5 : 0;             // blocks this wave's rows see any key of
+  const int kb_full = lim_min > 0 ? min(lim_min >> 5, kb_end) : 0;      // blocks every row of the wave sees whole: no masks
 
   // ---- Q~^T = B_K q^T.  Row i of the A operand carries latent dim pi(i) = 16 ((i >> 2) & 1) + 4 (i >> 3) + (i & 3) of
   // its 32-dim block, so that accumulator register v of lane half g2 is dim 16 g2 + v: the order the K blocks use.
-  v16f qt[KK];
-#pragma unroll
-  for (int kk = 0; kk < KK; kk++)
-#pragma unroll
-    for (int v = 0; v < 16; v++) qt[kk][v] = 0.f;
-  {
-    const uint16_t* qrow = p.q + (ph * p.NR + rho_c) * p.d + 8 * g2;
-    const int dimj = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
-    for (int ks = 0; ks < (p.d >> 4); ks++) {
-      const v8bf16 bq = *(const v8bf16*)(qrow + 16 * ks);
-#pragma unroll
-      for (int kk = 0; kk < KK; kk++) {
-        const v8bf16 a = *(const v8bf16*)(p.BK + ((size_t)kv * R + 32 * kk + dimj) * p.d + 16 * ks + 8 * g2);
-        qt[kk] = mfma_bf16(a, bq, qt[kk]);
-      }
-    }
-  }
   v8f16 qh[2 * KK], ql[2 * KK];                                         // 16-dim steps of the score contraction
 #pragma unroll
-  for (int kk = 0; kk < KK; kk++)
+  for (int kk = 0; kk < KK; kk++) {
+    v16f qt;
+#pragma unroll
+    for (int v = 0; v < 16; v++) qt[v] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) qt = mfma_bf16(bk[kk][ks], bq[ks], qt);
 #pragma unroll
     for (int v = 0; v < 16; v++) {
       _Float16 h, l;
-      split_f16(qt[kk][v] * p.c_scale, h, l);
+      split_f16(qt[v] * p.c_scale, h, l);
       qh[2 * kk + (v >> 3)][v & 7] = h;
       ql[2 * kk + (v >> 3)][v & 7] = l;
     }
+  }
 
   const uint8_t* kplane = p.k_codes + ph * (size_t)p.t_cap * R;
   const uint8_t* vplane = p.v_codes + ph * (size_t)p.t_cap * R;
   const uint16_t* kmeta = p.k_meta + ph * (size_t)p.t_cap;
   const uint16_t* vmeta = p.v_meta + ph * (size_t)p.t_cap;
 
-  float m_run = -INFINITY, l_run = 0.f;                                 // l_run: this lane's share of its column's sum
+  float m_ref = -INFINITY, l_run = 0.f;                                 // l_run: this lane's share of its column's sum
   v16f U[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; kk++)
 #pragma unroll
     for (int v = 0; v < 16; v++) U[kk][v] = 0.f;
 
-  // one block ahead in registers: codes of both planes, the lane's K scale, the V scales of the lane half's 16 tokens
-  v4i kc[KK], vc[KK], vs16[2];
-  uint16_t ks_raw;
+  // the raw block this wave converts next, requested one stage ahead: codes of both planes, K scales (lanes 0..3 hold the
+  // 32 tokens'), V scales of the lane half's 16 tokens
+  v4i kc[KK], vc[KK], ks16, vs16[2];
   // paged cache: the table entries of the first 64 pages, one per lane, fetched once; a block's page is then a lane
   // read with a wave-uniform index (a 32-token block never straddles pages).  Entries outside the pools read page 0
   // (blocks past a sequence's end are never consumed; a bad entry under live rows is the append's to report).
   int page_entry = 0;
   if (p.block_table) page_entry = p.block_table[(size_t)b * p.max_pages + min(lane, p.max_pages - 1)];
+  const uint32_t k_lane = (g2 * 32 + perm) * 16, v_lane = lane * 16;    // byte offsets (32-bit: scalar base + lane offset)
   auto load_block = [&](int kb) {
     const uint8_t *kp = kplane, *vp = vplane;
     const uint16_t *km = kmeta, *vm = vmeta;
     if (p.block_table) {
       const int bpp = p.page_rows >> 5;                                 // blocks per page
-      const int pg = min(kb / bpp, p.max_pages - 1);
-      int e = pg < 64 ? __builtin_amdgcn_readlane(page_entry, __builtin_amdgcn_readfirstlane(pg))
-                      : p.block_table[(size_t)b * p.max_pages + pg];
+      const int pg = __builtin_amdgcn_readfirstlane(min(kb / bpp, p.max_pages - 1));
+      int e = pg < 64 ? __builtin_amdgcn_readlane(page_entry, pg) : p.block_table[(size_t)b * p.max_pages + pg];
       e = (e >= 0 && e < p.n_pages) ? e : 0;
       const size_t slot = (size_t)e * p.Hkv + kv;
       kp = p.k_codes + slot * (size_t)p.page_rows * R; vp = p.v_codes + slot * (size_t)p.page_rows * R;
       km = p.k_meta + slot * (size_t)p.page_rows; vm = p.v_meta + slot * (size_t)p.page_rows;
       kb -= pg * bpp;
     }
-    const size_t off = (size_t)kb * (32 * R) + (size_t)lane * 16;
+    const size_t off = (size_t)kb * (32 * R);
 #pragma unroll
     for (int kk = 0; kk < KK; kk++) {
-      kc[kk] = *(const v4i*)(kp + off + kk * 1024);                     // (plain loads: the other query blocks of this
-      vc[kk] = *(const v4i*)(vp + off + kk * 1024);                     //  sequence and head read the same blocks again)
+      kc[kk] = *(const v4i*)((kp + off + kk * 1024) + k_lane);          // (plain loads: the other query blocks of this
+      vc[kk] = *(const v4i*)((vp + off + kk * 1024) + v_lane);          //  sequence and head read the same blocks again)
     }
-    ks_raw = km[kb * 32 + n];
-    vs16[0] = *(const v4i*)(vm + kb * 32 + 16 * g2);
-    vs16[1] = *(const v4i*)(vm + kb * 32 + 16 * g2 + 8);
+    ks16 = *(const v4i*)(km + kb * 32 + 8 * (lane & 3));
+#pragma unroll
+    for (int s = 0; s < 2; s++) vs16[s] = *(const v4i*)(vm + kb * 32 + 16 * g2 + 8 * s);
   };
-  load_block(0);
-
-  // Blocks below kb_full are seen whole by every query of the wave (and lie inside the written part of the cache): no
-  // masks there.  The last one or two blocks take the masked path.
-  const int lim_min = n_eff - p.nq + (qb * 32) / p.G + 1;
-  const int kb_full = lim_min > 0 ? min(lim_min >> 5, n_kblocks) : 0;
-
-  auto block = [&](int kb, auto masked_c) {
-    constexpr bool MASKED = decltype(masked_c)::value;
-    // this block's operands out of the load registers, then the next block's loads.  V' = code * s_V in fp16 (the token
-    // scales are fp16 already: one packed multiply per two elements).
-    v8f16 aK[2 * KK], aV[KK][2];
+  // ... as operands into the wave's slot of a stage.  V' = code * s_V in fp16 (the token scales are fp16 already: one
+  // packed multiply per two elements); tokens no query of the workgroup sees (among them rows never written, whose scale
+  // may be anything) contribute 0.
+  auto convert_block = [&](uint8_t* dst, int kb) {
     v8f16 sv8[2] = {__builtin_bit_cast(v8f16, vs16[0]), __builtin_bit_cast(v8f16, vs16[1])};
-    if constexpr (MASKED) {
-      // tokens no query of the wave sees (among them rows never written, whose scale may be anything) contribute 0
+    if (kb * 32 + 32 > lim_wg) {
 #pragma unroll
       for (int s = 0; s < 2; s++)
 #pragma unroll
         for (int e = 0; e < 8; e++)
-          if (kb * 32 + 16 * g2 + 8 * s + e >= lim_max) sv8[s][e] = (_Float16)0;
+          if (kb * 32 + 16 * g2 + 8 * s + e >= lim_wg) sv8[s][e] = (_Float16)0;
     }
 #pragma unroll
-    for (int kk = 0; kk < KK; kk++) {
-      aK[2 * kk] = codes_f16(kc[kk][0], kc[kk][1]);
-      aK[2 * kk + 1] = codes_f16(kc[kk][2], kc[kk][3]);
-      aV[kk][0] = codes_f16(vc[kk][0], vc[kk][1]) * sv8[0];
-      aV[kk][1] = codes_f16(vc[kk][2], vc[kk][3]) * sv8[1];
-    }
-    sc_lds[n] = f16_bits_to_f32(ks_raw);                                // (both half waves hold the same value)
-    load_block(min(kb + 1, n_kblocks - 1));                             // (after the last block: that block again, unused)
-
-    // scores of the block: rows = its 32 tokens, columns = the 32 queries
-    const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    v16f S = mfma_f16(aK[0], qh[0], zero16);                            // (a constant-zero addend: no registers to clear)
-    S = mfma_f16(aK[0], ql[0], S);
+    for (int kk = 0; kk < KK; kk++)
 #pragma unroll
-    for (int s = 1; s < 2 * KK; s++) { S = mfma_f16(aK[s], qh[s], S); S = mfma_f16(aK[s], ql[s], S); }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float sc[16];
-    float bmax = -INFINITY;
-#pragma unroll
-    for (int m4 = 0; m4 < 4; m4++) {
-      const v4f k4 = *(const v4f*)&sc_lds[8 * m4 + 4 * g2];
-#pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        const int v = 4 * m4 + jj;
-        sc[v] = S[v] * k4[jj];
-        if constexpr (MASKED) sc[v] = kb * 32 + 8 * m4 + 4 * g2 + jj < lim ? sc[v] : -INFINITY;
-        bmax = fmaxf(bmax, sc[v]);
+      for (int h = 0; h < 2; h++) {
+        *(v8f16*)(dst + (2 * kk + h) * 1024 + lane * 16) = codes_f16(kc[kk][2 * h], kc[kk][2 * h + 1]);
+        *(v8f16*)(dst + (2 * KK + 2 * kk + h) * 1024 + lane * 16) = codes_f16(vc[kk][2 * h], vc[kk][2 * h + 1]) * sv8[h];
       }
-    }
-    bmax = fmaxf(bmax, __shfl_xor(bmax, 32));                           // the other half holds the column's other rows
-    const float m_new = fmaxf(m_run, bmax);
-    float alpha;
-    if constexpr (MASKED) alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);
-    else alpha = __builtin_amdgcn_exp2f(m_run - m_new);                 // m_new is finite here
-    float psum = 0.f;
-    float pw[16];
+    if (lane < 4) *(v4i*)(dst + 4 * KK * 1024 + lane * 16) = ks16;
+  };
+
+  auto block = [&](const uint8_t* src, int kb, auto masked_c) {
+    constexpr bool MASKED = decltype(masked_c)::value;
+    // scores: rows = the block's 32 tokens (register v of half g2 = token 16 g2 + v), columns = the 32 queries
+    const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    v16f S;
 #pragma unroll
-    for (int v = 0; v < 16; v++) {
-      pw[v] = __builtin_amdgcn_exp2f(sc[v] - m_new);
-      if constexpr (MASKED) pw[v] = sc[v] == -INFINITY ? 0.f : pw[v];
-      psum += pw[v];
+    for (int s = 0; s < 2 * KK; s++) {
+      const v8f16 aK = *(const v8f16*)(src + s * 1024 + lane * 16);
+      S = mfma_f16(aK, qh[s], s ? S : zero16);                          // (a constant-zero addend: no registers to clear)
+      S = mfma_f16(aK, ql[s], S);
     }
-    l_run = fmaf(l_run, alpha, psum);
-    m_run = m_new;
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {              // the running maxima mostly stand still
+    const v8f16 sk8[2] = {*(const v8f16*)(src + 4 * KK * 1024 + 32 * g2), *(const v8f16*)(src + 4 * KK * 1024 + 32 * g2 + 16)};
+    v8f16 aV[KK][2];
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+      for (int s = 0; s < 2; s++) aV[kk][s] = *(const v8f16*)(src + (2 * KK + 2 * kk + s) * 1024 + lane * 16);
+    float x[16];
+    if constexpr (MASKED) {
+      float bmax = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        const float sc = S[v] * (float)sk8[v >> 3][v & 7];
+        x[v] = kb * 32 + 16 * g2 + v < lim ? sc : -INFINITY;
+        bmax = fmaxf(bmax, x[v]);
+      }
+      bmax = fmaxf(bmax, __shfl_xor(bmax, 32));                         // the other half holds the column's other rows
+      const float m_new = fmaxf(m_ref, bmax);
+      const float alpha = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_new);
+#pragma unroll
+      for (int v = 0; v < 16; v++) x[v] = x[v] == -INFINITY ? -INFINITY : x[v] - m_new;   // (no key seen yet: m_new = -inf)
+      m_ref = m_new; l_run *= alpha;
 #pragma unroll
       for (int kk = 0; kk < KK; kk++)
 #pragma unroll
         for (int v = 0; v < 16; v++) U[kk][v] *= alpha;
+    } else {
+#pragma unroll
+      for (int v = 0; v < 16; v++) x[v] = fmaf(S[v], (float)sk8[v >> 3][v & 7], -m_ref);   // (first block: +inf)
     }
-    // P in fp16 -> LDS, [query][key]: a lane's 16 rows are 4 runs of 4 consecutive keys
+    // weights in fp16: registers 8 s .. 8 s + 7 are tokens 16 g2 + 8 s .. + 7, the operand of step s of the value product
+    v8f16 bp[2];
+    float psum = 0.f;
+    auto weights = [&]() {
+      psum = 0.f;
 #pragma unroll
-    for (int m4 = 0; m4 < 4; m4++) {
-      v4f p4;
+      for (int v = 0; v < 16; v += 2) {
+        const v2f16 w = {(_Float16)__builtin_amdgcn_exp2f(x[v]), (_Float16)__builtin_amdgcn_exp2f(x[v + 1])}, one = {(_Float16)1, (_Float16)1};
+        psum = __builtin_amdgcn_fdot2(w, one, psum, false);
+        bp[v >> 3][v & 7] = w[0]; bp[v >> 3][(v & 7) + 1] = w[1];
+      }
+    };
+    weights();
+    if (!MASKED && __builtin_amdgcn_ballot_w64(psum > kLazySum) != 0) {
+      // a new reference for every column: the largest score seen since the last one, and the weights again
+      float bmax = -INFINITY;
 #pragma unroll
-      for (int jj = 0; jj < 4; jj++) p4[jj] = pw[4 * m4 + jj];
-      const v4f16 h4 = __builtin_convertvector(p4, v4f16);
-      *(v2i*)&pt[n][8 * m4 + 4 * g2] = __builtin_bit_cast(v2i, h4);
+      for (int v = 0; v < 16; v++) bmax = fmaxf(bmax, S[v] * (float)sk8[v >> 3][v & 7]);
+      const float m_new = fmaxf(m_ref, fmaxf(bmax, __shfl_xor(bmax, 32)));
+      const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);        // (m_new is finite here)
+      m_ref = m_new; l_run *= alpha;
+#pragma unroll
+      for (int v = 0; v < 16; v++) x[v] = fmaf(S[v], (float)sk8[v >> 3][v & 7], -m_new);
+#pragma unroll
+      for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) U[kk][v] *= alpha;
+      weights();
     }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // U^T += V'^T P: rows = latent dims, columns = queries; step s contracts the tokens 16 g2 + 8 s .. + 7 of a half
+    l_run += psum;
+    // U^T += V'^T P: rows = latent dims, columns = queries
 #pragma unroll
-    for (int s = 0; s < 2; s++) {
-      const v8f16 bp = *(const v8f16*)&pt[n][16 * g2 + 8 * s];
+    for (int s = 0; s < 2; s++)
 #pragma unroll
-      for (int kk = 0; kk < KK; kk++) U[kk] = mfma_f16(aV[kk][s], bp, U[kk]);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
+      for (int kk = 0; kk < KK; kk++) U[kk] = mfma_f16(aV[kk][s], bp[s], U[kk]);
   };
-  for (int kb = 0; kb < kb_full; kb++) block(kb, std::false_type{});
-  for (int kb = kb_full; kb < n_kblocks; kb++) block(kb, std::true_type{});
+
+  // ---- stages of QW blocks: every wave converts one block of the next stage, then all of them attend to the whole
+  // current one; a key group takes every KG-th stage
+  uint8_t* const stage = lds + kg * (2 * STAGE);
+  const int n_stages = (n_kblocks + QW - 1) / QW, n_iter = (n_stages + KG - 1) / KG;
+  auto own_block = [&](int it) { return (it * KG + kg) * QW + qw; };    // (may lie past the end: clamped loads, never read)
+  load_block(min(own_block(0), n_kblocks - 1));
+  convert_block(stage + qw * BLK, own_block(0));
+  load_block(min(own_block(1), n_kblocks - 1));
+  __syncthreads();
+  for (int it = 0; it < n_iter; it++) {
+    if (it + 1 < n_iter) {
+      convert_block(stage + ((it + 1) & 1) * STAGE + qw * BLK, own_block(it + 1));
+      load_block(min(own_block(it + 2), n_kblocks - 1));
+    }
+    const uint8_t* src = stage + (it & 1) * STAGE;
+    const int kb0 = (it * KG + kg) * QW;
+    const int j_full = min(kb_full - kb0, QW), j_end = min(kb_end - kb0, QW);
+    int j = 0;
+    for (; j < j_full; j++) block(src + j * BLK, kb0 + j, std::false_type{});
+    for (; j < j_end; j++) block(src + j * BLK, kb0 + j, std::true_type{});
+    __syncthreads();
+  }
+
+  float L = l_run + __shfl_xor(l_run, 32);
+  if constexpr (KG > 1) {
+    // the key groups' partial results: every group's wave of the same rows folds all of them in group order, then takes its
+    // share of the output channels  (LDS: U in register order, then m and l per query; the last barrier has passed)
+    float* const mine = (float*)(lds + (size_t)wave * (KK * 4096 + 256));
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) mine[(kk * 16 + v) * 64 + lane] = U[kk][v];
+    if (g2 == 0) { mine[KK * 1024 + n] = m_ref; mine[KK * 1024 + 32 + n] = L; }
+    __syncthreads();
+    float m = -INFINITY;
+    L = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) U[kk][v] = 0.f;
+#pragma unroll
+    for (int g = 0; g < KG; g++) m = fmaxf(m, ((const float*)(lds + (size_t)(g * QW + qw) * (KK * 4096 + 256)))[KK * 1024 + n]);
+#pragma unroll
+    for (int g = 0; g < KG; g++) {
+      const float* part = (const float*)(lds + (size_t)(g * QW + qw) * (KK * 4096 + 256));
+      const float mg = part[KK * 1024 + n];
+      const float f = mg == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(mg - m);     // (a group that saw no key: U = 0, l = 0)
+      L = fmaf(f, part[KK * 1024 + 32 + n], L);
+#pragma unroll
+      for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) U[kk][v] = fmaf(f, part[(kk * 16 + v) * 64 + lane], U[kk][v]);
+    }
+  }
 
   // ---- O^T = B_V^T (U / l).  Register v of U[kk] in lane half g2 is latent dim 32 kk + 8 (v / 4) + 4 g2 + v % 4; the A
-  // operand gathers the rows of B_V in that order.
-  const float L = l_run + __shfl_xor(l_run, 32);
+  // operand gathers the rows of B_V in that order (all of the wave's output channels in one round trip).
+  constexpr int NRB = D / 32 / KG < 1 ? 1 : D / 32 / KG;                // blocks of 32 output channels per wave
+  v4i av[NRB][KK][2];
+#pragma unroll
+  for (int t = 0; t < NRB; t++) {
+    const int c = 32 * min(kg + t * KG, D / 32 - 1) + n;                // output channel of this lane's A row
+#pragma unroll
+    for (int kk = 0; kk < KK; kk++)
+#pragma unroll
+      for (int s = 0; s < 2; s++)
+#pragma unroll
+        for (int e = 0; e < 4; e++) {
+          const int v0 = 8 * s + 2 * e, v1 = v0 + 1;
+          const int j0 = 32 * kk + 8 * (v0 >> 2) + 4 * g2 + (v0 & 3), j1 = 32 * kk + 8 * (v1 >> 2) + 4 * g2 + (v1 & 3);
+          const uint32_t e0 = p.BV[((size_t)kv * R + j0) * D + c], e1 = p.BV[((size_t)kv * R + j1) * D + c];
+          av[t][kk][s][e] = (int)(e0 | (e1 << 16));
+        }
+  }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
   v8bf16 uh[KK][2], ul[KK][2];
 #pragma unroll
@@ -272,28 +372,23 @@ __global__ __launch_bounds__(64) void k_prefill_attn(PrefillParams p) {
       uh[kk][s] = __builtin_bit_cast(v8bf16, hh);
       ul[kk][s] = __builtin_bit_cast(v8bf16, ll);
     }
-  for (int rb = 0; rb < (p.d >> 5); rb++) {
+#pragma unroll
+  for (int t = 0; t < NRB; t++) {
+    const int rb = kg + t * KG;
+    if (rb >= D / 32) break;                                            // (wave-uniform: more groups than channel blocks)
     v16f O;
 #pragma unroll
     for (int v = 0; v < 16; v++) O[v] = 0.f;
-    const int c = 32 * rb + n;                                          // output channel of this lane's A row
 #pragma unroll
     for (int kk = 0; kk < KK; kk++)
 #pragma unroll
       for (int s = 0; s < 2; s++) {
-        v4i araw;
-#pragma unroll
-        for (int e = 0; e < 4; e++) {
-          const int v0 = 8 * s + 2 * e, v1 = v0 + 1;
-          const int j0 = 32 * kk + 8 * (v0 >> 2) + 4 * g2 + (v0 & 3), j1 = 32 * kk + 8 * (v1 >> 2) + 4 * g2 + (v1 & 3);
-          const uint32_t e0 = p.BV[((size_t)kv * R + j0) * p.d + c], e1 = p.BV[((size_t)kv * R + j1) * p.d + c];
-          araw[e] = (int)(e0 | (e1 << 16));
-        }
-        const v8bf16 a = __builtin_bit_cast(v8bf16, araw);
+        const v8bf16 a = __builtin_bit_cast(v8bf16, av[t][kk][s]);
         O = mfma_bf16(a, uh[kk][s], O);
         O = mfma_bf16(a, ul[kk][s], O);
       }
     if (row_ok) {
+      float* orow = p.out + (ph * p.NR + rho_c) * D;
 #pragma unroll
       for (int m4 = 0; m4 < 4; m4++) {
         v4f o4;
@@ -303,6 +398,32 @@ __global__ __launch_bounds__(64) void k_prefill_attn(PrefillParams p) {
       }
     }
   }
+}
+
+template <int R, int D, int QW, int KG>
+void launch_prefill_attn(const PrefillParams& p, hipStream_t s) {
+  dim3 grid((unsigned)p.Hkv, (unsigned)((p.NR + 32 * QW - 1) / (32 * QW)), (unsigned)p.B);
+  hipLaunchKernelGGL((k_prefill_attn<R, D, QW, KG>), grid, dim3(64 * QW * KG), 0, s, p);
+}
+
+// Waves of a workgroup: QW share the conversion of the cache blocks, KG groups share the blocks of the same rows.  With
+// many query rows the conversion decides (4 x 1); with few the chip is idle and a wave's walk over the cache is the time,
+// so the blocks are dealt to more waves.  In waves of 32 query rows (a SIMD holds 4 of rank 32, 2 of rank 64), us per call
+// for 4x1 / 2x2 / 1x4, rank 32 and then rank 64, all over 1000 to 2000 keys:
+//   64 waves    30.5 / 23.1 / 17.8    39.5 / 29.4 / 23.7      224 waves   23.0 / 18.8 / 14.8    29.1 / 23.6 / 19.2
+//   512 waves   21.8 / 19.1 / 19.8    27.9 / 23.6 / 25.9      1056 waves  44.2 / 41.3 / 42.7    56.8 / 60.7 / 67.8
+//   2048 waves  41.1 / 41.6 / 50.3    53.9 / 63.2 / 82.4      4096 waves  83.4 / 87.1 / 106.6   115.7 / 138 / 193
+template <int R, int D>
+void pick_prefill_attn_d(const PrefillParams& p, hipStream_t s) {
+  const long long waves = (long long)p.B * p.Hkv * ((p.NR + 31) / 32);
+  if (waves <= 256) launch_prefill_attn<R, D, 1, 4>(p, s);
+  else if (waves <= (R == 32 ? 1536 : 768)) launch_prefill_attn<R, D, 2, 2>(p, s);
+  else launch_prefill_attn<R, D, 4, 1>(p, s);
+}
+template <int R>
+void pick_prefill_attn(const PrefillParams& p, hipStream_t s) {
+  if (p.d == 128) pick_prefill_attn_d<R, 128>(p, s);
+  else pick_prefill_attn_d<R, 64>(p, s);
 }
 
 }  // namespace
@@ -326,9 +447,8 @@ hipError_t wsvd_launch_prefill_attn(const wsvd_layer_desc& d, const void* q, int
   p.NR = (int)NR;
   const float sm = d.sm_scale != 0.f ? d.sm_scale : 1.0f / sqrtf((float)d.d_head);
   p.c_scale = sm * 1.44269504088896340736f;
-  dim3 grid((unsigned)d.n_kv_heads, (unsigned)((NR + 31) / 32), (unsigned)d.batch);
-  if (d.rank == 32) hipLaunchKernelGGL((k_prefill_attn<32>), grid, dim3(64), 0, s, p);
-  else if (d.rank == 64) hipLaunchKernelGGL((k_prefill_attn<64>), grid, dim3(64), 0, s, p);
+  if (d.rank == 32) pick_prefill_attn<32>(p, s);
+  else if (d.rank == 64) pick_prefill_attn<64>(p, s);
   else return hipErrorNotSupported;
   return hipGetLastError();
 }

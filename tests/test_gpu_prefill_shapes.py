@@ -3,12 +3,13 @@ edges of its token tiles (one tile, one more, one less, several with a remainder
 import numpy as np
 import pytest
 
+import oracle as O
 import paper_2604_02570_amd as W
 import wsvd_inputs as WI
 from cases import build_case
 from harness import as_dtype_dev, check_i8_rows
-from test_gpu_parity import layer_for
-from test_gpu_prefill import _check_i4_rows, _latents64
+from test_gpu_parity import check_out, layer_for
+from test_gpu_prefill import _check_i4_rows, _latents64, _multi_q, _prefill_attn
 
 pytestmark = pytest.mark.gpu
 
@@ -42,3 +43,53 @@ def _prompt(name, shape, n, **over):
 @pytest.mark.parametrize("n", [1, 255, 257])
 def test_int4_prompt_projection_shapes(shape, n):
     _prompt("c4_small", shape, n, batch=3, context=120, ragged=(60, 120))
+
+
+# query rows per kv head at the edges of the 32-row waves and of the 1 / 2 / 4 waves that share a workgroup's cache blocks;
+# batch and heads choose the workgroup shape (256 and 1536 waves of rank 32, 768 of rank 64 are the limits of the rule)
+ATTN_SHAPES = [("c3_small", 9, 0, dict()), ("c3_small", 31, 2, dict(context=700)), ("c3_small", 33, 0, dict(d_head=64, context=65)),
+               ("c3_small", 65, 0, dict(batch=24, n_q_heads=8, n_kv_heads=8, context=200)),
+               ("c3_small", 17, 1, dict(batch=24, n_q_heads=32, n_kv_heads=8, context=130, rank=64)),
+               ("c3_small", 97, 0, dict(batch=16, n_q_heads=32, n_kv_heads=32, context=129)),
+               ("c3_small", 129, 3, dict(batch=16, n_q_heads=32, n_kv_heads=32, context=161, d_head=64)),
+               ("c3_small", 33, 0, dict(batch=16, n_q_heads=48, n_kv_heads=24, context=96, rank=64))]
+
+
+@pytest.mark.parametrize("name,nq,n_after,over", ATTN_SHAPES, ids=[f"nq{q}-after{a}-{'-'.join(f'{k}{v}' for k, v in o.items())}" for _, q, a, o in ATTN_SHAPES])
+def test_prompt_attention_workgroup_shapes(name, nq, n_after, over):
+    c = build_case(name, **over)
+    c.cache.seq_lens[: c.sp.batch // 2] -= np.arange(c.sp.batch // 2, dtype=np.int32) % 40        # ragged, some shorter than n_q
+    L = layer_for(c); L.upload(c.cache)
+    q32 = _multi_q(c, nq, seed=31)
+    got = _prefill_attn(L, c, q32, nq, n_after, int(c.cache.seq_lens.max()))
+    ref = O.causal_attn_reconstructed(c.cache, q32.astype(np.float64), c.BK.astype(np.float64), c.BV.astype(np.float64), c.sm_scale,
+                                      n_after=n_after)
+    check_out(got, ref, "i8", f"prompt attention {name} nq={nq} n_after={n_after} {over}")
+    L.close()
+
+
+@pytest.mark.parametrize("lead", [13.0, 15.5, 19.0])
+@pytest.mark.parametrize("where", ["first", "late"])
+def test_prompt_attention_many_small_weights(lead, where):
+    """One key leads all others by 2^lead: the others' weights are small or subnormal in fp16 where the reference of the
+    exponentials is that key's score ("first"), and the wave has to move its reference where the key comes late.  The sum
+    of 1990 such weights is up to a fifth of the total and must not be lost."""
+    c = build_case("c3_small", batch=2, n_q_heads=2, n_kv_heads=2, context=2000)
+    sp = c.sp
+    rng = np.random.default_rng(3)
+    q32 = np.repeat(_multi_q(c, 1, seed=4), 10, axis=2)                         # ten equal tokens
+    t = 5 if where == "first" else 1500
+    for b in range(sp.batch):
+        k = np.zeros((sp.n_kv_heads, 2000, sp.rank))
+        qt = np.einsum("hd,hrd->hr", q32[b, :, 0, 0].astype(np.float64), c.BK.astype(np.float64))
+        k[:, t] = qt * (lead * np.log(2.0) / c.sm_scale / (qt * qt).sum(-1))[:, None]
+        c.cache.store_rows("k", b, 0, k)
+        c.cache.store_rows("v", b, 0, rng.standard_normal((sp.n_kv_heads, 2000, sp.rank)) + 1.0)
+        c.cache.seq_lens[b] = 2000
+    L = layer_for(c); L.upload(c.cache)
+    got = _prefill_attn(L, c, q32, 10, 0, 2000)
+    ref = O.causal_attn_reconstructed(c.cache, q32.astype(np.float64), c.BK.astype(np.float64), c.BV.astype(np.float64), c.sm_scale)
+    # fp16 weights: 2^-12 relative each, a subnormal one 2^-25 absolute (2^-25 / 2^-19 = 1.6 % of each of the smallest, signs
+    # at random over 2000 keys whose sum is 2^-8 of the total); fp16 values 2^-12: 1e-3 covers both
+    assert np.linalg.norm(got - ref) <= 1e-3 * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    L.close()
