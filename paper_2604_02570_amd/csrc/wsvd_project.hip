@@ -230,6 +230,16 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int kProjKC = 64, kProjXRow = 144;
 constexpr int kProjABytes = 8 * 4 * 1024, kProjXBytes = 256 * kProjXRow, kProjStage = kProjABytes + kProjXBytes;
 
+// Workgroup -> (channel group, token group).  Consecutive workgroup ids land on different XCDs (8 of them, each with
+// its own L2): when the number of token groups allows it, XCD i takes the token groups = i (mod 8), so a line of hidden
+// states is fetched by one XCD only, and the workgroups running together on an XCD cover all channel groups of a few
+// token groups, walking through the factors in step.
+WSVD_DEV void project_groups(const ProjectParams& p, int& cg, int& tg) {
+  const int L = blockIdx.x;
+  if (p.n_tg % 8 == 0) { const int sl = L >> 3; cg = sl % p.n_cg; tg = (sl / p.n_cg) * 8 + (L & 7); }
+  else { cg = L % p.n_cg; tg = L / p.n_cg; }
+}
+
 template <int R, int WAVES, bool I4>
 __global__ __launch_bounds__(64 * WAVES) void k_prefill_project_lds(ProjectParams p) {
   extern __shared__ __align__(16) uint8_t proj_lds[];
@@ -238,16 +248,8 @@ __global__ __launch_bounds__(64 * WAVES) void k_prefill_project_lds(ProjectParam
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g2 = lane >> 5;
   const int wc = wave & 1, wt = wave >> 1;
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
-  // Workgroup -> (channel group, token group).  Consecutive workgroup ids land on different XCDs (8 of them, each with
-  // its own L2): when the number of token groups allows it, XCD i takes the token groups = i (mod 8), so a line of hidden
-  // states is fetched by one XCD only, and the workgroups running together on an XCD cover all channel groups of a few
-  // token groups, walking through the factors in step.
   int cg, tg;
-  {
-    const int L = blockIdx.x;
-    if (p.n_tg % 8 == 0) { const int sl = L >> 3; cg = sl % p.n_cg; tg = (sl / p.n_cg) * 8 + (L & 7); }
-    else { cg = L % p.n_cg; tg = L / p.n_cg; }
-  }
+  project_groups(p, cg, tg);
   const int sq = tg / p.tg_seq, by = tg % p.tg_seq;                     // sequence of the launch, 256-token group in it
   const int seq = p.seq0 + sq;
   const int n0 = p.seq_lens[seq];
@@ -336,6 +338,109 @@ __global__ __launch_bounds__(64 * WAVES) void k_prefill_project_lds(ProjectParam
   project_store<R, CT, TT, I4>(p, acc, ct0, tb, seq, n0);
 }
 
+// The projection with the hidden states staged through LDS and the factors straight from memory into the registers that
+// feed the matrix cores (the packed image is the operand, a wave's channels are its own, so LDS would only cost it a write
+// and a read).  A workgroup of 4 waves owns 128 CT channels (wave w the CT tiles from 4 CT cg + CT w on) x 32 TT tokens;
+// every wave multiplies with all of the workgroup's tokens.  DEPTH chunks of 64 model dims are on their way in registers,
+// two LDS stages of hidden states take turns, one barrier per chunk.  For problems that do not fill the chip with 256 x 256
+// tiles: bound by the chain of a chunk (barrier, LDS read, products), so more and smaller workgroups win until they are
+// two to a CU, then the re-reading of the operands decides.  us per call (length update of 4-5 us included), d_model 4096,
+// 32 kv heads of rank 32; old = the kernel without LDS, 2 x 1 tiles per wave (below 2^22 latents) / four-wave 256 x 256:
+//   tokens               11     200    3 x 333   4 x 500   2 x 2048   8 x 1024   16 x 2048
+//   128 x 32  (1, 1)     19.0   19.8    49.2      84.6       161        334        1276
+//   256 x 64  (2, 2)     38.7   40.4    44.4      49.7        82        150         627
+//   256 x 256             100    105     109       108       112        134         543
+//   old                  37.4   51.0    84.4       103       120        139         553
+// (Both operands through LDS with 2 x 2 waves: 23.2 us at 11 and 49-51 us at 3 x 333 tokens.)
+template <int R, int CT, int TT, bool I4>
+__global__ __launch_bounds__(256) void k_prefill_project_direct(ProjectParams p) {
+  constexpr int RT = R / 32, DEPTH = 4;                                 // (2 or 8 chunks ahead: within 5 %)
+  static_assert(CT % RT == 0, "a head's channels stay in one wave");
+  static_assert(DEPTH % 2 == 0, "LDS stage and register set follow from the position in the unrolled loop");
+  constexpr int NX = TT, NS = kProjKC / 16;                             // 16-byte pieces of x per thread and chunk; steps
+  constexpr int STAGE = 32 * TT * kProjXRow;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE];
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g2 = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
+  int cg, tg;
+  project_groups(p, cg, tg);
+  const int sq = tg / p.tg_seq, by = tg % p.tg_seq;
+  const int seq = p.seq0 + sq;
+  const int n0 = p.seq_lens[seq];
+  const int n_steps = p.E >> 4, n_chunks = p.E / kProjKC;
+  const int ct0 = (cg * 4 + wave) * CT;                                 // first channel tile of this wave
+  const uint8_t* asrc[CT];
+#pragma unroll
+  for (int c = 0; c < CT; c++) {
+    const int ct = min(ct0 + c, tiles - 1);
+    asrc[c] = (const uint8_t*)p.A[ct / tiles_plane] + (size_t)(ct % tiles_plane) * n_steps * 1024;
+  }
+  const uint8_t* xbase = (const uint8_t*)p.x + (size_t)sq * p.n_tok * p.E * 2;
+  uint32_t xoff[NX];
+#pragma unroll
+  for (int j = 0; j < NX; j++)                                          // (the launcher keeps n_tok * E * 2 below 2^31)
+    xoff[j] = (uint32_t)min(by * 32 * TT + (tid >> 3) + 32 * j, p.n_tok - 1) * (uint32_t)(p.E * 2) + (tid & 7) * 16;
+  const int xdst = (tid >> 3) * kProjXRow + (tid & 7) * 16;             // + 32 j rows
+  const uint32_t aoff = lane * 16;
+  v8bf16 ra[DEPTH][CT][NS];
+  v4u rx[DEPTH][NX];
+  auto fetch_a = [&](int b, int c) {
+    c = min(c, n_chunks - 1);                                           // (past the end: the last chunk again, not used)
+#pragma unroll
+    for (int cc = 0; cc < CT; cc++)
+#pragma unroll
+      for (int ks = 0; ks < NS; ks++) ra[b][cc][ks] = *(const v8bf16*)((asrc[cc] + (size_t)c * 4096 + ks * 1024) + aoff);
+  };
+  auto fetch_x = [&](int b, int c) {
+    c = min(c, n_chunks - 1);
+#pragma unroll
+    for (int j = 0; j < NX; j++) rx[b][j] = *(const v4u*)((xbase + (size_t)c * (kProjKC * 2)) + xoff[j]);
+  };
+  auto commit = [&](int b, int st) {
+#pragma unroll
+    for (int j = 0; j < NX; j++) *(v4u*)(lds + st * STAGE + 32 * j * kProjXRow + xdst) = rx[b][j];
+  };
+  v16f acc[CT][TT];
+#pragma unroll
+  for (int c = 0; c < CT; c++)
+#pragma unroll
+    for (int tt = 0; tt < TT; tt++)
+#pragma unroll
+      for (int v = 0; v < 16; v++) acc[c][tt][v] = 0.f;
+#pragma unroll
+  for (int u = 0; u < DEPTH; u++) { fetch_x(u, u); fetch_a(u, u); }
+  commit(0, 0);
+  fetch_x(0, DEPTH);
+  __syncthreads();
+  const int x_off = n * kProjXRow + g2 * 16;
+  // chunk c sits in LDS stage c & 1 and in factor set c % DEPTH; set (c + 1) % DEPTH of the hidden states holds chunk c + 1
+  for (int c0 = 0; c0 < n_chunks; c0 += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++) {
+      if (c0 + u < n_chunks) {                                          // (uniform)
+        commit((u + 1) % DEPTH, (u + 1) & 1);
+        fetch_x((u + 1) % DEPTH, c0 + u + 1 + DEPTH);
+        const uint8_t* base = lds + (u & 1) * STAGE + x_off;
+#pragma unroll
+        for (int ks = 0; ks < NS; ks++) {
+          v8bf16 fb[TT];
+#pragma unroll
+          for (int tt = 0; tt < TT; tt++) fb[tt] = *(const v8bf16*)(base + tt * 32 * kProjXRow + ks * 32);
+#pragma unroll
+          for (int cc = 0; cc < CT; cc++)
+#pragma unroll
+            for (int tt = 0; tt < TT; tt++) acc[cc][tt] = mfma_bf16(ra[u][cc][ks], fb[tt], acc[cc][tt]);
+        }
+        fetch_a(u, c0 + u + DEPTH);
+        __syncthreads();
+      }
+    }
+  }
+  if (ct0 >= tiles) return;
+  project_store<R, CT, TT, I4>(p, acc, ct0, by, seq, n0);
+}
+
 // after the projection: the lengths move on by the rows that fitted (one thread per sequence)
 __global__ void k_prefill_bump(int* seq_lens, int seq0, int n_seq, int n_tok, int t_cap, int* err_word, int even_only) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
@@ -354,6 +459,13 @@ void launch_project(const ProjectParams& p, int n_seq, hipStream_t s) {
   const int tiles = 2 * p.Hkv * (R / 32), tok_wg = 32 * TT * (4 / WC);
   dim3 grid((unsigned)((tiles + WC * CT - 1) / (WC * CT)), (unsigned)((p.n_tok + tok_wg - 1) / tok_wg), (unsigned)n_seq);
   hipLaunchKernelGGL((k_prefill_project<R, CT, TT, WC, I4>), grid, dim3(256), 0, s, p);
+}
+
+template <int R, int CT, int TT, bool I4 = false>
+void launch_project_direct(ProjectParams p, int n_seq, hipStream_t s) {
+  const int tiles = 2 * p.Hkv * (R / 32);
+  p.n_cg = (tiles + 4 * CT - 1) / (4 * CT); p.tg_seq = (p.n_tok + 32 * TT - 1) / (32 * TT); p.n_tg = p.tg_seq * n_seq;
+  hipLaunchKernelGGL((k_prefill_project_direct<R, CT, TT, I4>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(256), 0, s, p);
 }
 
 template <int R, int WAVES, bool I4 = false>
@@ -391,11 +503,17 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   if (paged) { p.block_table = paged->block_table; p.page_rows = paged->page_rows; p.max_pages = paged->max_pages; p.n_pages = paged->n_pages; }
   const int n_seq = seq < 0 ? d.batch : 1;
   p.seq0 = seq < 0 ? 0 : seq;
-  // small problems: small wave tiles, so that there are enough waves; prompt-sized ones: the LDS-staged kernel
-  // (option "project_shape": 1 = staged, 44 / 42 / 24 / 21 = variants of the direct kernel, for tuning and tests)
+  // Which kernel: by how many workgroups each tile size gives on 256 CUs (see the table at k_prefill_project_direct).
+  //   11: 128 channels x 32 tokens while that is at most two workgroups per CU;
+  //   22: 256 x 64 while the 256 x 256 tiles of the staged kernel would leave more than a third of the CUs idle;
+  //   2 : 256 x 256 tiles, eight waves (1: four waves; 44 / 42 / 24 / 21: the kernel without LDS, also where a sequence's
+  //       hidden states take 2^31 bytes or more).  The "project_shape" option asks for 1, 2, 44, 42, 24 or 21 (tuning, tests).
   const long long work = (long long)n_seq * n_tok * d.n_kv_heads * d.rank;
   const bool staged_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
-  int shape = ctx->opt.project_shape ? ctx->opt.project_shape : (work >= (1LL << 22) ? (staged_ok ? 1 : 44) : 21);
+  const long long ch = 2LL * d.n_kv_heads * d.rank;
+  const long long small_wgs = (ch + 127) / 128 * ((n_tok + 31) / 32) * n_seq, big_wgs = (ch + 255) / 256 * ((n_tok + 255) / 256) * n_seq;
+  int shape = ctx->opt.project_shape;
+  if (!shape) shape = !staged_ok ? 44 : small_wgs <= 512 ? 11 : big_wgs <= 160 ? 22 : 2;
   if ((shape == 1 || shape == 2) && !staged_ok) shape = 44;
   hipError_t e = hipSuccess;
   if (d.rank > 64) {
@@ -403,11 +521,19 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
     const bool big = work >= (1LL << 22);
     if (d.rank == 96) { if (big) launch_project<96, 3, 4, 4>(p, n_seq, s); else launch_project<96, 3, 1, 4>(p, n_seq, s); }
     else { if (big) launch_project<128, 4, 4, 4>(p, n_seq, s); else launch_project<128, 4, 1, 4>(p, n_seq, s); }
+  } else if (shape == 11) {
+    if (i4) launch_project_direct<32, 1, 1, true>(p, n_seq, s);
+    else if (d.rank == 32) launch_project_direct<32, 1, 1>(p, n_seq, s);
+    else launch_project_direct<64, 2, 1>(p, n_seq, s);
+  } else if (shape == 22) {
+    if (i4) launch_project_direct<32, 2, 2, true>(p, n_seq, s);
+    else if (d.rank == 32) launch_project_direct<32, 2, 2>(p, n_seq, s);
+    else launch_project_direct<64, 2, 2>(p, n_seq, s);
   } else if (shape == 1 || shape == 2) {
     const int tiles = 2 * p.Hkv * (d.rank / 32);
     p.n_cg = (tiles + 7) / 8; p.tg_seq = (n_tok + 255) / 256; p.n_tg = p.tg_seq * n_seq;
     const bool w8 = shape == 2;
-    if (i4) e = launch_project_lds<32, 4, true>(p, s);
+    if (i4) e = launch_project_lds<32, 8, true>(p, s);
     else if (d.rank == 32) e = w8 ? launch_project_lds<32, 8>(p, s) : launch_project_lds<32, 4>(p, s);
     else e = w8 ? launch_project_lds<64, 8>(p, s) : launch_project_lds<64, 4>(p, s);
   } else if (i4) {

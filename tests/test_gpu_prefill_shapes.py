@@ -45,6 +45,15 @@ def test_int4_prompt_projection_shapes(shape, n):
     _prompt("c4_small", shape, n, batch=3, context=120, ragged=(60, 120))
 
 
+# (a small prompt takes 128 x 32 tiles; more than 512 of them, 256 x 64: channel tiles that end inside a workgroup's group,
+# tokens at the edges of a tile and one sequence of several)
+@pytest.mark.parametrize("name,n,over", [("c3_small", 1, dict()), ("c3_small", 33, dict(n_q_heads=7, n_kv_heads=7)), ("c3_small", 64, dict(rank=64)),
+                                         ("c3_small", 345, dict(n_q_heads=32, n_kv_heads=32)), ("c3_small", 321, dict(rank=64, n_q_heads=18, n_kv_heads=18)),
+                                         ("c4_small", 353, dict(n_q_heads=34, n_kv_heads=34, ragged=(60, 120)))])
+def test_prompt_projection_tile_rule(name, n, over):
+    _prompt(name, 0, n, **{**dict(batch=3, context=120), **over})
+
+
 # query rows per kv head at the edges of the 32-row waves and of the 1 / 2 / 4 waves that share a workgroup's cache blocks;
 # batch and heads choose the workgroup shape (256 and 1536 waves of rank 32, 768 of rank 64 are the limits of the rule)
 ATTN_SHAPES = [("c3_small", 9, 0, dict()), ("c3_small", 31, 2, dict(context=700)), ("c3_small", 33, 0, dict(d_head=64, context=65)),
