@@ -285,7 +285,8 @@ wsvd_status wsvd_decode_attn_rope(wsvd_ctx *ctx, const wsvd_layer_desc *desc, co
  * sums the slices, quantises, stores the new rows and takes them from registers, so the hand-off between the
  * append's workgroups is the kernel boundary itself ("step_deferred" setting of wsvd_test.h; the stored codes may
  * differ from wsvd_latent_append's where the fp32 sums, taken in another order, fall on the other side of a rounding
- * boundary).  Every other combination: the append kernel and the attention kernel back to back.  A single-launch
+ * boundary).  F32 and BF16 latents: the same two launches, the partial sums being the append's own, so rows and outputs
+ * are bit for bit those of the two calls.  Every other combination: the append kernel and the attention kernel back to back.  A single-launch
  * kernel also exists ("fused_step" setting); it measured no faster on MI355X, so it is not the default.
  *   max_seq_len: host upper bound on the sequence lengths AFTER the append (>= 1).
  * Capacity handling as in wsvd_latent_append: a full sequence is attended as it is and reported by wsvd_check.

@@ -29,7 +29,7 @@ wsvd_status wsvd_timeline_set_buffer(wsvd_ctx *ctx, void *dev_ptr, size_t bytes)
  *   "fused_step":     wsvd_decode_step uses 0 = two launches (default), 1 = the single-launch kernel where one exists,
  *                     2 = the single-launch kernel or WSVD_E_UNSUPPORTED
  *   "step_deferred":  which two launches: 1 = projection launch + attention launch that finishes the row where that
- *                     pair exists (default), 2 = that pair or WSVD_E_UNSUPPORTED, 0 = always the append kernel + the
+ *                     pair exists (default), 2 = the int8 pair or WSVD_E_UNSUPPORTED, 0 = always the append kernel + the
  *                     attention kernel
  *   "timeline_kernel": profiling build, wsvd_decode_step: 0 = the attention launch writes the stamps (default), 1 = the
  *                     projection launch does (slots: 0 entry, 1 loads issued, 2 hidden states staged, 3 products

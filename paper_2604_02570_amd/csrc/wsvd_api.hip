@@ -582,6 +582,7 @@ static hipError_t launch_step_attention(wsvd_ctx* ctx, const wsvd_layer_desc& d,
   p.new_k = parts; p.new_v = parts + plane; p.new_ld = (long)d.n_kv_heads * d.rank;
   p.n_parts = n_parts; p.part_stride = (long)(2 * plane); p.pending = pending;
   if (ctx->opt.timeline_kernel == 1) p.timeline = nullptr;
+  if (d.latent_dtype == WSVD_F32 || d.latent_dtype == WSVD_BF16) return wsvd_launch_attn_generic(p, d.latent_dtype, d.rank, grid, s);
   return wsvd_launch_attn_newrow(p, d.rank, grid, threads, s);
 }
 
@@ -628,7 +629,9 @@ wsvd_status wsvd_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const v
                                                             max_seq_len, out, s)
                                   : hipErrorNotSupported;
   if (e == hipErrorNotSupported && ctx->opt.fused_step == 2) return WSVD_E_UNSUPPORTED;
-  if (e == hipErrorNotSupported && ctx->opt.step_deferred && ctx->opt.append_mode == 0 && wsvd_step_deferred_ok(*desc)) {
+  // (step_deferred 2 insists on the int8 pair)
+  const bool deferred = wsvd_step_deferred_ok(*desc) || (ctx->opt.step_deferred == 1 && wsvd_step_deferred_float_ok(*desc));
+  if (e == hipErrorNotSupported && ctx->opt.step_deferred && ctx->opt.append_mode == 0 && deferred) {
     // projection launch (partial sums, lengths advanced), then the attention launch that finishes the rows
     float* parts = nullptr;
     int* pending = nullptr;

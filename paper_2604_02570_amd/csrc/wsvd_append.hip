@@ -12,18 +12,32 @@
 #include "wsvd_dev.h"
 #include "wsvd_append_body.h"
 
+// The decode step's projection launch: sequence b's length moves on now, its row is still to be written.  A full sequence
+// is reported and left alone.
+WSVD_DEV void append_defer_bump(const AppendParams& p, int b, int n) {
+  const bool ok = n >= 0 && n < p.t_cap;
+  if (ok) p.seq_lens[b] = n + 1;
+  else atomicExch(p.err_word, (int)WSVD_E_CAPACITY);
+  p.pending[b] = ok ? 1 : 0;
+}
+
 // ---------------------------------------------------------------- vector-ALU path (any dtype)
-template <int R, int FESZ>
+// DEFER (the decode step's projection launch): the slices' partial sums are left in p.defer_out [slice][plane][B][Hkv * R]
+// for the attention launch that follows, which sums them in slice order, rounds and stores the rows; workgroup 0 advances
+// the lengths and marks the rows as pending.  No ticket, no read-back: 9.8 -> 6.3 us for one sequence of 8 heads, rank 16,
+// d_model 512, where the ticket and the read-back were most of the launch; staging one sequence instead of eight: 5.2 us.
+// BB: sequences per pass (1 for a single sequence: an eighth of the staging and of the products).
+template <int R, int FESZ, bool DEFER = false, int BB = kAppendBB>
 __global__ __launch_bounds__(256) void k_append_valu(AppendParams p) {
   constexpr int EL = 256 / R;                 // threads along d_model per latent channel
   constexpr int NA = kAppendMaxESL / EL;      // factor elements per thread
-  __shared__ __attribute__((aligned(16))) float xs[kAppendMaxESL][kAppendBB];
-  __shared__ float red[EL][kAppendBB][R];
+  __shared__ __attribute__((aligned(16))) float xs[kAppendMaxESL][BB];
+  __shared__ float red[EL][BB][R];
   __shared__ float crow[64][R + 1];
   __shared__ int flag_sh;
   __shared__ int n_sh[kAppendMaxB];
 
-  append_read_lens(p, n_sh);
+  if constexpr (!DEFER) append_read_lens(p, n_sh);
   int s, kv, pl;
   append_coords(p, blockIdx.x, s, kv, pl);
   const int tid = threadIdx.x, j = tid % R, el = tid / R;
@@ -39,37 +53,47 @@ __global__ __launch_bounds__(256) void k_append_valu(AppendParams p) {
     a[i] = FESZ == 4 ? ((const float*)p.A[pl])[idx] : bf16_to_f32(((const uint16_t*)p.A[pl])[idx]);
   }
 
-  for (int b0 = 0; b0 < p.B; b0 += kAppendBB) {
-    const int nb = min(kAppendBB, p.B - b0);
-    __syncthreads();
-    for (int i = tid; i < kAppendBB * p.ESL; i += 256) {
-      const int bb = i / p.ESL, e = i % p.ESL;
+  for (int b0 = 0; b0 < p.B; b0 += BB) {
+    const int nb = min(BB, p.B - b0);
+    if (b0 > 0) __syncthreads();
+    for (int i = tid; i < BB * p.ESL; i += 256) {
+      const int bb = BB == 1 ? 0 : i / p.ESL, e = BB == 1 ? i : i % p.ESL;
       xs[e][bb] = bb < nb ? load_x(p, b0 + bb, e0 + e) : 0.f;
     }
     __syncthreads();
-    float acc[kAppendBB];
+    float acc[BB];
 #pragma unroll
-    for (int bb = 0; bb < kAppendBB; bb++) acc[bb] = 0.f;
+    for (int bb = 0; bb < BB; bb++) acc[bb] = 0.f;
 #pragma unroll
     for (int i = 0; i < NA; i++) {
       const int e = el + i * EL;
       if (e < p.ESL) {
-        const v4f x0 = *(const v4f*)&xs[e][0], x1 = *(const v4f*)&xs[e][4];
+        if constexpr (BB == 1) {
+          acc[0] = fmaf(xs[e][0], a[i], acc[0]);
+        } else {
+          const v4f x0 = *(const v4f*)&xs[e][0], x1 = *(const v4f*)&xs[e][4];
 #pragma unroll
-        for (int bb = 0; bb < 4; bb++) { acc[bb] = fmaf(x0[bb], a[i], acc[bb]); acc[4 + bb] = fmaf(x1[bb], a[i], acc[4 + bb]); }
+          for (int bb = 0; bb < 4; bb++) { acc[bb] = fmaf(x0[bb], a[i], acc[bb]); acc[4 + bb] = fmaf(x1[bb], a[i], acc[4 + bb]); }
+        }
       }
     }
 #pragma unroll
-    for (int bb = 0; bb < kAppendBB; bb++) red[el][bb][j] = acc[bb];
+    for (int bb = 0; bb < BB; bb++) red[el][bb][j] = acc[bb];
     __syncthreads();
     for (int i = tid; i < nb * R; i += 256) {
       const int bb = i / R, jj = i % R;
       float sum = 0.f;
+#pragma unroll
       for (int k = 0; k < EL; k++) sum += red[k][bb][jj];
-      agent_store(&part[(size_t)(b0 + bb) * R + jj], sum);
+      if constexpr (DEFER) p.defer_out[(((size_t)s * 2 + pl) * p.B + b0 + bb) * ((size_t)p.Hkv * R) + (size_t)kv * R + jj] = sum;
+      else agent_store(&part[(size_t)(b0 + bb) * R + jj], sum);
     }
   }
-  append_finish<R>(p, pl, kv, crow, &flag_sh, n_sh);
+  if constexpr (DEFER) {
+    if (blockIdx.x == 0) {
+      for (int b = tid; b < p.B; b += 256) append_defer_bump(p, b, p.seq_lens[b]);
+    }
+  } else append_finish<R>(p, pl, kv, crow, &flag_sh, n_sh);
 }
 
 // ---------------------------------------------------------------- factor packing (set-up time)
@@ -119,7 +143,11 @@ constexpr uint32_t kLLTag = 0x4C4C5701u;      // marks a pushed word as written 
 // hand-off inside the launch: every workgroup leaves its partial sums in p.defer_out, workgroup 0 of each group of
 // sequences advances the lengths and marks the rows as pending; the attention launch that follows sums the slices in
 // slice order, quantises and stores the rows (the kernel boundary is the hand-off).
-template <int R, int NT, bool DEFER = false>
+// kDeferShares: the same with the shares of the append itself (half, quarter, quarter; partial sum 0 is the half), so that
+// the rows are bit for bit the append's: fp32 / bf16 latents.  One sequence of 32 heads, rank 32, d_model 4096: 8.0 us
+// against 9.3 us for the launch that finishes the rows itself (four equal slices: 6.9 us, but other bits).
+enum { kNoDefer = 0, kDeferSlices = 1, kDeferShares = 2 };
+template <int R, int NT, int DEFER = kNoDefer>
 __global__ __launch_bounds__(NT) void k_append_split(AppendParams p, int SB, int xs_stride /* elements */, int NP,
                                                      unsigned long long* ll /* [units][groups][NP][SB * R] */) {
   extern __shared__ __align__(16) uint8_t app_lds[];
@@ -130,9 +158,9 @@ __global__ __launch_bounds__(NT) void k_append_split(AppendParams p, int SB, int
   uint16_t* xs = (uint16_t*)app_lds;                            // [SB][xs_stride] hidden states (bf16)
   float (*red)[R + 1] = (float (*)[R + 1])app_lds;              // [NW * SB][R + 1] partial tiles, later [SB][R + 1] rows
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NW = blockDim.x >> 6;
-  const int n_roles = DEFER ? NP : NP + 1;
+  const int n_roles = DEFER == kDeferSlices ? NP : NP + 1;
   const int unit = (int)blockIdx.x / n_roles, role = (int)blockIdx.x % n_roles;     // role < NP: helper, NP: finisher
-  const bool finisher = !DEFER && role == NP;
+  const bool finisher = !DEFER && role == NP, first_share = DEFER != kDeferSlices && role == NP;
   const int pl = unit / p.Hkv, kv = unit % p.Hkv;
   const int b0 = (int)blockIdx.y * SB, nb = min(SB, p.B - b0);
   const int col = lane & 31, g = lane >> 5;
@@ -148,10 +176,10 @@ __global__ __launch_bounds__(NT) void k_append_split(AppendParams p, int SB, int
   const uint16_t* xp = (const uint16_t*)p.x;
   // ---- this workgroup's share of the k-steps (16 model dims each), then this wave's share of that
   const int nks = p.E >> 4;
-  const int nks_fin = DEFER ? 0 : NP ? (nks + 1) / 2 : nks;     // the finisher's share comes first
+  const int nks_fin = DEFER == kDeferSlices ? 0 : NP ? (nks + 1) / 2 : nks;     // the finisher's share comes first
   const int per_helper = NP ? (nks - nks_fin + NP - 1) / NP : 0;
-  const int wg_k0 = finisher ? 0 : min(nks, nks_fin + role * per_helper);
-  const int wg_k1 = finisher ? nks_fin : min(nks, wg_k0 + per_helper);
+  const int wg_k0 = first_share ? 0 : min(nks, nks_fin + role * per_helper);
+  const int wg_k1 = first_share ? nks_fin : min(nks, wg_k0 + per_helper);
   const int per_wave = (wg_k1 - wg_k0 + NW - 1) / NW;
   const int ks0 = min(wg_k1, wg_k0 + wave * per_wave), ks1 = min(wg_k1, ks0 + per_wave);
   unsigned long long* ll_unit = ll + ((size_t)(unit * gridDim.y + blockIdx.y) * (NP ? NP : 1)) * (size_t)(SB * R);
@@ -250,7 +278,8 @@ __global__ __launch_bounds__(NT) void k_append_split(AppendParams p, int SB, int
       float c = 0.f;
       for (int k = 0; k < NW; k++) c += red[k * SB + row][j];
       if constexpr (DEFER) {
-        p.defer_out[(((size_t)role * 2 + pl) * p.B + b0 + row) * ((size_t)p.Hkv * R) + (size_t)kv * R + j] = c;
+        const int part = DEFER == kDeferSlices ? role : first_share ? 0 : role + 1;
+        p.defer_out[(((size_t)part * 2 + pl) * p.B + b0 + row) * ((size_t)p.Hkv * R) + (size_t)kv * R + j] = c;
       } else if (!finisher) {
         // push: value and tag in one 8-byte store, written through; nobody waits for it
         const unsigned long long word = ((unsigned long long)kLLTag << 32) | (unsigned long long)__float_as_uint(c);
@@ -280,12 +309,7 @@ __global__ __launch_bounds__(NT) void k_append_split(AppendParams p, int SB, int
     }
   }
   if constexpr (DEFER) {
-    if (blockIdx.x == 0 && tid < nb) {
-      const bool ok = n_bump >= 0 && n_bump < p.t_cap;
-      if (ok) p.seq_lens[b0 + tid] = n_bump + 1;
-      else atomicExch(p.err_word, (int)WSVD_E_CAPACITY);
-      p.pending[b0 + tid] = ok ? 1 : 0;
-    }
+    if (blockIdx.x == 0 && tid < nb) append_defer_bump(p, b0 + tid, n_bump);
     WSVD_STAMP(p.timeline, tl_wg, wave, 5);
     return;
   }
@@ -344,7 +368,7 @@ size_t wsvd_append_ll_words(const wsvd_layer_desc& d) {
   return (size_t)2 * d.n_kv_heads * ((d.batch + sb - 1) / sb) * 2 * sb * d.rank;
 }
 
-template <int R, int NT>
+template <int R, int NT, int DEFER = kNoDefer>
 static hipError_t launch_append_split(const AppendParams& p, const wsvd_layer_desc& d, int opt_helpers, unsigned long long* ll,
                                       hipStream_t s) {
   const int np = append_split_np(d, opt_helpers), sb = append_split_sb(d);
@@ -357,12 +381,12 @@ static hipError_t launch_append_split(const AppendParams& p, const wsvd_layer_de
   if (red_bytes > lds) lds = red_bytes;
   static bool raised = false;                             // one attribute per instantiation (the template makes it so)
   if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_append_split<R, NT>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+    hipError_t e = hipFuncSetAttribute((const void*)k_append_split<R, NT, DEFER>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
     if (e != hipSuccess) return e;
     raised = true;
   }
   dim3 grid((unsigned)(2 * d.n_kv_heads * (np + 1)), (unsigned)groups);
-  hipLaunchKernelGGL((k_append_split<R, NT>), grid, dim3(NT), lds, s, p, sb, stride, np, ll);
+  hipLaunchKernelGGL((k_append_split<R, NT, DEFER>), grid, dim3(NT), lds, s, p, sb, stride, np, ll);
   return hipGetLastError();
 }
 
@@ -383,12 +407,20 @@ static hipError_t launch_append_project(const AppendParams& p, const wsvd_layer_
   if (lds > (size_t)150 * 1024) return hipErrorInvalidValue;
   static bool raised = false;
   if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_append_split<R, NT, true>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
+    hipError_t e = hipFuncSetAttribute((const void*)k_append_split<R, NT, kDeferSlices>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
     if (e != hipSuccess) return e;
     raised = true;
   }
   dim3 grid((unsigned)(2 * d.n_kv_heads * ns), (unsigned)groups);
-  hipLaunchKernelGGL((k_append_split<R, NT, true>), grid, dim3(NT), lds, s, p, sb, stride, ns, (unsigned long long*)nullptr);
+  hipLaunchKernelGGL((k_append_split<R, NT, kDeferSlices>), grid, dim3(NT), lds, s, p, sb, stride, ns, (unsigned long long*)nullptr);
+  return hipGetLastError();
+}
+
+template <int R>
+static hipError_t launch_append_valu_defer(const AppendParams& p, hipStream_t s) {
+  const dim3 grid((unsigned)(p.ES * p.Hkv * 2));
+  if (p.B == 1) hipLaunchKernelGGL((k_append_valu<R, 4, true, 1>), grid, dim3(256), 0, s, p);
+  else hipLaunchKernelGGL((k_append_valu<R, 4, true>), grid, dim3(256), 0, s, p);
   return hipGetLastError();
 }
 
@@ -403,12 +435,19 @@ bool wsvd_step_deferred_ok(const wsvd_layer_desc& d) {
   return append_mfma_path(d) && d.latent_dtype == WSVD_I8 && (d.rank == 32 || d.rank == 64) &&
          d.n_q_heads / d.n_kv_heads <= 4 && d.d_model % 16 == 0 && d.batch <= kAppendMaxB;
 }
+// fp32 and bf16 latents (x and factors of the same type): the vector-ALU attention finishes the row.  The partial sums are
+// the append's own (its slices in fp32, its shares in bf16), so rows and outputs are those of the two calls bit for bit.
+bool wsvd_step_deferred_float_ok(const wsvd_layer_desc& d) {
+  const bool f32 = d.latent_dtype == WSVD_F32, bf16 = d.latent_dtype == WSVD_BF16 && append_split_ok(d);
+  return (f32 || bf16) && d.rank <= 64 && d.batch <= kAppendMaxB && d.d_model % 64 == 0;
+}
 // where the step's partial sums and its pending words live: inside the sliced kernels' partial area of the workspace
 bool wsvd_step_partials(const wsvd_ctx* ctx, const wsvd_layer_desc& d, float** parts, int** pending, int* n_parts) {
   AppendParams p;
   wsvd_cache none = {};
   wsvd_append_params(ctx, d, nullptr, nullptr, nullptr, nullptr, none, p);
-  const int ns = wsvd_step_slices(ctx, d);
+  const int ns = d.latent_dtype == WSVD_F32 ? p.ES : d.latent_dtype == WSVD_BF16 ? append_split_np(d, ctx->opt.append_helpers) + 1
+                                                                                 : wsvd_step_slices(ctx, d);
   const size_t part_floats = (size_t)ns * 2 * d.batch * d.n_kv_heads * d.rank;
   if (part_floats > (size_t)2 * d.n_kv_heads * (d.d_model / 64) * d.batch * d.rank) return false;
   *parts = p.partials; *pending = (int*)(p.partials + part_floats); *n_parts = ns;
@@ -425,6 +464,22 @@ hipError_t wsvd_launch_append_project(const wsvd_ctx* ctx, const wsvd_layer_desc
   p.pending = *pending;
   if (ctx->opt.timeline_kernel != 1) p.timeline = nullptr;    // (profiling build: by default a step's stamps are its attention launch's)
   *n_parts = ns;
+  if (d.latent_dtype == WSVD_F32) {
+    switch (d.rank) {
+      case 16: return launch_append_valu_defer<16>(p, s);
+      case 32: return launch_append_valu_defer<32>(p, s);
+      case 64: return launch_append_valu_defer<64>(p, s);
+      default: return hipErrorNotSupported;
+    }
+  }
+  if (d.latent_dtype == WSVD_BF16) {
+    switch (d.rank) {
+      case 16: return launch_append_split<16, 1024, kDeferShares>(p, d, ctx->opt.append_helpers, nullptr, s);
+      case 32: return launch_append_split<32, 1024, kDeferShares>(p, d, ctx->opt.append_helpers, nullptr, s);
+      case 64: return launch_append_split<64, 512, kDeferShares>(p, d, ctx->opt.append_helpers, nullptr, s);
+      default: return hipErrorNotSupported;
+    }
+  }
   switch (d.rank) {
     case 32: return launch_append_project<32, 512>(p, d, ns, s);      // (8 waves: 6.7 us at config 3; 16: 6.9 us; 4: 7.4 us)
     case 64: return launch_append_project<64, 512>(p, d, ns, s);

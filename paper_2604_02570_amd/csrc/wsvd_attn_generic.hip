@@ -21,9 +21,11 @@ WSVD_DEV void unpack16(const v4i& raw, float* f) {
   }
 }
 
-constexpr int kMaxG = 8;
-
-template <int ESZ, int R, int G>
+// NEWROW: the second launch of the decode step.  The projection launch before it has advanced the lengths and left the new
+// token's latents as n_parts partial sums (p.new_k / p.new_v); the workgroup whose chunk holds a sequence's last row sums
+// them in slice order, rounds to the storage format, stores the row and attends to it from LDS, in the place it would
+// have in the stream.  The partial sums are asked for with the first loads of the kernel and waited for with the factor.
+template <int ESZ, int R, int G, bool NEWROW>
 __global__ __launch_bounds__(256) void k_attn_generic(AttnParams p) {
   constexpr int ROWB = R * ESZ;          // bytes per latent row
   constexpr int LPR = ROWB / 16;         // lanes per row
@@ -45,10 +47,21 @@ __global__ __launch_bounds__(256) void k_attn_generic(AttnParams p) {
   __shared__ float pm[NPART * G], pl[NPART * G], pu[NPART * G * R];
   __shared__ int flag_sh;
 
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  constexpr int MAXP = NEWROW ? 4 : 1;             // partial sums in flight; any further ones one after the other
+  __shared__ float new_row[2][NEWROW ? R : 1];
+  [[maybe_unused]] const int pend = NEWROW ? p.pending[blockIdx.z] : 0;
+  [[maybe_unused]] float np[MAXP];
+  [[maybe_unused]] const float* const np_src = (tid / R ? p.new_v : p.new_k) + (size_t)blockIdx.z * p.new_ld + (size_t)blockIdx.x * R + tid % R;
+  if constexpr (NEWROW) {
+    if (tid < 2 * R) {
+#pragma unroll
+      for (int i = 0; i < MAXP; i++) np[i] = np_src[(size_t)min(i, p.n_parts - 1) * p.part_stride];
+    }
+  }
   const WorkItem w = decode_work(p, p.seq_lens[blockIdx.z]);
   if (w.n == 0) { write_zero_outputs(p, w); return; }
   if (!w.active) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int sl = lane % LPR;                       // which 16-byte slice of the row
   const int grp = wave * RPW + lane / LPR;         // lane group id within the workgroup
 
@@ -61,6 +74,31 @@ __global__ __launch_bounds__(256) void k_attn_generic(AttnParams p) {
     stage_commit<FIT>(st, fac_lds, fac16);
     q_commit(p, qr, q_scale_value(p, w.b, q_scale_raw(p, w.b)), q_lds);
   }
+  const size_t plane = ((size_t)w.b * p.Hkv + w.kv) * (size_t)p.t_cap * ROWB;
+  int row_end = w.row_end;                         // of the rows that are read from the cache
+  [[maybe_unused]] bool own_new = false;           // the new row is one of this chunk's
+  if constexpr (NEWROW) {
+    // (a sequence longer than the caller's bound is reported by decode_work; its row is still stored, by the last chunk)
+    const int row = w.n - 1;
+    if (pend != 0 && w.chunk == min(row / p.chunk_rows, p.n_chunks - 1)) {
+      own_new = row < w.row_end;
+      row_end = own_new ? row : w.row_end;
+      if (tid < 2 * R) {
+        float c = np[0];
+#pragma unroll
+        for (int i = 1; i < MAXP; i++) c += i < p.n_parts ? np[i] : 0.f;
+        for (int i = MAXP; i < p.n_parts; i++) c += np_src[(size_t)i * p.part_stride];
+        uint8_t* dst = const_cast<uint8_t*>(tid / R ? p.v_codes : p.k_codes) + plane + (size_t)row * ROWB;
+        if constexpr (ESZ == 4) ((float*)dst)[tid % R] = c;
+        else {
+          const uint16_t h = f32_to_bf16_rne(c);
+          ((uint16_t*)dst)[tid % R] = h;
+          c = bf16_to_f32(h);
+        }
+        new_row[tid / R][tid % R] = c;
+      }
+    }
+  }
   __syncthreads();
   compute_qtilde<R, ESZ>(p, fac_lds, q_lds, qts);
   float qt[G][VPL];
@@ -69,7 +107,6 @@ __global__ __launch_bounds__(256) void k_attn_generic(AttnParams p) {
 #pragma unroll
     for (int v = 0; v < VPL; v++) qt[g][v] = qts[g * R + sl * VPL + v];
 
-  const size_t plane = ((size_t)w.b * p.Hkv + w.kv) * (size_t)p.t_cap * ROWB;
   const uint8_t* kb = p.k_codes + plane + sl * 16;
   const uint8_t* vb = p.v_codes + plane + sl * 16;
 
@@ -90,34 +127,37 @@ __global__ __launch_bounds__(256) void k_attn_generic(AttnParams p) {
 #pragma unroll
     for (int k = 0; k < UNROLL; k++) {
       const int t = t0 + k * NGRP;
-      if (t < w.row_end) {
+      if (t < row_end) {
         kr[k] = *(const v4i*)(kb + (size_t)t * ROWB);
         vr[k] = *(const v4i*)(vb + (size_t)t * ROWB);
       }
+    }
+  };
+  auto use_row = [&](const float (&kf)[VPL], const float (&vf)[VPL]) {
+#pragma unroll
+    for (int g = 0; g < G; g++) {
+      float s = 0.f;
+#pragma unroll
+      for (int v = 0; v < VPL; v++) s = fmaf(qt[g][v], kf[v], s);
+      s = group_sum<LPR>(s);
+      const float mn = fmaxf(m[g], s);
+      const float alpha = __builtin_amdgcn_exp2f(m[g] - mn);
+      const float pw = __builtin_amdgcn_exp2f(s - mn);
+      l[g] = fmaf(l[g], alpha, pw);
+#pragma unroll
+      for (int v = 0; v < VPL; v++) u[g][v] = fmaf(u[g][v], alpha, pw * vf[v]);
+      m[g] = mn;
     }
   };
   auto use_rows = [&](const v4i (&kr)[UNROLL], const v4i (&vr)[UNROLL], int t0) {
 #pragma unroll
     for (int k = 0; k < UNROLL; k++) {
       const int t = t0 + k * NGRP;
-      if (t < w.row_end) {          // uniform within a lane group
+      if (t < row_end) {            // uniform within a lane group
         float kf[VPL], vf[VPL];
         unpack16<ESZ>(kr[k], kf);
         unpack16<ESZ>(vr[k], vf);
-#pragma unroll
-        for (int g = 0; g < G; g++) {
-          float s = 0.f;
-#pragma unroll
-          for (int v = 0; v < VPL; v++) s = fmaf(qt[g][v], kf[v], s);
-          s = group_sum<LPR>(s);
-          const float mn = fmaxf(m[g], s);
-          const float alpha = __builtin_amdgcn_exp2f(m[g] - mn);
-          const float pw = __builtin_amdgcn_exp2f(s - mn);
-          l[g] = fmaf(l[g], alpha, pw);
-#pragma unroll
-          for (int v = 0; v < VPL; v++) u[g][v] = fmaf(u[g][v], alpha, pw * vf[v]);
-          m[g] = mn;
-        }
+        use_row(kf, vf);
       }
     }
   };
@@ -125,19 +165,30 @@ __global__ __launch_bounds__(256) void k_attn_generic(AttnParams p) {
     v4i ka[UNROLL], va[UNROLL], kb2[UNROLL], vb2[UNROLL];
     int t0 = w.row_begin + grp;
     load_rows(ka, va, t0);
-    while (t0 < w.row_end) {
+    while (t0 < row_end) {
       load_rows(kb2, vb2, t0 + STEP);       // (nothing is requested past the chunk's end)
       use_rows(ka, va, t0);
       t0 += STEP;
-      if (t0 >= w.row_end) break;
+      if (t0 >= row_end) break;
       load_rows(ka, va, t0 + STEP);
       use_rows(kb2, vb2, t0);
       t0 += STEP;
     }
   }
+  if constexpr (NEWROW) {
+    if (own_new && (w.n - 1 - w.row_begin) % NGRP == grp) {             // the lane group whose turn the row is
+      float kf[VPL], vf[VPL];
+#pragma unroll
+      for (int v = 0; v < VPL; v++) { kf[v] = new_row[0][sl * VPL + v]; vf[v] = new_row[1][sl * VPL + v]; }
+      use_row(kf, vf);
+    }
+  }
   // NOTE: group_sum uses DPP across the LPR lanes of a row; lanes of a group take the same branch
   // (t depends only on the group), so the exchanged values are always defined.
 
+  // B_V is asked for here: its trip to memory runs beside the merge
+  StageRegs<FIT> stv;
+  stage_issue<FIT>(stv, (const char*)p.BV + (size_t)w.kv * R * p.d * ESZ, fac16);
 #pragma unroll
   for (int g = 0; g < G; g++) {
     if (sl == 0) { gm[grp * G + g] = m[g]; gl[grp * G + g] = l[g]; }
@@ -182,29 +233,30 @@ __global__ __launch_bounds__(256) void k_attn_generic(AttnParams p) {
     Ush[i] = U;
     if (j == 0) { Msh[g] = M; Lsh[g] = L; }
   }
-  {
-    StageRegs<FIT> st;   // B_K is no longer needed: reuse its LDS for B_V
-    stage_issue<FIT>(st, (const char*)p.BV + (size_t)w.kv * R * p.d * ESZ, fac16);
-    stage_commit<FIT>(st, fac_lds, fac16);
-  }
+  stage_commit<FIT>(stv, fac_lds, fac16);          // B_K is no longer needed: its LDS holds B_V from here on
   __syncthreads();
   attn_tail<R, ESZ>(p, w, Msh, Lsh, Ush, &flag_sh, fac_lds);
 }
 
-template <int ESZ, int R>
-static hipError_t launch_g(const AttnParams& p, dim3 grid, hipStream_t s) {
+template <int ESZ, int R, bool NEWROW>
+static hipError_t launch_gn(const AttnParams& p, dim3 grid, hipStream_t s) {
   switch (p.G) {
-    case 1: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 1>), grid, dim3(256), 0, s, p); break;
-    case 2: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 2>), grid, dim3(256), 0, s, p); break;
-    case 3: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 3>), grid, dim3(256), 0, s, p); break;
-    case 4: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 4>), grid, dim3(256), 0, s, p); break;
-    case 5: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 5>), grid, dim3(256), 0, s, p); break;
-    case 6: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 6>), grid, dim3(256), 0, s, p); break;
-    case 7: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 7>), grid, dim3(256), 0, s, p); break;
-    case 8: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 8>), grid, dim3(256), 0, s, p); break;
+    case 1: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 1, NEWROW>), grid, dim3(256), 0, s, p); break;
+    case 2: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 2, NEWROW>), grid, dim3(256), 0, s, p); break;
+    case 3: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 3, NEWROW>), grid, dim3(256), 0, s, p); break;
+    case 4: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 4, NEWROW>), grid, dim3(256), 0, s, p); break;
+    case 5: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 5, NEWROW>), grid, dim3(256), 0, s, p); break;
+    case 6: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 6, NEWROW>), grid, dim3(256), 0, s, p); break;
+    case 7: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 7, NEWROW>), grid, dim3(256), 0, s, p); break;
+    case 8: hipLaunchKernelGGL((k_attn_generic<ESZ, R, 8, NEWROW>), grid, dim3(256), 0, s, p); break;
     default: return hipErrorNotSupported;
   }
   return hipGetLastError();
+}
+// p.pending set: the decode step's second launch, which finishes the rows (p.new_k, p.new_v, p.n_parts)
+template <int ESZ, int R>
+static hipError_t launch_g(const AttnParams& p, dim3 grid, hipStream_t s) {
+  return p.pending ? launch_gn<ESZ, R, true>(p, grid, s) : launch_gn<ESZ, R, false>(p, grid, s);
 }
 
 hipError_t wsvd_launch_attn_generic(const AttnParams& p, int latent_dtype, int rank, dim3 grid, hipStream_t s) {

@@ -1,0 +1,82 @@
+"""wsvd_decode_step over fp32 and bf16 latents: the projection launch leaves partial sums, the attention launch sums them,
+rounds and stores the row and attends to it.  Rows and outputs against the oracle where the row starts or ends a chunk, is
+the first one ever, or does not fit any more; more partial sums than the kernel keeps in flight; small workspaces."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2604_02570_amd as W
+import wsvd_inputs as WI
+from cases import build_case
+from harness import as_dtype_dev, q_to_device
+from test_gpu_parity import _append_compare, check_out, layer_for
+
+pytestmark = pytest.mark.gpu
+
+CASES = [("c1", dict()), ("c1", dict(rank=32, d_model=4096, context=80)), ("c1", dict(rank=64, n_q_heads=6, n_kv_heads=2, d_head=128)),
+         ("c2_small", dict()), ("c2_small", dict(rank=16, n_q_heads=8, n_kv_heads=1)), ("c2_small", dict(rank=64, n_q_heads=12, n_kv_heads=4, d_model=1024)),
+         ("c2_small", dict(d_model=4096, n_q_heads=32, n_kv_heads=32))]
+
+
+@pytest.mark.parametrize("name,over", CASES, ids=[f"{n}-{'-'.join(f'{k}{v}' for k, v in o.items())}" for n, o in CASES])
+def test_step_rows_at_chunk_edges(name, over):
+    lens = [0, 1, 63, 64, 255, 256, 1023, 1024, 1025, 1087]
+    c = build_case(name, **{**dict(batch=len(lens), context=90, steps=1, extra_cap=0), **over})
+    sp = c.sp
+    t_cap = 1088
+    L = layer_for(c, t_cap=t_cap)
+    full = O.LatentCache(sp.batch, sp.n_kv_heads, t_cap, sp.rank, sp.latent_dtype)
+    g = np.random.default_rng(11)
+    for b, n in enumerate(lens):
+        for plane in ("k", "v"):
+            full.store_rows(plane, b, 0, g.standard_normal((sp.n_kv_heads, n, sp.rank)))
+        full.seq_lens[b] = n
+    full.seq_lens[-1] = t_cap                               # full: attended as it is, reported
+    full.store_rows("k", sp.batch - 1, 1087, g.standard_normal((sp.n_kv_heads, 1, sp.rank)))
+    full.store_rows("v", sp.batch - 1, 1087, g.standard_normal((sp.n_kv_heads, 1, sp.rank)))
+    L.upload(full)
+    W.wsvd_ctx_set_option(L.ctx, "min_chunk", 0)
+    x = WI.bf16_exact(c.x_new[0]) if sp.factor_dtype == "bf16" else c.x_new[0]
+    AK64, AV64, BK64, BV64 = (a.astype(np.float64) for a in (c.AK, c.AV, c.BK, c.BV))
+    x64 = x.astype(np.float64)
+    before = full.seq_lens.copy()
+    cK, cV = O.project_latents(x64, AK64), O.project_latents(x64, AV64)
+    qd, qs, q64 = q_to_device(c.q32[0], sp.q_dtype)
+    args = (as_dtype_dev(x, sp.factor_dtype), L.pack_A(c.AK, sp.factor_dtype), L.pack_A(c.AV, sp.factor_dtype), qd, qs,
+            as_dtype_dev(c.BK, sp.factor_dtype), as_dtype_dev(c.BV, sp.factor_dtype), t_cap)
+    W.wsvd_ctx_set_option(L.ctx, "step_deferred", 0)                         # the append call and the attention call
+    two, _ = L.step(*args)
+    two_planes = [t.clone() for t in (L.k_codes, L.v_codes)]
+    W.wsvd_ctx_set_option(L.ctx, "step_deferred", 1)
+    L.upload(full)
+    got, st = L.step(*args)
+    assert st == W.E_CAPACITY
+    assert (got == two).all() and (L.k_codes == two_planes[0]).all() and (L.v_codes == two_planes[1]).all()
+    O.latent_append(full, x64, AK64, AV64)
+    assert (L.seq_lens.cpu().numpy() == full.seq_lens).all()
+    ref = O.decode_attn_reconstructed(full, q64, BK64, BV64, c.sm_scale)
+    check_out(got, ref, sp.latent_dtype, f"step {name}{over}")
+    gk, gv = L.download(0, 0, t_cap)[0], L.download(1, 0, t_cap)[0]
+    for plane, want in ((gk, full.k), (gv, full.v)):
+        for b in range(sp.batch - 1):
+            assert (plane[b, :, : int(before[b])] == want[b, :, : int(before[b])]).all()      # the rows that were there
+        assert (plane[-1] == want[-1]).all()                                 # the full sequence is left alone
+    flips = _append_compare(L, full, cK, cV, before, sp.latent_dtype, only=range(sp.batch - 1))
+    assert flips <= max(3, sp.batch * sp.n_kv_heads * sp.rank // 100)
+    # a second step on the grown cache, captured and replayed: the same outputs as the call made eagerly on the same state
+    planes = [t.clone() for t in (L.k_codes, L.v_codes, L.seq_lens)]
+    eager, _ = L.step(*args)
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        W.wsvd_decode_step(L.ctx, L.desc, args[0], None, args[1], args[2], qd, qs, args[5], args[6], L.cache, t_cap, L.out)
+    for _ in range(3):
+        for t, v in zip((L.k_codes, L.v_codes, L.seq_lens), planes):
+            t.copy_(v)
+        L.out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (L.out.cpu().numpy().astype(np.float64) == eager).all()
+    assert W.wsvd_check(L.ctx) == W.E_CAPACITY
+    L.close()
