@@ -95,20 +95,20 @@ __global__ __launch_bounds__(256) void k_quantize_act_i8(const void* __restrict_
 // per element as the kernel above (max is exact in any order), so the stored bits are identical.
 constexpr int kActThreads = 1024;
 constexpr int kActPasses = 4;
-template <int ESZ>   // 4: fp32, 2: bf16
+template <int ESZ, int PASSES>   // ESZ 4: fp32, 2: bf16; PASSES: what the row needs, a surplus pass would cost its loads
 __global__ __launch_bounds__(kActThreads) void k_quantize_act_i8_row(const void* __restrict__ x, int n16 /* 16-byte units per row */,
                                                                       int8_t* __restrict__ codes, uint16_t* __restrict__ scale) {
   constexpr int EPU = 16 / ESZ;      // elements per 16-byte unit
   __shared__ float red[kActThreads / 64];
   const int tid = threadIdx.x;
   const v4i* src = (const v4i*)x + (size_t)blockIdx.x * n16;
-  v4i raw[kActPasses];
+  v4i raw[PASSES];
 #pragma unroll
-  for (int it = 0; it < kActPasses; it++) raw[it] = src[min(it * kActThreads + tid, n16 - 1)];   // unconditional, clamped
-  float f[kActPasses][EPU];
+  for (int it = 0; it < PASSES; it++) raw[it] = src[min(it * kActThreads + tid, n16 - 1)];   // unconditional, clamped
+  float f[PASSES][EPU];
   float a = 0.f;
 #pragma unroll
-  for (int it = 0; it < kActPasses; it++)
+  for (int it = 0; it < PASSES; it++)
 #pragma unroll
     for (int e = 0; e < EPU; e++) {
       if (ESZ == 4) f[it][e] = __int_as_float(raw[it][e]);
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_act_i8_row(const void*
   const float sc = f16_bits_to_f32(sh);
   uint32_t* dst = (uint32_t*)(codes + (size_t)blockIdx.x * n16 * EPU);
 #pragma unroll
-  for (int it = 0; it < kActPasses; it++) {
+  for (int it = 0; it < PASSES; it++) {
     const int u = it * kActThreads + tid;
     if (u < n16) {
 #pragma unroll
@@ -154,8 +154,17 @@ hipError_t wsvd_launch_quantize_act_i8(const void* x, int x_dtype, int64_t rows,
                     cols / epu <= (int64_t)kActThreads * kActPasses && ((uintptr_t)x & 15u) == 0 && ((uintptr_t)codes & 3u) == 0;
   if (fast) {
     const int n16 = (int)(cols / epu);
-    if (esz == 4) hipLaunchKernelGGL((k_quantize_act_i8_row<4>), dim3((unsigned)rows), dim3(kActThreads), 0, s, x, n16, codes, (uint16_t*)scale_f16);
-    else hipLaunchKernelGGL((k_quantize_act_i8_row<2>), dim3((unsigned)rows), dim3(kActThreads), 0, s, x, n16, codes, (uint16_t*)scale_f16);
+    const dim3 grid((unsigned)rows), block(kActThreads);
+    uint16_t* sc = (uint16_t*)scale_f16;
+#define WSVD_QUANT_ROW(P)                                                                                       \
+  if (esz == 4) hipLaunchKernelGGL((k_quantize_act_i8_row<4, P>), grid, block, 0, s, x, n16, codes, sc);        \
+  else hipLaunchKernelGGL((k_quantize_act_i8_row<2, P>), grid, block, 0, s, x, n16, codes, sc)
+    switch ((n16 + kActThreads - 1) / kActThreads) {
+      case 1: WSVD_QUANT_ROW(1); break;
+      case 2: WSVD_QUANT_ROW(2); break;
+      default: WSVD_QUANT_ROW(kActPasses); break;
+    }
+#undef WSVD_QUANT_ROW
   } else {
     hipLaunchKernelGGL(k_quantize_act_i8, dim3((unsigned)rows), dim3(256), 0, s, x, x_dtype, cols, codes, (uint16_t*)scale_f16);
   }

@@ -1,0 +1,30 @@
+"""Edges of the row kernels' pass counts and of the latent store's look-ahead: the oracle comparisons of the neighbouring
+files at the sizes where a wrong count would show."""
+import pytest
+
+import test_gpu_block as TB
+import test_gpu_layer as TL
+import test_gpu_parity as TP
+
+pytestmark = pytest.mark.gpu
+
+# 1024 threads x 4 channels a pass (16 bytes of the row each): one element on either side of every pass boundary
+EDGES = [4092, 4096, 4100, 8192, 8196, 12288, 12292]
+
+
+@pytest.mark.parametrize("cols", EDGES)
+def test_rmsnorm_and_swiglu_pass_edges(cols):
+    TL.test_rmsnorm_quant_matches_oracle(2, cols, cols % 8 == 0)
+    TL.test_rmsnorm_quant_matches_oracle(3, cols, cols % 8 != 0)
+    TL.test_swiglu_quant_matches_oracle(2, cols)
+
+
+@pytest.mark.parametrize("cols,dt", [(c, "f32") for c in EDGES] + [(c, "bf16") for c in (8184, 8192, 8200, 16384, 16392)])
+def test_quantize_act_pass_edges(cols, dt):
+    TP.test_quantize_act_i8_bit_exact(3, cols, dt)
+
+
+# 2 Hkv r latents per sequence over 1024 threads, four of them requested ahead: below, at and past that count
+@pytest.mark.parametrize("hkv,r", [(1, 32), (16, 32), (17, 32), (32, 64), (33, 64)])
+def test_latent_store_look_ahead_edges(hkv, r):
+    TB.test_latent_store_matches_oracle("c3_small", dict(n_q_heads=hkv, n_kv_heads=hkv, rank=r, batch=3, context=70))
