@@ -1,5 +1,5 @@
-"""Edges of the row kernels' pass counts and of the latent store's look-ahead: the oracle comparisons of the neighbouring
-files at the sizes where a wrong count would show."""
+"""Edges of the row kernels' pass counts, of the latent store's look-ahead and of the append's walk over the hidden states:
+the oracle comparisons of the neighbouring files at the sizes where a wrong count would show."""
 import pytest
 
 import test_gpu_block as TB
@@ -28,3 +28,11 @@ def test_quantize_act_pass_edges(cols, dt):
 @pytest.mark.parametrize("hkv,r", [(1, 32), (16, 32), (17, 32), (32, 64), (33, 64)])
 def test_latent_store_look_ahead_edges(hkv, r):
     TB.test_latent_store_matches_oracle("c3_small", dict(n_q_heads=hkv, n_kv_heads=hkv, rank=r, batch=3, context=70))
+
+
+# (batch, d_model): shares of the hidden states with fewer and more 16-byte pieces per row than threads, walks that do and
+# do not divide the workgroup, both group sizes and a partly filled last group
+@pytest.mark.parametrize("batch,d_model", [(1, 64), (5, 192), (17, 1088), (33, 3584), (16, 4160), (9, 16448)])
+@pytest.mark.parametrize("name,rank", [("c3_small", 32), ("c3_small", 64), ("c4_small", 32), ("c2_small", 32)])
+def test_append_walk_edges(name, rank, batch, d_model):
+    TP.test_append_matches_oracle(name, dict(rank=rank, n_q_heads=2, n_kv_heads=2, batch=batch, d_model=d_model, context=40))
