@@ -46,9 +46,10 @@ WSVD_DEV float block_max(float v, float* red) {
 // int8 codes of 4 values under the activation rule (scale = fp16(max / 127), guarded; round to nearest even; clamp)
 WSVD_DEV uint32_t pack_codes(const v4f& f, float sc) {
   uint32_t pk = 0;
+  const float inv = 1.0f / sc;
 #pragma unroll
   for (int e = 0; e < 4; e++) {
-    float v = __builtin_rintf(f[e] / sc);
+    float v = __builtin_rintf(div_by_scale(f[e], sc, inv));
     v = fminf(fmaxf(v, -127.f), 127.f);
     pk |= ((uint32_t)(int)v & 0xFFu) << (8 * e);
   }

@@ -66,7 +66,7 @@ WSVD_DEV void store_row_i8(const ProjectParams& p, const v16f (&a)[RT], int pl, 
   m = fmaxf(m, __shfl_xor(m, 32));
   uint16_t sh = 0x3C00u;
   if (m != 0.f) sh = guard_scale_f16(m / 127.0f);
-  const float sc = f16_bits_to_f32(sh);
+  const float sc = f16_bits_to_f32(sh), inv = 1.0f / sc;
   if (!on) return;
   const ProjRow pr = project_row(p, pl, seq, kv, t, R);
   if (!pr.ok) return;
@@ -78,7 +78,7 @@ WSVD_DEV void store_row_i8(const ProjectParams& p, const v16f (&a)[RT], int pl, 
       int q[4];
 #pragma unroll
       for (int jj = 0; jj < 4; jj++) {
-        q[jj] = (int)fminf(fmaxf(__builtin_rintf(a[rt][4 * m4 + jj] / sc), -127.f), 127.f);
+        q[jj] = (int)fminf(fmaxf(__builtin_rintf(div_by_scale(a[rt][4 * m4 + jj], sc, inv)), -127.f), 127.f);
         pk |= ((uint32_t)q[jj] & 0xFFu) << (8 * jj);
       }
       const int j0 = 32 * rt + 8 * m4 + 4 * g2;                         // channels j0 .. j0 + 3
@@ -104,7 +104,7 @@ WSVD_DEV void store_row_i4(const ProjectParams& p, const v16f& a, int pl, int se
   float z = 0.f;
   const bool flat = (hi == lo);
   if (!flat) sh = guard_scale_f16((hi - lo) / 15.0f);
-  const float sc = f16_bits_to_f32(sh);
+  const float sc = f16_bits_to_f32(sh), inv = 1.0f / sc;
   if (!flat) z = fminf(fmaxf(__builtin_rintf(-lo / sc), 0.f), 15.f);
   const int zi = (int)z;
   ProjRow pr = {nullptr, 0, t, false};
@@ -114,7 +114,7 @@ WSVD_DEV void store_row_i4(const ProjectParams& p, const v16f& a, int pl, int se
     int q[4];
 #pragma unroll
     for (int jj = 0; jj < 4; jj++) {
-      const float v = fminf(fmaxf(__builtin_rintf(a[4 * m4 + jj] / sc), -64.f), 64.f);
+      const float v = fminf(fmaxf(__builtin_rintf(div_by_scale(a[4 * m4 + jj], sc, inv)), -64.f), 64.f);
       const int qq = (int)v + zi;
       q[jj] = qq < 0 ? 0 : (qq > 15 ? 15 : qq);
     }

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_act_i8_row(const void*
   for (int k = 1; k < kActThreads / 64; k++) a = fmaxf(a, red[k]);
   uint16_t sh = 0x3C00u;
   if (a != 0.f) sh = guard_scale_f16(a / 127.0f);
-  const float sc = f16_bits_to_f32(sh);
+  const float sc = f16_bits_to_f32(sh), inv = 1.0f / sc;
   uint32_t* dst = (uint32_t*)(codes + (size_t)blockIdx.x * n16 * EPU);
 #pragma unroll
   for (int it = 0; it < PASSES; it++) {
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(kActThreads) void k_quantize_act_i8_row(const void*
         uint32_t pk = 0;
 #pragma unroll
         for (int e = 0; e < 4; e++) {
-          float v = __builtin_rintf(f[it][w4 * 4 + e] / sc);
+          float v = __builtin_rintf(div_by_scale(f[it][w4 * 4 + e], sc, inv));
           v = fminf(fmaxf(v, -127.f), 127.f);
           pk |= ((uint32_t)(int)v & 0xFFu) << (8 * e);
         }
