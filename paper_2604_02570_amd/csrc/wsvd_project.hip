@@ -507,14 +507,14 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   //   11: 128 channels x 32 tokens while that is at most two workgroups per CU;
   //   22: 256 x 64 while the 256 x 256 tiles of the staged kernel would leave more than a third of the CUs idle;
   //   2 : 256 x 256 tiles, eight waves (1: four waves; 44 / 42 / 24 / 21: the kernel without LDS, also where a sequence's
-  //       hidden states take 2^31 bytes or more).  The "project_shape" option asks for 1, 2, 44, 42, 24 or 21 (tuning, tests).
+  //       hidden states take 2^31 bytes or more).  The "project_shape" option asks for any of them (tuning, tests).
   const long long work = (long long)n_seq * n_tok * d.n_kv_heads * d.rank;
   const bool staged_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
   const long long ch = 2LL * d.n_kv_heads * d.rank;
   const long long small_wgs = (ch + 127) / 128 * ((n_tok + 31) / 32) * n_seq, big_wgs = (ch + 255) / 256 * ((n_tok + 255) / 256) * n_seq;
   int shape = ctx->opt.project_shape;
   if (!shape) shape = !staged_ok ? 44 : small_wgs <= 512 ? 11 : big_wgs <= 160 ? 22 : 2;
-  if ((shape == 1 || shape == 2) && !staged_ok) shape = 44;
+  if ((shape == 1 || shape == 2 || shape == 11 || shape == 22) && !staged_ok) shape = 44;
   hipError_t e = hipSuccess;
   if (d.rank > 64) {
     // ranks 96 / 128: a wave owns the 3 / 4 channel tiles of one head and 1 or 4 token tiles

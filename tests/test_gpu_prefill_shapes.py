@@ -54,6 +54,16 @@ def test_prompt_projection_tile_rule(name, n, over):
     _prompt(name, 0, n, **{**dict(batch=3, context=120), **over})
 
 
+# the two tile kernels with hidden states through LDS keep four chunks of 64 model dims in flight: fewer chunks than that, a
+# last round that is not full, and (70 tokens of 4 sequences in 64-token tiles, 40 in 32-token tiles) a number of token groups
+# that is a multiple of the 8 dies
+@pytest.mark.parametrize("d_model", [64, 128, 192, 320, 576])
+@pytest.mark.parametrize("shape,n", [(11, 40), (22, 70), (11, 33), (22, 65)])
+@pytest.mark.parametrize("name,over", [("c3_small", dict()), ("c3_small", dict(rank=64)), ("c4_small", dict(ragged=(60, 120)))], ids=["i8", "i8-r64", "i4"])
+def test_prompt_projection_chunk_tails(name, over, shape, n, d_model):
+    _prompt(name, shape, n, **{**dict(batch=4 if n in (40, 70) else 3, context=120, d_model=d_model), **over})
+
+
 # query rows per kv head at the edges of the 32-row waves and of the 1 / 2 / 4 waves that share a workgroup's cache blocks;
 # batch and heads choose the workgroup shape (256 and 1536 waves of rank 32, 768 of rank 64 are the limits of the rule)
 ATTN_SHAPES = [("c3_small", 9, 0, dict()), ("c3_small", 31, 2, dict(context=700)), ("c3_small", 33, 0, dict(d_head=64, context=65)),
