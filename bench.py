@@ -80,8 +80,8 @@ def parse():
                     help="c5: wsvd_latent_store + wsvd_decode_attn instead of the single-launch wsvd_decode_attn_store")
     ap.add_argument("--linear-direct", action="store_true",
                     help="W4A8 linear layers read their operands straight from memory instead of staging them through LDS (tuning)")
-    ap.add_argument("--project-shape", type=int, default=0, choices=[0, 1, 2, 11, 21, 22, 24, 42, 44],
-                    help="prefill: channel tiles x token tiles per wavefront of the tiled projection (tuning; 0 = the library's choice)")
+    ap.add_argument("--project-shape", type=int, default=0, choices=[0, 2, 11, 22, 44],
+                    help="prefill: tile shape of the projection, the project_shape option of wsvd_test.h (tuning; 0 = the library's choice)")
     ap.add_argument("--timeline", action="store_true",
                     help="c3 attention only, through the profiling build of the library (libwsvd_timeline.so): prints when, "
                          "relative to the first wavefront's start, the wavefronts of a launch pass the kernel's marked points")

@@ -24,7 +24,8 @@ struct ProjectParams {
   int* seq_lens;
   int* err_word;
   int Hkv, E, t_cap, n_tok, seq0;   // direct kernel: grid z = sequence - seq0
-  int n_cg, tg_seq, n_tg;           // staged kernel: channel groups, token groups per sequence and in all
+  int n_cg, tg_seq, n_tg;           // tile kernels: channel groups, token groups per sequence and in all
+  bool token_affine;                // tile kernels: see project_groups
   // paged cache only (else null): codes / meta are pools of n_pages pages, a page = page_rows rows of every kv head in the
   // layout of a contiguous plane; block_table [B][max_pages]
   const int* block_table;
@@ -220,8 +221,8 @@ __global__ __launch_bounds__(256) void k_prefill_project(ProjectParams p) {
   project_store<R, CT, TT, I4>(p, acc, ct0, tb, seq, n0);
 }
 
-// The same projection with both operands staged through LDS: a workgroup of 4 waves (2 x 2, each 4 x 4 tiles) owns
-// 256 channels x 256 tokens.  Per chunk of 64 model dims it copies 32 KiB of the factor image (already in operand order)
+// The same projection with both operands staged through LDS: a workgroup of 8 waves (2 x 4, each 4 x 2 tiles) owns
+// 256 channels x 256 tokens (4 waves of 4 x 4 tiles: 3 % slower).  Per chunk of 64 model dims it copies 32 KiB of the factor image (already in operand order)
 // and 256 whole 128-byte lines of hidden states (rows padded to 144 bytes in LDS, which makes the operand reads free of
 // bank conflicts), so that the first-level cache sees whole lines once per workgroup instead of 32-byte pieces once per
 // wave.  Two LDS stages: the next chunk travels global -> registers during the products of the current one and is
@@ -231,18 +232,25 @@ constexpr int kProjKC = 64, kProjXRow = 144;
 constexpr int kProjABytes = 8 * 4 * 1024, kProjXBytes = 256 * kProjXRow, kProjStage = kProjABytes + kProjXBytes;
 
 // Workgroup -> (channel group, token group).  Consecutive workgroup ids land on different XCDs (8 of them, each with
-// its own L2): when the number of token groups allows it, XCD i takes the token groups = i (mod 8), so a line of hidden
-// states is fetched by one XCD only, and the workgroups running together on an XCD cover all channel groups of a few
-// token groups, walking through the factors in step.
+// its own L2).  Token-affine: XCD i takes the token groups = i (mod 8), so a line of hidden states is fetched by one XCD
+// only and every XCD walks through all factors.  Otherwise the channel groups go round: with a number of them that shares
+// factors with 8, an XCD sees the same few channel groups all the time and all tokens.  The 256 x 256 tiles are
+// token-affine where the number of token groups allows it (either way within 2 %).  The smaller tiles keep the factors with
+// an XCD, unless their groups are odd in number (each XCD would see all of them anyway) or all factors fit an L2 and the
+// tokens are the larger operand.  us per call, factors / tokens kept, 32 kv heads of rank 32, d_model 4096 (16.8 MB of
+// factors), 128 x 32 tiles: 16 x 3 tokens 21 / 27, 64 x 16 61 / 79, 2 x 2048 129 / 164; rank 64: 16 x 16 35 / 46, 64 x 4
+// 95 / 154, 8 x 1024 401 / 905; 18 heads of rank 64 (9 groups): 16 x 64 66 / 57; 16 heads of rank 32, d_model 2048 (4.2 MB):
+// 16 x 16 13.6 / 16.2, 8 x 1024 75 / 70; 8 heads of rank 64, d_model 4096 (8.4 MB): 16 x 16 32 / 35, 8 x 700 85 / 80.
 WSVD_DEV void project_groups(const ProjectParams& p, int& cg, int& tg) {
   const int L = blockIdx.x;
-  if (p.n_tg % 8 == 0) { const int sl = L >> 3; cg = sl % p.n_cg; tg = (sl / p.n_cg) * 8 + (L & 7); }
+  if (p.token_affine) { const int sl = L >> 3; cg = sl % p.n_cg; tg = (sl / p.n_cg) * 8 + (L & 7); }
   else { cg = L % p.n_cg; tg = L / p.n_cg; }
 }
 
-template <int R, int WAVES, bool I4>
-__global__ __launch_bounds__(64 * WAVES) void k_prefill_project_lds(ProjectParams p) {
+template <int R, bool I4>
+__global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
   extern __shared__ __align__(16) uint8_t proj_lds[];
+  constexpr int WAVES = 8;
   constexpr int RT = R / 32, CT = 4, TT = 16 / WAVES;                   // 2 x (WAVES / 2) waves, each 4 x TT tiles
   constexpr int NT = 64 * WAVES, NLD = 2048 / NT;                       // threads; 16-byte pieces of A (and of x) per thread and chunk
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g2 = lane >> 5;
@@ -344,14 +352,9 @@ __global__ __launch_bounds__(64 * WAVES) void k_prefill_project_lds(ProjectParam
 // every wave multiplies with all of the workgroup's tokens.  DEPTH chunks of 64 model dims are on their way in registers,
 // two LDS stages of hidden states take turns, one barrier per chunk.  For problems that do not fill the chip with 256 x 256
 // tiles: bound by the chain of a chunk (barrier, LDS read, products), so more and smaller workgroups win until they are
-// two to a CU, then the re-reading of the operands decides.  us per call (length update of 4-5 us included), d_model 4096,
-// 32 kv heads of rank 32; old = the kernel without LDS, 2 x 1 tiles per wave (below 2^22 latents) / four-wave 256 x 256:
-//   tokens               11     200    3 x 333   4 x 500   2 x 2048   8 x 1024   16 x 2048
-//   128 x 32  (1, 1)     19.0   19.8    49.2      84.6       161        334        1276
-//   256 x 64  (2, 2)     38.7   40.4    44.4      49.7        82        150         627
-//   256 x 256             100    105     109       108       112        134         543
-//   old                  37.4   51.0    84.4       103       120        139         553
-// (Both operands through LDS with 2 x 2 waves: 23.2 us at 11 and 49-51 us at 3 x 333 tokens.)
+// two to a CU, then the re-reading of the operands decides (project_shape_rule has the figures).  The kernel without LDS in
+// 2 x 1 tiles, which served these sizes before: 50 us at 1 x 200, 83 at 3 x 333, 58 at 64 x 4 and 97 at 64 x 32 tokens of
+// rank 32.  (Both operands through LDS with 2 x 2 waves: 23.2 us at 11 and 49-51 us at 3 x 333 tokens.)
 template <int R, int CT, int TT, bool I4>
 __global__ __launch_bounds__(256) void k_prefill_project_direct(ProjectParams p) {
   constexpr int RT = R / 32, DEPTH = 4;                                 // (2 or 8 chunks ahead: within 5 %)
@@ -461,24 +464,59 @@ void launch_project(const ProjectParams& p, int n_seq, hipStream_t s) {
   hipLaunchKernelGGL((k_prefill_project<R, CT, TT, WC, I4>), grid, dim3(256), 0, s, p);
 }
 
+void project_grid(ProjectParams& p, int n_seq, int ch_wg, int tok_wg, int R) {
+  p.n_cg = (2 * p.Hkv * R + ch_wg - 1) / ch_wg; p.tg_seq = (p.n_tok + tok_wg - 1) / tok_wg; p.n_tg = p.tg_seq * n_seq;
+  p.token_affine = p.n_tg % 8 == 0;
+}
+
 template <int R, int CT, int TT, bool I4 = false>
 void launch_project_direct(ProjectParams p, int n_seq, hipStream_t s) {
-  const int tiles = 2 * p.Hkv * (R / 32);
-  p.n_cg = (tiles + 4 * CT - 1) / (4 * CT); p.tg_seq = (p.n_tok + 32 * TT - 1) / (32 * TT); p.n_tg = p.tg_seq * n_seq;
+  project_grid(p, n_seq, 128 * CT, 32 * TT, R);
+  // (which operand stays with an XCD: see project_groups)
+  const long long ch = 2LL * p.Hkv * R;
+  const bool l2_holds_factors = ch * p.E * 2 <= (9LL << 20);
+  if (p.n_cg % 2 == 0 && !(l2_holds_factors && (long long)n_seq * p.n_tok >= ch)) p.token_affine = false;
   hipLaunchKernelGGL((k_prefill_project_direct<R, CT, TT, I4>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(256), 0, s, p);
 }
 
-template <int R, int WAVES, bool I4 = false>
-hipError_t launch_project_lds(const ProjectParams& p, hipStream_t s) {
+template <int R, bool I4 = false>
+hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
   static bool raised = false;             // the kernel's limit of dynamic LDS, raised once per instantiation
   const size_t lds = 2 * (size_t)kProjStage;
   if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_lds<R, WAVES, I4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_lds<R, I4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     raised = true;
   }
-  hipLaunchKernelGGL((k_prefill_project_lds<R, WAVES, I4>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(64 * WAVES), lds, s, p);
+  project_grid(p, n_seq, 256, 256, R);
+  hipLaunchKernelGGL((k_prefill_project_lds<R, I4>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(512), lds, s, p);
   return hipGetLastError();
+}
+
+// The tile size, by how often 256 workgroups (one per CU) have to run one after the other, q = ceil(workgroups / 256):
+//   11: 128 channels (rank 64: 256) x 32 tokens, about 18 (27) us a round at d_model 4096 after the first;
+//   22: 256 x 64, about 36 us a round;    2: 256 x 256, 100 us a round and 30 more as its rows fill with tokens.
+// So 11 while its rounds are at most 2 (1) times those of 22: a quarter (half) of the area costs half (three quarters) of
+// the time.  And 2 instead of 22 when its rounds, priced by the tokens they hold, cost less.  us per call with the length
+// update, 32 kv heads, d_model 4096:
+//   rank 32    16 x 3  16 x 32  64 x 4  64 x 32  3 x 333  4 x 500  16 x 130  16 x 260  2 x 2048  8 x 1024  16 x 2048
+//   11           21      25       51      63        48       66       76        140       137       242       1017
+//   22           39      41       64      70        43       47       70        115        87       155        611
+//   2           102     101      205     207       106      105      105        126       121       134        514
+//   rank 64    16 x 3  16 x 32  64 x 4  64 x 32  3 x 333  4 x 500  16 x 130  16 x 260  2 x 2048  8 x 1024
+//   11           37      35       95     111        78      110      134        238       226       412
+//   22           42      42      120     132        67       78      109        179       152       284
+//   2           112     112      418     429       107      109      122        254       137       262
+int project_shape_rule(int Hkv, int R, int n_tok, int n_seq) {
+  const long long ch = 2LL * Hkv * R, ch11 = 4LL * R;
+  auto rounds = [&](long long ch_wg, int tok_wg) {
+    const long long wgs = (ch + ch_wg - 1) / ch_wg * ((n_tok + tok_wg - 1) / tok_wg) * n_seq;
+    return (wgs + 255) / 256;
+  };
+  const long long q22 = rounds(256, 64), q2 = rounds(256, 256);
+  if (rounds(ch11, 32) <= (R == 32 ? 2 : 1) * q22) return 11;
+  const long long held = 100LL * n_tok / ((n_tok + 255) / 256 * 256LL);       // per cent of a 256-token tile
+  return q2 * (100 + 30 * held / 100) < 38 * q22 ? 2 : 22;
 }
 
 }  // namespace
@@ -498,27 +536,19 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   p.meta[0] = (uint16_t*)cache.k_meta; p.meta[1] = (uint16_t*)cache.v_meta;
   p.seq_lens = cache.seq_lens; p.err_word = ctx->err_word;
   p.Hkv = d.n_kv_heads; p.E = d.d_model; p.t_cap = d.t_cap; p.n_tok = n_tok;
-  p.n_cg = p.tg_seq = p.n_tg = 0;
+  p.n_cg = p.tg_seq = p.n_tg = 0; p.token_affine = false;
   p.block_table = nullptr; p.page_rows = p.max_pages = p.n_pages = 0;
   if (paged) { p.block_table = paged->block_table; p.page_rows = paged->page_rows; p.max_pages = paged->max_pages; p.n_pages = paged->n_pages; }
   const int n_seq = seq < 0 ? d.batch : 1;
   p.seq0 = seq < 0 ? 0 : seq;
-  // Which kernel: by how many workgroups each tile size gives on 256 CUs (see the table at k_prefill_project_direct).
-  //   11: 128 channels x 32 tokens while that is at most two workgroups per CU;
-  //   22: 256 x 64 while the 256 x 256 tiles of the staged kernel would leave more than a third of the CUs idle;
-  //   2 : 256 x 256 tiles, eight waves (1: four waves; 44 / 42 / 24 / 21: the kernel without LDS, also where a sequence's
-  //       hidden states take 2^31 bytes or more).  The "project_shape" option asks for any of them (tuning, tests).
-  const long long work = (long long)n_seq * n_tok * d.n_kv_heads * d.rank;
-  const bool staged_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
-  const long long ch = 2LL * d.n_kv_heads * d.rank;
-  const long long small_wgs = (ch + 127) / 128 * ((n_tok + 31) / 32) * n_seq, big_wgs = (ch + 255) / 256 * ((n_tok + 255) / 256) * n_seq;
+  const bool tiles_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
   int shape = ctx->opt.project_shape;
-  if (!shape) shape = !staged_ok ? 44 : small_wgs <= 512 ? 11 : big_wgs <= 160 ? 22 : 2;
-  if ((shape == 1 || shape == 2 || shape == 11 || shape == 22) && !staged_ok) shape = 44;
+  if (!shape) shape = project_shape_rule(d.n_kv_heads, d.rank, n_tok, n_seq);
+  if (!tiles_ok || (shape != 11 && shape != 22)) shape = tiles_ok && shape <= 2 ? 2 : 44;
   hipError_t e = hipSuccess;
   if (d.rank > 64) {
     // ranks 96 / 128: a wave owns the 3 / 4 channel tiles of one head and 1 or 4 token tiles
-    const bool big = work >= (1LL << 22);
+    const bool big = (long long)n_seq * n_tok * d.n_kv_heads * d.rank >= (1LL << 22);
     if (d.rank == 96) { if (big) launch_project<96, 3, 4, 4>(p, n_seq, s); else launch_project<96, 3, 1, 4>(p, n_seq, s); }
     else { if (big) launch_project<128, 4, 4, 4>(p, n_seq, s); else launch_project<128, 4, 1, 4>(p, n_seq, s); }
   } else if (shape == 11) {
@@ -529,27 +559,13 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
     if (i4) launch_project_direct<32, 2, 2, true>(p, n_seq, s);
     else if (d.rank == 32) launch_project_direct<32, 2, 2>(p, n_seq, s);
     else launch_project_direct<64, 2, 2>(p, n_seq, s);
-  } else if (shape == 1 || shape == 2) {
-    const int tiles = 2 * p.Hkv * (d.rank / 32);
-    p.n_cg = (tiles + 7) / 8; p.tg_seq = (n_tok + 255) / 256; p.n_tg = p.tg_seq * n_seq;
-    const bool w8 = shape == 2;
-    if (i4) e = launch_project_lds<32, 8, true>(p, s);
-    else if (d.rank == 32) e = w8 ? launch_project_lds<32, 8>(p, s) : launch_project_lds<32, 4>(p, s);
-    else e = w8 ? launch_project_lds<64, 8>(p, s) : launch_project_lds<64, 4>(p, s);
-  } else if (i4) {
-    if (shape == 44) launch_project<32, 4, 4, 4, true>(p, n_seq, s);
-    else launch_project<32, 2, 1, 4, true>(p, n_seq, s);
-  } else if (d.rank == 32) {
-    if (shape == 44) launch_project<32, 4, 4, 4>(p, n_seq, s);
-    else if (shape == 42) launch_project<32, 4, 2, 4>(p, n_seq, s);
-    else if (shape == 24) launch_project<32, 2, 4, 4>(p, n_seq, s);
-    else launch_project<32, 2, 1, 4>(p, n_seq, s);
-  } else {
-    if (shape == 44) launch_project<64, 4, 4, 4>(p, n_seq, s);
-    else if (shape == 42) launch_project<64, 4, 2, 4>(p, n_seq, s);
-    else if (shape == 24) launch_project<64, 2, 4, 4>(p, n_seq, s);
-    else launch_project<64, 2, 1, 4>(p, n_seq, s);
-  }
+  } else if (shape == 2) {
+    if (i4) e = launch_project_lds<32, true>(p, n_seq, s);
+    else if (d.rank == 32) e = launch_project_lds<32>(p, n_seq, s);
+    else e = launch_project_lds<64>(p, n_seq, s);
+  } else if (i4) launch_project<32, 4, 4, 4, true>(p, n_seq, s);
+  else if (d.rank == 32) launch_project<32, 4, 4, 4>(p, n_seq, s);
+  else launch_project<64, 4, 4, 4>(p, n_seq, s);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_prefill_bump, dim3((n_seq + 63) / 64), dim3(64), 0, s, cache.seq_lens, p.seq0, n_seq, n_tok, d.t_cap, ctx->err_word, i4 ? 1 : 0);

@@ -2,6 +2,7 @@
 edges of its token tiles (one tile, one more, one less, several with a remainder) and sequences that already hold rows."""
 import numpy as np
 import pytest
+import torch
 
 import oracle as O
 import paper_2604_02570_amd as W
@@ -62,6 +63,40 @@ def test_prompt_projection_tile_rule(name, n, over):
 @pytest.mark.parametrize("name,over", [("c3_small", dict()), ("c3_small", dict(rank=64)), ("c4_small", dict(ragged=(60, 120)))], ids=["i8", "i8-r64", "i4"])
 def test_prompt_projection_chunk_tails(name, over, shape, n, d_model):
     _prompt(name, shape, n, **{**dict(batch=4 if n in (40, 70) else 3, context=120, d_model=d_model), **over})
+
+
+@pytest.mark.parametrize("rank", [32, 64])
+@pytest.mark.parametrize("batch,n", [(64, 4), (64, 32), (16, 64), (16, 260), (1, 300), (8, 1024)])
+def test_prompt_projection_takes_a_fitting_tile(batch, n, rank):
+    """Many short prompts, prompts just past a multiple of 256 tokens, one prompt, full batches: the tile that is taken by
+    itself is about as fast as the best one asked for (a tile that does not fit the prompts costs a factor of 2 to 4)."""
+    E, Hkv, t_cap = 4096, 32, (n + 63) // 64 * 64
+    desc = W.layer_desc(batch, Hkv, Hkv, 128, E, rank, t_cap, "i8", "bf16", "bf16", "bf16", "f32", 0.0)
+    ctx = W.wsvd_create(0)
+    cb, mb = W.wsvd_cache_bytes(desc)
+    codes, meta = ([torch.zeros(b, dtype=torch.uint8, device="cuda") for _ in range(2)] for b in (cb, mb))
+    lens = torch.zeros(batch, dtype=torch.int32, device="cuda")
+    cache = W.make_cache(*codes, *meta, lens)
+    x = torch.randn(batch * n, E, device="cuda").to(torch.bfloat16)
+    A = [torch.randn(W.wsvd_factor_a_bytes(desc) // 2, device="cuda").to(torch.bfloat16) for _ in range(2)]
+
+    def us(shape):
+        W.wsvd_ctx_set_option(ctx, "project_shape", shape)
+        best = float("inf")
+        for _ in range(4):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for _ in range(10):
+                lens.zero_()
+                W.wsvd_prefill_append(ctx, desc, x, None, n, -1, *A, cache)
+            b.record(); torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 100)
+        return best
+
+    t = {shape: us(shape) for shape in (11, 22, 2, 0)}
+    assert W.wsvd_check(ctx) == 0
+    assert t[0] <= 1.35 * min(t.values()), t
+    W.wsvd_destroy(ctx)
 
 
 # query rows per kv head at the edges of the 32-row waves and of the 1 / 2 / 4 waves that share a workgroup's cache blocks;
