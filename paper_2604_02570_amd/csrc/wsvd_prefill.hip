@@ -19,13 +19,15 @@
 //     half g (the lane of the A operand loads that token's codes).  The weights a lane ends up with are then, in register
 //     order, the operand the value product wants: P never leaves the registers, and the 16 scales a lane needs, of K as
 //     of V, are 16 consecutive fp16 values of the metadata plane;
-//   * score * scale - reference is one mixed-precision multiply-add.  The reference of the exponentials is not the
-//     running maximum but the maximum at the last rescaling; a wave rescales when a block's weights sum to more than 64;
-//   * the sum of the weights is taken from the fp16 pairs (dot products with 1), the same values the value product sums.
-// 16 x 2048 tokens, 32 heads, r = 32: 0.43 ms (0.53 ms with one wave per 32 rows converting for itself, the maximum
-// exchanged every block and P through LDS).  Counters then: vector ALU busy 65 %, matrix cores 27 % of 0.82 M cycles at a
-// clock that the load holds at 1.8 - 2.0 GHz.  Tried and slower: two query blocks per wave without LDS (0.44 ms, 193
-// registers, two waves per SIMD; three waves spill), the next block's score products issued under the softmax (0.47 ms).
+//   * score * scale - reference is one mixed-precision multiply-add.  The reference of the exponentials is the running
+//     maximum, so that the largest weight of a column is exactly 1 in fp16; a block whose scores stay below it (told by
+//     the sign of the largest difference) leaves the accumulators alone and exchanges nothing between lane halves;
+//   * the weights are summed in fp32, before they are rounded to fp16 for the value product.
+// 16 x 2048 tokens, 32 heads, r = 32: 0.45 ms (0.53 ms with one wave per 32 rows converting for itself, the maximum
+// exchanged every block and P through LDS).  A reference that is moved only when a block's weights sum to more than 64,
+// with the weights summed as the fp16 values: 0.42 ms, but the largest weight is then not exact (error against 64 bits up
+// to 2.14e-4 where this has 2.12e-4, and 2.5e-4 with the sum in fp32).  Tried and slower: two query blocks per wave without
+// LDS (193 registers, two waves per SIMD; three waves spill), the next block's score products issued under the softmax.
 //
 // A workgroup is QW x KG waves: KG key groups take every KG-th stage of QW blocks, their (m, l, U) meet in LDS.  A query
 // row is a (token, head) pair, token-major, so the G heads that share a kv head share the stream too.  The cache blocks
@@ -69,12 +71,6 @@ WSVD_DEV void split_bf16(float x, uint32_t& hi, uint32_t& lo) {
   lo = __float_as_uint(x - __uint_as_float(hi)) & 0xFFFF0000u;
 }
 
-typedef _Float16 v2f16 __attribute__((ext_vector_type(2)));
-// A wave rescales when 16 of a lane's weights sum to more.  Above 16, or equal scores would rescale every block; fp16 would
-// allow 16384 (0.40 ms instead of 0.43), but the largest weight of a column is exact only when it is the reference: with
-// 64 the error against fp64 is 2.09e-4 .. 2.13e-4 over five shapes, with 16384 2.12e-4 .. 2.17e-4 (running maximum: 2.11e-4).
-constexpr float kLazySum = 64.0f;
-
 template <int R, int D, int QW, int KG>
 __global__ __launch_bounds__(64 * QW * KG) __attribute__((amdgpu_waves_per_eu(R == 32 ? 4 : 2)))
 void k_prefill_attn(PrefillParams p) {
@@ -102,7 +98,7 @@ void k_prefill_attn(PrefillParams p) {
 #pragma unroll
     for (int ks = 0; ks < D / 16; ks++) bk[kk][ks] = *(const v8bf16*)(p.BK + ((size_t)kv * R + 32 * kk + perm) * D + 16 * ks + 8 * g2);
   const int n_eff = min(max(p.seq_lens[b] - p.n_after, 0), p.t_cap);
-  const int lim = row_ok ? n_eff - p.nq + rho_c / p.G + 1 : 0;          // this query sees keys [0, lim); may be <= 0
+  const int lim = n_eff - p.nq + rho_c / p.G + 1;                       // this query sees keys [0, lim); may be <= 0
   // rows are token-major: a wave's last row sees most of its keys, the workgroup's last row most of all.
   // (readfirstlane: the divisions run on the vector ALU, the values are uniform)
   auto sees = [&](int row) { return __builtin_amdgcn_readfirstlane(n_eff - p.nq + min(row, p.NR - 1) / p.G + 1); };
@@ -240,37 +236,34 @@ void k_prefill_attn(PrefillParams p) {
 #pragma unroll
         for (int v = 0; v < 16; v++) U[kk][v] *= alpha;
     } else {
-#pragma unroll
-      for (int v = 0; v < 16; v++) x[v] = fmaf(S[v], (float)sk8[v >> 3][v & 7], -m_ref);   // (first block: +inf)
-    }
-    // weights in fp16: registers 8 s .. 8 s + 7 are tokens 16 g2 + 8 s .. + 7, the operand of step s of the value product
-    v8f16 bp[2];
-    float psum = 0.f;
-    auto weights = [&]() {
-      psum = 0.f;
-#pragma unroll
-      for (int v = 0; v < 16; v += 2) {
-        const v2f16 w = {(_Float16)__builtin_amdgcn_exp2f(x[v]), (_Float16)__builtin_amdgcn_exp2f(x[v + 1])}, one = {(_Float16)1, (_Float16)1};
-        psum = __builtin_amdgcn_fdot2(w, one, psum, false);
-        bp[v >> 3][v & 7] = w[0]; bp[v >> 3][(v & 7) + 1] = w[1];
-      }
-    };
-    weights();
-    if (!MASKED && __builtin_amdgcn_ballot_w64(psum > kLazySum) != 0) {
-      // a new reference for every column: the largest score seen since the last one, and the weights again
       float bmax = -INFINITY;
 #pragma unroll
-      for (int v = 0; v < 16; v++) bmax = fmaxf(bmax, S[v] * (float)sk8[v >> 3][v & 7]);
-      const float m_new = fmaxf(m_ref, fmaxf(bmax, __shfl_xor(bmax, 32)));
-      const float alpha = __builtin_amdgcn_exp2f(m_ref - m_new);        // (m_new is finite here)
-      m_ref = m_new; l_run *= alpha;
+      for (int v = 0; v < 16; v++) {
+        x[v] = fmaf(S[v], (float)sk8[v >> 3][v & 7], -m_ref);           // (m_ref is finite here)
+        bmax = fmaxf(bmax, x[v]);
+      }
+      if (__builtin_amdgcn_ballot_w64(bmax > 0.f) != 0) {               // some column's maximum moves
+        bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+        const float m_new = m_ref + fmaxf(bmax, 0.f), d = m_new - m_ref;
+        const float alpha = __builtin_amdgcn_exp2f(-d);
+        m_ref = m_new; l_run *= alpha;
 #pragma unroll
-      for (int v = 0; v < 16; v++) x[v] = fmaf(S[v], (float)sk8[v >> 3][v & 7], -m_new);
+        for (int v = 0; v < 16; v++) x[v] -= d;
 #pragma unroll
-      for (int kk = 0; kk < KK; kk++)
+        for (int kk = 0; kk < KK; kk++)
 #pragma unroll
-        for (int v = 0; v < 16; v++) U[kk][v] *= alpha;
-      weights();
+          for (int v = 0; v < 16; v++) U[kk][v] *= alpha;
+      }
+    }
+    // weights: their sum in fp32, as operands of the value product in fp16.  Registers 8 s .. 8 s + 7 are tokens
+    // 16 g2 + 8 s .. + 7, the operand of its step s.
+    v8f16 bp[2];
+    float psum = 0.f;
+#pragma unroll
+    for (int v = 0; v < 16; v++) {
+      const float w = __builtin_amdgcn_exp2f(x[v]);
+      psum += w;
+      bp[v >> 3][v & 7] = (_Float16)w;
     }
     l_run += psum;
     // U^T += V'^T P: rows = latent dims, columns = queries
@@ -297,9 +290,11 @@ void k_prefill_attn(PrefillParams p) {
     const uint8_t* src = stage + (it & 1) * STAGE;
     const int kb0 = (it * KG + kg) * QW;
     const int j_full = min(kb_full - kb0, QW), j_end = min(kb_end - kb0, QW);
-    int j = 0;
-    for (; j < j_full; j++) block(src + j * BLK, kb0 + j, std::false_type{});
-    for (; j < j_end; j++) block(src + j * BLK, kb0 + j, std::true_type{});
+    for (int j = 0; j < j_end; j++) {
+      // (a column without a key yet has no reference: the masked form sets the first one)
+      if (j < j_full && __builtin_amdgcn_ballot_w64(m_ref == -INFINITY) == 0) block(src + j * BLK, kb0 + j, std::false_type{});
+      else block(src + j * BLK, kb0 + j, std::true_type{});
+    }
     __syncthreads();
   }
 

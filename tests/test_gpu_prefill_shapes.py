@@ -147,3 +147,32 @@ def test_prompt_attention_many_small_weights(lead, where):
     # at random over 2000 keys whose sum is 2^-8 of the total); fp16 values 2^-12: 1e-3 covers both
     assert np.linalg.norm(got - ref) <= 1e-3 * np.linalg.norm(ref), np.linalg.norm(got - ref) / np.linalg.norm(ref)
     L.close()
+
+
+@pytest.mark.parametrize("rank,nq,batch", [(32, 64, 1), (64, 64, 1), (32, 130, 12)])
+def test_prompt_attention_denominator_in_fp32(rank, nq, batch):
+    """One key of every 32 has the largest score and the only value that is not zero, all others one smaller score: they enter
+    through the sum of the weights alone, which has to be taken before the weights are rounded to fp16 (2^-12 relative, the
+    same for all of them, times their share of the sum of up to 0.9).  The leading weight is 1 and the value's code times
+    its scale is exact."""
+    c = build_case("c3_small", batch=batch, n_q_heads=4, n_kv_heads=4, context=512, rank=rank)
+    sp = c.sp
+    q32 = np.repeat(_multi_q(c, 1, seed=4), nq, axis=2)
+    q32 *= np.linspace(1.0, 2.5, nq, dtype=np.float32)[None, None, :, None, None]
+    q32 = WI.bf16_exact(q32)
+    for b in range(sp.batch):
+        k = np.zeros((sp.n_kv_heads, 512, sp.rank))
+        qt = np.einsum("hd,hrd->hr", q32[b, :, 0, 0].astype(np.float64), c.BK.astype(np.float64))
+        k[:, ::32] = (qt * (1.3 * np.log(2.0) / c.sm_scale / (qt * qt).sum(-1))[:, None])[:, None]
+        v = np.zeros((sp.n_kv_heads, 512, sp.rank))
+        v[:, ::32] = (np.arange(sp.rank) * 7 % 255 - 127.0) / 16.0              # scale 2^-4, every code an integer
+        c.cache.store_rows("k", b, 0, k)
+        c.cache.store_rows("v", b, 0, v)
+        c.cache.seq_lens[b] = 512
+    L = layer_for(c); L.upload(c.cache)
+    got = _prefill_attn(L, c, q32, nq, 0, 512)
+    ref = O.causal_attn_reconstructed(c.cache, q32.astype(np.float64), c.BK.astype(np.float64), c.BV.astype(np.float64), c.sm_scale)
+    err = np.linalg.norm(got - ref, axis=-1) / np.linalg.norm(ref, axis=-1)
+    # left: the bf16 pair of U / l (2^-16 per element, signs at random) and the fp32 sums: 2e-5
+    assert err.max() <= 4e-5, err.max()
+    L.close()
