@@ -356,7 +356,8 @@ wsvd_status wsvd_prefill_append(wsvd_ctx *ctx, const wsvd_layer_desc *desc, cons
  *   desc->q_dtype (F32 or BF16; WSVD_E_DTYPE for I8), out F32.  I8 latents, BF16 factors (WSVD_E_UNSUPPORTED otherwise).
  *   n_q * G <= 8: the decode kernel with one query slot per (token, head); the workspace must be large enough for a
  *   descriptor with Hkv * n_q * G query heads (WSVD_E_WORKSPACE otherwise).  n_q * G > 8: a tiled kernel, BF16 queries
- *   only (WSVD_E_UNSUPPORTED for F32), no workspace, any n_q (a whole prompt in one call); max_seq_len is not used by it.
+ *   only (WSVD_E_UNSUPPORTED for F32), no workspace, any n_q (a whole prompt in one call); max_seq_len only steers how it
+ *   splits the work (less than n_q + n_after: taken as t_cap).
  *   Its value product runs on fp16 operands (code * scale and the softmax weights, each rounded to 2^-12 relative):
  *   outputs agree with the exact result to about 2e-4 relative, the slot kernel's to about 1e-5.
  *   Stream, pointer and error conventions as wsvd_decode_attn.

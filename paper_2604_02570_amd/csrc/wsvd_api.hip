@@ -287,7 +287,7 @@ wsvd_status wsvd_prefill_attn(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const 
   if ((int64_t)n_q * Gr > 8 || (ctx->opt.prefill_tiled && desc->q_dtype == WSVD_BF16)) {
     // more query rows than the decode kernel has slots: the tiled kernel (one wavefront per 32 query rows)
     if (desc->q_dtype != WSVD_BF16) return WSVD_E_UNSUPPORTED;
-    hipError_t e = wsvd_launch_prefill_attn(*desc, q, n_q, n_after, B_K, B_V, *cache, out, (hipStream_t)hip_stream);
+    hipError_t e = wsvd_launch_prefill_attn(*desc, q, n_q, n_after, B_K, B_V, *cache, max_seq_len, out, (hipStream_t)hip_stream);
     if (e == hipErrorNotSupported) return WSVD_E_UNSUPPORTED;
     return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;
   }
@@ -505,7 +505,7 @@ wsvd_status wsvd_prefill_attn_paged(wsvd_ctx* ctx, const wsvd_layer_desc* desc, 
   if (max_seq_len > desc->t_cap) return WSVD_E_CAPACITY;
   if (desc->latent_dtype != WSVD_I8 || desc->factor_dtype != WSVD_BF16 || desc->q_dtype != WSVD_BF16) return WSVD_E_UNSUPPORTED;
   wsvd_cache view = {cache->k_codes, cache->v_codes, cache->k_meta, cache->v_meta, cache->seq_lens};
-  hipError_t e = wsvd_launch_prefill_attn(*desc, q, n_q, n_after, B_K, B_V, view, out, (hipStream_t)hip_stream, cache);
+  hipError_t e = wsvd_launch_prefill_attn(*desc, q, n_q, n_after, B_K, B_V, view, max_seq_len, out, (hipStream_t)hip_stream, cache);
   if (e == hipErrorNotSupported) return WSVD_E_UNSUPPORTED;
   return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;
 }

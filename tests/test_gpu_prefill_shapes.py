@@ -100,13 +100,25 @@ def test_prompt_projection_takes_a_fitting_tile(batch, n, rank):
 
 
 # query rows per kv head at the edges of the 32-row waves and of the 1 / 2 / 4 waves that share a workgroup's cache blocks;
-# batch and heads choose the workgroup shape (256 and 1536 waves of rank 32, 768 of rank 64 are the limits of the rule)
+# batch, heads, rows and key blocks choose the workgroup shape
 ATTN_SHAPES = [("c3_small", 9, 0, dict()), ("c3_small", 31, 2, dict(context=700)), ("c3_small", 33, 0, dict(d_head=64, context=65)),
                ("c3_small", 65, 0, dict(batch=24, n_q_heads=8, n_kv_heads=8, context=200)),
                ("c3_small", 17, 1, dict(batch=24, n_q_heads=32, n_kv_heads=8, context=130, rank=64)),
                ("c3_small", 97, 0, dict(batch=16, n_q_heads=32, n_kv_heads=32, context=129)),
                ("c3_small", 129, 3, dict(batch=16, n_q_heads=32, n_kv_heads=32, context=161, d_head=64)),
-               ("c3_small", 33, 0, dict(batch=16, n_q_heads=48, n_kv_heads=24, context=96, rank=64))]
+               ("c3_small", 33, 0, dict(batch=16, n_q_heads=48, n_kv_heads=24, context=96, rank=64)),
+               # one wave of rows, the key blocks dealt to 1, 2 and 4 waves: fewer blocks than waves, one more, several each
+               ("c3_small", 12, 0, dict(context=20)), ("c3_small", 20, 0, dict(context=64)), ("c3_small", 20, 5, dict(context=90)),
+               ("c3_small", 40, 0, dict(context=97, rank=64)), ("c3_small", 40, 1, dict(context=290, rank=64, d_head=64)),
+               ("c3_small", 33, 0, dict(batch=8, n_q_heads=32, n_kv_heads=32, context=600, rank=64)),
+               ("c3_small", 33, 2, dict(batch=8, n_q_heads=32, n_kv_heads=32, context=1030, rank=64)),
+               ("c3_small", 33, 0, dict(batch=14, n_q_heads=32, n_kv_heads=32, context=600)),
+               # a full chip: one, two and four waves of rows, full groups of four and not
+               ("c3_small", 20, 0, dict(batch=40, n_q_heads=32, n_kv_heads=32, context=50, rank=64)),
+               ("c3_small", 40, 0, dict(batch=36, n_q_heads=32, n_kv_heads=32, context=70)),
+               ("c3_small", 40, 0, dict(batch=17, n_q_heads=32, n_kv_heads=32, context=1030, rank=64)),
+               ("c3_small", 70, 0, dict(batch=24, n_q_heads=32, n_kv_heads=32, context=1040)),
+               ("c3_small", 150, 0, dict(batch=16, n_q_heads=32, n_kv_heads=32, context=160))]
 
 
 @pytest.mark.parametrize("name,nq,n_after,over", ATTN_SHAPES, ids=[f"nq{q}-after{a}-{'-'.join(f'{k}{v}' for k, v in o.items())}" for _, q, a, o in ATTN_SHAPES])
@@ -176,3 +188,41 @@ def test_prompt_attention_denominator_in_fp32(rank, nq, batch):
     # left: the bf16 pair of U / l (2^-16 per element, signs at random) and the fp32 sums: 2e-5
     assert err.max() <= 4e-5, err.max()
     L.close()
+
+
+@pytest.mark.parametrize("rank", [32, 64])
+def test_prompt_attention_short_prompts_keep_the_waves_busy(rank):
+    """64 sequences of 16 tokens, over their own 16 keys, have the query rows of 16 sequences of 64 tokens over 64 keys, and a
+    quarter of the scores: with every wave of the launch at work they take about the same time (waves without rows or without
+    a key block to attend to make it 1.7 and 2.5 times)."""
+    def us(batch, n):
+        desc = W.layer_desc(batch, 32, 32, 128, 4096, rank, 64, "i8", "bf16", "bf16", "bf16", "f32", 0.0)
+        ctx = W.wsvd_create(0)
+        cb, mb = W.wsvd_cache_bytes(desc)
+        g = torch.Generator(device="cuda").manual_seed(1)
+        codes = [torch.randint(-127, 128, (cb,), dtype=torch.int8, device="cuda", generator=g) for _ in range(2)]
+        meta = [torch.full((mb // 2,), 0.02, dtype=torch.float16, device="cuda") for _ in range(2)]
+        lens = torch.full((batch,), n, dtype=torch.int32, device="cuda")
+        q = torch.randn(batch, 32, n, 1, 128, device="cuda", generator=g).to(torch.bfloat16)
+        B = [(torch.randn(32, rank, 128, device="cuda", generator=g) * rank ** -0.5).to(torch.bfloat16) for _ in range(2)]
+        out = torch.zeros(batch, 32, n, 1, 128, device="cuda")
+        cache = W.make_cache(*codes, *meta, lens)
+        stream = torch.cuda.Stream()
+        run = lambda: W.wsvd_prefill_attn(ctx, desc, q, n, 0, *B, cache, n, out, stream)
+        torch.cuda.synchronize()
+        run()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(20):
+                run()
+        best = float("inf")
+        for _ in range(6):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record(); graph.replay(); b.record(); torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 50)
+        assert W.wsvd_check(ctx) == 0
+        W.wsvd_destroy(ctx)
+        return best
+
+    t16, t64 = us(64, 16), us(16, 64)
+    assert t16 <= 1.4 * t64, (t16, t64)
