@@ -14,7 +14,8 @@ from test_gpu_parity import _append_compare, check_out, layer_for
 
 pytestmark = pytest.mark.gpu
 
-CASES = [("c1", dict()), ("c1", dict(rank=32, d_model=4096, context=80)), ("c1", dict(rank=64, n_q_heads=6, n_kv_heads=2, d_head=128)),
+CASES = [("c1", dict()), ("c1", dict(rank=32, d_model=4096, context=80)), ("c1", dict(rank=16, d_model=4160, context=80)),
+         ("c1", dict(rank=64, d_model=1536, n_q_heads=10, n_kv_heads=2, d_head=128)), ("c1", dict(rank=64, d_model=1600, context=80)), ("c1", dict(rank=64, n_q_heads=6, n_kv_heads=2, d_head=128)),
          ("c2_small", dict()), ("c2_small", dict(rank=16, n_q_heads=8, n_kv_heads=1)), ("c2_small", dict(rank=64, n_q_heads=12, n_kv_heads=4, d_model=1024)),
          ("c2_small", dict(d_model=4096, n_q_heads=32, n_kv_heads=32))]
 
@@ -80,3 +81,42 @@ def test_step_rows_at_chunk_edges(name, over):
         assert (L.out.cpu().numpy().astype(np.float64) == eager).all()
     assert W.wsvd_check(L.ctx) == W.E_CAPACITY
     L.close()
+
+
+@pytest.mark.parametrize("d_model,rank", [(4160, 64), (4160, 32), (4096, 32)])
+def test_many_partial_sums_cost_no_more_than_the_two_calls(d_model, rank):
+    """fp32, up to d_model / 64 partial sums per row: the step with the finishing attention takes no longer than the append and
+    the attention (fetching the sums one after the other took 7 % longer)."""
+    desc = W.layer_desc(2, 8, 8, 128, d_model, rank, 128, "f32", "f32", "f32", "f32", "f32", 0.0)
+    ctx = W.wsvd_create(0)
+    ws = torch.empty(W.wsvd_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
+    W.wsvd_set_workspace(ctx, ws)
+    cb, _ = W.wsvd_cache_bytes(desc)
+    g = torch.Generator(device="cuda").manual_seed(2)
+    rnd = lambda *n: torch.randn(n, device="cuda", generator=g)
+    planes, meta = [rnd(cb // 4) for _ in range(2)], torch.zeros(16, dtype=torch.uint8, device="cuda")
+    lens = torch.full((2,), 64, dtype=torch.int32, device="cuda")
+    lens0 = lens.clone()
+    cache = W.make_cache(*planes, meta, meta, lens)
+    x, q, A, B = rnd(2, d_model), rnd(2, 8, 128), [rnd(W.wsvd_factor_a_bytes(desc) // 4) * 0.02 for _ in range(2)], [rnd(8, rank, 128) for _ in range(2)]
+    out = torch.zeros(2, 8, 128, device="cuda")
+    stream = torch.cuda.Stream()
+    graphs = []
+    for deferred in (0, 1):
+        W.wsvd_ctx_set_option(ctx, "step_deferred", deferred)
+        torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=stream):
+            for _ in range(10):
+                lens.copy_(lens0)
+                W.wsvd_decode_step(ctx, desc, x, None, *A, q, None, *B, cache, 65, out, stream)
+        graphs.append(graph)
+    best = [float("inf")] * 2
+    for _ in range(10):
+        for i, graph in enumerate(graphs):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record(); graph.replay(); b.record(); torch.cuda.synchronize()
+            best[i] = min(best[i], a.elapsed_time(b) * 100)
+    assert W.wsvd_check(ctx) == 0
+    assert best[1] <= 1.03 * best[0], best
+    W.wsvd_destroy(ctx)
