@@ -198,26 +198,28 @@ __global__ __launch_bounds__(NT) void k_append_split(AppendParams p, int SB, int
   };
   // ---- hidden states of the share -> LDS: whole 16-byte pieces, kPieces per thread and trip in flight (wave-uniform
   // predicate per piece); the factor batches go out between the first trip's requests and its LDS writes, so that a
-  // wave's first k-steps cost one round trip.  A thread walks its pieces (row, position) by the workgroup's stride: two
-  // divisions per piece (address and LDS place) took the vector ALU as long as the loads took (append + attention of 64
-  // sequences over int4 latents 53.3 -> 52.3 us, 23 paged sequences 36.0 -> 35.0 us).  Eight pieces in flight: another
-  // 0.5 us less for 64 sequences, but 0.5 to 4 us more for up to 32 and for the slices of the int8 step (registers).
+  // wave's first k-steps cost one round trip.  The row of piece i is i / ppr by a reciprocal: (i + 1/2) / ppr is at least
+  // 1 / (2 ppr) away from every integer, more than the product is off (a row number below 32 times 2^-22; ppr < 2^13, or the
+  // row is 0), so its integer part is exact.  Two integer divisions per piece / one
+  // per thread and a walk from piece to piece / this, append + attention over 130 cached rows: 64 sequences of 32 heads,
+  // int8, 31.5 / 30.2 / 29.4 us, 23 paged ones 20.7 / 20.0 / 19.6, one sequence of 8 heads, d_model 512, 10.9 / 11.1 / 10.9.
+  // Eight pieces in flight: 0.5 us less for 64 sequences, but 0.5 to 4 us more for up to 32 and for the slices of the int8
+  // step (registers).
   constexpr int kPieces = 4;
-  const int ppr = (wg_k1 - wg_k0) * 2, ppr1 = max(ppr, 1);      // 16-byte pieces per row (none: an empty share)
-  const int n_pieces = nb * ppr, walk_r = (int)blockDim.x / ppr1, walk_c = (int)blockDim.x - walk_r * ppr1;
-  int pr = tid / ppr1, pc = tid - pr * ppr1;
+  const int ppr = (wg_k1 - wg_k0) * 2, n_pieces = nb * ppr;     // 16-byte pieces per row (none: an empty share)
+  const float per_row = __builtin_amdgcn_rcpf((float)ppr);
   bool first = true;
   for (int i0 = 0; i0 < n_pieces || first; i0 += kPieces * (int)blockDim.x) {
     v4i piece[kPieces];
-    int to[kPieces];                                            // LDS element of the piece, -1: none
+    int to[kPieces];                                            // LDS element of the piece
 #pragma unroll
     for (int it = 0; it < kPieces; it++) {
-      const bool on = pr < nb;
-      to[it] = on ? pr * xs_stride + pc * 8 : -1;
-      if (i0 + it * (int)blockDim.x + (wave << 6) < n_pieces)   // some lane of this wave has a piece
-        piece[it] = *(const v4i*)(xp + (size_t)(b0 + (on ? pr : nb - 1)) * p.E + (size_t)wg_k0 * 16 + (on ? pc : ppr - 1) * 8);
-      pr += walk_r; pc += walk_c;
-      if (pc >= ppr1) { pc -= ppr1; pr++; }
+      if (i0 + it * (int)blockDim.x + (wave << 6) < n_pieces) { // some lane of this wave has a piece
+        const int i = min(i0 + it * (int)blockDim.x + tid, n_pieces - 1);
+        const int row = (int)(((float)i + 0.5f) * per_row), at = (i - row * ppr) * 8;
+        piece[it] = *(const v4i*)(xp + (size_t)(b0 + row) * p.E + (size_t)wg_k0 * 16 + at);
+        to[it] = row * xs_stride + at;
+      }
     }
     if (first) { load_a(0, ks0); load_a(1, ks0 + KB); first = false; WSVD_STAMP(p.timeline, tl_wg, wave, 1); }
 #pragma unroll
