@@ -68,6 +68,11 @@ WSVD_DEV float load_x(const AppendParams& p, int b, int e) {
   return load_as_f32(p.x, idx, p.x_dtype);
 }
 
+// The planes' pointers by selection: where the plane differs from lane to lane (the latent store), an index into the
+// parameters would put them into scratch memory.
+WSVD_DEV uint8_t* plane_codes(const AppendParams& p, int pl) { return pl ? p.codes[1] : p.codes[0]; }
+WSVD_DEV uint16_t* plane_meta(const AppendParams& p, int pl) { return pl ? p.meta[1] : p.meta[0]; }
+
 // Where row t of (b, kv) lives: the plane of its codes (row_bytes per row), the index of its metadata entry, and the row
 // index inside that plane.  Contiguous cache: one plane of t_cap rows per (b, kv).  Paged cache (quantised latents): the
 // page block_table[b][t / page_rows] of the pools holds page_rows rows of every kv head in the same layout; an entry
@@ -82,7 +87,7 @@ WSVD_DEV RowAddr append_row_addr(const AppendParams& p, int pl, int b, int kv, i
   RowAddr a;
   if (!p.block_table) {
     const size_t ph = (size_t)b * p.Hkv + kv;
-    a.plane = p.codes[pl] + ph * (size_t)p.t_cap * row_bytes; a.meta = ph * p.t_cap + t; a.t = t; a.ok = true;
+    a.plane = plane_codes(p, pl) + ph * (size_t)p.t_cap * row_bytes; a.meta = ph * p.t_cap + t; a.t = t; a.ok = true;
     return a;
   }
   const int pg = min(t / p.page_rows, p.max_pages - 1);
@@ -91,7 +96,7 @@ WSVD_DEV RowAddr append_row_addr(const AppendParams& p, int pl, int b, int kv, i
   if (!a.ok) { phys = 0; atomicExch(p.err_word, (int)WSVD_E_SHAPE); }
   const size_t slot = (size_t)phys * p.Hkv + kv;
   a.t = t - pg * p.page_rows;
-  a.plane = p.codes[pl] + slot * (size_t)p.page_rows * row_bytes; a.meta = slot * p.page_rows + a.t;
+  a.plane = plane_codes(p, pl) + slot * (size_t)p.page_rows * row_bytes; a.meta = slot * p.page_rows + a.t;
   return a;
 }
 
@@ -112,9 +117,9 @@ template <int R>
 WSVD_DEV void store_row_lanes(const AppendParams& p, int pl, int b, int kv, int t, int j, float c, bool on = true) {
   const size_t ph = (size_t)b * p.Hkv + kv;
   if (p.latent_dtype == WSVD_F32) {
-    ((float*)p.codes[pl])[(ph * p.t_cap + t) * R + j] = c;
+    ((float*)plane_codes(p, pl))[(ph * p.t_cap + t) * R + j] = c;
   } else if (p.latent_dtype == WSVD_BF16) {
-    ((uint16_t*)p.codes[pl])[(ph * p.t_cap + t) * R + j] = f32_to_bf16_rne(c);
+    ((uint16_t*)plane_codes(p, pl))[(ph * p.t_cap + t) * R + j] = f32_to_bf16_rne(c);
   } else if (p.latent_dtype == WSVD_I8) {
     const float a = lanes_max<R>(fabsf(c));
     uint16_t sh = 0x3C00u;
@@ -126,7 +131,7 @@ WSVD_DEV void store_row_lanes(const AppendParams& p, int pl, int b, int kv, int 
     if (on) ra = append_row_addr(p, pl, b, kv, t, R);
     if (ra.ok) {
       put_u8(p, ra.plane + (pl == 0 ? i8_k_offset(ra.t, j, R) : i8_v_offset(ra.t, j, R)), (uint8_t)(int8_t)(int)v);
-      if (j == 0) put_u16(p, &p.meta[pl][ra.meta], sh);
+      if (j == 0) put_u16(p, &plane_meta(p, pl)[ra.meta], sh);
     }
   } else {  // I4, R == 32
     const float hi = lanes_max<R>(fmaxf(c, 0.f)), lo = -lanes_max<R>(fmaxf(-c, 0.f));
@@ -155,8 +160,8 @@ WSVD_DEV void store_row_lanes(const AppendParams& p, int pl, int b, int kv, int 
       put_u8(p, bp, nib ? (uint8_t)((old & 0x0F) | (q << 4)) : (uint8_t)((old & 0xF0) | q));
     }
     if (j == 0 && ra.ok) {
-      put_u16(p, &p.meta[pl][ra.meta * 2], sh);
-      put_u16(p, &p.meta[pl][ra.meta * 2 + 1], f32_to_f16_bits_rne((float)zi));
+      put_u16(p, &plane_meta(p, pl)[ra.meta * 2], sh);
+      put_u16(p, &plane_meta(p, pl)[ra.meta * 2 + 1], f32_to_f16_bits_rne((float)zi));
     }
   }
 }

@@ -3,6 +3,9 @@ declares, the binding mirrors them, and host-only calls validate their arguments
 import ctypes
 import os
 import re
+import struct
+import subprocess
+import tempfile
 
 import pytest
 
@@ -62,3 +65,37 @@ def test_host_only_validation_and_sizes():
     with pytest.raises(W.WsvdError) as e:
         W.wsvd_ctx_set_option(None, "max_threads", 256)        # a context is required: the setting lives in it
     assert e.value.status == W.E_NULL
+
+
+def kernel_scratch_bytes():
+    """Scratch memory per lane of every kernel of the built library, by (mangled) name: the notes of its gfx950 code objects."""
+    data = open(W.LIB_PATH, "rb").read()
+    magic, sizes = b"__CLANG_OFFLOAD_BUNDLE__", {}
+    for m in re.finditer(magic, data):
+        (n,) = struct.unpack_from("<Q", data, m.start() + len(magic))
+        at = m.start() + len(magic) + 8
+        for _ in range(n):
+            offset, size, name = struct.unpack_from("<QQQ", data, at)
+            at += 24
+            target, at = data[at:at + name], at + name
+            if size == 0 or b"gfx950" not in target:
+                continue
+            with tempfile.NamedTemporaryFile(suffix=".co") as f:
+                f.write(data[m.start() + offset:m.start() + offset + size]); f.flush()
+                notes = subprocess.run(["/opt/rocm/llvm/bin/llvm-readelf", "--notes", f.name], capture_output=True, text=True, check=True).stdout
+            for kernel in notes.split("\n  - ")[1:]:
+                name = re.search(r"\.name:\s+(_Z\S+)", kernel)
+                if name:
+                    sizes[name[1]] = int(re.search(r"\.private_segment_fixed_size:\s+(\d+)", kernel)[1])
+    return sizes
+
+
+def test_row_and_prompt_kernels_use_no_scratch_memory():
+    """The kernels of the append, the latent store, the row quantisers and the prompt keep everything in registers (the
+    prompt projection without LDS, for sequences of 2^31 bytes and more and for rank 128, is the known exception)."""
+    sizes = kernel_scratch_bytes()
+    for part, least in (("k_latent_store", 3), ("k_append", 6), ("k_prefill_attn", 24), ("k_prefill_project_direct", 6),
+                        ("k_prefill_project_lds", 3), ("k_rmsnorm_quant", 8), ("k_swiglu_quant", 4), ("k_quantize_act", 3), ("k_attn_generic", 96)):
+        found = {k: v for k, v in sizes.items() if part in k}
+        assert len(found) >= least, (part, sorted(found))
+        assert not any(found.values()), {k: v for k, v in found.items() if v}
