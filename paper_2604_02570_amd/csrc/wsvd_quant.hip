@@ -162,6 +162,7 @@ hipError_t wsvd_launch_quantize_act_i8(const void* x, int x_dtype, int64_t rows,
     switch ((n16 + kActThreads - 1) / kActThreads) {
       case 1: WSVD_QUANT_ROW(1); break;
       case 2: WSVD_QUANT_ROW(2); break;
+      case 3: WSVD_QUANT_ROW(3); break;
       default: WSVD_QUANT_ROW(kActPasses); break;
     }
 #undef WSVD_QUANT_ROW

@@ -95,7 +95,7 @@ def test_row_and_prompt_kernels_use_no_scratch_memory():
     prompt projection without LDS, for sequences of 2^31 bytes and more and for rank 128, is the known exception)."""
     sizes = kernel_scratch_bytes()
     for part, least in (("k_latent_store", 3), ("k_append", 6), ("k_prefill_attn", 24), ("k_prefill_project_direct", 6),
-                        ("k_prefill_project_lds", 3), ("k_rmsnorm_quant", 8), ("k_swiglu_quant", 4), ("k_quantize_act", 3), ("k_attn_generic", 96)):
+                        ("k_prefill_project_lds", 3), ("k_rmsnorm_quant", 8), ("k_swiglu_quant", 4), ("k_quantize_act", 9), ("k_attn_generic", 96)):
         found = {k: v for k, v in sizes.items() if part in k}
         assert len(found) >= least, (part, sorted(found))
         assert not any(found.values()), {k: v for k, v in found.items() if v}
