@@ -486,7 +486,7 @@ int prefill_attn_rule(int R, long long waves, int rows32, int key_blocks) {
   const int quarter = R == 32 ? 256 : 128;                              // of the waves a chip holds at 1 (rank 64: 1/2) per SIMD
   const bool long_walk = key_blocks >= 32;
   if (waves <= quarter) return key_blocks >= 3 ? kPa14 : key_blocks == 2 ? kPa12 : kPa11;
-  if (waves <= 2 * quarter) return key_blocks >= 6 ? kPa14 : kPa11;
+  if (waves <= 2 * quarter) return key_blocks < 6 ? kPa11 : R == 32 && rows32 >= 2 && key_blocks < 12 ? kPa22 : kPa14;
   if (waves <= 1408) {
     if (key_blocks < 16) return R == 64 && waves <= 512 && key_blocks >= 8 ? kPa22 : kPa11;
     if (R == 64 && key_blocks >= (waves <= 512 ? 32 : 64)) return waves <= 1280 ? kPa14 : kPa41;
