@@ -51,7 +51,7 @@ wsvd_status wsvd_timeline_set_buffer(wsvd_ctx *ctx, void *dev_ptr, size_t bytes)
  * over them).  The partial sums and the pending words of that step are still in the workspace, the lengths of `cache`
  * must already include the step's row (any cache that went through such a step with the same hidden states will do):
  * the launch stores the same rows again and returns the same output, so a benchmark can time this kernel alone.
- * Arguments as wsvd_decode_attn.  WSVD_E_UNSUPPORTED where wsvd_decode_step has no such pair of launches.
+ * Arguments as wsvd_decode_attn.  For the int8 pair only ("step_deferred" 2); WSVD_E_UNSUPPORTED otherwise.
  */
 wsvd_status wsvd_test_step_attention(wsvd_ctx *ctx, const wsvd_layer_desc *desc, const void *q, const void *q_scale,
                                      const void *B_K, const void *B_V, wsvd_cache *cache, int32_t max_seq_len, void *out,

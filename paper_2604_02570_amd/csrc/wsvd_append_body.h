@@ -28,8 +28,9 @@ struct AppendParams {
   // paged cache only (else null): codes / meta are pools of n_pages pages, a page = page_rows rows of every kv head
   const int* block_table;    // [B][max_pages]
   int page_rows, max_pages, n_pages;
-  // projection-only launch of the decode step (k_append_split<.., true>): partial sums [slice][plane][B][Hkv * R] fp32,
-  // and one word per sequence saying that its length was advanced and the row is still to be written
+  // projection-only launch of the decode step (the DEFER forms of k_append_split and k_append_valu): partial sums
+  // [slice][plane][B][Hkv * R] fp32, and one word per sequence saying that its length was advanced and the row is still to
+  // be written
   float* defer_out;
   int* pending;
 };

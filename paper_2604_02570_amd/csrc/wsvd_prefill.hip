@@ -10,8 +10,9 @@
 //                                                                   relative each)
 //   epilogue  O^T [d x 32 queries] = B_V^T (U / l)                  bf16 MFMA, U an bf16 pair
 //
-// The loop is bound by the vector ALU (16 exponentials at half rate are a quarter of it; the products hide behind it only
-// in part, about 10 cycles each remain), so it is laid out to spend few vector instructions per score:
+// The loop is bound by the vector ALU (81 vector instructions per 32 x 32 block and wave, of which the 16 exponentials run
+// at half rate, 8.3 against 4.2 cycles: a third of it; the products hide behind it only in part, about 10 cycles each
+// remain), so it is laid out to spend few vector instructions per score:
 //   * the QW waves of a key group convert the codes of QW cache blocks to fp16 operands once, one block each, through two
 //     LDS stages, and each attends its own 32 query rows to all of them (48 of the conversion's instructions per block
 //     become 12 and 6 LDS reads; a single wave of rows converts for itself, without LDS: 64 x 9 tokens of rank 64 over 1000
@@ -27,9 +28,12 @@
 //   * the weights are summed in fp32, before they are rounded to fp16 for the value product.
 // 16 x 2048 tokens, 32 heads, r = 32: 0.43 ms (0.53 ms with one wave per 32 rows converting for itself, the maximum
 // exchanged every block and P through LDS).  A reference that is moved only when a block's weights sum to more than 64,
-// with the weights summed as the fp16 values: 0.42 ms, but the largest weight is then not exact (error against 64 bits up
-// to 2.14e-4 where this has 2.12e-4, and 2.5e-4 with the sum in fp32).  Tried and slower: two query blocks per wave without
-// LDS (193 registers, two waves per SIMD; three waves spill), the next block's score products issued under the softmax.
+// with the weights summed as the fp16 values: the same time there, but the largest weight is then not exact (error against
+// 64 bits up to 2.14e-4 where this has 2.12e-4, and 2.5e-4 with the sum in fp32).  With scores so small that such a
+// reference never moves, the maxima that do cost 7 % (0.53 ms against 0.49 at the clock that data leaves, 0.64 with one wave
+// per 32 rows).  Tried, no gain: the lane halves' exchange by v_permlane32_swap instead of LDS.  Tried and slower: two query
+// blocks per wave without LDS (193 registers, two waves per SIMD; three waves spill), the next block's score products issued
+// under the softmax.
 //
 // A workgroup is QW x KG waves: KG key groups take every KG-th stage of QW blocks, their (m, l, U) meet in LDS.  A query
 // row is a (token, head) pair, token-major, so the G heads that share a kv head share the stream too.  The cache blocks
