@@ -24,7 +24,8 @@ struct ProjectParams {
   int* seq_lens;
   int* err_word;
   int Hkv, E, t_cap, n_tok, seq0;   // direct kernel: grid z = sequence - seq0
-  int n_cg, tg_seq, n_tg;           // tile kernels: channel groups, token groups per sequence and in all
+  int rows;                         // rows that tiles are cut from: n_tok, or n_seq * n_tok (tiles across sequences)
+  int n_cg, tg_seq, n_tg;           // tile kernels: channel groups, token groups per set of rows and in all
   bool token_affine;                // tile kernels: see project_groups
   // paged cache only (else null): codes / meta are pools of n_pages pages, a page = page_rows rows of every kv head in the
   // layout of a contiguous plane; block_table [B][max_pages]
@@ -138,31 +139,37 @@ WSVD_DEV void store_row_i4(const ProjectParams& p, const v16f& a, int pl, int se
 // is a template parameter and no loop leaves early: every index into acc has to be a constant after unrolling.  (With
 // both formats in one body the loops stayed rolled, acc was indexed at run time and all 256 accumulators of a lane lived
 // in scratch memory: 10.2 ms for 16 x 2048 tokens against 0.5 ms.)
-template <int R, int CT, int TT, bool I4>
-WSVD_DEV void project_store(const ProjectParams& p, v16f (&acc)[CT][TT], int ct0, int tb, int seq, int n0) {
+// SPAN: a tile's rows run on into the next sequences (row % n_tok of sequence seq + row / n_tok); otherwise all are of
+// sequence seq.  n0: the rows that a row's sequence holds, asked for ahead of the store.
+template <bool SPAN>
+WSVD_DEV int row_length(const ProjectParams& p, int seq, int row) {
+  return p.seq_lens[SPAN ? seq + min(row, p.rows - 1) / p.n_tok : seq];
+}
+template <int R, int CT, int TT, bool I4, bool SPAN>
+WSVD_DEV void project_store_tile(const ProjectParams& p, const v16f (&acc)[CT][TT], int h, int tt, int ct0, int row0, int seq, int n0) {
   constexpr int RT = R / 32;
   static_assert(!I4 || R == 32, "int4 latents have rank 32");
-  const int n = threadIdx.x & 31;
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
+  const int ct = ct0 + h * RT;
+  const int pl = ct / tiles_plane, kv = (ct % tiles_plane) / RT;        // (wave-uniform)
+  const int row = row0 + 32 * tt + (threadIdx.x & 31), sq = SPAN ? min(row, p.rows - 1) / p.n_tok : 0;
+  const int tok = row - sq * p.n_tok, t = n0 + tok;                     // this lane's token of the prompt, its cache row
+  const bool on = ct < tiles && row < p.rows && n0 >= 0 && t < p.t_cap;
+  if constexpr (I4) {
+    store_row_i4(p, acc[h][tt], pl, seq + sq, kv, t, on && (n0 & 1) == 0, tok + 1 < p.n_tok && t + 1 < p.t_cap);
+  } else {
+    v16f a[RT];
 #pragma unroll
-  for (int h = 0; h < CT / RT; h++) {
-    const int ct = ct0 + h * RT;
-    const int pl = ct / tiles_plane, kv = (ct % tiles_plane) / RT;      // (wave-uniform)
-#pragma unroll
-    for (int tt = 0; tt < TT; tt++) {
-      const int tok = (tb * TT + tt) * 32 + n;                          // this lane's token of the prompt
-      const int t = n0 + tok;                                           // and its cache row
-      const bool on = ct < tiles && tok < p.n_tok && n0 >= 0 && t < p.t_cap;
-      if constexpr (I4) {
-        store_row_i4(p, acc[h][tt], pl, seq, kv, t, on && (n0 & 1) == 0, tok + 1 < p.n_tok && t + 1 < p.t_cap);
-      } else {
-        v16f a[RT];
-#pragma unroll
-        for (int rt = 0; rt < RT; rt++) a[rt] = acc[h * RT + rt][tt];
-        store_row_i8<RT>(p, a, pl, seq, kv, t, on);
-      }
-    }
+    for (int rt = 0; rt < RT; rt++) a[rt] = acc[h * RT + rt][tt];
+    store_row_i8<RT>(p, a, pl, seq + sq, kv, t, on);
   }
+}
+template <int R, int CT, int TT, bool I4, bool SPAN>
+WSVD_DEV void project_store(const ProjectParams& p, const v16f (&acc)[CT][TT], int ct0, int row0, int seq, const int (&n0)[TT]) {
+#pragma unroll
+  for (int h = 0; h < CT / (R / 32); h++)
+#pragma unroll
+    for (int tt = 0; tt < TT; tt++) project_store_tile<R, CT, TT, I4, SPAN>(p, acc, h, tt, ct0, row0, seq, n0[tt]);
 }
 
 template <int R, int CT, int TT, int WC, bool I4 = false, int ST = 3>
@@ -175,7 +182,9 @@ __global__ __launch_bounds__(256) void k_prefill_project(ProjectParams p) {
   const int tb = blockIdx.y * (4 / WC) + wave / WC;                     // its group of TT token tiles
   if (ct0 >= tiles || tb * 32 * TT >= p.n_tok) return;
   const int seq = p.seq0 + blockIdx.z;
-  const int n0 = p.seq_lens[seq];
+  int n0[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<false>(p, seq, 0);
   const int n_steps = p.E >> 4;
   const uint16_t* ap[CT];
 #pragma unroll
@@ -218,7 +227,7 @@ __global__ __launch_bounds__(256) void k_prefill_project(ProjectParams p) {
       }
     }
   }
-  project_store<R, CT, TT, I4>(p, acc, ct0, tb, seq, n0);
+  project_store<R, CT, TT, I4, false>(p, acc, ct0, tb * TT * 32, seq, n0);
 }
 
 // The same projection with both operands staged through LDS: a workgroup of 8 waves (2 x 4, each 4 x 2 tiles) owns
@@ -247,7 +256,7 @@ WSVD_DEV void project_groups(const ProjectParams& p, int& cg, int& tg) {
   else { cg = L % p.n_cg; tg = L / p.n_cg; }
 }
 
-template <int R, bool I4>
+template <int R, bool I4, bool SPAN>
 __global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
   extern __shared__ __align__(16) uint8_t proj_lds[];
   constexpr int WAVES = 8;
@@ -258,9 +267,11 @@ __global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
   int cg, tg;
   project_groups(p, cg, tg);
-  const int sq = tg / p.tg_seq, by = tg % p.tg_seq;                     // sequence of the launch, 256-token group in it
-  const int seq = p.seq0 + sq;
-  const int n0 = p.seq_lens[seq];
+  const int sq = tg / p.tg_seq, by = tg % p.tg_seq;                     // set of rows, 256-row group in it
+  const int seq = p.seq0 + sq;                                          // (its first sequence)
+  int n0[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, by * 256 + (wt * TT + tt) * 32 + n);
   const int n_steps = p.E >> 4, n_chunks = p.E / kProjKC;
   // what this thread copies per chunk: 16 bytes of each of the 8 channel tiles, 16 bytes of 8 of the 256 token rows
   // (uniform base pointers plus 32-bit per-thread offsets: the loads address through scalar registers)
@@ -275,8 +286,7 @@ __global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
     const int ct = min(cg * 8 + (u >> 8), tiles - 1);
     asrc[j] = (const uint8_t*)p.A[ct / tiles_plane] + (size_t)(ct % tiles_plane) * n_steps * 1024;
     const int row = u >> 3, sg = u & 7;
-    const int tok = min(by * 256 + row, p.n_tok - 1);
-    xoff[j] = (uint32_t)tok * (uint32_t)(p.E * 2) + sg * 16;            // the launcher keeps n_tok * E * 2 below 2^31
+    xoff[j] = (uint32_t)min(by * 256 + row, p.rows - 1) * (uint32_t)(p.E * 2) + sg * 16;   // the launcher keeps rows * E * 2 below 2^31
     xdst[j] = kProjABytes + row * kProjXRow + sg * 16;
   }
   v4u rg[2 * NLD];                                                      // the chunk on its way: NLD pieces of A, NLD of x
@@ -341,38 +351,40 @@ __global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
     }
     __syncthreads();
   }
-  const int ct0 = (cg * 2 + wc) * CT, tb = by * (8 / TT) + wt;
-  if (ct0 >= tiles || tb * 32 * TT >= p.n_tok) return;
-  project_store<R, CT, TT, I4>(p, acc, ct0, tb, seq, n0);
+  const int ct0 = (cg * 2 + wc) * CT, row0 = by * 256 + wt * 32 * TT;
+  if (ct0 >= tiles || row0 >= p.rows) return;
+  project_store<R, CT, TT, I4, SPAN>(p, acc, ct0, row0, seq, n0);
 }
 
 // The projection with the hidden states staged through LDS and the factors straight from memory into the registers that
 // feed the matrix cores (the packed image is the operand, a wave's channels are its own, so LDS would only cost it a write
-// and a read).  A workgroup of 4 waves owns 128 CT channels (wave w the CT tiles from 4 CT cg + CT w on) x 32 TT tokens;
-// every wave multiplies with all of the workgroup's tokens.  DEPTH chunks of 64 model dims are on their way in registers,
-// two LDS stages of hidden states take turns, one barrier per chunk.  For problems that do not fill the chip with 256 x 256
-// tiles: bound by the chain of a chunk (barrier, LDS read, products), so more and smaller workgroups win until they are
-// two to a CU, then the re-reading of the operands decides (project_shape_rule has the figures).  The kernel without LDS in
-// 2 x 1 tiles, which served these sizes before: 50 us at 1 x 200, 83 at 3 x 333, 58 at 64 x 4 and 97 at 64 x 32 tokens of
-// rank 32.  (Both operands through LDS with 2 x 2 waves: 23.2 us at 11 and 49-51 us at 3 x 333 tokens.)
-template <int R, int CT, int TT, bool I4>
-__global__ __launch_bounds__(256) void k_prefill_project_direct(ProjectParams p) {
-  constexpr int RT = R / 32, DEPTH = 4;                                 // (2 or 8 chunks ahead: within 5 %)
+// and a read).  A workgroup owns 32 CT WC channels x 32 TT rows; its waves are KS groups of WC (wave w of a group: the CT
+// channel tiles from CT (WC cg + w) on, all of the workgroup's rows).  Group g takes the chunks g, g + KS, .. of 64 model dims
+// through two LDS stages of its own, DEPTH chunks on their way in registers, one barrier per round; the groups' sums meet in
+// LDS.  For problems that do not fill the chip with 256 x 256 tiles.  What bounds it is what a CU takes in, 64 bytes a clock
+// (126 B/ns measured out of L2 on few CUs, 95 to 105 on all): (channels + rows) x d_model x 2 bytes per workgroup, 128 x 32
+// at 125 B/ns, 128 x 64 at 72 with all CUs busy.  Hence as few bytes as the number of workgroups allows (project_shape_rule),
+// and the contraction split inside the workgroup where its tile is too small to keep 8 waves busy otherwise.
+template <int R, int CT, int TT, int WC, int KS, int DEPTH, bool I4, bool SPAN>
+__global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(ProjectParams p) {
+  constexpr int RT = R / 32;
   static_assert(CT % RT == 0, "a head's channels stay in one wave");
   static_assert(DEPTH % 2 == 0, "LDS stage and register set follow from the position in the unrolled loop");
-  constexpr int NX = TT, NS = kProjKC / 16;                             // 16-byte pieces of x per thread and chunk; steps
+  static_assert((4 * TT) % WC == 0, "a group's threads copy whole rows");
+  constexpr int NX = 4 * TT / WC, NS = kProjKC / 16;                    // 16-byte pieces of x per thread and chunk; steps
   constexpr int STAGE = 32 * TT * kProjXRow;
-  __shared__ __attribute__((aligned(16))) uint8_t lds[2 * STAGE];
-  const int tid = threadIdx.x, lane = tid & 63, n = lane & 31, g2 = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  extern __shared__ __align__(16) uint8_t proj_lds[];
+  const int lane = threadIdx.x & 63, n = lane & 31, g2 = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wc = wave % WC, kg = wave / WC;
+  const int gt = wc * 64 + lane;                                        // thread of its group
+  uint8_t* const lds = proj_lds + kg * 2 * STAGE;
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
   int cg, tg;
   project_groups(p, cg, tg);
   const int sq = tg / p.tg_seq, by = tg % p.tg_seq;
   const int seq = p.seq0 + sq;
-  const int n0 = p.seq_lens[seq];
-  const int n_steps = p.E >> 4, n_chunks = p.E / kProjKC;
-  const int ct0 = (cg * 4 + wave) * CT;                                 // first channel tile of this wave
+  const int n_steps = p.E >> 4, n_chunks = p.E / kProjKC, n_iter = (n_chunks + KS - 1) / KS;
+  const int ct0 = (cg * WC + wc) * CT;                                  // first channel tile of this wave
   const uint8_t* asrc[CT];
 #pragma unroll
   for (int c = 0; c < CT; c++) {
@@ -382,27 +394,28 @@ __global__ __launch_bounds__(256) void k_prefill_project_direct(ProjectParams p)
   const uint8_t* xbase = (const uint8_t*)p.x + (size_t)sq * p.n_tok * p.E * 2;
   uint32_t xoff[NX];
 #pragma unroll
-  for (int j = 0; j < NX; j++)                                          // (the launcher keeps n_tok * E * 2 below 2^31)
-    xoff[j] = (uint32_t)min(by * 32 * TT + (tid >> 3) + 32 * j, p.n_tok - 1) * (uint32_t)(p.E * 2) + (tid & 7) * 16;
-  const int xdst = (tid >> 3) * kProjXRow + (tid & 7) * 16;             // + 32 j rows
+  for (int j = 0; j < NX; j++)                                          // (the launcher keeps rows * E * 2 below 2^31)
+    xoff[j] = (uint32_t)min(by * 32 * TT + (gt >> 3) + 8 * WC * j, p.rows - 1) * (uint32_t)(p.E * 2) + (gt & 7) * 16;
+  const int xdst = (gt >> 3) * kProjXRow + (gt & 7) * 16;               // + 8 WC j rows
   const uint32_t aoff = lane * 16;
   v8bf16 ra[DEPTH][CT][NS];
   v4u rx[DEPTH][NX];
-  auto fetch_a = [&](int b, int c) {
-    c = min(c, n_chunks - 1);                                           // (past the end: the last chunk again, not used)
+  auto chunk = [&](int it) { return min(it * KS + kg, n_chunks - 1); }; // (past the end: the last chunk again, not used)
+  auto fetch_a = [&](int b, int it) {
+    const int c = chunk(it);
 #pragma unroll
     for (int cc = 0; cc < CT; cc++)
 #pragma unroll
       for (int ks = 0; ks < NS; ks++) ra[b][cc][ks] = *(const v8bf16*)((asrc[cc] + (size_t)c * 4096 + ks * 1024) + aoff);
   };
-  auto fetch_x = [&](int b, int c) {
-    c = min(c, n_chunks - 1);
+  auto fetch_x = [&](int b, int it) {
+    const int c = chunk(it);
 #pragma unroll
     for (int j = 0; j < NX; j++) rx[b][j] = *(const v4u*)((xbase + (size_t)c * (kProjKC * 2)) + xoff[j]);
   };
   auto commit = [&](int b, int st) {
 #pragma unroll
-    for (int j = 0; j < NX; j++) *(v4u*)(lds + st * STAGE + 32 * j * kProjXRow + xdst) = rx[b][j];
+    for (int j = 0; j < NX; j++) *(v4u*)(lds + st * STAGE + 8 * WC * j * kProjXRow + xdst) = rx[b][j];
   };
   v16f acc[CT][TT];
 #pragma unroll
@@ -417,31 +430,80 @@ __global__ __launch_bounds__(256) void k_prefill_project_direct(ProjectParams p)
   fetch_x(0, DEPTH);
   __syncthreads();
   const int x_off = n * kProjXRow + g2 * 16;
-  // chunk c sits in LDS stage c & 1 and in factor set c % DEPTH; set (c + 1) % DEPTH of the hidden states holds chunk c + 1
-  for (int c0 = 0; c0 < n_chunks; c0 += DEPTH) {
+  // round it of the group's chunks sits in LDS stage it & 1 and in factor set it % DEPTH; set (it + 1) % DEPTH of the hidden
+  // states holds round it + 1
+  auto round = [&](int u, int it, bool mine) {                          // (u = it % DEPTH, a constant after unrolling)
+    commit((u + 1) % DEPTH, (u + 1) & 1);
+    fetch_x((u + 1) % DEPTH, it + 1 + DEPTH);
+    const uint8_t* base = lds + (u & 1) * STAGE + x_off;
+    if (mine) {
 #pragma unroll
-    for (int u = 0; u < DEPTH; u++) {
-      if (c0 + u < n_chunks) {                                          // (uniform)
-        commit((u + 1) % DEPTH, (u + 1) & 1);
-        fetch_x((u + 1) % DEPTH, c0 + u + 1 + DEPTH);
-        const uint8_t* base = lds + (u & 1) * STAGE + x_off;
+      for (int ks = 0; ks < NS; ks++) {
+        v8bf16 fb[TT];
 #pragma unroll
-        for (int ks = 0; ks < NS; ks++) {
-          v8bf16 fb[TT];
+        for (int tt = 0; tt < TT; tt++) fb[tt] = *(const v8bf16*)(base + tt * 32 * kProjXRow + ks * 32);
 #pragma unroll
-          for (int tt = 0; tt < TT; tt++) fb[tt] = *(const v8bf16*)(base + tt * 32 * kProjXRow + ks * 32);
+        for (int cc = 0; cc < CT; cc++)
 #pragma unroll
-          for (int cc = 0; cc < CT; cc++)
-#pragma unroll
-            for (int tt = 0; tt < TT; tt++) acc[cc][tt] = mfma_bf16(ra[u][cc][ks], fb[tt], acc[cc][tt]);
-        }
-        fetch_a(u, c0 + u + DEPTH);
-        __syncthreads();
+          for (int tt = 0; tt < TT; tt++) acc[cc][tt] = mfma_bf16(ra[u][cc][ks], fb[tt], acc[cc][tt]);
       }
     }
+    fetch_a(u, it + DEPTH);
+    __syncthreads();
+  };
+  // The loop takes DEPTH rounds at a time and has no branch inside: with a round that could be skipped, the compiler has to
+  // assume that only the last one's requests are in flight and drains all of them once per DEPTH rounds, which doubled the time.
+  const int n_main = n_chunks / KS / DEPTH * DEPTH;
+  for (int it = 0; it < n_main; it += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++) round(u, it + u, true);
   }
-  if (ct0 >= tiles) return;
-  project_store<R, CT, TT, I4>(p, acc, ct0, by, seq, n0);
+  for (int it = n_main; it < n_iter; it += DEPTH) {
+#pragma unroll
+    for (int u = 0; u < DEPTH; u++)
+      if (it + u < n_iter) round(u, it + u, (it + u) * KS + kg < n_chunks);
+  }
+  int n0[TT];                                                           // (asked for here: no registers during the products)
+#pragma unroll
+  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, (by * TT + tt) * 32 + n);
+  if constexpr (KS == 1) {
+    if (ct0 >= tiles) return;
+    project_store<R, CT, TT, I4, SPAN>(p, acc, ct0, by * 32 * TT, seq, n0);
+  } else {
+    // the groups' sums meet in LDS: unit u (the channels of a head x 32 rows) is added up in group order and stored by group
+    // u % KS, from the pieces the other groups leave there
+    constexpr int NU = CT / RT * TT;
+    float* const mine = (float*)proj_lds + lane;
+    auto piece = [&](int u, int g) { return ((u * (KS - 1) + (g > u % KS ? g - 1 : g)) * WC + wc) * (RT * 1024); };
+#pragma unroll
+    for (int u = 0; u < NU; u++) {
+      if (u % KS == kg) continue;
+      const int at = piece(u, kg);
+#pragma unroll
+      for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) mine[at + (rt * 16 + v) * 64] = acc[u / TT * RT + rt][u % TT][v];
+    }
+    __syncthreads();
+    if (ct0 >= tiles) return;
+#pragma unroll
+    for (int u = 0; u < NU; u++) {
+      if (u % KS != kg) continue;
+#pragma unroll
+      for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+        for (int v = 0; v < 16; v++) {
+          float sum = 0.f;
+#pragma unroll
+          for (int g = 0; g < KS; g++) {
+            const float x = g == u % KS ? acc[u / TT * RT + rt][u % TT][v] : mine[piece(u, g) + (rt * 16 + v) * 64];
+            sum = g ? sum + x : x;
+          }
+          acc[u / TT * RT + rt][u % TT][v] = sum;
+        }
+      project_store_tile<R, CT, TT, I4, SPAN>(p, acc, u / TT, u % TT, ct0, by * 32 * TT, seq, n0[u % TT]);
+    }
+  }
 }
 
 // after the projection: the lengths move on by the rows that fitted (one thread per sequence)
@@ -464,59 +526,93 @@ void launch_project(const ProjectParams& p, int n_seq, hipStream_t s) {
   hipLaunchKernelGGL((k_prefill_project<R, CT, TT, WC, I4>), grid, dim3(256), 0, s, p);
 }
 
-void project_grid(ProjectParams& p, int n_seq, int ch_wg, int tok_wg, int R) {
-  p.n_cg = (2 * p.Hkv * R + ch_wg - 1) / ch_wg; p.tg_seq = (p.n_tok + tok_wg - 1) / tok_wg; p.n_tg = p.tg_seq * n_seq;
+void project_grid(ProjectParams& p, int n_seq, int ch_wg, int tok_wg, int R, bool i4) {
+  // Tiles across sequences where that saves a round of workgroups (a last tile of few rows is cheap: 16 x 260 tokens, three
+  // rounds of 256 x 64 either way, 105 us in 640 workgroups and 110 in 520; 64 x 4 tokens 53 and 16) and the rows' offsets fit
+  // 32 bits; int4 stores pair the rows of neighbouring lanes, so there a sequence has to begin in an even lane.
+  p.n_cg = (2 * p.Hkv * R + ch_wg - 1) / ch_wg;
+  const long long own = (long long)((p.n_tok + tok_wg - 1) / tok_wg) * n_seq, all = ((long long)n_seq * p.n_tok + tok_wg - 1) / tok_wg;
+  const bool span = (all * p.n_cg + 255) / 256 < (own * p.n_cg + 255) / 256 && (long long)n_seq * p.n_tok * p.E * 2 < (1LL << 31) &&
+                    (!i4 || p.n_tok % 2 == 0);
+  p.rows = span ? n_seq * p.n_tok : p.n_tok;
+  p.n_tg = (int)(span ? all : own);
+  p.tg_seq = span ? p.n_tg : (int)(own / n_seq);
   p.token_affine = p.n_tg % 8 == 0;
 }
 
-template <int R, int CT, int TT, bool I4 = false>
-void launch_project_direct(ProjectParams p, int n_seq, hipStream_t s) {
-  project_grid(p, n_seq, 128 * CT, 32 * TT, R);
+template <int R, int CT, int TT, int WC, int KS, int DEPTH, bool I4, bool SPAN>
+hipError_t launch_project_direct_span(const ProjectParams& p, hipStream_t s) {
+  constexpr int RT = R / 32, STAGES = KS * 2 * 32 * TT * kProjXRow, PIECES = CT / RT * TT * (KS - 1) * WC * RT * 4096;
+  constexpr int LDS = STAGES > PIECES ? STAGES : PIECES;
+  static bool raised = false;             // (as in launch_project_lds_span)
+  if (LDS > 65536 && !raised) {
+    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_direct<R, CT, TT, WC, KS, DEPTH, I4, SPAN>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (e != hipSuccess) return e;
+    raised = true;
+  }
+  hipLaunchKernelGGL((k_prefill_project_direct<R, CT, TT, WC, KS, DEPTH, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(64 * WC * KS), LDS, s, p);
+  return hipGetLastError();
+}
+// (tiles that stay inside a sequence keep its plane's address in scalar registers: 2 to 3 % of short calls, 1.5 % of 16 x 2048
+// tokens in 256 x 256 tiles)
+template <int R, int CT, int TT, int WC, int KS, int DEPTH, bool I4 = false>
+hipError_t launch_project_direct(ProjectParams p, int n_seq, hipStream_t s) {
+  project_grid(p, n_seq, 32 * WC * CT, 32 * TT, R, I4);
   // (which operand stays with an XCD: see project_groups)
   const long long ch = 2LL * p.Hkv * R;
   const bool l2_holds_factors = ch * p.E * 2 <= (9LL << 20);
   if (p.n_cg % 2 == 0 && !(l2_holds_factors && (long long)n_seq * p.n_tok >= ch)) p.token_affine = false;
-  hipLaunchKernelGGL((k_prefill_project_direct<R, CT, TT, I4>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(256), 0, s, p);
+  return p.rows == p.n_tok ? launch_project_direct_span<R, CT, TT, WC, KS, DEPTH, I4, false>(p, s) :
+                             launch_project_direct_span<R, CT, TT, WC, KS, DEPTH, I4, true>(p, s);
 }
 
-template <int R, bool I4 = false>
-hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
+template <int R, bool I4, bool SPAN>
+hipError_t launch_project_lds_span(const ProjectParams& p, hipStream_t s) {
   static bool raised = false;             // the kernel's limit of dynamic LDS, raised once per instantiation
   const size_t lds = 2 * (size_t)kProjStage;
   if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_lds<R, I4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_lds<R, I4, SPAN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     raised = true;
   }
-  project_grid(p, n_seq, 256, 256, R);
-  hipLaunchKernelGGL((k_prefill_project_lds<R, I4>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(512), lds, s, p);
+  hipLaunchKernelGGL((k_prefill_project_lds<R, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(512), lds, s, p);
   return hipGetLastError();
 }
+template <int R, bool I4 = false>
+hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
+  project_grid(p, n_seq, 256, 256, R, I4);
+  return p.rows == p.n_tok ? launch_project_lds_span<R, I4, false>(p, s) : launch_project_lds_span<R, I4, true>(p, s);
+}
 
-// The tile size, by how often 256 workgroups (one per CU) have to run one after the other, q = ceil(workgroups / 256):
-//   11: 128 channels (rank 64: 256) x 32 tokens, about 18 (27) us a round at d_model 4096 after the first;
-//   22: 256 x 64, about 36 us a round;    2: 256 x 256, 100 us a round and 30 more as its rows fill with tokens.
-// So 11 while its rounds are at most 2 (1) times those of 22: a quarter (half) of the area costs half (three quarters) of
-// the time.  And 2 instead of 22 when its rounds, priced by the tokens they hold, cost less.  us per call with the length
-// update, 32 kv heads, d_model 4096:
-//   rank 32    16 x 3  16 x 32  64 x 4  64 x 32  3 x 333  4 x 500  16 x 130  16 x 260  2 x 2048  8 x 1024  16 x 2048
-//   11           21      25       51      63        48       66       76        140       137       242       1017
-//   22           39      41       64      70        43       47       70        115        87       155        611
-//   2           102     101      205     207       106      105      105        126       121       134        514
-//   rank 64    16 x 3  16 x 32  64 x 4  64 x 32  3 x 333  4 x 500  16 x 130  16 x 260  2 x 2048  8 x 1024
-//   11           37      35       95     111        78      110      134        238       226       412
-//   22           42      42      120     132        67       78      109        179       152       284
-//   2           112     112      418     429       107      109      122        254       137       262
-int project_shape_rule(int Hkv, int R, int n_tok, int n_seq) {
-  const long long ch = 2LL * Hkv * R, ch11 = 4LL * R;
-  auto rounds = [&](long long ch_wg, int tok_wg) {
-    const long long wgs = (ch + ch_wg - 1) / ch_wg * ((n_tok + tok_wg - 1) / tok_wg) * n_seq;
-    return (wgs + 255) / 256;
-  };
-  const long long q22 = rounds(256, 64), q2 = rounds(256, 256);
-  if (rounds(ch11, 32) <= (R == 32 ? 2 : 1) * q22) return 11;
-  const long long held = 100LL * n_tok / ((n_tok + 255) / 256 * 256LL);       // per cent of a 256-token tile
-  return q2 * (100 + 30 * held / 100) < 38 * q22 ? 2 : 22;
+// The tile size.  256 workgroups (one per CU) run side by side; a round of them costs (chain + busy * load^2) * d_model / 4096
+// us, load being the share of the CUs that it keeps busy (1 but for the last round), and what does not depend on d_model (first requests, sums,
+// store) shows once in full and 0.4 times for every further round, because a CU has the next workgroup beside it.  The shape
+// that costs least.  Smaller tiles read the operands more often (see k_prefill_project_direct), larger ones leave CUs idle.
+// us per call with the copy of the lengths and their update (about 6 us of it), 32 kv heads of rank 32 / 64, d_model 4096:
+//                   1 x 200   16 x 32   1 x 400   3 x 333   4 x 500  16 x 130  2 x 2048  8 x 1024    64 x 4
+//    5:  64 x  32     16/23     25/42     24/40     41/77    71/147    78/156   141/288   267/553     17/24
+//   11: 128 x  32     20/22     22/36     20/34     35/63    62/119    73/134   119/229   230/456     20/23
+//   12: 128 x  64     25/30     27/31     26/31     31/49     53/89    71/106   101/168   192/342     26/31
+//   22: 256 x  64     42/41     41/43     42/42     43/47     47/78    72/111    84/149   158/304     44/42
+//   25: 256 x 128     54/55     53/59     56/55     57/56     57/69    65/122    74/135   141/267     56/57
+//    2: 256 x 256    103/103   102/109   105/104   107/105   106/106   104/121   114/134   135/261   110/109
+//   former kernels    19/35     27/40     25/35     45/70     53/83    75/115    92/144   141/278    59/106
+// (those: 11, of rank 64 in 256 x 32, 22 without the split, 2; tiles that ended with each sequence)
+struct ProjectShape { int code, ch, tok; float fixed[2], chain, busy; };              // fixed: rank 32, 64
+constexpr ProjectShape kProjectShapes[] = {
+    {5, 64, 32, {2.f, 2.4f}, 6.3f, 0.8f},  {11, 128, 32, {2.f, 3.2f}, 10.5f, 2.5f}, {12, 128, 64, {3.6f, 2.5f}, 17.f, 5.f},
+    {22, 256, 64, {5.4f, 4.5f}, 30.f, 5.f}, {25, 256, 128, {6.f, 6.f}, 44.f, 18.f},  {2, 256, 256, {11.f, 11.f}, 89.f, 32.f}};
+int project_shape_rule(const ProjectParams& p, int n_seq, int R, bool i4) {
+  int best = 0;
+  float least = 0.f;
+  for (const ProjectShape& k : kProjectShapes) {
+    ProjectParams g = p;
+    project_grid(g, n_seq, k.ch, k.tok, R, i4);
+    const float wgs = (float)g.n_cg * (float)g.n_tg, rounds = ceilf(wgs / 256.f), load = wgs / 256.f - (rounds - 1.f);
+    const float cost = k.fixed[R == 64] * (0.6f + 0.4f * rounds) + (rounds * k.chain + (rounds - 1.f + load * load) * k.busy) * (float)p.E / 4096.f;
+    if (!best || cost < least) { best = k.code; least = cost; }
+  }
+  return best;
 }
 
 }  // namespace
@@ -535,7 +631,7 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   p.codes[0] = (uint8_t*)cache.k_codes; p.codes[1] = (uint8_t*)cache.v_codes;
   p.meta[0] = (uint16_t*)cache.k_meta; p.meta[1] = (uint16_t*)cache.v_meta;
   p.seq_lens = cache.seq_lens; p.err_word = ctx->err_word;
-  p.Hkv = d.n_kv_heads; p.E = d.d_model; p.t_cap = d.t_cap; p.n_tok = n_tok;
+  p.Hkv = d.n_kv_heads; p.E = d.d_model; p.t_cap = d.t_cap; p.n_tok = p.rows = n_tok;
   p.n_cg = p.tg_seq = p.n_tg = 0; p.token_affine = false;
   p.block_table = nullptr; p.page_rows = p.max_pages = p.n_pages = 0;
   if (paged) { p.block_table = paged->block_table; p.page_rows = paged->page_rows; p.max_pages = paged->max_pages; p.n_pages = paged->n_pages; }
@@ -543,22 +639,35 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   p.seq0 = seq < 0 ? 0 : seq;
   const bool tiles_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
   int shape = ctx->opt.project_shape;
-  if (!shape) shape = project_shape_rule(d.n_kv_heads, d.rank, n_tok, n_seq);
-  if (!tiles_ok || (shape != 11 && shape != 22)) shape = tiles_ok && shape <= 2 ? 2 : 44;
+  if (!shape) shape = project_shape_rule(p, n_seq, d.rank, i4);
+  const bool direct = shape == 5 || shape == 11 || shape == 12 || shape == 22 || shape == 25;
+  if (!tiles_ok || !direct) shape = tiles_ok && shape <= 2 ? 2 : 44;
   hipError_t e = hipSuccess;
   if (d.rank > 64) {
     // ranks 96 / 128: a wave owns the 3 / 4 channel tiles of one head and 1 or 4 token tiles
     const bool big = (long long)n_seq * n_tok * d.n_kv_heads * d.rank >= (1LL << 22);
     if (d.rank == 96) { if (big) launch_project<96, 3, 4, 4>(p, n_seq, s); else launch_project<96, 3, 1, 4>(p, n_seq, s); }
     else { if (big) launch_project<128, 4, 4, 4>(p, n_seq, s); else launch_project<128, 4, 1, 4>(p, n_seq, s); }
+  } else if (shape == 5) {
+    if (i4) e = launch_project_direct<32, 1, 1, 2, 2, 4, true>(p, n_seq, s);
+    else if (d.rank == 32) e = launch_project_direct<32, 1, 1, 2, 2, 4>(p, n_seq, s);
+    else e = launch_project_direct<64, 2, 1, 1, 2, 4>(p, n_seq, s);
   } else if (shape == 11) {
-    if (i4) launch_project_direct<32, 1, 1, true>(p, n_seq, s);
-    else if (d.rank == 32) launch_project_direct<32, 1, 1>(p, n_seq, s);
-    else launch_project_direct<64, 2, 1>(p, n_seq, s);
+    if (i4) e = launch_project_direct<32, 1, 1, 4, 1, 4, true>(p, n_seq, s);
+    else if (d.rank == 32) e = launch_project_direct<32, 1, 1, 4, 1, 4>(p, n_seq, s);
+    else e = launch_project_direct<64, 2, 1, 2, 2, 4>(p, n_seq, s);
+  } else if (shape == 12) {
+    if (i4) e = launch_project_direct<32, 1, 2, 4, 2, 4, true>(p, n_seq, s);
+    else if (d.rank == 32) e = launch_project_direct<32, 1, 2, 4, 2, 4>(p, n_seq, s);
+    else e = launch_project_direct<64, 2, 2, 2, 2, 2>(p, n_seq, s);
   } else if (shape == 22) {
-    if (i4) launch_project_direct<32, 2, 2, true>(p, n_seq, s);
-    else if (d.rank == 32) launch_project_direct<32, 2, 2>(p, n_seq, s);
-    else launch_project_direct<64, 2, 2>(p, n_seq, s);
+    if (i4) e = launch_project_direct<32, 2, 2, 4, 1, 4, true>(p, n_seq, s);
+    else if (d.rank == 32) e = launch_project_direct<32, 2, 2, 4, 1, 4>(p, n_seq, s);
+    else e = launch_project_direct<64, 2, 2, 4, 1, 4>(p, n_seq, s);
+  } else if (shape == 25) {
+    if (i4) e = launch_project_direct<32, 2, 4, 4, 2, 2, true>(p, n_seq, s);
+    else if (d.rank == 32) e = launch_project_direct<32, 2, 4, 4, 2, 2>(p, n_seq, s);
+    else e = launch_project_direct<64, 2, 4, 4, 2, 2>(p, n_seq, s);
   } else if (shape == 2) {
     if (i4) e = launch_project_lds<32, true>(p, n_seq, s);
     else if (d.rank == 32) e = launch_project_lds<32>(p, n_seq, s);

@@ -65,6 +65,39 @@ def test_prompt_projection_chunk_tails(name, over, shape, n, d_model):
     _prompt(name, shape, n, **{**dict(batch=4 if n in (40, 70) else 3, context=120, d_model=d_model), **over})
 
 
+# tiles are cut from the rows of all sequences (int4: only where a sequence has an even number of tokens): several sequences in
+# a tile, a tile's edge inside one; the contraction split over the wave groups of a workgroup: fewer chunks than groups, a last
+# round that not every group has
+@pytest.mark.parametrize("d_model", [64, 192, 448])
+@pytest.mark.parametrize("shape,n", [(5, 9), (5, 34), (11, 22), (12, 21), (12, 66), (22, 22), (25, 43), (25, 130), (2, 90)])
+@pytest.mark.parametrize("name,over", [("c3_small", dict()), ("c3_small", dict(rank=64)), ("c4_small", dict(ragged=(60, 120)))], ids=["i8", "i8-r64", "i4"])
+def test_prompt_projection_tiles_across_sequences(name, over, shape, n, d_model):
+    _prompt(name, shape, n, **{**dict(batch=4, context=120, d_model=d_model), **over})
+
+
+@pytest.mark.parametrize("shape", [5, 12, 25, 2])
+def test_prompt_projection_full_sequence_inside_a_tile(shape):
+    """A sequence without room in the middle of a tile: reported, its own rows that fit are stored, its neighbours get theirs."""
+    n = 20
+    c = build_case("c3_small", batch=4, context=100, extra_cap=60)
+    L = layer_for(c)
+    lens = np.array([7, L.t_cap - 5, 0, 40], dtype=np.int32)
+    c.cache.seq_lens[:] = lens
+    L.upload(c.cache)
+    X = np.stack([WI.bf16_exact(WI.hidden_states(c.sp, n, 1.0, which="ctx", sub=70 + b)) for b in range(4)])
+    W.wsvd_ctx_set_option(L.ctx, "project_shape", shape)
+    W.wsvd_prefill_append(L.ctx, L.desc, as_dtype_dev(X.reshape(4 * n, -1), "bf16"), None, n, -1, L.pack_A(c.AK, "bf16"), L.pack_A(c.AV, "bf16"), L.cache)
+    assert W.wsvd_check(L.ctx) == W.E_CAPACITY
+    assert (L.seq_lens.cpu().numpy() == np.minimum(lens + n, L.t_cap)).all()
+    for b in range(4):
+        m = min(n, L.t_cap - int(lens[b]))
+        for plane, A in ((0, c.AK), (1, c.AV)):
+            c64 = _latents64(X[b], A)[..., :m, :]
+            gc, gs, _ = L.download(plane, int(lens[b]), m)
+            check_i8_rows(gc[b].reshape(c64.shape), gs[b].reshape(c64.shape[:-1]), c64, f"shape {shape} seq {b} plane {plane}")
+    L.close()
+
+
 @pytest.mark.parametrize("rank", [32, 64])
 @pytest.mark.parametrize("batch,n", [(64, 4), (64, 32), (16, 64), (16, 260), (1, 300), (8, 1024)])
 def test_prompt_projection_takes_a_fitting_tile(batch, n, rank):
