@@ -1820,7 +1820,7 @@ hipError_t wsvd_launch_attn_rope(const wsvd_ctx* ctx, const wsvd_layer_desc& d, 
   int threads;
   // always 8 waves per workgroup: the register budget allows no more, and the N build divides its work over exactly
   // that many threads (waves without a tile of their own idle through the loop)
-  wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p, grid, threads, 512);
+  wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p, grid, threads, 512, 8);
   RopeArgs ra;
   const double two_pi = 6.283185307179586476925286766559;
   for (int i = 0; i < 64; i++) {
