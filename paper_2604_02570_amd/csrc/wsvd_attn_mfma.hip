@@ -118,18 +118,24 @@ constexpr int kMaxTilesPerFlush = 1024;   // 64 tokens * 127 * 127 per tile and 
 // NT = launch bound (threads); the workgroup may be launched with any multiple of 64 threads up to NT.
 // STAGED: the variants that build something from B_K in LDS (rotary) or fold partial sums there (latent query) keep
 // the staging areas; the plain kernel absorbs the query per wave on the matrix cores and needs none of them.
-template <int R, int G, bool STAGED>
+template <int R, int G, int STAGED>
 struct AttnStaging {
   v4i bk_lds[R * 128 * 2 / 16], bv_lds[R * 128 * 2 / 16];
   __attribute__((aligned(16))) float q_lds[G * 128];
   float qts[G * R];
 };
 template <int R, int G>
-struct AttnStaging<R, G, false> {
+struct AttnStaging<R, G, 0> {
   v4i bk_lds[1], bv_lds[1];
   float q_lds[1], qts[1];
 };
-template <int R, int G, int NT, bool STAGED = true>
+template <int R, int G>
+struct AttnStaging<R, G, 2> {               // rotary variant with a table: rows of B_K padded by 16 bytes, B_V as the plain kernel
+  v4i bk_lds[R * (128 * 2 / 16 + 1)], bv_lds[1];
+  __attribute__((aligned(16))) float q_lds[G * 128];
+  float qts[1];
+};
+template <int R, int G, int NT, int STAGED = 1>
 struct AttnMfmaShared : AttnStaging<R, G, STAGED> {
   static constexpr int NWMAX = NT / 64;
   __attribute__((aligned(16))) int8_t qlimb[1][G][3][R];    // limbs of q~ in operand k-order
@@ -173,6 +179,20 @@ struct RopeShared {
   float rot[2][D / 2][2];                           // cos, sin of theta_i * shift for the two block-to-block shifts
   uint32_t fmax_bits[D / 2];                        // per frequency: largest |entry| of its two rows over all heads
 };
+// The form for one query head per kv head at rank 32.  There the features themselves would be the work: turning 64 of them per
+// lane and block and multiplying them with 64 outputs is 192 of the 296 vector instructions of a block, and nothing shares them.
+// So the roles are exchanged: the rotation up to the start t0 of a run of 128 tokens goes into the query (a wave rebuilds its N
+// for every run: with p, p' the query pair turned by theta_i (n-1-t0), N' = (p k_i + p' k_i', p' k_i - p k_i')), and what a token
+// b of the run adds is the same for every head, sequence and run: cos theta_i b, sin theta_i b, a table in LDS.  One product
+// W = N' F(b) on the matrix cores gives the latent-space query of every token of a block, and the score is W . c: 16 multiply-adds
+// per lane.  N' (at most 2^14) and F (times 2^10) are fp16 pairs, hi hi + lo hi + hi lo, all in normal range down to 2^-24 of
+// their largest.  24 products of 32 cycles per block of 32 tokens and wave bound it; for more query heads or rank 64 the form
+// above needs fewer (16 per head and 32; its rotation is shared by the heads).
+template <int D, int NT>
+struct RopeTable {
+  __attribute__((aligned(16))) _Float16 feat[4][D / 16][2][512];   // [32-token block of the run][step][hi, lo][lane][8]
+  __attribute__((aligned(16))) float turned[NT / 64][D / 2][2];    // per wave: the query pairs of the run
+};
 struct RopeArgs {
   uint32_t fq[64];                                  // theta_i / 2 pi as a 32-bit binary fraction of a revolution
   float rot[2][64][2];                              // cos, sin of theta_i * 32 and of theta_i * (64 * 8 - 32): the
@@ -186,6 +206,26 @@ WSVD_DEV void phase_sincos_fast(uint32_t phase, float& c, float& s) {
   const float rev = (float)(int32_t)phase * (1.0f / 4294967296.0f);
   c = __builtin_amdgcn_cosf(rev);
   s = __builtin_amdgcn_sinf(rev);
+}
+
+// the same to an ulp of fp32: the angle within an eighth of a revolution of a quarter turn, then the power series
+WSVD_DEV void phase_sincos(uint32_t phase, float& c, float& s) {
+  const uint32_t quad = (phase + 0x20000000u) >> 30;
+  const float x = (float)(int32_t)(phase - (quad << 30)) * 1.4629180792671596e-9f;      // 2 pi / 2^32
+  const float y = x * x;
+  const float sn = fmaf(x * y, fmaf(y, fmaf(y, fmaf(y, 1.f / 362880.f, -1.f / 5040.f), 1.f / 120.f), -1.f / 6.f), x);
+  const float cs = fmaf(y, fmaf(y, fmaf(y, fmaf(y, fmaf(y, -1.f / 3628800.f, 1.f / 40320.f), -1.f / 720.f), 1.f / 24.f), -0.5f), 1.f);
+  const float a = quad & 1 ? sn : cs, b = quad & 1 ? cs : sn;
+  c = __uint_as_float(__float_as_uint(a) ^ (((quad + 1) & 2) << 30));                   // quarters 1 and 2: negative cosine
+  s = __uint_as_float(__float_as_uint(b) ^ ((quad & 2) << 30));
+}
+
+// two values as fp16 pairs, in the instructions that take two: elements i, i + 1 of hi and lo
+WSVD_DEV void split_fp16_two(float x, float y, v8h& hi, v8h& lo, int i) {
+  asm volatile("" : "+v"(x), "+v"(y));                                                  // (see split_fp16_pair)
+  const _Float16 hx = (_Float16)x, hy = (_Float16)y;
+  hi[i] = hx; hi[i + 1] = hy;
+  lo[i] = (_Float16)fmaf((float)hx, -1.f, x); lo[i + 1] = (_Float16)fmaf((float)hy, -1.f, y);
 }
 
 // x * scale as an fp16 pair hi + lo.  The fp32 product is pinned in a register first: otherwise the compiler forms hi
@@ -207,11 +247,14 @@ WSVD_DEV void split_fp16_pair(float x, float scale, _Float16& hi, _Float16& lo) 
 // NEWROW: the second launch of the decode step.  The projection launch before it has advanced the lengths and left the
 // new token's latents as partial sums; the workgroup whose chunk holds a sequence's last row sums them, quantises and
 // stores the row (as the append would have) and patches it into the registers of the wave that consumes its tile.
-template <int R, int G, bool I4, int NT, bool FUSED, int ROPE_D = 0, bool LATENT = false, bool PAGED = false, bool NEWROW = false>
-WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE_D != 0 || LATENT)>& sh, const int cx, const int cy,
-                             const int cz, RopeShared<R, G, (ROPE_D ? ROPE_D : 64)>* rs = nullptr, const RopeArgs* ra = nullptr) {
+template <int R, int G, bool I4, int NT, bool FUSED, int ROPE_D = 0, bool LATENT = false, bool PAGED = false, bool NEWROW = false,
+          bool TABLE = false>
+WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABLE ? 2 : ROPE_D != 0 || LATENT)>& sh, const int cx,
+                             const int cy, const int cz, RopeShared<R, G, (ROPE_D ? ROPE_D : 64)>* rs = nullptr, const RopeArgs* ra = nullptr,
+                             RopeTable<(ROPE_D ? ROPE_D : 64), NT>* rtab = nullptr) {
   constexpr bool ROPE = ROPE_D != 0;
-  constexpr bool STAGED = ROPE || LATENT;
+  static_assert(!TABLE || (ROPE && R == 32 && G == 1), "rotation table: one query head at rank 32");
+  constexpr bool STAGED = ROPE || LATENT, LATE_BV = !STAGED || TABLE;      // B_V in registers, asked for at the stream's end
   using RG = RopeGeom<(ROPE_D ? ROPE_D : 64)>;
   static_assert(!ROPE || !FUSED, "rotary variant: stand-alone launch");
   static_assert(!LATENT || (!ROPE && !FUSED), "latent-query variant: stand-alone launch, no rotation");
@@ -289,6 +332,16 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
   TileRegs<R, I4> buf[DEPTH];
   const int chunk_tiles = p.chunk_rows >> 6;
   int T = (int)cy * chunk_tiles + wave;
+  // with a rotation table a wave takes runs of two tiles, so that it turns its query once per 128 tokens; single tiles where
+  // a chunk has not two for every wave
+  constexpr int NKS = TABLE ? ROPE_D / 16 : 1;
+  [[maybe_unused]] const int run_sh = TABLE && chunk_tiles >= 2 * NW ? 1 : 0;
+  [[maybe_unused]] float t_qa = 0.f, t_qb = 0.f, t_delta = 0.f;
+  [[maybe_unused]] uint32_t t_fq = 0u;
+  auto tile_at = [&](int j) {
+    if constexpr (TABLE) return (int)cy * chunk_tiles + (((j >> run_sh) * NW + wave) << run_sh) + (j & run_sh);
+    else return T + j * NW;
+  };
   // unconditional (clamped to the chunk's last allocated tile): see stage_issue
   const int spec_last = min(((int)cy + 1) * chunk_tiles, p.t_cap >> 6) - 1;
   constexpr int MAXP = 4;                                        // NEWROW: partial sums per latent element, at most
@@ -497,7 +550,7 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
     }
   } else {
   const int fac16 = R * p.d * 2 / 16;
-  StageRegs<FIT> stk, stv;
+  [[maybe_unused]] StageRegs<FIT> stk, stv;
   QRegs qr;
   // LATENT: q~[g][j] = sum_i c_Q[g][i] (B_Q B_K^T)[h][i][j].  Work item (quarter of the i range, g, j), j fastest so
   // that a wave's loads of the fold are contiguous; up to 16 products per item, the quarters meet in LDS.
@@ -527,11 +580,11 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
     }
   } else {
   stage_issue<FIT>(stk, (const char*)p.BK + (size_t)cx * R * p.d * 2, fac16);
-  stage_issue<FIT>(stv, (const char*)p.BV + (size_t)cx * R * p.d * 2, fac16);
+  if constexpr (!TABLE) stage_issue<FIT>(stv, (const char*)p.BV + (size_t)cx * R * p.d * 2, fac16);
   q_issue(p, cz, cx, qr);
   }
 #pragma unroll
-  for (int i = 0; i < DEPTH; i++) load_tile<R, I4>(buf[i], kplane, vplane, kmeta, vmeta, min(T + i * NW, spec_last), lane);
+  for (int i = 0; i < DEPTH; i++) load_tile<R, I4>(buf[i], kplane, vplane, kmeta, vmeta, min(tile_at(i), spec_last), lane);
   WSVD_STAMP(tl, tl_wg, wave, 1);
 
   // ---- query absorption and its limbs
@@ -545,13 +598,62 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
     __syncthreads();
     if (tid < G * R) qts[tid] = (qpart[tid] + qpart[G * R + tid] + qpart[2 * G * R + tid] + qpart[3 * G * R + tid]) * p.c_scale;
   } else {
-  stage_commit<FIT>(stk, bk_lds, fac16);
-  stage_commit<FIT>(stv, bv_lds, fac16);
+  if constexpr (TABLE) {
+    // the table: a slot = one lane's 8 elements of one step (4 frequencies: cosine, sine), hi and lo; a thread takes a slot of all
+    // four blocks, 32 tokens further by a fixed rotation each
+    for (int slot = tid; slot < NKS * 64; slot += (int)blockDim.x) {
+      const int l = slot & 63, ks = slot >> 6;
+      float c[4], sn[4];
+      v4f r[2];
+#pragma unroll
+      for (int f = 0; f < 4; f++) {
+        const int i = 8 * ks + 4 * (l >> 5) + f;
+        phase_sincos(ra->fq[i] * (uint32_t)(l & 31), c[f], sn[f]);
+        c[f] *= 1024.f; sn[f] *= 1024.f;
+        r[f >> 1][2 * (f & 1)] = ra->rot[0][i][0]; r[f >> 1][2 * (f & 1) + 1] = ra->rot[0][i][1];
+      }
+#pragma unroll
+      for (int blk = 0; blk < 4; blk++) {
+        v8h hi, lo;
+#pragma unroll
+        for (int f = 0; f < 4; f++) {
+          split_fp16_two(c[f], sn[f], hi, lo, 2 * f);
+          const float rc = r[f >> 1][2 * (f & 1)], rn = r[f >> 1][2 * (f & 1) + 1], c0 = c[f];
+          c[f] = fmaf(c0, rc, -(sn[f] * rn));
+          sn[f] = fmaf(sn[f], rc, c0 * rn);
+        }
+        *(v8h*)&rtab->feat[blk][ks][0][l * 8] = hi;
+        *(v8h*)&rtab->feat[blk][ks][1][l * 8] = lo;
+      }
+    }
+#pragma unroll
+    for (int ps = 0; ps < FIT; ps++) {                // rows of B_K, padded
+      const int i = tid + ps * (int)blockDim.x;
+      if (i < fac16) bk_lds[i + i / (ROPE_D / 8)] = stk.v[ps];
+    }
+  } else stage_commit<FIT>(stk, bk_lds, fac16);
+  if constexpr (!TABLE) stage_commit<FIT>(stv, bv_lds, fac16);
   q_commit(p, qr, 1.f, q_lds);          // an int8 query's scale is applied to delta below
   }
   __syncthreads();
   WSVD_STAMP(tl, tl_wg, wave, 2);
-  if constexpr (ROPE) {
+  if constexpr (TABLE) {
+    // one unit for the whole of N: |p k + p' k'| <= 2 max |q| max |k|, whatever the rotation
+    constexpr int Dh = ROPE_D / 2;
+    t_qa = q_lds[lane & (Dh - 1)]; t_qb = q_lds[(lane & (Dh - 1)) + Dh];
+    float kmax = 0.f;
+    for (int i = lane; i < R * ROPE_D / 8; i += 64) {
+      const v4i w4 = bk_lds[i + i / (ROPE_D / 8)];
+#pragma unroll
+      for (int x = 0; x < 4; x++)
+        kmax = fmaxf(kmax, fmaxf(fabsf(__uint_as_float((uint32_t)w4[x] << 16)), fabsf(__uint_as_float((uint32_t)w4[x] & 0xFFFF0000u))));
+    }
+    const float bound = 2.f * wave_max(fmaxf(fabsf(t_qa), fabsf(t_qb))) * wave_max(kmax);
+    const float unit = bound > 0.f ? 16384.f / bound : 0.f;
+    t_qa *= unit; t_qb *= unit;
+    t_delta = bound * p.c_scale * (1.f / (16384.f * 1024.f));
+    t_fq = ra->fq[lane & (Dh - 1)];
+  } else if constexpr (ROPE) {
     constexpr int Dh = ROPE_D / 2;
     // block-to-block rotations: +32 tokens (second block of a tile), then on to the wave's next tile
     if (tid < 2 * Dh) {
@@ -673,13 +775,13 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
   float delta[G], zsum[G];
 #pragma unroll
   for (int g = 0; g < G; g++) {
-    delta[g] = qdelta[g] * qs;
+    delta[g] = (TABLE ? t_delta : qdelta[g]) * qs;
     zsum[g] = I4 ? qzsum[g] : 0.f;
   }
 
   // rotary variant: this lane's position features (its token of the current block, the frequencies of its half)
-  float fc[ROPE ? RG::NFH : 1], fs[ROPE ? RG::NFH : 1];
-  if constexpr (ROPE) {
+  float fc[ROPE && !TABLE ? RG::NFH : 1], fs[ROPE && !TABLE ? RG::NFH : 1];
+  if constexpr (ROPE && !TABLE) {
     const int hf = lane >> 5;
     const uint32_t dist = (uint32_t)(n_raw - 1 - (T * 64 + (lane & 31)));   // query position minus key position
 #pragma unroll
@@ -691,7 +793,7 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
   }
   // advance the features by one of the two block-to-block shifts: the distance shrinks, so the angle turns back
   auto rope_advance = [&](int which) {
-    if constexpr (ROPE) {
+    if constexpr (ROPE && !TABLE) {
       const int hf = lane >> 5;
 #pragma unroll
       for (int i = 0; i < RG::NFH; i += 2) {
@@ -700,6 +802,44 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
         fc[i] = fmaf(c0, r4[0], s0 * r4[1]);      fs[i] = fmaf(s0, r4[0], -(c0 * r4[1]));
         fc[i + 1] = fmaf(c1, r4[2], s1 * r4[3]);  fs[i + 1] = fmaf(s1, r4[2], -(c1 * r4[3]));
       }
+    }
+  };
+
+  // rotary variant with a table: N' of the run that starts at row t0, in operand registers
+  [[maybe_unused]] v8h nh[TABLE ? NKS : 1], nl[TABLE ? NKS : 1];
+  [[maybe_unused]] auto turn_query = [&](int t0) {
+    if constexpr (TABLE) {
+      constexpr int Dh = ROPE_D / 2;
+      float c, sn;
+      phase_sincos(t_fq * (uint32_t)(n_raw - 1 - t0), c, sn);
+      float* mine = &rtab->turned[wave][0][0];
+      if (lane < Dh) {
+        mine[2 * lane] = fmaf(t_qa, c, -(t_qb * sn));
+        mine[2 * lane + 1] = fmaf(t_qb, c, t_qa * sn);
+      }
+      // the wave's own LDS writes, then reads: same-wave LDS operations execute in order
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      // this lane's row of B_K: latent dim pi(lane % 32) (accumulator register v of half h then is dim 16 h + v, the order of
+      // the lane's codes), of each step's 8 frequencies the 4 of its half
+      const int n = lane & 31, row = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
+      const char* kr = (const char*)bk_lds + row * (2 * ROPE_D + 16) + 8 * (lane >> 5);
+#pragma unroll
+      for (int ks = 0; ks < NKS; ks++) {
+        const v2i bk_lo = *(const v2i*)(kr + 16 * ks), bk_hi = *(const v2i*)(kr + ROPE_D + 16 * ks);
+        const v4f p01 = *(const v4f*)&mine[2 * (8 * ks + 4 * (lane >> 5))], p23 = *(const v4f*)&mine[2 * (8 * ks + 4 * (lane >> 5)) + 4];
+#pragma unroll
+        for (int f = 0; f < 4; f++) {
+          const float pa = f < 2 ? p01[2 * f] : p23[2 * f - 4], pb = f < 2 ? p01[2 * f + 1] : p23[2 * f - 3];
+          const uint32_t wk = (uint32_t)bk_lo[f >> 1], wl2 = (uint32_t)bk_hi[f >> 1];
+          const float k0 = __uint_as_float(f & 1 ? wk & 0xFFFF0000u : wk << 16), k1 = __uint_as_float(f & 1 ? wl2 & 0xFFFF0000u : wl2 << 16);
+          split_fp16_two(fmaf(pa, k0, pb * k1), fmaf(pb, k0, -(pa * k1)), nh[ks], nl[ks], 2 * f);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
     }
   };
 
@@ -804,6 +944,8 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
     float rdot[G];
     if constexpr (ROPE) {
       float sb[2][G];
+      [[maybe_unused]] const int run_pos = TABLE ? (tile - (int)cy * chunk_tiles) & run_sh : 0;   // tile of its run
+      if constexpr (TABLE) { if (run_pos == 0) turn_query(tile * 64); }
       // N^T c for one (operand block, head) at a time, the next product issued while the last one's 16 outputs are
       // folded into the score; the scheduling fences keep the compiler from hoisting all products (16 registers each)
       constexpr int NI = G * RG::NMB;
@@ -844,6 +986,28 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
           bop[2 * kk] = __builtin_bit_cast(v8h, codes_f16(t.k[kk][blk][0], t.k[kk][blk][1]));
           bop[2 * kk + 1] = __builtin_bit_cast(v8h, codes_f16(t.k[kk][blk][2], t.k[kk][blk][3]));
         }
+        }
+        if constexpr (TABLE) {
+          // W = N' F of this block's tokens (rows: latent dims), then its dot product with the lane's codes
+          const _Float16* fb = &rtab->feat[2 * run_pos + blk][0][0][lane * 8];
+          v16f W = {0};
+          v8h f_hi[2], f_lo[2];                             // (the next step's operands under this step's products)
+          f_hi[0] = *(const v8h*)fb; f_lo[0] = *(const v8h*)(fb + 512);
+#pragma unroll
+          for (int ks = 0; ks < NKS; ks++) {
+            if (ks + 1 < NKS) {
+              f_hi[(ks + 1) & 1] = *(const v8h*)(fb + (ks + 1) * 1024);
+              f_lo[(ks + 1) & 1] = *(const v8h*)(fb + (ks + 1) * 1024 + 512);
+            }
+            W = __builtin_amdgcn_mfma_f32_32x32x16_f16(nh[ks], f_hi[ks & 1], W, 0, 0, 0);
+            W = __builtin_amdgcn_mfma_f32_32x32x16_f16(nl[ks], f_hi[ks & 1], W, 0, 0, 0);
+            W = __builtin_amdgcn_mfma_f32_32x32x16_f16(nh[ks], f_lo[ks & 1], W, 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+          }
+#pragma unroll
+          for (int v = 0; v < 16; v++) part[0] = fmaf(W[v], (float)bop[v >> 3][v & 7], part[0]);
+          sb[blk][0] = part[0] + __shfl_xor(part[0], 32);   // the other half wave: the other dims
+          continue;
         }
         v16f dc = product(0);
 #pragma unroll
@@ -890,7 +1054,7 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
       const float wt = valid ? pw * vsc : 0.f;
       if (__builtin_amdgcn_ballot_w64(wt > wref[g]) != 0) {       // a weight beyond the fixed-point range
         flush(g);
-        wref[g] = 2.f * wave_max(wt);
+        wref[g] = (TABLE ? 1.125f : 2.f) * wave_max(wt);
         winv[g] = kLimbFull * __builtin_amdgcn_rcpf(wref[g]);
         omega[g] = wref[g] * (1.f / kLimbFull);
       }
@@ -940,20 +1104,27 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
   // The steady-state rounds issue their refills unconditionally, in straight-line code: a load under a branch
   // makes the compiler's wait-count bookkeeping drain the whole queue before every use, which would serialise
   // the prefetch.  Only the last rounds, where refills run out, use conditional loads.
-  const int n = T < tile_end ? (tile_end - T + NW - 1) / NW : 0;
+  int n = T < tile_end ? (tile_end - T + NW - 1) / NW : 0;
+  if constexpr (TABLE) {
+    if (run_sh) {
+      const int m = tile_end - (int)cy * chunk_tiles, pairs = (m + 1) >> 1;
+      n = wave < pairs ? 2 * ((pairs - wave + NW - 1) / NW) : 0;
+      if ((m & 1) && wave < pairs && (pairs - 1 - wave) % NW == 0) n--;          // the last run is a single tile
+    }
+  }
   int done = 0;
   while (done + 2 * DEPTH <= n) {
 #pragma unroll
-    for (int i = 0; i < DEPTH; i++) compute(kRefill, buf[i], T + (done + i) * NW, T + (done + i + DEPTH) * NW);
+    for (int i = 0; i < DEPTH; i++) compute(kRefill, buf[i], tile_at(done + i), tile_at(done + i + DEPTH));
     done += DEPTH;
   }
   // B_V is only needed by the epilogue.  Each thread asks for the elements of its own outputs now, when the steady
   // part of the stream is over (16 latent-dim x column-pair dwords or fewer per output pass; the 8-16 KB of a head's
   // B_V are shared by many workgroups and sit in L2): they arrive behind the last tiles, so nothing waits for them.
-  constexpr int BVP = STAGED ? 1 : (G * 64 * 4 + 255) / 256;     // output passes at the smallest workgroup (256 threads)
+  constexpr int BVP = !LATE_BV ? 1 : (G * 64 * 4 + 255) / 256;     // output passes at the smallest workgroup (256 threads)
   const int half_d = p.d >> 1, hd_shift = p.d == 128 ? 6 : 5, n_pair = G * half_d, bv_items = n_pair * 4;   // d is 64 or 128
   uint32_t bvr[BVP][R / 4];
-  if constexpr (!STAGED) {
+  if constexpr (LATE_BV) {
     const uint32_t* bv32 = (const uint32_t*)p.BV + (size_t)cx * R * half_d;     // bf16 pairs (c, c + 1) of B_V[kv]
 #pragma unroll
     for (int ps = 0; ps < BVP; ps++) {
@@ -967,14 +1138,14 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
 #pragma unroll
   for (int i = 0; i < DEPTH; i++) {
     if (done + i < n) {
-      compute(kNoRefill, buf[i], T + (done + i) * NW, 0);
-      if (done + i + DEPTH < n) tile_load(buf[i], T + (done + i + DEPTH) * NW, 0);
+      compute(kNoRefill, buf[i], tile_at(done + i), 0);
+      if (done + i + DEPTH < n) tile_load(buf[i], tile_at(done + i + DEPTH), 0);
     }
   }
   done += DEPTH;
 #pragma unroll
   for (int i = 0; i < DEPTH; i++)
-    if (done + i < n) compute(kNoRefill, buf[i], T + (done + i) * NW, 0);
+    if (done + i < n) compute(kNoRefill, buf[i], tile_at(done + i), 0);
 
   if (FUSED) {
     // the tile with the row appended by this launch, taken by the wave whose turn it would have been
@@ -1037,7 +1208,7 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
   }
   __syncthreads();
   WSVD_STAMP(tl, tl_wg, wave, 9);
-  if constexpr (STAGED) {
+  if constexpr (!LATE_BV) {
     attn_tail<R, 2>(p, w, Msh, Lsh, Ush, &flag_sh, LATENT ? nullptr : (const void*)bv_lds);
   } else {
     if (!attn_merge_splits<R>(p, w, Msh, Lsh, Ush, &flag_sh)) return;
@@ -1076,13 +1247,13 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (ROPE
 
 template <int R, int G, bool I4, int NT, bool PAGED = false>
 __global__ __launch_bounds__(NT) void k_attn_mfma(AttnParams p) {
-  __shared__ AttnMfmaShared<R, G, NT, false> sh;
+  __shared__ AttnMfmaShared<R, G, NT, 0> sh;
   attn_mfma_body<R, G, I4, NT, false, 0, false, PAGED>(p, sh, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 template <int R, int G, int NT>
 __global__ __launch_bounds__(NT) void k_attn_mfma_newrow(AttnParams p) {
-  __shared__ AttnMfmaShared<R, G, NT, false> sh;
+  __shared__ AttnMfmaShared<R, G, NT, 0> sh;
   attn_mfma_body<R, G, false, NT, false, 0, false, false, true>(p, sh, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
@@ -1790,17 +1961,29 @@ hipError_t wsvd_launch_attn_mfma(const AttnParams& p, int latent_dtype, int rank
 }
 
 // ---------------------------------------------------------------- rotary variant: launch
-template <int R, int G, int D, int NT, bool I4 = false>
-__global__ __launch_bounds__(NT) void k_attn_rope(AttnParams p, RopeArgs ra) {
-  __shared__ AttnMfmaShared<R, G, NT> sh;
-  __shared__ RopeShared<R, G, D> rs;
-  attn_mfma_body<R, G, I4, NT, false, D>(p, sh, blockIdx.x, blockIdx.y, blockIdx.z, &rs, &ra);
+template <int R, int G, int D, int NT, bool I4, bool TABLE = false>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(2))) void k_attn_rope(AttnParams p, RopeArgs ra) {
+  __shared__ AttnMfmaShared<R, G, NT, TABLE ? 2 : 1> sh;
+  if constexpr (TABLE) {
+    __shared__ RopeTable<D, NT> rt;
+    attn_mfma_body<R, G, I4, NT, false, D, false, false, false, true>(p, sh, blockIdx.x, blockIdx.y, blockIdx.z, nullptr, &ra, &rt);
+  } else {
+    __shared__ RopeShared<R, G, D> rs;
+    attn_mfma_body<R, G, I4, NT, false, D>(p, sh, blockIdx.x, blockIdx.y, blockIdx.z, &rs, &ra);
+  }
 }
 
+template <int R, int G, int D, bool I4>
+static void launch_rope_d(const AttnParams& p, const RopeArgs& ra, dim3 grid, bool table, hipStream_t s) {
+  if constexpr (R == 32 && G == 1) {
+    if (table) { hipLaunchKernelGGL((k_attn_rope<R, G, D, 256, I4, true>), grid, dim3(256), 0, s, p, ra); return; }
+  }
+  hipLaunchKernelGGL((k_attn_rope<R, G, D, 512, I4>), grid, dim3(512), 0, s, p, ra);
+}
 template <int R, int G, bool I4 = false>
-static hipError_t launch_rope(const AttnParams& p, const RopeArgs& ra, dim3 grid, int threads, hipStream_t s) {
-  if (p.d == 128) hipLaunchKernelGGL((k_attn_rope<R, G, 128, 512, I4>), grid, dim3(threads), 0, s, p, ra);
-  else if (p.d == 64) hipLaunchKernelGGL((k_attn_rope<R, G, 64, 512, I4>), grid, dim3(threads), 0, s, p, ra);
+static hipError_t launch_rope(const AttnParams& p, const RopeArgs& ra, dim3 grid, bool table, hipStream_t s) {
+  if (p.d == 128) launch_rope_d<R, G, 128, I4>(p, ra, grid, table, s);
+  else if (p.d == 64) launch_rope_d<R, G, 64, I4>(p, ra, grid, table, s);
   else return hipErrorNotSupported;
   return hipGetLastError();
 }
@@ -1818,9 +2001,14 @@ hipError_t wsvd_launch_attn_rope(const wsvd_ctx* ctx, const wsvd_layer_desc& d, 
   AttnParams p;
   dim3 grid;
   int threads;
-  // always 8 waves per workgroup: the register budget allows no more, and the N build divides its work over exactly
-  // that many threads (waves without a tile of their own idle through the loop)
-  wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p, grid, threads, 512, 8);
+  // The features kernel takes 8 waves per workgroup: the register budget allows no more, and the N build divides its work over
+  // exactly that many threads (waves without a tile of their own idle through the loop).  The table kernel takes 4, and two of
+  // its workgroups share a CU, so that one's table, prologue and end run beside the other's stream: it needs more (sequence, kv
+  // head) units than CUs (256 units, 2048 rows: 21.5 us with features, 25.3 with the table), and its lead over the N build and
+  // start values, which every unit pays for, is used up at about 4096 rows.  us, features / table: 512 units of 64 rows
+  // 15.0 / 11.1, 700 rows 22.2 / 20.8, 2048 rows 40.6 / 36.7, 4096 rows 66 / 66; 2048 units of 200 rows 57 / 40.
+  const bool table = d.rank == 32 && G == 1 && d.batch * d.n_kv_heads > ctx->n_cu && max_seq_len <= 4096;
+  wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p, grid, threads, table ? 256 : 512, 8);
   RopeArgs ra;
   const double two_pi = 6.283185307179586476925286766559;
   for (int i = 0; i < 64; i++) {
@@ -1846,20 +2034,20 @@ hipError_t wsvd_launch_attn_rope(const wsvd_ctx* ctx, const wsvd_layer_desc& d, 
     hipError_t e;
     if (i4) {
       switch (gl) {
-        case 1: e = launch_rope<32, 1, true>(p, ra, grid, threads, s); break;
-        case 2: e = launch_rope<32, 2, true>(p, ra, grid, threads, s); break;
-        case 3: e = launch_rope<32, 3, true>(p, ra, grid, threads, s); break;
-        default: e = launch_rope<32, 4, true>(p, ra, grid, threads, s); break;
+        case 1: e = launch_rope<32, 1, true>(p, ra, grid, table, s); break;
+        case 2: e = launch_rope<32, 2, true>(p, ra, grid, table, s); break;
+        case 3: e = launch_rope<32, 3, true>(p, ra, grid, table, s); break;
+        default: e = launch_rope<32, 4, true>(p, ra, grid, table, s); break;
       }
     } else if (d.rank == 32) {
       switch (gl) {
-        case 1: e = launch_rope<32, 1>(p, ra, grid, threads, s); break;
-        case 2: e = launch_rope<32, 2>(p, ra, grid, threads, s); break;
-        case 3: e = launch_rope<32, 3>(p, ra, grid, threads, s); break;
-        default: e = launch_rope<32, 4>(p, ra, grid, threads, s); break;
+        case 1: e = launch_rope<32, 1>(p, ra, grid, table, s); break;
+        case 2: e = launch_rope<32, 2>(p, ra, grid, table, s); break;
+        case 3: e = launch_rope<32, 3>(p, ra, grid, table, s); break;
+        default: e = launch_rope<32, 4>(p, ra, grid, table, s); break;
       }
     } else {
-      e = gl == 1 ? launch_rope<64, 1>(p, ra, grid, threads, s) : launch_rope<64, 2>(p, ra, grid, threads, s);
+      e = gl == 1 ? launch_rope<64, 1>(p, ra, grid, table, s) : launch_rope<64, 2>(p, ra, grid, table, s);
     }
     if (e != hipSuccess) return e;
   }
