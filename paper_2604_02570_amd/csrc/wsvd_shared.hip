@@ -6,13 +6,16 @@
 // so the latent stream is read ONCE for all heads (not once per head, as a per-head kernel run on the shared latent
 // would), at the price of R-dimensional per-head queries and outputs: Q~_h = B_Kh q_h and o_h = B_Vh^T u_h move
 // 2 * H * R * d factor elements per step where the per-head scheme moves 2 * H * r * d.
-//   k_shared_absorb   Q~ [B, H, R] = (sm_scale log2 e) B_Kh q_h              bf16 MFMA, one wave per (head, 32 latent dims)
-//   k_shared_attn     per (sequence, split of its 128-token chunks): scores on int8 MFMA (the cache codes are the A
-//                     operand as stored; Q~ as three 7-bit limbs in LDS is the B operand), softmax down the head
-//                     columns, value product on fp16 MFMA with each wave owning a quarter of the R output dims;
-//                     partial (m, l, U) per split
+//   k_shared_absorb_limbs  Q~ [B, H, R] = (sm_scale log2 e) B_Kh q_h         bf16 MFMA, one wave per (head, 32 latent dims),
+//                     as three 7-bit limbs per quarter of the rank (ranks above 1024: k_shared_absorb, fp32)
+//   k_shared_attn     per (sequence, split of its 128-token chunks, part of the value dims): scores on int8 MFMA (the cache
+//                     codes are the A operand as stored; Q~ as three 7-bit limbs in LDS is the B operand), softmax down
+//                     the head columns, value product on fp16 MFMA with each wave owning a quarter of the part's output
+//                     dims; partial (m, l, U) per split
 //   k_shared_out      merge of the splits, u = U / l, o_h = B_Vh^T u_h         vector ALU, one workgroup per (head, sequence)
 // 32x32 accumulator layout throughout: lane L holds column L % 32, rows 8 (v / 4) + 4 (L / 32) + v % 4, v = 0..15.
+#include <type_traits>
+
 #include "wsvd_dev.h"
 #include "wsvd_internal.h"
 
@@ -20,7 +23,15 @@ namespace {
 
 constexpr int kSharedHeads = 32;          // the heads are the 32 columns of the products
 constexpr int kSharedChunk = 128;         // tokens per workgroup pass: one 32-token block per wave
+// A sequence's queries as limbs, [3][R / 32][64 lanes][16 B], and behind them the value of a unit, [quarter][head].  The
+// images lie an odd number of 256-byte pieces apart (the lanes of a store hold 32 sequences); the room for one is that of
+// the same queries in fp32, 128 R bytes.
+constexpr size_t shared_image_bytes(int R) { return (size_t)96 * R + 1280; }
+static_assert(shared_image_bytes(256) <= 128 * 256, "the smallest rank's images fit");
 constexpr float kLimbRange = 1040000.f;   // |Q~ / delta| stays below 2^20: three signed 7-bit limbs
+
+typedef float v2f __attribute__((ext_vector_type(2)));
+typedef int v2i_u __attribute__((ext_vector_type(2), aligned(2)));       // the K scales are aligned to their elements only
 
 struct SharedParams {
   const uint16_t* q;          // bf16 [B, H, d]
@@ -31,7 +42,7 @@ struct SharedParams {
   const uint16_t* k_scale;    // fp16 [B][t_cap]
   const uint16_t* v_scale;
   const int* seq_lens;
-  float* qt;                  // workspace: Q~ [B, H, R]
+  float* qt;                  // workspace: Q~ [B, H, R]; up to rank 1024 its limbs, [B] images
   float* qmax;                //            max |Q~| per (sequence, head) (ranks above 1024 only)
   float* pm;                  // workspace: partial running maxima [B, S, H]
   float* pl;                  //            partial sums           [B, S, H]
@@ -43,18 +54,27 @@ struct SharedParams {
 };
 
 // ---------------------------------------------------------------- Q~ = c B_Kh q_h
+// All of a wave's operands are requested together (one trip to memory instead of one per step of the contraction).
+template <int D>
 __global__ __launch_bounds__(64) void k_shared_absorb(SharedParams p) {
   const int lane = threadIdx.x, n = lane & 31, g2 = lane >> 5;
   const int jb = blockIdx.x, h = blockIdx.y;
-  const uint16_t* arow = p.BK + ((size_t)h * p.R + 32 * jb + n) * p.d + 8 * g2;
+  const uint16_t* arow = p.BK + ((size_t)h * p.R + 32 * jb + n) * D + 8 * g2;
+  v8bf16 a[D / 16];
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) a[ks] = *(const v8bf16*)(arow + 16 * ks);
   for (int bb = 0; bb < p.B; bb += 32) {
     const int b = bb + n;
-    const uint16_t* qrow = p.q + ((size_t)min(b, p.B - 1) * kSharedHeads + h) * p.d + 8 * g2;
+    const uint16_t* qrow = p.q + ((size_t)min(b, p.B - 1) * kSharedHeads + h) * D + 8 * g2;
+    v8bf16 x[D / 16];
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) x[ks] = *(const v8bf16*)(qrow + 16 * ks);
+    __builtin_amdgcn_sched_barrier(0);
     v16f acc;
 #pragma unroll
     for (int v = 0; v < 16; v++) acc[v] = 0.f;
-    for (int ks = 0; ks < (p.d >> 4); ks++)
-      acc = mfma_bf16(*(const v8bf16*)(arow + 16 * ks), *(const v8bf16*)(qrow + 16 * ks), acc);
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ks++) acc = mfma_bf16(a[ks], x[ks], acc);
     if (b < p.B) {
       float* dst = p.qt + ((size_t)b * kSharedHeads + h) * p.R + 32 * jb + 4 * g2;
 #pragma unroll
@@ -68,22 +88,95 @@ __global__ __launch_bounds__(64) void k_shared_absorb(SharedParams p) {
   }
 }
 
+// ---------------------------------------------------------------- the same up to rank 1024, as the score product reads it
+// One workgroup per (head, quarter of the rank, 32 sequences) holds that piece of Q~ in registers, so its maximum is known
+// on the spot and the three signed 7-bit limbs of round(Q~ / delta) leave in the order of the int8 product's B operand:
+// lane (head, g2) of step ks holds dims 32 ks + 16 g2 .. + 15.  Every quarter has its own delta: with one per head (32
+// workgroups of 256 KB of factors each) the launch took 13.5 us at rank 1024.  Converted by every split's workgroup instead,
+// the limbs cost 2800 vector instructions, 20 KB of code run once, before the first score.
+template <int D, int R>
+__global__ __launch_bounds__(R / 2) __attribute__((amdgpu_waves_per_eu(2, 4))) void k_shared_absorb_limbs(SharedParams p) {
+  constexpr int NW = R / 128;                                           // waves: a block of 32 dims each
+  __shared__ float wmax[NW][32];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, g2 = lane >> 5;
+  const int h = blockIdx.x, quarter = blockIdx.y, b = 32 * blockIdx.z + n, jb = quarter * NW + wave;
+  const uint16_t* qrow = p.q + ((size_t)min(b, p.B - 1) * kSharedHeads + h) * D + 8 * g2;
+  const uint16_t* arow = p.BK + ((size_t)h * R + 32 * jb + n) * D + 8 * g2;
+  v8bf16 a[D / 16], x[D / 16];
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) { x[ks] = *(const v8bf16*)(qrow + 16 * ks); a[ks] = *(const v8bf16*)(arow + 16 * ks); }
+  __builtin_amdgcn_sched_barrier(0);
+  v16f acc;
+#pragma unroll
+  for (int v = 0; v < 16; v++) acc[v] = 0.f;
+#pragma unroll
+  for (int ks = 0; ks < D / 16; ks++) acc = mfma_bf16(a[ks], x[ks], acc);
+  float amax = 0.f;
+#pragma unroll
+  for (int v = 0; v < 16; v++) {
+    acc[v] *= p.c_scale;
+    amax = fmaxf(amax, fabsf(acc[v]));
+  }
+  amax = fmaxf(amax, __shfl_xor(amax, 32));
+  if (g2 == 0) wmax[wave][n] = amax;
+  __syncthreads();
+  float hm = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; w++) hm = fmaxf(hm, wmax[w][n]);
+  const float delta = hm > 0.f ? hm / kLimbRange : 1.0f;                // value of one unit of the integer query
+  const float inv_delta = 1.0f / delta;
+  if (b >= p.B) return;
+  uint8_t* image = (uint8_t*)p.qt + (size_t)b * shared_image_bytes(R);
+  if (wave == 0 && g2 == 0) ((float*)(image + 96 * R))[quarter * kSharedHeads + h] = delta;
+  uint32_t w[3][4];                                                     // [limb][m4]: dims 8 m4 + 4 g2 .. + 3
+#pragma unroll
+  for (int m4 = 0; m4 < 4; m4++) {
+    w[0][m4] = w[1][m4] = w[2][m4] = 0;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const int Q = (int)__builtin_rintf(acc[4 * m4 + e] * inv_delta);
+      const int a0 = ((Q + 64) & 127) - 64, Q1 = (Q - a0) >> 7;         // Q = a0 + 128 Q1 exactly
+      const int a1 = ((Q1 + 64) & 127) - 64, a2 = (Q1 - a1) >> 7;
+      w[0][m4] |= ((uint32_t)a0 & 0xFFu) << (8 * e);
+      w[1][m4] |= ((uint32_t)a1 & 0xFFu) << (8 * e);
+      w[2][m4] |= ((uint32_t)a2 & 0xFFu) << (8 * e);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 3; t++) {         // the two halves of the wave swap pieces: each keeps the 16 dims of its own half
+    const uint32_t o0 = (uint32_t)__shfl_xor((int)(g2 ? w[t][0] : w[t][2]), 32);
+    const uint32_t o1 = (uint32_t)__shfl_xor((int)(g2 ? w[t][1] : w[t][3]), 32);
+    const v4i o = g2 ? v4i{(int)o0, (int)w[t][2], (int)o1, (int)w[t][3]} : v4i{(int)w[t][0], (int)o0, (int)w[t][1], (int)o1};
+    *(v4i*)(image + (size_t)t * (32 * R) + jb * 1024 + (h + 32 * g2) * 16) = o;
+  }
+}
+
 // ---------------------------------------------------------------- attention over the shared latent, all heads at once
-// LDS: limbs [3][R / 32][64 lanes][16 B], then 4 float tables [4 waves][32], then P tiles [4 waves][32 heads][40] fp16.
-template <int R>
+// One workgroup per CU with one or two chunks of 128 tokens each: what bounds it beside the stream is what runs once, so code
+// is short (the limbs come ready made) and every request leaves as early as registers allow.  16 sequences of 2048 rows,
+// rank 1024 (67 MB): 34.5 -> 22.2 us; 1 of 8191 rows 36.2 -> 15.6; 64 of 2047 rows, rank 256 27.6 -> 19.8.
+// LDS: limbs [3][R / 32][64 lanes][16 B], then 3 float tables [4 waves][32], P tiles [4 waves][32 heads][40] fp16, value
+// scales [4 waves][128 tokens] fp16 (each wave its own copy).
+template <int R, int VH>
 __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
   constexpr int NKS = R / 32;             // 32-dim steps of the score contraction
-  constexpr int NKK = R / 128;            // 32-dim sub-blocks of the value dims one wave owns
+  constexpr int NKK = R / VH / 128;       // 32-dim sub-blocks of the value dims one wave owns
   extern __shared__ __align__(16) uint8_t sh_lds[];
   v4i* limbs = (v4i*)sh_lds;                                            // [3][NKS][64]
   float* hmax = (float*)(sh_lds + 3 * NKS * 1024);                      // [4][32] each
   float* cmax = hmax + 128;
   float* csum = cmax + 128;
-  float* ksc = csum + 128;
-  _Float16* pt = (_Float16*)(ksc + 128);                                // [4][32][40]
+  _Float16* pt = (_Float16*)(csum + 128);                               // [4][32][40]
+  uint32_t* vsl = (uint32_t*)(pt + 4 * 32 * 40);                        // [4][64] pairs of fp16
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g2 = lane >> 5;
-  const int split = blockIdx.x, b = blockIdx.y;
+  // (the wave's number in a scalar register: the planes' addresses are a scalar base and one offset per lane)
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, g2 = lane >> 5;
+  // workgroups go to the 8 dies in turn: the VH workgroups of the same tokens follow each other on one die, and so do the
+  // splits of a sequence, which read the same limbs, where the sequences come in whole groups of 8
+  const int unit = (blockIdx.x & 7) + 8 * (blockIdx.x / (8 * VH)), vh = (blockIdx.x >> 3) % VH;
+  if (unit >= p.B * p.S) return;
+  const int b = (p.B & 7) == 0 ? (unit & 7) + 8 * (unit / (8 * p.S)) : unit / p.S;
+  const int split = (p.B & 7) == 0 ? (unit >> 3) % p.S : unit % p.S;
   const int n_b = min(max(p.seq_lens[b], 0), p.t_cap);
   const int n_chunks = (n_b + kSharedChunk - 1) / kSharedChunk;
   const int per = (n_chunks + p.S - 1) / p.S;
@@ -99,106 +192,91 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
   const uint16_t* kmeta = p.k_scale + (size_t)b * p.t_cap;
   const uint16_t* vmeta = p.v_scale + (size_t)b * p.t_cap;
 
-  // ---- Q~ of head n as three signed 7-bit limbs of round(Q~ / delta_n): lane (n, g2) of step ks holds dims
-  // 32 ks + 16 g2 .. + 15, the B operand of the int8 product as it is
-  const float* qrow = p.qt + ((size_t)b * kSharedHeads + n) * R + 16 * g2;
-  constexpr int NQ = NKS / 4;                                           // steps this wave converts
-  v4f xq[NQ][4];                                                        // read once, all requests in flight together
+  // ---- the limbs of the sequence's queries, a quarter by each wave
+  const uint8_t* qimage = (const uint8_t*)p.qt + (size_t)b * shared_image_bytes(R);
+  const v4i* image = (const v4i*)qimage + wave * (3 * NKS / 4) * 64 + lane;
+  float delta[4];
 #pragma unroll
-  for (int i = 0; i < NQ; i++)
+  for (int i = 0; i < 4; i++) delta[i] = ((const float*)(qimage + 96 * R))[i * kSharedHeads + n];
+  v4i lq[3 * NKS / 4];
 #pragma unroll
-    for (int i4 = 0; i4 < 4; i4++) xq[i][i4] = *(const v4f*)(qrow + 32 * (wave + 4 * i) + 4 * i4);
-  float amax = 0.f;
+  for (int i = 0; i < 3 * NKS / 4; i++) lq[i] = image[i * 64];
+  // this wave's 32 tokens of a chunk: K scales of the accumulator's rows and all R / 32 operand blocks (and the V scales of
+  // all 128 tokens).  The first chunk's
+  // are requested here, behind the limbs
+  v2i ksr[4];
+  uint32_t vsr;
+  const uint32_t lane16 = 16 * lane;
+  v4i ka[NKS];
+  const auto request_scales = [&](int c) {
 #pragma unroll
-  for (int i = 0; i < NQ; i++)
+    for (int m4 = 0; m4 < 4; m4++) ksr[m4] = *(const v2i_u*)(kmeta + c * kSharedChunk + 32 * wave + 8 * m4 + 4 * g2);
+    vsr = *(const uint32_t*)(vmeta + c * kSharedChunk + 2 * lane);
+  };
+  const auto request_keys = [&](int c, int part4) {                     // a quarter of the chunk's blocks
+    const uint8_t* kp = kplane + (size_t)(c * 4 + wave) * (32 * R);
 #pragma unroll
-    for (int i4 = 0; i4 < 4; i4++)
-      amax = fmaxf(amax, fmaxf(fmaxf(fabsf(xq[i][i4][0]), fabsf(xq[i][i4][1])), fmaxf(fabsf(xq[i][i4][2]), fabsf(xq[i][i4][3]))));
-  amax = fmaxf(amax, __shfl_xor(amax, 32));
-  if (g2 == 0) hmax[wave * 32 + n] = amax;
-  __syncthreads();
-  const float hm = fmaxf(fmaxf(hmax[n], hmax[32 + n]), fmaxf(hmax[64 + n], hmax[96 + n]));
-  const float delta = hm > 0.f ? hm / kLimbRange : 1.0f;                // value of one unit of the integer query
-  const float inv_delta = 1.0f / delta;
-#pragma unroll
-  for (int i = 0; i < NQ; i++) {
-    const int ks = wave + 4 * i;
-    v4i l0, l1, l2;
-#pragma unroll
-    for (int i4 = 0; i4 < 4; i4++) {
-      uint32_t w0 = 0, w1 = 0, w2 = 0;
-#pragma unroll
-      for (int e = 0; e < 4; e++) {
-        const int Q = (int)__builtin_rintf(xq[i][i4][e] * inv_delta);
-        const int a0 = ((Q + 64) & 127) - 64, Q1 = (Q - a0) >> 7;       // Q = a0 + 128 Q1 exactly
-        const int a1 = ((Q1 + 64) & 127) - 64, a2 = (Q1 - a1) >> 7;
-        w0 |= ((uint32_t)a0 & 0xFFu) << (8 * e);
-        w1 |= ((uint32_t)a1 & 0xFFu) << (8 * e);
-        w2 |= ((uint32_t)a2 & 0xFFu) << (8 * e);
-      }
-      l0[i4] = (int)w0; l1[i4] = (int)w1; l2[i4] = (int)w2;
+    for (int ks = 0; ks < NKS / 4; ks++)
+      {
+      const v4i* src = (const v4i*)(kp + (part4 * (NKS / 4) + ks) * 1024 + lane16);
+      ka[part4 * (NKS / 4) + ks] = VH > 1 ? *src : __builtin_nontemporal_load(src);
     }
-    limbs[(0 * NKS + ks) * 64 + lane] = l0;
-    limbs[(1 * NKS + ks) * 64 + lane] = l1;
-    limbs[(2 * NKS + ks) * 64 + lane] = l2;
-  }
+  };
+  request_scales(c0);
+#pragma unroll
+  for (int i = 0; i < 4; i++) request_keys(c0, i);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int i = 0; i < 3 * NKS / 4; i++) limbs[(wave * (3 * NKS / 4) + i) * 64 + lane] = lq[i];
   __syncthreads();
 
   float m_run = -INFINITY, l_run = 0.f;                                 // of head n (every wave keeps its own copy)
-  v16f U[NKK];                                                          // rows = this wave's dims, columns = heads
+  v16f U[NKK];                                                          // rows = heads, columns = this wave's dims
 #pragma unroll
   for (int kk = 0; kk < NKK; kk++)
 #pragma unroll
     for (int v = 0; v < 16; v++) U[kk][v] = 0.f;
 
-  for (int c = c0; c < c1; c++) {
-    // ---- scores of this wave's 32 tokens against all heads
-    const int t0 = c * kSharedChunk + 32 * wave;
-    if (g2 == 0) ksc[wave * 32 + n] = f16_bits_to_f32(kmeta[t0 + n]);
-    v16i a0, a1, a2;
-#pragma unroll
-    for (int v = 0; v < 16; v++) { a0[v] = 0; a1[v] = 0; a2[v] = 0; }
-    // the K operands of the chunk: all R / 32 requests of this wave's 32 tokens in flight together (one trip to memory
-    // per chunk instead of one per batch)
-    v4i ka[NKS];
-    {
-      const uint8_t* kp = kplane + (size_t)(t0 >> 5) * (32 * R) + (size_t)lane * 16;
-#pragma unroll
-      for (int ks = 0; ks < NKS; ks++) ka[ks] = __builtin_nontemporal_load((const v4i*)(kp + (size_t)ks * 1024));
-    }
-#pragma unroll
-    for (int ks = 0; ks < NKS; ks++) {
-      a0 = mfma_i8(ka[ks], limbs[(0 * NKS + ks) * 64 + lane], a0);
-      a1 = mfma_i8(ka[ks], limbs[(1 * NKS + ks) * 64 + lane], a1);
-      a2 = mfma_i8(ka[ks], limbs[(2 * NKS + ks) * 64 + lane], a2);
-      if ((ks & 3) == 3) __builtin_amdgcn_sched_barrier(0);             // keeps the limb reads from piling up in registers
-    }
-    // the chunk's value blocks are requested now, all at once: they arrive during the softmax
-    const int cbase = c * kSharedChunk;
-    v4i vc[4][NKK], vsr[4][2];
+  v4i vc[4][NKK];
+  // One chunk: every quarter of the score product frees a quarter of the key registers and is followed by the requests of
+  // one 32-token block of the values; every block of the value product is followed by the requests of a quarter of the
+  // next chunk's keys.  So a whole plane's piece of the chunk (R x 128 bytes) is on its way at any time.
+  const auto chunk = [&](int c, auto more) {
+    const int cbase = c * kSharedChunk, t0 = cbase + 32 * wave;
+    float sc[16];
 #pragma unroll
     for (int tw = 0; tw < 4; tw++) {
-      const int tv = min(cbase + 32 * tw, (n_b - 1) & ~31);             // (a block past the end: the last one again, unused)
-      const uint8_t* vp = vplane + (size_t)(tv >> 5) * (32 * R) + (size_t)(wave * NKK) * 1024 + (size_t)lane * 16;
+      v16i a0, a1, a2;
 #pragma unroll
-      for (int kk = 0; kk < NKK; kk++) vc[tw][kk] = __builtin_nontemporal_load((const v4i*)(vp + kk * 1024));
-      vsr[tw][0] = *(const v4i*)(vmeta + tv + 16 * g2);
-      vsr[tw][1] = *(const v4i*)(vmeta + tv + 16 * g2 + 8);
+      for (int v = 0; v < 16; v++) { a0[v] = 0; a1[v] = 0; a2[v] = 0; }
+#pragma unroll
+      for (int i = 0; i < NKS / 4; i++) {
+        const int ks = tw * (NKS / 4) + i;
+        a0 = mfma_i8(ka[ks], limbs[(0 * NKS + ks) * 64 + lane], a0);
+        a1 = mfma_i8(ka[ks], limbs[(1 * NKS + ks) * 64 + lane], a1);
+        a2 = mfma_i8(ka[ks], limbs[(2 * NKS + ks) * 64 + lane], a2);
+        if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);            // keeps the limb reads from piling up in registers
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const int tv = min(cbase + 32 * tw, (n_b - 1) & ~31);             // (a block past the end: the last one again, unused)
+      const uint8_t* vp = vplane + (size_t)(tv >> 5) * (32 * R) + (size_t)((4 * vh + wave) * NKK) * 1024;
+#pragma unroll
+      for (int kk = 0; kk < NKK; kk++) vc[tw][kk] = __builtin_nontemporal_load((const v4i*)(vp + kk * 1024 + lane16));
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        const float s = fmaf(16384.f, (float)a2[v], fmaf(128.f, (float)a1[v], (float)a0[v]));
+        sc[v] = tw == 0 ? s * delta[0] : fmaf(s, delta[tw], sc[v]);
+      }
     }
-    __builtin_amdgcn_sched_barrier(0);
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    float sc[16];
     float bmax = -INFINITY;
 #pragma unroll
     for (int m4 = 0; m4 < 4; m4++) {
-      const v4f k4 = *(const v4f*)&ksc[wave * 32 + 8 * m4 + 4 * g2];
+      const v4f k4 = __builtin_convertvector(__builtin_bit_cast(v4f16, ksr[m4]), v4f);
 #pragma unroll
       for (int jj = 0; jj < 4; jj++) {
         const int v = 4 * m4 + jj;
-        const float s = fmaf(16384.f, (float)a2[v], fmaf(128.f, (float)a1[v], (float)a0[v])) * delta * k4[jj];
-        sc[v] = t0 + 8 * m4 + 4 * g2 + jj < n_b ? s : -INFINITY;        // rows past the sequence's end
+        sc[v] = t0 + 8 * m4 + 4 * g2 + jj < n_b ? sc[v] * k4[jj] : -INFINITY;   // rows past the sequence's end
         bmax = fmaxf(bmax, sc[v]);
       }
     }
@@ -207,6 +285,7 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
     __syncthreads();
     const float m_new = fmaxf(m_run, fmaxf(fmaxf(cmax[n], cmax[32 + n]), fmaxf(cmax[64 + n], cmax[96 + n])));
     const float alpha = m_run == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run - m_new);   // m_new is finite: the chunk has a row
+    const bool rescale = c != c0 && __builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0;        // (U is 0 at the first chunk)
     float pw[16], psum = 0.f;
 #pragma unroll
     for (int v = 0; v < 16; v++) {
@@ -214,7 +293,11 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
       psum += pw[v];
     }
     psum += __shfl_xor(psum, 32);
-    if (g2 == 0) csum[wave * 32 + n] = psum;
+    if (g2 == 0) { csum[wave * 32 + n] = psum; hmax[wave * 32 + n] = alpha; }   // (the query's maxima are no longer read)
+    {                                     // rows never written may hold any scale: they contribute 0
+      const int tl = cbase + 2 * lane;
+      vsl[wave * 64 + lane] = tl + 1 < n_b ? vsr : tl < n_b ? vsr & 0xFFFFu : 0u;
+    }
     _Float16* ptw = pt + (wave * 32 + n) * 40;
 #pragma unroll
     for (int m4 = 0; m4 < 4; m4++) {
@@ -226,50 +309,52 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
     __syncthreads();
     l_run = fmaf(l_run, alpha, (csum[n] + csum[32 + n]) + (csum[64 + n] + csum[96 + n]));
     m_run = m_new;
+    if constexpr (decltype(more)::value) request_scales(c + 1);
 
     // ---- value product: this wave's quarter of the R dims, all four token blocks of the chunk
-    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) {
+    if (rescale) {
 #pragma unroll
-      for (int kk = 0; kk < NKK; kk++)
+      for (int m4 = 0; m4 < 4; m4++) {
+        const v4f al = *(const v4f*)&hmax[wave * 32 + 8 * m4 + 4 * g2];
 #pragma unroll
-        for (int v = 0; v < 16; v++) U[kk][v] *= alpha;
+        for (int kk = 0; kk < NKK; kk++)
+#pragma unroll
+          for (int jj = 0; jj < 4; jj++) U[kk][4 * m4 + jj] *= al[jj];
+      }
     }
 #pragma unroll
     for (int tw = 0; tw < 4; tw++) {
       const int tv = cbase + 32 * tw;
       if (tv < n_b) {
-        v8f16 sv8[2] = {__builtin_bit_cast(v8f16, vsr[tw][0]), __builtin_bit_cast(v8f16, vsr[tw][1])};
-        if (tv + 32 > n_b) {      // rows never written may hold any scale: they contribute 0
-#pragma unroll
-          for (int s = 0; s < 2; s++)
-#pragma unroll
-            for (int e = 0; e < 8; e++)
-              if (tv + 16 * g2 + 8 * s + e >= n_b) sv8[s][e] = (_Float16)0;
-        }
+        const v8f16 sv0 = *(const v8f16*)&vsl[wave * 64 + 16 * tw + 8 * g2];
+        const v8f16 sv1 = *(const v8f16*)&vsl[wave * 64 + 16 * tw + 8 * g2 + 4];
         const v8f16 bp0 = *(const v8f16*)&pt[(tw * 32 + n) * 40 + 16 * g2];
         const v8f16 bp1 = *(const v8f16*)&pt[(tw * 32 + n) * 40 + 16 * g2 + 8];
 #pragma unroll
         for (int kk = 0; kk < NKK; kk++) {
-          U[kk] = mfma_f16(codes_f16(vc[tw][kk][0], vc[tw][kk][1]) * sv8[0], bp0, U[kk]);
-          U[kk] = mfma_f16(codes_f16(vc[tw][kk][2], vc[tw][kk][3]) * sv8[1], bp1, U[kk]);
+          U[kk] = mfma_f16(bp0, codes_f16(vc[tw][kk][0], vc[tw][kk][1]) * sv0, U[kk]);
+          U[kk] = mfma_f16(bp1, codes_f16(vc[tw][kk][2], vc[tw][kk][3]) * sv1, U[kk]);
         }
       }
+      if constexpr (decltype(more)::value) {
+        __builtin_amdgcn_sched_barrier(0);
+        request_keys(c + 1, tw);
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
-    __syncthreads();                                                    // the tables and P tiles are reused by the next chunk
-  }
+    if constexpr (decltype(more)::value) __syncthreads();               // the tables and P tiles are reused by the next chunk
+  };
+  for (int c = c0; c + 1 < c1; c++) chunk(c, std::true_type{});
+  chunk(c1 - 1, std::false_type{});
 
-  // ---- partial result of this split
-  if (wave == 0 && g2 == 0) { p.pm[part * kSharedHeads + n] = m_run; p.pl[part * kSharedHeads + n] = l_run; }
-  float* pu = p.pu + (part * kSharedHeads + n) * R + (size_t)(wave * NKK) * 32 + 4 * g2;
+  // ---- partial result of this split: a store instruction writes two heads' whole 128-byte lines (the heads as columns
+  // made it 64 pieces of 16 bytes, 4 KB apart)
+  if (vh == 0 && wave == 0 && g2 == 0) { p.pm[part * kSharedHeads + n] = m_run; p.pl[part * kSharedHeads + n] = l_run; }
+  float* pu = p.pu + (part * kSharedHeads + 4 * g2) * R + (size_t)((4 * vh + wave) * NKK) * 32 + n;
 #pragma unroll
-  for (int kk = 0; kk < NKK; kk++)
+  for (int v = 0; v < 16; v++)
 #pragma unroll
-    for (int m4 = 0; m4 < 4; m4++) {
-      v4f o;
-#pragma unroll
-      for (int jj = 0; jj < 4; jj++) o[jj] = U[kk][4 * m4 + jj];
-      *(v4f*)(pu + 32 * kk + 8 * m4) = o;
-    }
+    for (int kk = 0; kk < NKK; kk++) pu[(size_t)(8 * (v >> 2) + (v & 3)) * R + 32 * kk] = U[kk][v];
 }
 
 // ---------------------------------------------------------------- the same for ranks above 1024 (up to 4096)
@@ -502,116 +587,129 @@ __global__ __launch_bounds__(256) void k_shared_attn_big(SharedParams p) {
 #pragma unroll
             for (int kk = 0; kk < NKK; kk++) {
               if (kk < nkk) {                                           // workgroup-uniform
-                U[kk] = mfma_f16(codes_f16(vc[tw][kk][0], vc[tw][kk][1]) * sv8[0], bp0, U[kk]);
-                U[kk] = mfma_f16(codes_f16(vc[tw][kk][2], vc[tw][kk][3]) * sv8[1], bp1, U[kk]);
+                U[kk] = mfma_f16(bp0, codes_f16(vc[tw][kk][0], vc[tw][kk][1]) * sv8[0], U[kk]);
+                U[kk] = mfma_f16(bp1, codes_f16(vc[tw][kk][2], vc[tw][kk][3]) * sv8[1], U[kk]);
               }
             }
           }
         }
       }
     }
-    float* pu = p.pu + (part * kSharedHeads + n) * R + (size_t)blk0 * 32 + 4 * g2;
+    float* pu = p.pu + (part * kSharedHeads + 4 * g2) * R + (size_t)blk0 * 32 + n;
 #pragma unroll
     for (int kk = 0; kk < NKK; kk++) {
       if (kk < nkk) {
 #pragma unroll
-        for (int m4 = 0; m4 < 4; m4++) {
-          v4f o;
-#pragma unroll
-          for (int jj = 0; jj < 4; jj++) o[jj] = U[kk][4 * m4 + jj];
-          *(v4f*)(pu + 32 * kk + 8 * m4) = o;
-        }
+        for (int v = 0; v < 16; v++) pu[(size_t)(8 * (v >> 2) + (v & 3)) * R + 32 * kk] = U[kk][v];
       }
     }
   }
 }
 
 // ---------------------------------------------------------------- merge of the splits and o_h = B_Vh^T u_h
-// One workgroup per (head, kOutSeqs sequences).  (4 sequences per workgroup read B_Vh a quarter as often but leave
-// three quarters of the CUs without a workgroup: measured 1.6 x slower at 16 sequences.)
-constexpr int kOutSeqs = 1;
-__global__ __launch_bounds__(256) void k_shared_out(SharedParams p) {
+// One workgroup per (head, sequence): a head's factors are read by all sequences, from the L2 of one die (32 heads in turn
+// over 8 dies).  What bounds it is the chain of memory trips, so the first partial results are requested before the weights
+// of the splits are known, and registers are kept to 64 so that a CU holds 32 waves: 16 sequences of rank 1024, 8 splits,
+// 10.1 us (16 splits, 256 threads with 4 trips for the partial results: 13.2).  Two or four sequences per workgroup read
+// B_Vh less often, but with 150 to 250 registers no more than 8 waves fit a CU (64 sequences of rank 256: 9.7 -> 18 us).
+template <int T>
+__global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8))) void k_shared_out(SharedParams p) {
+  constexpr int NR = T / 16;                                            // rows of B_Vh per step: 16 lanes of 8 channels each
   extern __shared__ __align__(16) uint8_t so_lds[];
-  float* wn = (float*)so_lds;                                           // [4][32 splits]: weight of a split / total sum
-  float* uT = wn + kOutSeqs * 32;                                       // [R][kOutSeqs]
-  float* red = uT + (size_t)p.R * kOutSeqs;                             // [16 slices][kOutSeqs][128 channels]
-  const int tid = threadIdx.x, h = blockIdx.x, b0 = blockIdx.y * kOutSeqs;
-  if ((tid >> 6) < kOutSeqs) {                                          // wave bi: lane s holds split s of sequence b0 + bi
-    const int bi = tid >> 6, sidx = tid & 63, b = b0 + bi;
-    const bool on = b < p.B && sidx < p.S;
-    const float m = on ? p.pm[((size_t)b * p.S + sidx) * kSharedHeads + h] : -INFINITY;
-    const float l = on ? p.pl[((size_t)b * p.S + sidx) * kSharedHeads + h] : 0.f;
-    float M = m;
+  float* wn = (float*)so_lds;                                           // [32 splits]: weight of a split / total sum
+  float* red = wn + 32;                                                 // [waves][128 channels]
+  float* uT = red + T / 64 * 128;                                       // [R]
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, h = blockIdx.x, b = blockIdx.y;
+  float m = -INFINITY, l = 0.f;
+  if (wave == 0 && lane < p.S) {                                        // lane s holds split s (at most 32)
+    m = p.pm[((size_t)b * p.S + lane) * kSharedHeads + h];
+    l = p.pl[((size_t)b * p.S + lane) * kSharedHeads + h];
+  }
+  const size_t sstride = (size_t)kSharedHeads * p.R;
+  const float* pu = p.pu + (((size_t)b * p.S) * kSharedHeads + h) * p.R;
+  v2f x[8];
+  const auto request_partials = [&](int j, int s0) {                    // 8 loads of 8 bytes in flight
 #pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) M = fmaxf(M, __shfl_xor(M, o));
-    const float w = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
-    float L = w * l;
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) L += __shfl_xor(L, o);
-    if (sidx < 32) wn[bi * 32 + sidx] = L > 0.f ? w / L : 0.f;
+    for (int i = 0; i < 8; i++) x[i] = *(const v2f*)(pu + min(s0 + i, p.S - 1) * sstride + j);
+  };
+  if (2 * tid < p.R) request_partials(2 * tid, 0);
+  __builtin_amdgcn_sched_barrier(0);
+  if (wave == 0) {
+    const float M = wave_max(m);
+    const float e = m == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m - M);
+    const float L = wave_sum(e * l);
+    if (lane < 32) wn[lane] = L > 0.f ? e / L : 0.f;                    // (past the last split: 0)
   }
   __syncthreads();
-  for (int j = tid; j < p.R; j += 256)
+  for (int j = 2 * tid; j < p.R; j += 2 * T) {
+    v2f u = {0.f, 0.f};
+    for (int s0 = 0; s0 < p.S; s0 += 8) {
+      if (j >= 2 * T || s0 > 0) request_partials(j, s0);
+      const v4f wa = *(const v4f*)&wn[s0], wb = *(const v4f*)&wn[s0 + 4];
 #pragma unroll
-    for (int bi = 0; bi < kOutSeqs; bi++) {
-      float u = 0.f;
-      if (b0 + bi < p.B) {
-        const float* src = p.pu + (((size_t)(b0 + bi) * p.S) * kSharedHeads + h) * p.R + j;
-        for (int s0 = 0; s0 < p.S; s0 += 16) {                          // 16 loads in flight (each trip of this loop is a
-          float x[16];                                                  // memory round trip); a split that wrote nothing has
-#pragma unroll                                                          // weight 0 and its (unwritten) values are dropped
-          for (int i = 0; i < 16; i++) x[i] = src[(size_t)min(s0 + i, p.S - 1) * kSharedHeads * p.R];
+      for (int i = 0; i < 8; i++) {                                     // a split that wrote nothing has weight 0 and its
+        const float ws = i < 4 ? wa[i & 3] : wb[i & 3];                 // (unwritten) values are dropped
+        u[0] += ws != 0.f ? ws * x[i][0] : 0.f;
+        u[1] += ws != 0.f ? ws * x[i][1] : 0.f;
+      }
+    }
+    *(v2f*)&uT[j] = u;
+  }
+  __syncthreads();
+  // thread (c8, js): output channels 8 c8 .. + 7 (one 16-byte load per row of B_Vh) of rows js, js + NR, ...
+  const int c8 = tid & 15, js = tid >> 4;
+  float acc[8];
 #pragma unroll
-          for (int i = 0; i < 16; i++) {
-            const float w = s0 + i < p.S ? wn[bi * 32 + s0 + i] : 0.f;
-            u += w != 0.f ? w * x[i] : 0.f;
-          }
+  for (int e = 0; e < 8; e++) acc[e] = 0.f;
+  if (8 * c8 < p.d) {
+    const uint16_t* bv = p.BV + ((size_t)h * p.R + js) * p.d + 8 * c8;
+    const auto rows = [&](int j, auto count) {                          // `count` loads in flight
+      constexpr int N = decltype(count)::value;
+      v4i w[N];
+#pragma unroll
+      for (int i = 0; i < N; i++) w[i] = *(const v4i*)(bv + (size_t)(j + i * NR) * p.d);
+#pragma unroll
+      for (int i = 0; i < N; i++) {
+        const float u = uT[j + i * NR + js];
+#pragma unroll
+        for (int e2 = 0; e2 < 4; e2++) {
+          acc[2 * e2] = fmaf(u, __uint_as_float((uint32_t)w[i][e2] << 16), acc[2 * e2]);
+          acc[2 * e2 + 1] = fmaf(u, __uint_as_float((uint32_t)w[i][e2] & 0xFFFF0000u), acc[2 * e2 + 1]);
         }
       }
-      uT[j * kOutSeqs + bi] = u;
-    }
-  __syncthreads();
-  // thread (c8, js): output channels 8 c8 .. + 7 (one 16-byte load per row of B_Vh) over slice js of the R dims
-  const int c8 = tid & 15, js = tid >> 4;
-  float acc[kOutSeqs][8];
+    };
+    int j = 0;
+    for (; j + 8 * NR <= p.R; j += 8 * NR) rows(j, std::integral_constant<int, 8>{});
+    for (; j < p.R; j += NR) rows(j, std::integral_constant<int, 1>{});
+  }
 #pragma unroll
-  for (int bi = 0; bi < kOutSeqs; bi++)
+  for (int e = 0; e < 8; e++) {                                         // the wave's 4 rows of a step
+    acc[e] += __shfl_xor(acc[e], 16);
+    acc[e] += __shfl_xor(acc[e], 32);
+  }
+  if (lane < 16 && 8 * c8 < p.d) {
 #pragma unroll
-    for (int e = 0; e < 8; e++) acc[bi][e] = 0.f;
-  if (8 * c8 < p.d) {
-    const int jn = p.R >> 4;                                            // rows per slice: a multiple of 16
-    const uint16_t* bv = p.BV + ((size_t)h * p.R + (size_t)js * jn) * p.d + 8 * c8;
-    for (int j0 = 0; j0 < jn; j0 += 8) {                                // 8 loads in flight
-      v4i w[8];
-#pragma unroll
-      for (int i = 0; i < 8; i++) w[i] = *(const v4i*)(bv + (size_t)(j0 + i) * p.d);
-#pragma unroll
-      for (int i = 0; i < 8; i++)
-#pragma unroll
-        for (int bi = 0; bi < kOutSeqs; bi++) {
-          const float u = uT[(js * jn + j0 + i) * kOutSeqs + bi];
-#pragma unroll
-          for (int e2 = 0; e2 < 4; e2++) {
-            acc[bi][2 * e2] = fmaf(u, __uint_as_float((uint32_t)w[i][e2] << 16), acc[bi][2 * e2]);
-            acc[bi][2 * e2 + 1] = fmaf(u, __uint_as_float((uint32_t)w[i][e2] & 0xFFFF0000u), acc[bi][2 * e2 + 1]);
-          }
-        }
-    }
-#pragma unroll
-    for (int bi = 0; bi < kOutSeqs; bi++)
-#pragma unroll
-      for (int e = 0; e < 8; e++) red[(js * kOutSeqs + bi) * 128 + 8 * c8 + e] = acc[bi][e];
+    for (int e = 0; e < 8; e++) red[wave * 128 + 8 * c8 + e] = acc[e];
   }
   __syncthreads();
-  for (int i = tid; i < kOutSeqs * p.d; i += 256) {
-    const int bi = i / p.d, c = i % p.d;
-    if (b0 + bi < p.B) {
-      float o = 0.f;
+  if (tid < p.d) {
+    float o = 0.f;
 #pragma unroll
-      for (int q = 0; q < 16; q++) o += red[(q * kOutSeqs + bi) * 128 + c];
-      p.out[((size_t)(b0 + bi) * kSharedHeads + h) * p.d + c] = o;
-    }
+    for (int q = 0; q < T / 64; q++) o += red[q * 128 + tid];
+    p.out[((size_t)b * kSharedHeads + h) * p.d + tid] = o;
   }
+}
+
+// Workgroups over which the value dims of the same tokens are divided (each computes the scores of all its tokens), up to
+// rank 1024.  Where (sequence, chunk) pairs are too few for the chip the parts fill it (1 sequence of 8191 rows, rank 1024:
+// 1 / 2 / 4 parts 23.7 / 17.5 / 15.6 us; 5 of 3000 rows, rank 512: 10.8 / 8.8 us).  At rank 1024 two parts also halve the
+// partial results, 33.6 MB at 16 sequences, for a second reading of the keys from the die's cache: the attention's time stays
+// at 22 us, the merge takes 10 instead of 13.  Otherwise one: 64 sequences of rank 256 19.3 us, with two 27.6; 31 of rank
+// 512 18.4 against 22.4.
+int shared_value_parts(int batch, int chunks, int rank) {
+  const long pairs = (long)batch * (chunks < 32 ? chunks : 32);
+  if (rank >= 512 && 4 * pairs <= 256) return 4;
+  return 2 * pairs <= 256 || rank == 1024 ? 2 : 1;
 }
 
 int shared_splits(int batch, int t_cap, int rank) {
@@ -653,17 +751,28 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   p.qmax = p.pu + (size_t)batch * p.S * kSharedHeads * rank;
   p.out = (float*)out;
 
-  hipLaunchKernelGGL(k_shared_absorb, dim3((unsigned)(rank / 32), kSharedHeads), dim3(64), 0, s, p);
+  const dim3 grid_a((unsigned)(rank / 32), kSharedHeads);
+  if (d_head != 64 && d_head != 128) return hipErrorNotSupported;
+  if (rank > 1024) {
+    if (d_head == 128) hipLaunchKernelGGL((k_shared_absorb<128>), grid_a, dim3(64), 0, s, p);
+    else hipLaunchKernelGGL((k_shared_absorb<64>), grid_a, dim3(64), 0, s, p);
+  } else {
+    const dim3 grid_l(kSharedHeads, 4, (unsigned)((batch + 31) / 32));
+    void (*fn)(SharedParams) =
+        rank == 256 ? (d_head == 128 ? k_shared_absorb_limbs<128, 256> : k_shared_absorb_limbs<64, 256>)
+        : rank == 512 ? (d_head == 128 ? k_shared_absorb_limbs<128, 512> : k_shared_absorb_limbs<64, 512>)
+                      : (d_head == 128 ? k_shared_absorb_limbs<128, 1024> : k_shared_absorb_limbs<64, 1024>);
+    hipLaunchKernelGGL(fn, grid_l, dim3((unsigned)rank / 2), 0, s, p);
+  }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 
-  const size_t lds_out = (size_t)(kOutSeqs * 32 + rank * kOutSeqs + 16 * kOutSeqs * 128) * sizeof(float);
-  static bool raised_out = false;                                       // up to 99 KB at rank 4096
-  if (!raised_out) {
-    e = hipFuncSetAttribute((const void*)k_shared_out, hipFuncAttributeMaxDynamicSharedMemorySize, (int)((128 + 4096 * kOutSeqs + 16 * kOutSeqs * 128) * sizeof(float)));
-    if (e != hipSuccess) return e;
-    raised_out = true;
-  }
+  // 512 threads shorten the chain of trips (1 sequence, rank 1024: 7.6 us, 256 threads 11.6; 2 of rank 3712: 17.5, 27.6);
+  // at rank 256 half of them have no partial result to read (64 sequences: 10.7, 256 threads 8.4)
+  const int t_out = rank == 256 ? 256 : 512;
+  const size_t lds_out = (size_t)(32 + t_out / 64 * 128 + rank) * sizeof(float);       // at most 21 KB
+  void (*fn_out)(SharedParams) = t_out == 512 ? k_shared_out<512> : k_shared_out<256>;
+  const dim3 grid_out(kSharedHeads, (unsigned)batch);
   if (rank > 1024) {
     hipLaunchKernelGGL(k_shared_qmax, dim3(kSharedHeads, (unsigned)batch), dim3(64), 0, s, p);
     const size_t lds_big = (size_t)3 * (kBigSlab / 32) * 1024 + (size_t)(2 + kBigChunks) * 128 * sizeof(float) +
@@ -677,27 +786,26 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
     hipLaunchKernelGGL(k_shared_attn_big, dim3((unsigned)p.S, (unsigned)batch), dim3(256), lds_big, s, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_shared_out, dim3(kSharedHeads, (unsigned)((batch + kOutSeqs - 1) / kOutSeqs)), dim3(256), lds_out, s, p);
+    hipLaunchKernelGGL(fn_out, grid_out, dim3((unsigned)t_out), lds_out, s, p);
     return hipGetLastError();
   }
-  const size_t lds_attn = (size_t)3 * (rank / 32) * 1024 + 4 * 128 * sizeof(float) + 4 * 32 * 40 * sizeof(_Float16);
-  const void* fn = rank == 256 ? (const void*)k_shared_attn<256> : rank == 512 ? (const void*)k_shared_attn<512>
-                                                                                 : (const void*)k_shared_attn<1024>;
-  static bool raised[3] = {false, false, false};                        // the kernels' limit of dynamic LDS, raised once
-  const int ri = rank == 256 ? 0 : rank == 512 ? 1 : 2;
-  if (!raised[ri]) {
-    e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_attn);
+  const size_t lds_attn = (size_t)3 * (rank / 32) * 1024 + 3 * 128 * sizeof(float) +
+                          4 * 32 * 40 * sizeof(_Float16) + 4 * 128 * sizeof(_Float16);
+  const int vh = shared_value_parts(batch, chunks_cap, rank);
+  p.S = max(1, min(256 / (batch * vh), p.S));                           // never more than the workspace is sized for
+  void (*fn)(SharedParams) = rank == 256   ? (vh == 2 ? k_shared_attn<256, 2> : k_shared_attn<256, 1>)
+                             : rank == 512 ? (vh == 4 ? k_shared_attn<512, 4> : vh == 2 ? k_shared_attn<512, 2> : k_shared_attn<512, 1>)
+                                           : (vh == 4 ? k_shared_attn<1024, 4> : k_shared_attn<1024, 2>);
+  static bool raised[2] = {false, false};                               // the limit of dynamic LDS, raised once (109 KB)
+  if (rank == 1024 && !raised[vh >> 2]) {
+    e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_attn);
     if (e != hipSuccess) return e;
-    raised[ri] = true;
+    raised[vh >> 2] = true;
   }
-  dim3 grid((unsigned)p.S, (unsigned)batch);
-  if (rank == 256) hipLaunchKernelGGL((k_shared_attn<256>), grid, dim3(256), lds_attn, s, p);
-  else if (rank == 512) hipLaunchKernelGGL((k_shared_attn<512>), grid, dim3(256), lds_attn, s, p);
-  else if (rank == 1024) hipLaunchKernelGGL((k_shared_attn<1024>), grid, dim3(256), lds_attn, s, p);
-  else return hipErrorNotSupported;
+  hipLaunchKernelGGL(fn, dim3((unsigned)((batch * p.S + 7) / 8 * 8 * vh)), dim3(256), lds_attn, s, p);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
 
-  hipLaunchKernelGGL(k_shared_out, dim3(kSharedHeads, (unsigned)((batch + kOutSeqs - 1) / kOutSeqs)), dim3(256), lds_out, s, p);
+  hipLaunchKernelGGL(fn_out, grid_out, dim3((unsigned)t_out), lds_out, s, p);
   return hipGetLastError();
 }
