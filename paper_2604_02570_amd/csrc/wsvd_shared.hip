@@ -7,7 +7,7 @@
 // would), at the price of R-dimensional per-head queries and outputs: Q~_h = B_Kh q_h and o_h = B_Vh^T u_h move
 // 2 * H * R * d factor elements per step where the per-head scheme moves 2 * H * r * d.
 //   k_shared_absorb_limbs  Q~ [B, H, R] = (sm_scale log2 e) B_Kh q_h         bf16 MFMA, one wave per (head, 32 latent dims),
-//                     as three 7-bit limbs per quarter of the rank (ranks above 1024: k_shared_absorb, fp32)
+//                     as three 7-bit limbs of a unit per piece of the rank
 //   k_shared_attn     per (sequence, split of its 128-token chunks, part of the value dims): scores on int8 MFMA (the cache
 //                     codes are the A operand as stored; Q~ as three 7-bit limbs in LDS is the B operand), softmax down
 //                     the head columns, value product on fp16 MFMA with each wave owning a quarter of the part's output
@@ -23,10 +23,10 @@ namespace {
 
 constexpr int kSharedHeads = 32;          // the heads are the 32 columns of the products
 constexpr int kSharedChunk = 128;         // tokens per workgroup pass: one 32-token block per wave
-// A sequence's queries as limbs, [3][R / 32][64 lanes][16 B], and behind them the value of a unit, [quarter][head].  The
-// images lie an odd number of 256-byte pieces apart (the lanes of a store hold 32 sequences); the room for one is that of
+// A sequence's queries as limbs, [3][R / 32][64 lanes][16 B], and behind them the value of a unit, [piece][head] (at most
+// 16 pieces).  The images lie an odd number of 256-byte pieces apart (the lanes of a store hold 32 sequences); the room for one is that of
 // the same queries in fp32, 128 R bytes.
-constexpr size_t shared_image_bytes(int R) { return (size_t)96 * R + 1280; }
+constexpr size_t shared_image_bytes(int R) { return (size_t)96 * R + 2304; }
 static_assert(shared_image_bytes(256) <= 128 * 256, "the smallest rank's images fit");
 constexpr float kLimbRange = 1040000.f;   // |Q~ / delta| stays below 2^20: three signed 7-bit limbs
 
@@ -42,66 +42,32 @@ struct SharedParams {
   const uint16_t* k_scale;    // fp16 [B][t_cap]
   const uint16_t* v_scale;
   const int* seq_lens;
-  float* qt;                  // workspace: Q~ [B, H, R]; up to rank 1024 its limbs, [B] images
-  float* qmax;                //            max |Q~| per (sequence, head) (ranks above 1024 only)
+  uint8_t* qt;                // workspace: Q~ as limbs, [B] images
   float* pm;                  // workspace: partial running maxima [B, S, H]
   float* pl;                  //            partial sums           [B, S, H]
   float* pu;                  //            partial U              [B, S, H, R]
   float* out;                 // fp32 [B, H, d]
   int B, d, R, t_cap, S;
-  int per;                    // chunks of 128 tokens per split (ranks above 1024: at most 4)
+  int per;                    // ranks above 1024: chunks of 128 tokens per split (at most 4),
+  int parts;                  //                   workgroups the slabs of the value dims are divided over
   float c_scale;              // sm_scale * log2(e)
 };
 
-// ---------------------------------------------------------------- Q~ = c B_Kh q_h
-// All of a wave's operands are requested together (one trip to memory instead of one per step of the contraction).
-template <int D>
-__global__ __launch_bounds__(64) void k_shared_absorb(SharedParams p) {
-  const int lane = threadIdx.x, n = lane & 31, g2 = lane >> 5;
-  const int jb = blockIdx.x, h = blockIdx.y;
-  const uint16_t* arow = p.BK + ((size_t)h * p.R + 32 * jb + n) * D + 8 * g2;
-  v8bf16 a[D / 16];
-#pragma unroll
-  for (int ks = 0; ks < D / 16; ks++) a[ks] = *(const v8bf16*)(arow + 16 * ks);
-  for (int bb = 0; bb < p.B; bb += 32) {
-    const int b = bb + n;
-    const uint16_t* qrow = p.q + ((size_t)min(b, p.B - 1) * kSharedHeads + h) * D + 8 * g2;
-    v8bf16 x[D / 16];
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) x[ks] = *(const v8bf16*)(qrow + 16 * ks);
-    __builtin_amdgcn_sched_barrier(0);
-    v16f acc;
-#pragma unroll
-    for (int v = 0; v < 16; v++) acc[v] = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < D / 16; ks++) acc = mfma_bf16(a[ks], x[ks], acc);
-    if (b < p.B) {
-      float* dst = p.qt + ((size_t)b * kSharedHeads + h) * p.R + 32 * jb + 4 * g2;
-#pragma unroll
-      for (int m4 = 0; m4 < 4; m4++) {
-        v4f o;
-#pragma unroll
-        for (int jj = 0; jj < 4; jj++) o[jj] = acc[4 * m4 + jj] * p.c_scale;
-        *(v4f*)(dst + 8 * m4) = o;
-      }
-    }
-  }
-}
-
-// ---------------------------------------------------------------- the same up to rank 1024, as the score product reads it
-// One workgroup per (head, quarter of the rank, 32 sequences) holds that piece of Q~ in registers, so its maximum is known
-// on the spot and the three signed 7-bit limbs of round(Q~ / delta) leave in the order of the int8 product's B operand:
-// lane (head, g2) of step ks holds dims 32 ks + 16 g2 .. + 15.  Every quarter has its own delta: with one per head (32
+// ---------------------------------------------------------------- Q~ = c B_Kh q_h, as the score product reads it
+// One workgroup per (head, piece of the rank, 32 sequences) holds that piece of Q~ in registers, so its maximum is known on
+// the spot and the three signed 7-bit limbs of round(Q~ / delta) leave in the order of the int8 product's B operand:
+// lane (head, g2) of step ks holds dims 32 ks + 16 g2 .. + 15.  A piece is a quarter of the rank up to 1024 and 256 dims
+// above (the last one may be 128).  Every piece has its own delta: with one per head (32
 // workgroups of 256 KB of factors each) the launch took 13.5 us at rank 1024.  Converted by every split's workgroup instead,
 // the limbs cost 2800 vector instructions, 20 KB of code run once, before the first score.
-template <int D, int R>
-__global__ __launch_bounds__(R / 2) __attribute__((amdgpu_waves_per_eu(2, 4))) void k_shared_absorb_limbs(SharedParams p) {
-  constexpr int NW = R / 128;                                           // waves: a block of 32 dims each
+template <int D, int NW>                                                // NW waves: a block of 32 dims each
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(2, 4))) void k_shared_absorb_limbs(SharedParams p) {
   __shared__ float wmax[NW][32];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), n = lane & 31, g2 = lane >> 5;
-  const int h = blockIdx.x, quarter = blockIdx.y, b = 32 * blockIdx.z + n, jb = quarter * NW + wave;
+  const int h = blockIdx.x, piece = blockIdx.y, b = 32 * blockIdx.z + n, jb = piece * NW + wave, R = p.R;
+  const bool past = 32 * jb >= R;                                       // a wave behind the last piece's end
   const uint16_t* qrow = p.q + ((size_t)min(b, p.B - 1) * kSharedHeads + h) * D + 8 * g2;
-  const uint16_t* arow = p.BK + ((size_t)h * R + 32 * jb + n) * D + 8 * g2;
+  const uint16_t* arow = p.BK + ((size_t)h * R + (past ? 0 : 32 * jb) + n) * D + 8 * g2;
   v8bf16 a[D / 16], x[D / 16];
 #pragma unroll
   for (int ks = 0; ks < D / 16; ks++) { x[ks] = *(const v8bf16*)(qrow + 16 * ks); a[ks] = *(const v8bf16*)(arow + 16 * ks); }
@@ -118,16 +84,16 @@ __global__ __launch_bounds__(R / 2) __attribute__((amdgpu_waves_per_eu(2, 4))) v
     amax = fmaxf(amax, fabsf(acc[v]));
   }
   amax = fmaxf(amax, __shfl_xor(amax, 32));
-  if (g2 == 0) wmax[wave][n] = amax;
+  if (g2 == 0) wmax[wave][n] = past ? 0.f : amax;
   __syncthreads();
   float hm = 0.f;
 #pragma unroll
   for (int w = 0; w < NW; w++) hm = fmaxf(hm, wmax[w][n]);
   const float delta = hm > 0.f ? hm / kLimbRange : 1.0f;                // value of one unit of the integer query
   const float inv_delta = 1.0f / delta;
-  if (b >= p.B) return;
-  uint8_t* image = (uint8_t*)p.qt + (size_t)b * shared_image_bytes(R);
-  if (wave == 0 && g2 == 0) ((float*)(image + 96 * R))[quarter * kSharedHeads + h] = delta;
+  if (b >= p.B || past) return;
+  uint8_t* image = p.qt + (size_t)b * shared_image_bytes(R);
+  if (wave == 0 && g2 == 0) ((float*)(image + (size_t)96 * R))[piece * kSharedHeads + h] = delta;
   uint32_t w[3][4];                                                     // [limb][m4]: dims 8 m4 + 4 g2 .. + 3
 #pragma unroll
   for (int m4 = 0; m4 < 4; m4++) {
@@ -193,7 +159,7 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
   const uint16_t* vmeta = p.v_scale + (size_t)b * p.t_cap;
 
   // ---- the limbs of the sequence's queries, a quarter by each wave
-  const uint8_t* qimage = (const uint8_t*)p.qt + (size_t)b * shared_image_bytes(R);
+  const uint8_t* qimage = p.qt + (size_t)b * shared_image_bytes(R);
   const v4i* image = (const v4i*)qimage + wave * (3 * NKS / 4) * 64 + lane;
   float delta[4];
 #pragma unroll
@@ -364,22 +330,10 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
 // run against them, the integer dot products of a slab being added to a float score per (token, head).  Softmax: one
 // maximum per head over all the workgroup's tokens (no running rescale), P kept in LDS as fp16.  Values: for every slab
 // a wave accumulates its quarter of the slab's dims over all chunks and writes that piece of the partial result.
-// The per-head scale of the integer query needs max |Q~| over the whole rank: k_shared_qmax computes it once per call.
-__global__ __launch_bounds__(64) void k_shared_qmax(SharedParams p) {
-  const int h = blockIdx.x, b = blockIdx.y, lane = threadIdx.x;
-  const float* q = p.qt + ((size_t)b * kSharedHeads + h) * p.R;
-  float a = 0.f;
-  for (int j0 = 0; j0 < p.R; j0 += 256) {                               // R is a multiple of 128: whole v4f pieces
-    const int j = j0 + 4 * lane;
-    if (j < p.R) {
-      const v4f x = *(const v4f*)(q + j);
-      a = fmaxf(a, fmaxf(fmaxf(fabsf(x[0]), fabsf(x[1])), fmaxf(fabsf(x[2]), fabsf(x[3]))));
-    }
-  }
-  a = wave_max(a);
-  if (lane == 0) p.qmax[b * kSharedHeads + h] = a;
-}
-
+// The slabs of the value dims are divided over p.parts workgroups where that fills the chip; each computes the scores of all
+// its tokens.  As above, what runs once is expensive, so the limbs come ready made, the value code is one chunk's
+// (102 -> 50 KB of code) and a slab's keys are requested together, the first chunk's behind the limbs.  16 sequences of 600
+// rows, rank 1920: 44.5 -> 28.1 us; 40 of 300 rows, rank 1280 38.2 -> 24.4; the launch for the heads' maxima is gone.
 constexpr int kBigSlab = 1024;            // latent dims per slab
 constexpr int kBigChunks = 4;             // chunks of 128 tokens per workgroup, at most
 
@@ -394,8 +348,11 @@ __global__ __launch_bounds__(256) void k_shared_attn_big(SharedParams p) {
   float* ksc = csum + 128;                                              // [NC][4][32]
   _Float16* pt = (_Float16*)(ksc + NC * 128);                           // [NC][4 token blocks][32 heads][40]
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g2 = lane >> 5;
-  const int split = blockIdx.x, b = blockIdx.y;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), n = lane & 31, g2 = lane >> 5;
+  const int unit = (blockIdx.x & 7) + 8 * (blockIdx.x / (8 * p.parts)), part_v = (blockIdx.x >> 3) % p.parts;   // as above
+  if (unit >= p.B * p.S) return;
+  const int b = (p.B & 7) == 0 ? (unit & 7) + 8 * (unit / (8 * p.S)) : unit / p.S;
+  const int split = (p.B & 7) == 0 ? (unit >> 3) % p.S : unit % p.S;
   const int R = p.R;
   const int n_b = min(max(p.seq_lens[b], 0), p.t_cap);
   const int n_chunks = (n_b + kSharedChunk - 1) / kSharedChunk;
@@ -409,9 +366,6 @@ __global__ __launch_bounds__(256) void k_shared_attn_big(SharedParams p) {
   const uint8_t* vplane = p.v_codes + (size_t)b * p.t_cap * R;
   const uint16_t* kmeta = p.k_scale + (size_t)b * p.t_cap;
   const uint16_t* vmeta = p.v_scale + (size_t)b * p.t_cap;
-  const float hm = p.qmax[b * kSharedHeads + n];
-  const float delta = hm > 0.f ? hm / kLimbRange : 1.0f;                // value of one unit of head n's integer query
-  const float inv_delta = 1.0f / delta;
   const int n_slabs = (R + kBigSlab - 1) / kBigSlab;
 
   // K scales of this wave's 32 tokens of every chunk
@@ -425,76 +379,70 @@ __global__ __launch_bounds__(256) void k_shared_attn_big(SharedParams p) {
   for (int c = 0; c < NC; c++)
 #pragma unroll
     for (int v = 0; v < 16; v++) sacc[c][v] = 0.f;
-  const float* qrow = p.qt + ((size_t)b * kSharedHeads + n) * R + 16 * g2;
+  const uint8_t* qimage = p.qt + (size_t)b * shared_image_bytes(R);
+  const uint32_t lane16 = 16 * lane;
   for (int sl = 0; sl < n_slabs; sl++) {
     const int d0 = sl * kBigSlab;
     const int nks = min(kBigSlab, R - d0) >> 5;                         // a multiple of 4
-    __syncthreads();                                                    // the previous slab's limbs are no longer read
-    // this wave converts steps wave, wave + 4, ...: lane (n, g2) of step ks holds dims d0 + 32 ks + 16 g2 .. + 15
+    // this wave moves steps wave, wave + 4, ... of the slab's limbs; the keys of the first chunk are requested behind them
+    v4i lq[NKS / 4][3], ka[NKS];
 #pragma unroll
-    for (int i0 = 0; i0 < NKS / 4; i0 += 4) {
-      v4f xq[4][4];
+    for (int i = 0; i < NKS / 4; i++)
+      if (4 * i < nks) {
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int ks = min(wave + 4 * (i0 + i), nks - 1);               // clamped: surplus steps are not stored
-#pragma unroll
-        for (int i4 = 0; i4 < 4; i4++) xq[i][i4] = *(const v4f*)(qrow + d0 + 32 * ks + 4 * i4);
+        for (int t = 0; t < 3; t++)
+          lq[i][t] = *(const v4i*)(qimage + (size_t)t * (32 * R) + (size_t)((d0 >> 5) + 4 * i + wave) * 1024 + lane16);
       }
+    float delta[4];                                                     // of 256 dims each
 #pragma unroll
-      for (int i = 0; i < 4; i++) {
-        const int ks = wave + 4 * (i0 + i);
-        if (ks < nks) {                                                 // wave-uniform
-          v4i l0, l1, l2;
+    for (int i = 0; i < 4; i++)
+      delta[i] = ((const float*)(qimage + (size_t)96 * R))[min((d0 >> 8) + i, (R - 1) >> 8) * kSharedHeads + n];
+    const auto request_keys = [&](int c) {
+      const uint8_t* kp = kplane + (size_t)((c0 + c) * 4 + wave) * (32 * (size_t)R) + (size_t)(d0 >> 5) * 1024;
 #pragma unroll
-          for (int i4 = 0; i4 < 4; i4++) {
-            uint32_t w0 = 0, w1 = 0, w2 = 0;
+      for (int k = 0; k < NKS; k += 4)
+        if (k < nks) {
 #pragma unroll
-            for (int e = 0; e < 4; e++) {
-              const int Q = (int)__builtin_rintf(xq[i][i4][e] * inv_delta);
-              const int a0 = ((Q + 64) & 127) - 64, Q1 = (Q - a0) >> 7;   // Q = a0 + 128 Q1 exactly
-              const int a1 = ((Q1 + 64) & 127) - 64, a2 = (Q1 - a1) >> 7;
-              w0 |= ((uint32_t)a0 & 0xFFu) << (8 * e);
-              w1 |= ((uint32_t)a1 & 0xFFu) << (8 * e);
-              w2 |= ((uint32_t)a2 & 0xFFu) << (8 * e);
-            }
-            l0[i4] = (int)w0; l1[i4] = (int)w1; l2[i4] = (int)w2;
-          }
-          limbs[(0 * NKS + ks) * 64 + lane] = l0;
-          limbs[(1 * NKS + ks) * 64 + lane] = l1;
-          limbs[(2 * NKS + ks) * 64 + lane] = l2;
+          for (int k1 = k; k1 < k + 4; k1++) ka[k1] = *(const v4i*)(kp + k1 * 1024 + lane16);
         }
+    };
+    request_keys(0);
+    __builtin_amdgcn_sched_barrier(0);
+    __syncthreads();                                                    // the previous slab's limbs are no longer read
+#pragma unroll
+    for (int i = 0; i < NKS / 4; i++)
+      if (4 * i < nks) {
+#pragma unroll
+        for (int t = 0; t < 3; t++) limbs[(t * NKS + 4 * i + wave) * 64 + lane] = lq[i][t];
       }
-    }
     __syncthreads();
 #pragma unroll
     for (int c = 0; c < NC; c++) {
       if (c0 + c < c1) {                                                // workgroup-uniform
-        const int t0 = (c0 + c) * kSharedChunk + 32 * wave;
-        const uint8_t* kp = kplane + (size_t)(t0 >> 5) * (32 * (size_t)R) + (size_t)(d0 >> 5) * 1024 + (size_t)lane * 16;
-        v16i a0, a1, a2;
+        if (c > 0) request_keys(c);
 #pragma unroll
-        for (int v = 0; v < 16; v++) { a0[v] = 0; a1[v] = 0; a2[v] = 0; }
+        for (int g = 0; g < 4; g++) {                                   // 256 dims with a unit of their own
+          if (8 * g < nks) {
+            v16i a0, a1, a2;
 #pragma unroll
-        for (int h0 = 0; h0 < NKS; h0 += 16) {
-          if (h0 < nks) {                                               // nks is a multiple of 4, not of 16: see below
-            v4i ka[16];
+            for (int v = 0; v < 16; v++) { a0[v] = 0; a1[v] = 0; a2[v] = 0; }
 #pragma unroll
-            for (int k = 0; k < 16; k++)
-              ka[k] = __builtin_nontemporal_load((const v4i*)(kp + (size_t)min(h0 + k, nks - 1) * 1024));   // clamped, masked below
-            __builtin_amdgcn_sched_barrier(0);
+            for (int k4 = 8 * g; k4 < 8 * g + 8; k4 += 4) {
+              if (k4 < nks) {
 #pragma unroll
-            for (int k = 0; k < 16; k++) {
-              if (h0 + k < nks) {
-                a0 = mfma_i8(ka[k], limbs[(0 * NKS + h0 + k) * 64 + lane], a0);
-                a1 = mfma_i8(ka[k], limbs[(1 * NKS + h0 + k) * 64 + lane], a1);
-                a2 = mfma_i8(ka[k], limbs[(2 * NKS + h0 + k) * 64 + lane], a2);
+                for (int k = k4; k < k4 + 4; k++) {
+                  a0 = mfma_i8(ka[k], limbs[(0 * NKS + k) * 64 + lane], a0);
+                  a1 = mfma_i8(ka[k], limbs[(1 * NKS + k) * 64 + lane], a1);
+                  a2 = mfma_i8(ka[k], limbs[(2 * NKS + k) * 64 + lane], a2);
+                }
+                __builtin_amdgcn_sched_barrier(0);                      // keeps the limb reads from piling up in registers
               }
-              if ((k & 3) == 3) __builtin_amdgcn_sched_barrier(0);      // keeps the limb reads from piling up in registers
             }
+#pragma unroll
+            for (int v = 0; v < 16; v++)
+              sacc[c][v] = fmaf(fmaf(16384.f, (float)a2[v], fmaf(128.f, (float)a1[v], (float)a0[v])), delta[g], sacc[c][v]);
           }
         }
-#pragma unroll
-        for (int v = 0; v < 16; v++) sacc[c][v] += fmaf(16384.f, (float)a2[v], fmaf(128.f, (float)a1[v], (float)a0[v]));
       }
     }
   }
@@ -510,7 +458,7 @@ __global__ __launch_bounds__(256) void k_shared_attn_big(SharedParams p) {
 #pragma unroll
       for (int jj = 0; jj < 4; jj++) {
         const int v = 4 * m4 + jj;
-        const float sv = sacc[c][v] * delta * k4[jj];
+        const float sv = sacc[c][v] * k4[jj];
         sacc[c][v] = (c0 + c < c1 && t0 + 8 * m4 + 4 * g2 + jj < n_b) ? sv : -INFINITY;   // rows past the sequence's end
         bmax = fmaxf(bmax, sacc[c][v]);
       }
@@ -539,13 +487,13 @@ __global__ __launch_bounds__(256) void k_shared_attn_big(SharedParams p) {
   psum += __shfl_xor(psum, 32);
   if (g2 == 0) csum[wave * 32 + n] = psum;
   __syncthreads();
-  if (wave == 0 && g2 == 0) {
+  if (part_v == 0 && wave == 0 && g2 == 0) {
     p.pm[part * kSharedHeads + n] = m_all;
     p.pl[part * kSharedHeads + n] = (csum[n] + csum[32 + n]) + (csum[64 + n] + csum[96 + n]);
   }
 
   // ---- values: slab by slab, this wave's quarter of the slab's dims over all chunks
-  for (int sl = 0; sl < n_slabs; sl++) {
+  for (int sl = part_v; sl < n_slabs; sl += p.parts) {
     const int d0 = sl * kBigSlab;
     const int nkk = min(kBigSlab, R - d0) >> 7;                         // 32-dim blocks per wave in this slab (1..8)
     const int blk0 = (d0 >> 5) + wave * nkk;                            // first 32-dim block of this wave
@@ -554,42 +502,41 @@ __global__ __launch_bounds__(256) void k_shared_attn_big(SharedParams p) {
     for (int kk = 0; kk < NKK; kk++)
 #pragma unroll
       for (int v = 0; v < 16; v++) U[kk][v] = 0.f;
+#pragma unroll 1
+    for (int c = 0; c < c1 - c0; c++) {
+      const int cbase = (c0 + c) * kSharedChunk;
+      // all of the chunk's blocks of this slab are requested at once
+      v4i vc[4][NKK], vsr[4][2];
 #pragma unroll
-    for (int c = 0; c < NC; c++) {
-      if (c0 + c < c1) {
-        const int cbase = (c0 + c) * kSharedChunk;
-        // all of the chunk's blocks of this slab are requested at once
-        v4i vc[4][NKK], vsr[4][2];
+      for (int tw = 0; tw < 4; tw++) {
+        const int tv = min(cbase + 32 * tw, (n_b - 1) & ~31);         // (a block past the end: the last one again, unused)
+        const uint8_t* vp = vplane + (size_t)(tv >> 5) * (32 * (size_t)R) + (size_t)blk0 * 1024;
 #pragma unroll
-        for (int tw = 0; tw < 4; tw++) {
-          const int tv = min(cbase + 32 * tw, (n_b - 1) & ~31);         // (a block past the end: the last one again, unused)
-          const uint8_t* vp = vplane + (size_t)(tv >> 5) * (32 * (size_t)R) + (size_t)blk0 * 1024 + (size_t)lane * 16;
+        for (int kk = 0; kk < NKK; kk++)
+          if (kk < nkk) vc[tw][kk] = __builtin_nontemporal_load((const v4i*)(vp + kk * 1024 + lane16));
+        vsr[tw][0] = *(const v4i*)(vmeta + tv + 16 * g2);
+        vsr[tw][1] = *(const v4i*)(vmeta + tv + 16 * g2 + 8);
+      }
+      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int kk = 0; kk < NKK; kk++) vc[tw][kk] = __builtin_nontemporal_load((const v4i*)(vp + (size_t)min(kk, nkk - 1) * 1024));
-          vsr[tw][0] = *(const v4i*)(vmeta + tv + 16 * g2);
-          vsr[tw][1] = *(const v4i*)(vmeta + tv + 16 * g2 + 8);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+      for (int tw = 0; tw < 4; tw++) {
+        const int tv = cbase + 32 * tw;
+        if (tv < n_b) {
+          v8f16 sv8[2] = {__builtin_bit_cast(v8f16, vsr[tw][0]), __builtin_bit_cast(v8f16, vsr[tw][1])};
+          if (tv + 32 > n_b) {      // rows never written may hold any scale: they contribute 0
 #pragma unroll
-        for (int tw = 0; tw < 4; tw++) {
-          const int tv = cbase + 32 * tw;
-          if (tv < n_b) {
-            v8f16 sv8[2] = {__builtin_bit_cast(v8f16, vsr[tw][0]), __builtin_bit_cast(v8f16, vsr[tw][1])};
-            if (tv + 32 > n_b) {      // rows never written may hold any scale: they contribute 0
+            for (int s2 = 0; s2 < 2; s2++)
 #pragma unroll
-              for (int s2 = 0; s2 < 2; s2++)
+              for (int e = 0; e < 8; e++)
+                if (tv + 16 * g2 + 8 * s2 + e >= n_b) sv8[s2][e] = (_Float16)0;
+          }
+          const v8f16 bp0 = *(const v8f16*)&pt[((c * 4 + tw) * 32 + n) * 40 + 16 * g2];
+          const v8f16 bp1 = *(const v8f16*)&pt[((c * 4 + tw) * 32 + n) * 40 + 16 * g2 + 8];
 #pragma unroll
-                for (int e = 0; e < 8; e++)
-                  if (tv + 16 * g2 + 8 * s2 + e >= n_b) sv8[s2][e] = (_Float16)0;
-            }
-            const v8f16 bp0 = *(const v8f16*)&pt[((c * 4 + tw) * 32 + n) * 40 + 16 * g2];
-            const v8f16 bp1 = *(const v8f16*)&pt[((c * 4 + tw) * 32 + n) * 40 + 16 * g2 + 8];
-#pragma unroll
-            for (int kk = 0; kk < NKK; kk++) {
-              if (kk < nkk) {                                           // workgroup-uniform
-                U[kk] = mfma_f16(bp0, codes_f16(vc[tw][kk][0], vc[tw][kk][1]) * sv8[0], U[kk]);
-                U[kk] = mfma_f16(bp1, codes_f16(vc[tw][kk][2], vc[tw][kk][3]) * sv8[1], U[kk]);
-              }
+          for (int kk = 0; kk < NKK; kk++) {
+            if (kk < nkk) {                                           // workgroup-uniform
+              U[kk] = mfma_f16(bp0, codes_f16(vc[tw][kk][0], vc[tw][kk][1]) * sv8[0], U[kk]);
+              U[kk] = mfma_f16(bp1, codes_f16(vc[tw][kk][2], vc[tw][kk][3]) * sv8[1], U[kk]);
             }
           }
         }
@@ -744,26 +691,19 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   p.per = (chunks_cap + p.S - 1) / p.S;
   if (rank > 1024 && (p.per > kBigChunks || rank % 128 != 0 || rank > 4096)) return hipErrorNotSupported;
   p.c_scale = sm_scale * 1.4426950408889634f;
-  p.qt = (float*)workspace;
-  p.pm = p.qt + (size_t)batch * kSharedHeads * rank;
+  p.qt = (uint8_t*)workspace;                                           // 128 R bytes for each of the images
+  p.pm = (float*)workspace + (size_t)batch * kSharedHeads * rank;
   p.pl = p.pm + (size_t)batch * p.S * kSharedHeads;
   p.pu = p.pl + (size_t)batch * p.S * kSharedHeads;
-  p.qmax = p.pu + (size_t)batch * p.S * kSharedHeads * rank;
   p.out = (float*)out;
 
-  const dim3 grid_a((unsigned)(rank / 32), kSharedHeads);
   if (d_head != 64 && d_head != 128) return hipErrorNotSupported;
-  if (rank > 1024) {
-    if (d_head == 128) hipLaunchKernelGGL((k_shared_absorb<128>), grid_a, dim3(64), 0, s, p);
-    else hipLaunchKernelGGL((k_shared_absorb<64>), grid_a, dim3(64), 0, s, p);
-  } else {
-    const dim3 grid_l(kSharedHeads, 4, (unsigned)((batch + 31) / 32));
-    void (*fn)(SharedParams) =
-        rank == 256 ? (d_head == 128 ? k_shared_absorb_limbs<128, 256> : k_shared_absorb_limbs<64, 256>)
-        : rank == 512 ? (d_head == 128 ? k_shared_absorb_limbs<128, 512> : k_shared_absorb_limbs<64, 512>)
-                      : (d_head == 128 ? k_shared_absorb_limbs<128, 1024> : k_shared_absorb_limbs<64, 1024>);
-    hipLaunchKernelGGL(fn, grid_l, dim3((unsigned)rank / 2), 0, s, p);
-  }
+  const int waves_a = rank > 1024 ? 8 : rank / 128;
+  const dim3 grid_a(kSharedHeads, (unsigned)((rank / 32 + waves_a - 1) / waves_a), (unsigned)((batch + 31) / 32));
+  void (*fn_a)(SharedParams) = waves_a == 2   ? (d_head == 128 ? k_shared_absorb_limbs<128, 2> : k_shared_absorb_limbs<64, 2>)
+                               : waves_a == 4 ? (d_head == 128 ? k_shared_absorb_limbs<128, 4> : k_shared_absorb_limbs<64, 4>)
+                                              : (d_head == 128 ? k_shared_absorb_limbs<128, 8> : k_shared_absorb_limbs<64, 8>);
+  hipLaunchKernelGGL(fn_a, grid_a, dim3((unsigned)waves_a * 64), 0, s, p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
 
@@ -774,7 +714,6 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   void (*fn_out)(SharedParams) = t_out == 512 ? k_shared_out<512> : k_shared_out<256>;
   const dim3 grid_out(kSharedHeads, (unsigned)batch);
   if (rank > 1024) {
-    hipLaunchKernelGGL(k_shared_qmax, dim3(kSharedHeads, (unsigned)batch), dim3(64), 0, s, p);
     const size_t lds_big = (size_t)3 * (kBigSlab / 32) * 1024 + (size_t)(2 + kBigChunks) * 128 * sizeof(float) +
                            (size_t)kBigChunks * 4 * 32 * 40 * sizeof(_Float16);
     static bool raised_big = false;
@@ -783,7 +722,11 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
       if (e != hipSuccess) return e;
       raised_big = true;
     }
-    hipLaunchKernelGGL(k_shared_attn_big, dim3((unsigned)p.S, (unsigned)batch), dim3(256), lds_big, s, p);
+    // as many parts as fit the chip at once: 2 sequences of 1500 rows, rank 3712, 1 / 2 / 4 parts 56.6 / 45.3 / 39.2 us; 16 of
+    // 600 rows, rank 1920 (80 workgroups), 33.5 / 28.1; with more than 256 workgroups there are two rounds (parts of nothing
+    // there: 49)
+    p.parts = max(1, min(256 / (batch * p.S), (rank + kBigSlab - 1) / kBigSlab));
+    hipLaunchKernelGGL(k_shared_attn_big, dim3((unsigned)((batch * p.S + 7) / 8 * 8 * p.parts)), dim3(256), lds_big, s, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(fn_out, grid_out, dim3((unsigned)t_out), lds_out, s, p);

@@ -19,6 +19,7 @@ CASES = [
     (512, 64, 1280, [1280 - 100 * b for b in range(9)]),           # 2, one
     (512, 128, 640, [640 - 16 * b for b in range(40)]),            # 1, one
     (256, 128, 512, [129, 0, 512]),                                # 2, one
+    (3712, 128, 1280, [1280 - 97 * b for b in range(12)]),         # two workgroups for four slabs of value dims, one
     (256, 64, 1024, [1024 - 31 * b for b in range(33)]),           # 1, two
 ]
 
