@@ -5,6 +5,10 @@
 
 namespace {
 
+// The lane's number from the hardware, for what follows the products: threadIdx would hold a register through them (one lane
+// register of scratch in the 256 x 128 tiles).
+WSVD_DEV int lane_number() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
 // ---------------------------------------------------------------- cache build for a whole prompt (int8 latents)
 // C^T [channels x tokens] = A^T x^T on bf16 MFMA.  The channels of both planes form one axis of 2 * Hkv * r / 32 tiles
 // of 32; a wavefront owns CT channel tiles x TT token tiles (CT * TT accumulators of 32 x 32), so each 1 KiB operand it
@@ -59,7 +63,7 @@ WSVD_DEV ProjRow project_row(const ProjectParams& p, int pl, int seq, int kv, in
 template <int RT>
 WSVD_DEV void store_row_i8(const ProjectParams& p, const v16f (&a)[RT], int pl, int seq, int kv, int t, bool on) {
   constexpr int R = 32 * RT;
-  const int g2 = (threadIdx.x & 63) >> 5;
+  const int g2 = lane_number() >> 5;
   float m = 0.f;
 #pragma unroll
   for (int rt = 0; rt < RT; rt++)
@@ -97,7 +101,7 @@ WSVD_DEV void store_row_i8(const ProjectParams& p, const v16f (&a)[RT], int pl, 
 // registers), V bytes pair rows t, t ^ 1 = this lane and its neighbour (the caller guarantees an even start row, so row
 // parity = lane parity).  next_on: the neighbour's row is stored too.
 WSVD_DEV void store_row_i4(const ProjectParams& p, const v16f& a, int pl, int seq, int kv, int t, bool on, bool next_on) {
-  const int lane = threadIdx.x & 63, g2 = lane >> 5;
+  const int lane = lane_number(), g2 = lane >> 5;
   float lo = 0.f, hi = 0.f;
 #pragma unroll
   for (int v = 0; v < 16; v++) { lo = fminf(lo, a[v]); hi = fmaxf(hi, a[v]); }
@@ -152,7 +156,7 @@ WSVD_DEV void project_store_tile(const ProjectParams& p, const v16f (&acc)[CT][T
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
   const int ct = ct0 + h * RT;
   const int pl = ct / tiles_plane, kv = (ct % tiles_plane) / RT;        // (wave-uniform)
-  const int row = row0 + 32 * tt + (threadIdx.x & 31), sq = SPAN ? min(row, p.rows - 1) / p.n_tok : 0;
+  const int row = row0 + 32 * tt + (lane_number() & 31), sq = SPAN ? min(row, p.rows - 1) / p.n_tok : 0;
   const int tok = row - sq * p.n_tok, t = n0 + tok;                     // this lane's token of the prompt, its cache row
   const bool on = ct < tiles && row < p.rows && n0 >= 0 && t < p.t_cap;
   if constexpr (I4) {
@@ -465,7 +469,7 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
   }
   int n0[TT];                                                           // (asked for here: no registers during the products)
 #pragma unroll
-  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, (by * TT + tt) * 32 + n);
+  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, (by * TT + tt) * 32 + (lane_number() & 31));
   if constexpr (KS == 1) {
     if (ct0 >= tiles) return;
     project_store<R, CT, TT, I4, SPAN>(p, acc, ct0, by * 32 * TT, seq, n0);
@@ -473,7 +477,7 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
     // the groups' sums meet in LDS: unit u (the channels of a head x 32 rows) is added up in group order and stored by group
     // u % KS, from the pieces the other groups leave there
     constexpr int NU = CT / RT * TT;
-    float* const mine = (float*)proj_lds + lane;
+    float* const mine = (float*)proj_lds + lane_number();
     auto piece = [&](int u, int g) { return ((u * (KS - 1) + (g > u % KS ? g - 1 : g)) * WC + wc) * (RT * 1024); };
 #pragma unroll
     for (int u = 0; u < NU; u++) {
