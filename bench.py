@@ -1029,7 +1029,7 @@ def run_shared(args, np, torch, W, WI):
                    "batch": B, "context": T, "heads": H, "rank": R, "cache_sets": n_sets, "launch": "hip_graph",
                    "launches_per_step": 3},
         # the step's three launches are timed together here; the kernel-trace summary under profiles/ splits them
-        "roofline": {"kernel": "wsvd_decode_attn_shared (k_shared_absorb + k_shared_attn + k_shared_out)", "bound": "hbm",
+        "roofline": {"kernel": "wsvd_decode_attn_shared (k_shared_absorb_limbs + k_shared_attn + k_shared_out)", "bound": "hbm",
                      "achieved": round(cache_bytes / (us * 1e-6) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(cache_bytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4), "traffic": MEASURED_TRAFFIC_SHARED_STEP,
                      "algorithmic_bytes_per_launch": int(cache_bytes),
@@ -1396,7 +1396,7 @@ def run_sweep(args, np, torch, W, WI):
                              "GBps": round(ph_bytes / (ph[0] * 1e-6) / 1e9, 1)},
                 "shared_latent": {"us": round(sh[0], 3), "us_min_max": [round(sh[1], 3), round(sh[2], 3)], "cache_bytes": int(sh_bytes),
                                   "up_projection_factor_bytes": int(fac_sh), "GBps_cache_plus_factors": round((sh_bytes + fac_sh) / (sh[0] * 1e-6) / 1e9, 1),
-                                  "launches": 4 if Rs_pad > 1024 else 3,
+                                  "launches": 3,
                                   "int8_score_GOP": round(3 * 2.0 * B * T * Rs_pad * H / 1e9, 1)},
                 "shared_over_per_head_time": round(sh[0] / ph[0], 3),
                 "cost_model": {"flops_ratio_shared_over_per_head": H, "note": "Eq. 2: per head r/R of the whole-matrix scheme's "
@@ -1407,7 +1407,7 @@ def run_sweep(args, np, torch, W, WI):
                              "frac": round(ph_bytes / (ph[0] * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4), "traffic": None,
                              "algorithmic_bytes_per_launch": int(ph_bytes), "avg_launch_us": round(ph[0], 3),
                              "other_bytes_per_launch": {"up_projection_factors": int(fac_ph)}},
-                "roofline_shared": {"kernel": "wsvd_decode_attn_shared (absorb + [qmax] + attention + merge/output)", "bound": "hbm",
+                "roofline_shared": {"kernel": "wsvd_decode_attn_shared (absorb + attention + merge/output)", "bound": "hbm",
                                     "achieved": round((sh_bytes + fac_sh) / (sh[0] * 1e-6) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                                     "frac": round((sh_bytes + fac_sh) / (sh[0] * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4), "traffic": None,
                                     "algorithmic_bytes_per_launch": int(sh_bytes + fac_sh), "avg_launch_us": round(sh[0], 3)},
