@@ -854,7 +854,7 @@ wsvd_status wsvd_linear_w4a8_split(wsvd_ctx* ctx, const int8_t* x, const void* x
 // Fills the kernel parameters and decides the decomposition: grid = (Hkv, n_chunks, B), threads per workgroup.
 void wsvd_attn_plan(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* q, const void* q_scale, const void* B_K,
                     const void* B_V, const wsvd_cache& cache, int max_seq_len, void* out, AttnParams& p, dim3& grid,
-                    int& threads, int force_threads, int waves_per_cu) {
+                    int& threads, int force_threads, int chunks) {
   p = AttnParams{};
   p.q = q; p.q_scale = (const uint16_t*)q_scale; p.BK = B_K; p.BV = B_V;
   p.k_codes = (const uint8_t*)cache.k_codes; p.v_codes = (const uint8_t*)cache.v_codes;
@@ -881,7 +881,7 @@ void wsvd_attn_plan(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* q
   // "wg_per_cu" scales the target: 4 (default) = as many wavefronts as fit on the chip at once (the generic kernels
   // and the rank-32 matrix-core kernels hold 16 per CU, the rank-64 ones 8), so that the grid runs in a single round:
   // a second round pays the prologue, the split merge and the B_V epilogue again with the memory system idle
-  const int resident = waves_per_cu ? waves_per_cu : mfma ? wsvd_attn_mfma_waves_per_cu(d.latent_dtype, d.rank, p.G) : 16;
+  const int resident = mfma ? wsvd_attn_mfma_waves_per_cu(d.latent_dtype, d.rank, p.G) : 16;
   const int waves_target = ctx->n_cu * resident * ctx->opt.wg_per_cu / 4;
   int waves_per_unit = (waves_target + n_units - 1) / n_units;
   const int max_tiles = max_rows / 64;
@@ -895,6 +895,8 @@ void wsvd_attn_plan(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* q
   }
   int chunks_wanted = waves_per_unit / nw;
   if (chunks_wanted < 1) chunks_wanted = 1;
+  const bool given = chunks > 0 && ctx->opt.min_chunk == 0 && ctx->opt.wg_per_cu == wsvd_options{}.wg_per_cu;
+  if (given) chunks_wanted = chunks;      // the caller's choice, where no setting of the context asks for another
   int chunk_rows = ((max_rows + chunks_wanted - 1) / chunks_wanted + 63) / 64 * 64;
   const bool auto_chunk = ctx->opt.min_chunk == 0;          // no explicit setting: the policy below may also undo a split
   int min_chunk = ctx->opt.min_chunk < 256 ? 256 : ctx->opt.min_chunk;
@@ -909,13 +911,8 @@ void wsvd_attn_plan(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* q
   // (about 60 GB/s: 2.35 us for the 139 KB of a 2048-row rank-32 int8 unit).  With at most one unit per two compute units
   // and below about 300 KB per (sequence, kv head) no split pays: 1 to 4 sequences of 32 heads and 2048 rows take
   // 7.8-9.0 us as one chunk and 9.4-10.7 us as two; from 8 sequences on the two are level, at 12 the split wins by 0.7 us.
-  // The rotary variant (it gives waves_per_cu: 8, not the 16 of the plain kernel) is bound by its arithmetic, 4.6 us per 1000
-  // rows of a workgroup, and splits from 1024 rows on.  One chunk / split, us: 32 units of 1500 rows 15.3 / 12.4, 2048 rows
-  // 17.8 / 13.2, 4096 rows 26.8 / 14.0; 700 rows 10.5 / 14 (256 units of 2048 rows, planned for 16 waves per CU, took two
-  // rounds of workgroups: 31.8 us, now 21.5).
-  const bool no_split = waves_per_cu ? max_rows < 1024 :
-      n_units * 2 <= ctx->n_cu && (size_t)max_rows * 2 * (size_t)(row_bytes_host(d) + meta_bytes_host(d)) < (size_t)300 * 1024;
-  if (auto_chunk && mfma && p.n_chunks > 1 && no_split) {
+  const bool no_split = n_units * 2 <= ctx->n_cu && (size_t)max_rows * 2 * (size_t)(row_bytes_host(d) + meta_bytes_host(d)) < (size_t)300 * 1024;
+  if (auto_chunk && !given && mfma && p.n_chunks > 1 && no_split) {
     p.chunk_rows = (max_rows + 63) / 64 * 64;
     p.n_chunks = 1;
   }

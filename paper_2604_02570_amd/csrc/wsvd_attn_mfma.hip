@@ -1990,6 +1990,25 @@ static hipError_t launch_rope(const AttnParams& p, const RopeArgs& ra, dim3 grid
 
 // I8 latents (rank 32 / 64) or I4 latents (rank 32); per launch rank 32 with up to 4 query heads per kv head, rank 64 with up to 2 (the N^T operand images of all heads
 // of the group live in LDS).  hipErrorNotSupported otherwise.
+// Context chunks of the features form, whose workgroups have a CU to themselves: a round of them takes about 7.6 us (N build,
+// start values, merge of the waves, B_V) and 4.65 us per 1000 rows of a chunk (both measured at rank 32, one query head; more
+// heads or rank 64 raise both), a split 2.8 us for the hand-off.  The number that costs least over its rounds: as many as fit
+// the CUs beside each other, and more only where one workgroup too many would cost a long second round.  us, chosen / one more
+// per unit: 52 units of 4096 rows 15.8 / 23.3, 88 of 2048 15.4 / 21.1, 136 of 2048 17.7 / 27.4, 200 of 8192 46 / 63; three
+// chunks and one: 257 of 8192 86 / 90; 1024 rows are level (32 units: 11.7 as one, 11.8 as two).
+static int rope_chunks(int n_cu, int n_units, int max_seq_len) {
+  const int tiles = (max(max_seq_len, 1) + 63) / 64;
+  int best = 1;
+  long least = 0;
+  const int most = min(tiles / 8, 2 * n_cu / n_units + 2);              // a tile for every wave
+  for (int k = 1; k <= max(1, most); k++) {
+    const int chunk = (tiles + k - 1) / k, n = (tiles + chunk - 1) / chunk;
+    const long cost = ((long)n_units * n + n_cu - 1) / n_cu * (1600 + 64 * chunk) + (n > 1 ? 600 : 0);   // in rows
+    if (k == 1 || cost < least) { best = k; least = cost; }
+  }
+  return best;
+}
+
 hipError_t wsvd_launch_attn_rope(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* q, const void* q_scale,
                                  const void* B_K, const void* B_V, const wsvd_cache& cache, int max_seq_len, double rope_base,
                                  void* out, hipStream_t s) {
@@ -2004,11 +2023,16 @@ hipError_t wsvd_launch_attn_rope(const wsvd_ctx* ctx, const wsvd_layer_desc& d, 
   // The features kernel takes 8 waves per workgroup: the register budget allows no more, and the N build divides its work over
   // exactly that many threads (waves without a tile of their own idle through the loop).  The table kernel takes 4, and two of
   // its workgroups share a CU, so that one's table, prologue and end run beside the other's stream: it needs more (sequence, kv
-  // head) units than CUs (256 units, 2048 rows: 21.5 us with features, 25.3 with the table), and its lead over the N build and
-  // start values, which every unit pays for, is used up at about 4096 rows.  us, features / table: 512 units of 64 rows
-  // 15.0 / 11.1, 700 rows 22.2 / 20.8, 2048 rows 40.6 / 36.7, 4096 rows 66 / 66; 2048 units of 200 rows 57 / 40.
-  const bool table = d.rank == 32 && G == 1 && d.batch * d.n_kv_heads > ctx->n_cu && max_seq_len <= 4096;
-  wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p, grid, threads, table ? 256 : 512, 8);
+  // head) units than CUs (256 units, 2048 rows: 18.4 us with features, 25.3 with the table).  Its lead over the N build and start
+  // values, which every unit pays for, shrinks with the rows, whose cost is the higher one: it is used up at 4096 rows where
+  // the features kernel would run a second, nearly empty round, at 2048 to 2600 where it fills its rounds.  us, features /
+  // table: 512 units of 64 rows 14.8 / 11.1, 2048 rows 38.0 / 38.2, 3600 rows 55.9 / 58.7; 520 of 2048 rows 52.8 / 51.3, 4096
+  // rows 82.8 / 87.8; 257 of 2048 rows 34.7 / 30.7, 4096 rows 54.5 / 49.7; 384 of 4096 rows 54.5 / 54.4.  It is not split: 288
+  // units of 2048 rows 29.7 us as one chunk, 34.9 as two.
+  const int n_units = d.batch * d.n_kv_heads;
+  const bool table = d.rank == 32 && G == 1 && n_units > ctx->n_cu && max_seq_len <= (2 * n_units <= 3 * ctx->n_cu ? 4096 : 2048);
+  wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p, grid, threads, table ? 256 : 512,
+                 table ? 1 : rope_chunks(ctx->n_cu, n_units, max_seq_len));
   RopeArgs ra;
   const double two_pi = 6.283185307179586476925286766559;
   for (int i = 0; i < 64; i++) {

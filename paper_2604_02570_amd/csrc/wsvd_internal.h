@@ -59,7 +59,7 @@ hipError_t wsvd_launch_attn(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const
 // output columns [0, n_first) go to out (row-major [M, n_first]), the rest to out2 ([M, N - n_first])
 void wsvd_attn_plan(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* q, const void* q_scale, const void* B_K,
                     const void* B_V, const wsvd_cache& cache, int max_seq_len, void* out, AttnParams& p, dim3& grid, int& threads,
-                    int force_threads, int waves_per_cu = 0);
+                    int force_threads, int chunks = 0);
 void wsvd_append_params(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* x, const void* x_scale, const void* A_K,
                         const void* A_V, const wsvd_cache& cache, AppendParams& p);
 int wsvd_append_mfma_waves(const wsvd_ctx* ctx, const wsvd_layer_desc& d);
