@@ -221,7 +221,8 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
         a0 = mfma_i8(ka[ks], limbs[(0 * NKS + ks) * 64 + lane], a0);
         a1 = mfma_i8(ka[ks], limbs[(1 * NKS + ks) * 64 + lane], a1);
         a2 = mfma_i8(ka[ks], limbs[(2 * NKS + ks) * 64 + lane], a2);
-        if ((i & 3) == 3) __builtin_amdgcn_sched_barrier(0);            // keeps the limb reads from piling up in registers
+        // keeps the limb reads from piling up in registers (rank 1024 in one part fills all 512: four steps' reads spill)
+        if ((i & (NKK == 8 ? 1 : 3)) == (NKK == 8 ? 1 : 3)) __builtin_amdgcn_sched_barrier(0);
       }
       __builtin_amdgcn_sched_barrier(0);
       const int tv = min(cbase + 32 * tw, (n_b - 1) & ~31);             // (a block past the end: the last one again, unused)
@@ -649,14 +650,25 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8))) void k_s
 
 // Workgroups over which the value dims of the same tokens are divided (each computes the scores of all its tokens), up to
 // rank 1024.  Where (sequence, chunk) pairs are too few for the chip the parts fill it (1 sequence of 8191 rows, rank 1024:
-// 1 / 2 / 4 parts 23.7 / 17.5 / 15.6 us; 5 of 3000 rows, rank 512: 10.8 / 8.8 us).  At rank 1024 two parts also halve the
-// partial results, 33.6 MB at 16 sequences, for a second reading of the keys from the die's cache: the attention's time stays
-// at 22 us, the merge takes 10 instead of 13.  Otherwise one: 64 sequences of rank 256 19.3 us, with two 27.6; 31 of rank
-// 512 18.4 against 22.4.
+// 1 / 2 / 4 parts 23.7 / 17.5 / 15.6 us; 5 of 3000 rows, rank 512: 10.8 / 8.8 us).  With one to a few pairs per workgroup two
+// parts still pay where the partial results are large: they halve them, 33.6 MB at 16 sequences of 2048 rows and rank 1024, for
+// a second reading of the keys from the die's cache.  With more the second score pass costs more than that.  us per call, one
+// part / two: rank 1024, 16 x 2048 rows 42 / 40, 20 x 2048 50 / 47, 33 x 2048 64 / 71, 65 x 2048 103 / 125, 64 x 8192 213 / 297;
+// rank 512, 16 x 2048 29 / 26, 20 x 2048 29 / 31; rank 256, 9 x 2048 17.3 / 18.1.  Beyond 64 sequences two parts would leave
+// one or two splits to choose from: 129 of 300 rows, rank 1024, 103 / 120.
 int shared_value_parts(int batch, int chunks, int rank) {
-  const long pairs = (long)batch * (chunks < 32 ? chunks : 32);
-  if (rank >= 512 && 4 * pairs <= 256) return 4;
-  return 2 * pairs <= 256 || rank == 1024 ? 2 : 1;
+  const long pairs = (long)batch * chunks;
+  if (rank >= 512 && 4L * batch * (chunks < 32 ? chunks : 32) <= 256) return 4;
+  return batch <= 64 && pairs <= (rank == 256 ? 128 : rank == 512 ? 256 : 320) ? 2 : 1;
+}
+
+// Splits of a sequence then: as many as fit the CUs, one more would be a second round (65 x 2048 rows, rank 1024: three 103 us,
+// four 130).  At rank 256 two workgroups fit a CU, so that from 129 sequences on two splits are still one round (129 x 2048
+// rows: 80 -> 69 us).
+int shared_splits_run(int batch, int parts, int rank, int most) {
+  int s = 256 / (batch * parts);
+  if (rank == 256 && parts == 1 && s == 1 && batch < 256) s = 2;
+  return s < 1 ? 1 : s < most ? s : most;                               // never more than the workspace is sized for
 }
 
 int shared_splits(int batch, int t_cap, int rank) {
@@ -735,15 +747,15 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   const size_t lds_attn = (size_t)3 * (rank / 32) * 1024 + 3 * 128 * sizeof(float) +
                           4 * 32 * 40 * sizeof(_Float16) + 4 * 128 * sizeof(_Float16);
   const int vh = shared_value_parts(batch, chunks_cap, rank);
-  p.S = max(1, min(256 / (batch * vh), p.S));                           // never more than the workspace is sized for
+  p.S = shared_splits_run(batch, vh, rank, p.S);
   void (*fn)(SharedParams) = rank == 256   ? (vh == 2 ? k_shared_attn<256, 2> : k_shared_attn<256, 1>)
                              : rank == 512 ? (vh == 4 ? k_shared_attn<512, 4> : vh == 2 ? k_shared_attn<512, 2> : k_shared_attn<512, 1>)
-                                           : (vh == 4 ? k_shared_attn<1024, 4> : k_shared_attn<1024, 2>);
-  static bool raised[2] = {false, false};                               // the limit of dynamic LDS, raised once (109 KB)
-  if (rank == 1024 && !raised[vh >> 2]) {
+                                           : (vh == 4 ? k_shared_attn<1024, 4> : vh == 2 ? k_shared_attn<1024, 2> : k_shared_attn<1024, 1>);
+  static bool raised[3] = {false, false, false};                        // the limit of dynamic LDS, raised once (109 KB)
+  if (rank == 1024 && !raised[vh >> 1]) {
     e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_attn);
     if (e != hipSuccess) return e;
-    raised[vh >> 2] = true;
+    raised[vh >> 1] = true;
   }
   hipLaunchKernelGGL(fn, dim3((unsigned)((batch * p.S + 7) / 8 * 8 * vh)), dim3(256), lds_attn, s, p);
   e = hipGetLastError();

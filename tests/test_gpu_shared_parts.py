@@ -1,8 +1,9 @@
 """Shared-latent decode attention where its launches change shape: value dims over one, two and four workgroups, one and
 several chunks per split, sequence counts in and out of whole groups of eight, both merge workgroups, empty sequences
-among them.  The oracle computes a sample of (sequence, head) pairs."""
+among them.  The oracle computes a sample of (sequence, head) pairs.  And the plan of large batches by their times."""
 import numpy as np
 import pytest
+import torch
 
 import paper_2604_02570_amd as W
 from test_gpu_parity import check_out
@@ -21,6 +22,9 @@ CASES = [
     (256, 128, 512, [129, 0, 512]),                                # 2, one
     (3712, 128, 1280, [1280 - 97 * b for b in range(12)]),         # two workgroups for four slabs of value dims, one
     (256, 64, 1024, [1024 - 31 * b for b in range(33)]),           # 1, two
+    (1024, 128, 768, [768 - 11 * b for b in range(66)]),           # 1 (all registers), two
+    (1024, 64, 384, [384 - 2 * b for b in range(130)]),            # 1, up to three in one split
+    (256, 128, 512, [512 - 3 * b for b in range(130)]),            # 1, two workgroups to a CU
 ]
 
 
@@ -38,3 +42,41 @@ def test_shared_latent_launch_shapes(rank, d, t_cap, lens):
     rng = np.random.default_rng(rank + len(lens))
     pairs = [(b, int(rng.integers(0, H))) for b in sorted({0, len(lens) - 1, *(int(x) for x in rng.integers(0, len(lens), 6))}) if lens[b]]
     check_out(got, c.oracle(heads=pairs), "i8", f"shared latent rank {rank}, {len(lens)} sequences, {len(pairs)} sampled pairs")
+
+
+def _us(batch, rows, rank):
+    """us per call of `batch` sequences of `rows` rows (a graph of ten calls)."""
+    d, t_cap = 128, (rows + 127) // 128 * 128
+    ctx = W.wsvd_create(0)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    codes = [torch.randint(-127, 128, (batch, t_cap * rank), dtype=torch.int8, device="cuda", generator=g) for _ in range(2)]
+    scale = torch.full((batch, t_cap), 0.02, dtype=torch.float16, device="cuda")
+    q = torch.randn(batch, H, d, device="cuda", generator=g).to(torch.bfloat16)
+    B = [(torch.randn(H, rank, d, device="cuda", generator=g) * rank ** -0.5).to(torch.bfloat16) for _ in range(2)]
+    lens = torch.full((batch,), rows, dtype=torch.int32, device="cuda")
+    ws = torch.empty(W.wsvd_shared_workspace_bytes(batch, H, d, rank, t_cap), dtype=torch.uint8, device="cuda")
+    out = torch.zeros(batch, H, d, device="cuda")
+    stream = torch.cuda.Stream()
+    run = lambda: W.wsvd_decode_attn_shared(ctx, batch, H, d, rank, t_cap, 0.0, q, *B, *codes, scale, scale, lens, ws, out, stream)
+    torch.cuda.synchronize()
+    run()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        for _ in range(10):
+            run()
+    best = float("inf")
+    for _ in range(5):
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record(); graph.replay(); b.record(); torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 100)
+    assert W.wsvd_check(ctx) == 0
+    W.wsvd_destroy(ctx)
+    return best
+
+
+# one sequence more than a count that divides the CUs, and full batches against a quarter of them, which has the same plan but
+# for the splits: 1.19, 1.25 and 2.7 times (half as many workgroups as CUs, or the scores computed twice: 1.45, 1.43 and 3.8)
+@pytest.mark.parametrize("rank,rows,few,many,limit", [(1024, 2048, 64, 65, 1.33), (256, 2048, 128, 129, 1.35), (1024, 8192, 16, 64, 3.2)])
+def test_shared_latent_large_batches_keep_the_cus_busy(rank, rows, few, many, limit):
+    t_few, t_many = _us(few, rows, rank), _us(many, rows, rank)
+    assert t_many <= limit * t_few, (t_few, t_many)
