@@ -39,9 +39,9 @@ wsvd_status wsvd_timeline_set_buffer(wsvd_ctx *ctx, void *dev_ptr, size_t bytes)
  *   "linear_direct":  1 = the W4A8 linear layers read their operands straight from memory (no LDS staging)
  *   "prefill_tiled":  1 = wsvd_prefill_attn and wsvd_prefill_append take their tiled kernels also for small calls
  *   "project_shape":  tile of the prefill projection, ranks 32 and 64: 0 = automatic; hidden states through LDS, factors
- *                     straight from memory: 5 = 64 channels x 32 rows, 11 = 128 x 32, 12 = 128 x 64, 22 = 256 x 64,
- *                     25 = 256 x 128; 2 = 256 x 256, both operands through LDS; 44 = no LDS.  1 is accepted as 2, and 21,
- *                     24, 42 as 44 (variants that nothing chose any more)
+ *                     straight from memory: 5 = 64 channels x 32 rows, 11 = 128 x 32, 12 = 128 x 64, 13 = 256 x 32 (rank
+ *                     32: as 11), 22 = 256 x 64, 25 = 256 x 128; 2 = 256 x 256, both operands through LDS; 44 = no LDS.  1 is
+ *                     accepted as 2, and 21, 24, 42 as 44 (variants that nothing chose any more)
  *   "static_limit_kib": wsvd_decode_attn_static treats its static array as this many KiB (0 = its real size, 8192): lets
  *                     a test see the WSVD_E_WORKSPACE rejection with buffers that are valid for the call
  */

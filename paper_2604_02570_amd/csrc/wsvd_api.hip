@@ -218,7 +218,7 @@ wsvd_status wsvd_ctx_set_option(wsvd_ctx* ctx, const char* name, int value) {
   if (!strcmp(name, "timeline_kernel") && value >= 0 && value <= 1) { o.timeline_kernel = value; return WSVD_OK; }
   if (!strcmp(name, "step_slices") && value >= 0 && value <= 4) { o.step_slices = value; return WSVD_OK; }
   if (!strcmp(name, "project_shape"))
-    for (int v : {0, 1, 2, 5, 11, 12, 21, 22, 24, 25, 42, 44})
+    for (int v : {0, 1, 2, 5, 11, 12, 13, 21, 22, 24, 25, 42, 44})
       if (value == v) { o.project_shape = value; return WSVD_OK; }
   return WSVD_E_SHAPE;
 }

@@ -588,32 +588,40 @@ hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
   return p.rows == p.n_tok ? launch_project_lds_span<R, I4, false>(p, s) : launch_project_lds_span<R, I4, true>(p, s);
 }
 
-// The tile size.  256 workgroups (one per CU) run side by side; a round of them costs (chain + busy * load^2) * d_model / 4096
-// us, load being the share of the CUs that it keeps busy (1 but for the last round), and what does not depend on d_model (first requests, sums,
-// store) shows once in full and 0.4 times for every further round, because a CU has the next workgroup beside it.  The shape
-// that costs least.  Smaller tiles read the operands more often (see k_prefill_project_direct), larger ones leave CUs idle.
-// us per call with the copy of the lengths and their update (about 6 us of it), 32 kv heads of rank 32 / 64, d_model 4096:
-//                   1 x 200   16 x 32   1 x 400   3 x 333   4 x 500  16 x 130  2 x 2048  8 x 1024    64 x 4
-//    5:  64 x  32     16/23     25/42     24/40     41/77    71/147    78/156   141/288   267/553     17/24
-//   11: 128 x  32     20/22     22/36     20/34     35/63    62/119    73/134   119/229   230/456     20/23
-//   12: 128 x  64     25/30     27/31     26/31     31/49     53/89    71/106   101/168   192/342     26/31
-//   22: 256 x  64     42/41     41/43     42/42     43/47     47/78    72/111    84/149   158/304     44/42
-//   25: 256 x 128     54/55     53/59     56/55     57/56     57/69    65/122    74/135   141/267     56/57
-//    2: 256 x 256    103/103   102/109   105/104   107/105   106/106   104/121   114/134   135/261   110/109
-//   former kernels    19/35     27/40     25/35     45/70     53/83    75/115    92/144   141/278    59/106
-// (those: 11, of rank 64 in 256 x 32, 22 without the split, 2; tiles that ended with each sequence)
-struct ProjectShape { int code, ch, tok; float fixed[2], chain, busy; };              // fixed: rank 32, 64
+// The tile size.  256 workgroups (one per CU) run side by side.  A round of them costs chain * d_model / 4096 us for the
+// contraction; what grows with the work that a round holds, the store of the rows and what the memory system adds, counts full
+// rounds once and the last one by the square of the share of the CUs that it keeps busy, because a CU has the next workgroup
+// beside it; `fixed` (first requests, sums, last store) shows once.  The shape that costs least.  Smaller tiles read the operands
+// more often (see k_prefill_project_direct), larger ones leave CUs idle.  The constants are fitted to 840 sizes (1 to 40 heads of
+// rank 32 or 64, d_model 64 to 8192, 2 to 40000 tokens): the choice is 0.6 % slower than the best of the shapes on average, 0.2
+// from d_model 512 on.  us per call with the update of the lengths (about 6 us with the clearing before it), 32 kv heads of rank
+// 32 / 64, d_model 4096; the last column 28 x 385 tokens at d_model 192, where the store is most of the time:
+//                   1 x 200   16 x 32   1 x 400   3 x 333   4 x 500  16 x 130  2 x 2048  8 x 1024    64 x 4    28 x 385
+//    5:  64 x  32     16/23     25/42     24/40     41/77    71/147    78/156   141/288   267/553     17/24      79/189
+//   11: 128 x  32     20/22     22/36     20/34     35/63    62/119    73/134   119/229   230/456     20/23      48/133
+//   12: 128 x  64     25/30     27/31     26/31     31/49     53/89    71/106   101/168   192/342     26/31      64/84
+//   22: 256 x  64     42/41     41/43     42/42     43/47     47/78    72/111    84/149   158/304     44/42      46/69
+//   25: 256 x 128     54/55     53/59     56/55     57/56     57/69    65/122    74/135   141/267     56/57      47/79
+//    2: 256 x 256    103/103   102/109   105/104   107/105   106/106   104/121   114/134   135/261   110/109     40/66
+// 13, 256 x 32, is there for rank 64: it reads the hidden states half as often as 11 and is the best where the contraction is
+// short (30 x 46 tokens of 8 heads, d_model 192: 10.0 us, the others 10.9 and more).
+struct ProjectShape { int code, ch, tok; float fixed[2], store[2], chain, busy; };    // fixed, store: rank 32, 64
 constexpr ProjectShape kProjectShapes[] = {
-    {5, 64, 32, {2.f, 2.4f}, 6.3f, 0.8f},  {11, 128, 32, {2.f, 3.2f}, 10.5f, 2.5f}, {12, 128, 64, {3.6f, 2.5f}, 17.f, 5.f},
-    {22, 256, 64, {5.4f, 4.5f}, 30.f, 5.f}, {25, 256, 128, {6.f, 6.f}, 44.f, 18.f},  {2, 256, 256, {11.f, 11.f}, 89.f, 32.f}};
+    {5, 64, 32, {2.f, 2.6f}, {0.9f, 1.2f}, 7.5f, 0.3f},     {11, 128, 32, {1.7f, 3.1f}, {0.85f, 1.7f}, 11.2f, 1.5f},
+    {12, 128, 64, {3.1f, 3.4f}, {3.4f, 1.9f}, 17.5f, 1.7f}, {13, 256, 32, {-1.f, 2.5f}, {0.f, 1.9f}, 21.5f, 0.f},
+    {22, 256, 64, {4.5f, 3.6f}, {3.3f, 2.8f}, 31.4f, 0.f},  {25, 256, 128, {5.9f, 4.7f}, {8.2f, 7.9f}, 47.5f, 7.6f},
+    {2, 256, 256, {6.8f, 5.6f}, {12.7f, 11.1f}, 95.f, 11.5f}};
 int project_shape_rule(const ProjectParams& p, int n_seq, int R, bool i4) {
   int best = 0;
   float least = 0.f;
   for (const ProjectShape& k : kProjectShapes) {
+    const float fixed = k.fixed[R == 64], store = k.store[R == 64];
+    if (fixed < 0.f) continue;                                          // not there at this rank
     ProjectParams g = p;
     project_grid(g, n_seq, k.ch, k.tok, R, i4);
     const float wgs = (float)g.n_cg * (float)g.n_tg, rounds = ceilf(wgs / 256.f), load = wgs / 256.f - (rounds - 1.f);
-    const float cost = k.fixed[R == 64] * (0.6f + 0.4f * rounds) + (rounds * k.chain + (rounds - 1.f + load * load) * k.busy) * (float)p.E / 4096.f;
+    const float held = rounds - 1.f + load * load;
+    const float cost = fixed + store * held + (rounds * k.chain + held * k.busy) * (float)p.E / 4096.f;
     if (!best || cost < least) { best = k.code; least = cost; }
   }
   return best;
@@ -644,7 +652,8 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   const bool tiles_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
   int shape = ctx->opt.project_shape;
   if (!shape) shape = project_shape_rule(p, n_seq, d.rank, i4);
-  const bool direct = shape == 5 || shape == 11 || shape == 12 || shape == 22 || shape == 25;
+  if (shape == 13 && d.rank == 32) shape = 11;
+  const bool direct = shape == 5 || shape == 11 || shape == 12 || shape == 13 || shape == 22 || shape == 25;
   if (!tiles_ok || !direct) shape = tiles_ok && shape <= 2 ? 2 : 44;
   hipError_t e = hipSuccess;
   if (d.rank > 64) {
@@ -664,6 +673,8 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
     if (i4) e = launch_project_direct<32, 1, 2, 4, 2, 4, true>(p, n_seq, s);
     else if (d.rank == 32) e = launch_project_direct<32, 1, 2, 4, 2, 4>(p, n_seq, s);
     else e = launch_project_direct<64, 2, 2, 2, 2, 2>(p, n_seq, s);
+  } else if (shape == 13) {
+    e = launch_project_direct<64, 2, 1, 4, 1, 4>(p, n_seq, s);
   } else if (shape == 22) {
     if (i4) e = launch_project_direct<32, 2, 2, 4, 1, 4, true>(p, n_seq, s);
     else if (d.rank == 32) e = launch_project_direct<32, 2, 2, 4, 1, 4>(p, n_seq, s);

@@ -69,7 +69,7 @@ def test_prompt_projection_chunk_tails(name, over, shape, n, d_model):
 # a tile, a tile's edge inside one; the contraction split over the wave groups of a workgroup: fewer chunks than groups, a last
 # round that not every group has
 @pytest.mark.parametrize("d_model", [64, 192, 448])
-@pytest.mark.parametrize("shape,n", [(5, 9), (5, 34), (11, 22), (12, 21), (12, 66), (22, 22), (25, 43), (25, 130), (2, 90)])
+@pytest.mark.parametrize("shape,n", [(5, 9), (5, 34), (11, 22), (12, 21), (12, 66), (13, 22), (13, 34), (22, 22), (25, 43), (25, 130), (2, 90)])
 @pytest.mark.parametrize("name,over", [("c3_small", dict()), ("c3_small", dict(rank=64)), ("c4_small", dict(ragged=(60, 120)))], ids=["i8", "i8-r64", "i4"])
 def test_prompt_projection_tiles_across_sequences(name, over, shape, n, d_model):
     _prompt(name, shape, n, **{**dict(batch=4, context=120, d_model=d_model), **over})
@@ -99,11 +99,25 @@ def test_prompt_projection_full_sequence_inside_a_tile(shape):
 
 
 @pytest.mark.parametrize("rank", [32, 64])
-@pytest.mark.parametrize("batch,n", [(64, 4), (64, 32), (16, 64), (16, 260), (1, 300), (8, 1024)])
+@pytest.mark.parametrize("batch,n", [(64, 4), (64, 32), (16, 64), (16, 260), (1, 300), (8, 1024), (3, 333), (2, 2048), (1, 200)])
 def test_prompt_projection_takes_a_fitting_tile(batch, n, rank):
     """Many short prompts, prompts just past a multiple of 256 tokens, one prompt, full batches: the tile that is taken by
     itself is about as fast as the best one asked for (a tile that does not fit the prompts costs a factor of 2 to 4)."""
-    E, Hkv, t_cap = 4096, 32, (n + 63) // 64 * 64
+    t = _tile_times(batch, n, rank, 4096)
+    assert t[0] <= 1.35 * min(t.values()), t
+
+
+@pytest.mark.parametrize("batch,n,rank,E", [(28, 385, 64, 192), (22, 241, 32, 320), (17, 286, 64, 64), (40, 220, 64, 320), (11, 659, 64, 512)])
+def test_prompt_projection_takes_a_fitting_tile_for_a_short_contraction(batch, n, rank, E):
+    """Many tokens and a small d_model: the store of the rows is a large part of the time (counted as a part of the work, the
+    choice is within a tenth of the best; counted once per call it takes tiles that are 1.3 to 1.4 times slower)."""
+    t = _tile_times(batch, n, rank, E)
+    assert t[0] <= 1.2 * min(t.values()), t
+
+
+def _tile_times(batch, n, rank, E):
+    """us per call of 32 kv heads for every tile that can be asked for, and (0) for the one that is taken by itself."""
+    Hkv, t_cap = 32, (n + 63) // 64 * 64
     desc = W.layer_desc(batch, Hkv, Hkv, 128, E, rank, t_cap, "i8", "bf16", "bf16", "bf16", "f32", 0.0)
     ctx = W.wsvd_create(0)
     cb, mb = W.wsvd_cache_bytes(desc)
@@ -126,10 +140,10 @@ def test_prompt_projection_takes_a_fitting_tile(batch, n, rank):
             best = min(best, a.elapsed_time(b) * 100)
         return best
 
-    t = {shape: us(shape) for shape in (11, 22, 2, 0)}
+    t = {shape: us(shape) for shape in (5, 11, 12, 13, 22, 25, 2, 0)}
     assert W.wsvd_check(ctx) == 0
-    assert t[0] <= 1.35 * min(t.values()), t
     W.wsvd_destroy(ctx)
+    return t
 
 
 # query rows per kv head at the edges of the 32-row waves and of the 1 / 2 / 4 waves that share a workgroup's cache blocks;
