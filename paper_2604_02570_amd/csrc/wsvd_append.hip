@@ -388,12 +388,9 @@ static hipError_t launch_append_split(const AppendParams& p, const wsvd_layer_de
   size_t lds = (size_t)sb * stride * 2;
   const size_t red_bytes = (size_t)nw * sb * (R + 1) * 4;
   if (red_bytes > lds) lds = red_bytes;
-  static bool raised = false;                             // one attribute per instantiation (the template makes it so)
-  if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_append_split<R, NT, DEFER>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-    if (e != hipSuccess) return e;
-    raised = true;
-  }
+  static LdsLimit limit;                                  // one per instantiation (the template makes it so)
+  hipError_t e = wsvd_raise_lds(limit, (const void*)k_append_split<R, NT, DEFER>, 150 * 1024);
+  if (e != hipSuccess) return e;
   dim3 grid((unsigned)(2 * d.n_kv_heads * (np + 1)), (unsigned)groups);
   hipLaunchKernelGGL((k_append_split<R, NT, DEFER>), grid, dim3(NT), lds, s, p, sb, stride, np, ll);
   return hipGetLastError();
@@ -414,12 +411,9 @@ static hipError_t launch_append_project(const AppendParams& p, const wsvd_layer_
   const size_t red_bytes = (size_t)nw * sb * (R + 1) * 4;
   if (red_bytes > lds) lds = red_bytes;
   if (lds > (size_t)150 * 1024) return hipErrorInvalidValue;
-  static bool raised = false;
-  if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_append_split<R, NT, kDeferSlices>, hipFuncAttributeMaxDynamicSharedMemorySize, 150 * 1024);
-    if (e != hipSuccess) return e;
-    raised = true;
-  }
+  static LdsLimit limit;
+  hipError_t e = wsvd_raise_lds(limit, (const void*)k_append_split<R, NT, kDeferSlices>, 150 * 1024);
+  if (e != hipSuccess) return e;
   dim3 grid((unsigned)(2 * d.n_kv_heads * ns), (unsigned)groups);
   hipLaunchKernelGGL((k_append_split<R, NT, kDeferSlices>), grid, dim3(NT), lds, s, p, sb, stride, ns, (unsigned long long*)nullptr);
   return hipGetLastError();

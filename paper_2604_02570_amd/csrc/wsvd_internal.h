@@ -4,6 +4,7 @@
 #include <stdint.h>
 
 #include "../../include/wsvd.h"
+#include "wsvd_lds_limit.h"
 
 // Per-context tuning and test settings (wsvd_ctx_set_option); defaults = automatic.
 struct wsvd_options {
@@ -37,6 +38,13 @@ struct wsvd_ctx {
 
 struct AttnParams;
 struct AppendParams;
+
+inline hipError_t wsvd_raise_lds(LdsLimit& limit, const void* kernel, int bytes) {
+  int device = 0;
+  hipError_t e = hipGetDevice(&device);
+  if (e != hipSuccess) return e;
+  return limit(device, [&] { return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
 
 hipError_t wsvd_launch_quantize_rows(int latent_dtype, int rank, const float* c, int64_t n_rows, void* codes, void* meta,
                                      hipStream_t s);

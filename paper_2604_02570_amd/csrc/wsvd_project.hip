@@ -548,11 +548,10 @@ template <int R, int CT, int TT, int WC, int KS, int DEPTH, bool I4, bool SPAN>
 hipError_t launch_project_direct_span(const ProjectParams& p, hipStream_t s) {
   constexpr int RT = R / 32, STAGES = KS * 2 * 32 * TT * kProjXRow, PIECES = CT / RT * TT * (KS - 1) * WC * RT * 4096;
   constexpr int LDS = STAGES > PIECES ? STAGES : PIECES;
-  static bool raised = false;             // (as in launch_project_lds_span)
-  if (LDS > 65536 && !raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_direct<R, CT, TT, WC, KS, DEPTH, I4, SPAN>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if constexpr (LDS > 65536) {
+    static LdsLimit limit;
+    hipError_t e = wsvd_raise_lds(limit, (const void*)k_prefill_project_direct<R, CT, TT, WC, KS, DEPTH, I4, SPAN>, LDS);
     if (e != hipSuccess) return e;
-    raised = true;
   }
   hipLaunchKernelGGL((k_prefill_project_direct<R, CT, TT, WC, KS, DEPTH, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(64 * WC * KS), LDS, s, p);
   return hipGetLastError();
@@ -572,13 +571,10 @@ hipError_t launch_project_direct(ProjectParams p, int n_seq, hipStream_t s) {
 
 template <int R, bool I4, bool SPAN>
 hipError_t launch_project_lds_span(const ProjectParams& p, hipStream_t s) {
-  static bool raised = false;             // the kernel's limit of dynamic LDS, raised once per instantiation
+  static LdsLimit limit;
   const size_t lds = 2 * (size_t)kProjStage;
-  if (!raised) {
-    hipError_t e = hipFuncSetAttribute((const void*)k_prefill_project_lds<R, I4, SPAN>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    raised = true;
-  }
+  hipError_t e = wsvd_raise_lds(limit, (const void*)k_prefill_project_lds<R, I4, SPAN>, (int)lds);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL((k_prefill_project_lds<R, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(512), lds, s, p);
   return hipGetLastError();
 }

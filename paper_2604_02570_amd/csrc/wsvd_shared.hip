@@ -728,12 +728,9 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   if (rank > 1024) {
     const size_t lds_big = (size_t)3 * (kBigSlab / 32) * 1024 + (size_t)(2 + kBigChunks) * 128 * sizeof(float) +
                            (size_t)kBigChunks * 4 * 32 * 40 * sizeof(_Float16);
-    static bool raised_big = false;
-    if (!raised_big) {
-      e = hipFuncSetAttribute((const void*)k_shared_attn_big, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_big);
-      if (e != hipSuccess) return e;
-      raised_big = true;
-    }
+    static LdsLimit limit_big;
+    e = wsvd_raise_lds(limit_big, (const void*)k_shared_attn_big, (int)lds_big);
+    if (e != hipSuccess) return e;
     // as many parts as fit the chip at once: 2 sequences of 1500 rows, rank 3712, 1 / 2 / 4 parts 56.6 / 45.3 / 39.2 us; 16 of
     // 600 rows, rank 1920 (80 workgroups), 33.5 / 28.1; with more than 256 workgroups there are two rounds (parts of nothing
     // there: 49)
@@ -751,11 +748,10 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   void (*fn)(SharedParams) = rank == 256   ? (vh == 2 ? k_shared_attn<256, 2> : k_shared_attn<256, 1>)
                              : rank == 512 ? (vh == 4 ? k_shared_attn<512, 4> : vh == 2 ? k_shared_attn<512, 2> : k_shared_attn<512, 1>)
                                            : (vh == 4 ? k_shared_attn<1024, 4> : vh == 2 ? k_shared_attn<1024, 2> : k_shared_attn<1024, 1>);
-  static bool raised[3] = {false, false, false};                        // the limit of dynamic LDS, raised once (109 KB)
-  if (rank == 1024 && !raised[vh >> 1]) {
-    e = hipFuncSetAttribute((const void*)fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_attn);
+  static LdsLimit limit[3];                                             // of the three kernels of rank 1024 (109 KB)
+  if (rank == 1024) {
+    e = wsvd_raise_lds(limit[vh >> 1], (const void*)fn, (int)lds_attn);
     if (e != hipSuccess) return e;
-    raised[vh >> 1] = true;
   }
   hipLaunchKernelGGL(fn, dim3((unsigned)((batch * p.S + 7) / 8 * 8 * vh)), dim3(256), lds_attn, s, p);
   e = hipGetLastError();
