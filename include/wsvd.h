@@ -373,9 +373,8 @@ wsvd_status wsvd_prefill_attn(wsvd_ctx *ctx, const wsvd_layer_desc *desc, const 
  *     K_h = C_K B_Kh,  V_h = C_V B_Vh,  o_h = softmax(sm_scale * q_h K_h^T) V_h       (sm_scale <= 0: 1 / sqrt(d_head)).
  * The kernels absorb B_Kh into the query and B_Vh into the output, and run all heads as the columns of one product over
  * the shared latent, which is therefore streamed once per step (not once per head).
- *   n_heads = 32; d_head 64 or 128; rank 256, 512 or 1024, or a multiple of 128 up to 4096 (these with t_cap <= 16384:
- *   one more small launch, the latent walked in slabs of 1024 dims); t_cap a multiple of 128 (WSVD_E_UNSUPPORTED /
- *   WSVD_E_SHAPE).
+ *   n_heads = 32; d_head 64 or 128; rank 256, 512 or 1024, or a multiple of 128 up to 4096 (these with t_cap <= 16384, the
+ *   latent walked in slabs of 1024 dims); t_cap a multiple of 128 (WSVD_E_UNSUPPORTED / WSVD_E_SHAPE).
  *   q [B, H, d] BF16, B_K and B_V [H, R, d] BF16, out [B, H, d] F32 (all DEVICE, 16-byte aligned).
  *   k_codes, v_codes: int8 latents, one plane of t_cap * R bytes per sequence, in 32-token blocks of 32 * R bytes.  Byte
  *   of (token t, dim j): K plane  (t / 32) * 32 R + (((j / 32) * 2 + (j % 32) / 16) * 32 + t % 32) * 16 + j % 16,

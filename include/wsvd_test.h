@@ -59,6 +59,12 @@ wsvd_status wsvd_test_step_attention(wsvd_ctx *ctx, const wsvd_layer_desc *desc,
                                      void *hip_stream);
 
 /*
+ * Measurement aid: how wsvd_decode_attn_shared divides its work at these sizes: context splits per sequence (each leaves a
+ * partial result of 32 rows of `rank` floats) and workgroups over which the value dims of the same tokens are divided.
+ */
+wsvd_status wsvd_test_shared_plan(int32_t batch, int32_t rank, int32_t t_cap, int32_t *splits, int32_t *parts);
+
+/*
  * Measurement aid, not part of the method: a kernel that only READS `bytes` bytes (DEVICE pointer, 16-byte
  * aligned) with `workgroups` workgroups of 512 threads, each streaming one contiguous share.  Benchmarks run it
  * over the buffers the attention streams to report what a pure reader reaches on the same data.

@@ -27,7 +27,7 @@ EXPORTS = ["wsvd_create", "wsvd_destroy", "wsvd_cache_bytes", "wsvd_workspace_by
            "wsvd_ctx_set_option", "wsvd_latent_append", "wsvd_latent_store", "wsvd_decode_attn", "wsvd_decode_attn_store", "wsvd_decode_attn_static",
            "wsvd_paged_cache_bytes", "wsvd_latent_append_paged", "wsvd_prefill_append_paged", "wsvd_prefill_attn_paged", "wsvd_decode_attn_paged", "wsvd_decode_attn_rope", "wsvd_decode_step", "wsvd_check", "wsvd_status_str",
            "wsvd_factor_a_bytes", "wsvd_pack_factor_a", "wsvd_quantize_rows", "wsvd_cache_import", "wsvd_cache_export", "wsvd_quantize_act_i8", "wsvd_linear_w4a8",
-           "wsvd_linear_w4a8_split", "wsvd_probe_stream_read", "wsvd_test_step_attention", "wsvd_fold_qk", "wsvd_fold_vo", "wsvd_decode_attn_latent",
+           "wsvd_linear_w4a8_split", "wsvd_probe_stream_read", "wsvd_test_step_attention", "wsvd_test_shared_plan", "wsvd_fold_qk", "wsvd_fold_vo", "wsvd_decode_attn_latent",
            "wsvd_rmsnorm_quant_i8", "wsvd_swiglu_quant_i8", "wsvd_prefill_append",
            "wsvd_prefill_attn", "wsvd_shared_workspace_bytes", "wsvd_decode_attn_shared", "wsvd_timeline_set_buffer"]
 
@@ -130,6 +130,7 @@ def lib():
                                           POINTER(Cache), c_void_p]
         L.wsvd_prefill_attn.argtypes = [c_void_p, POINTER(LayerDesc), c_void_p, c_int32, c_int32, c_void_p, c_void_p, POINTER(Cache),
                                         c_int32, c_void_p, c_void_p]
+        L.wsvd_test_shared_plan.argtypes = [c_int32, c_int32, c_int32, POINTER(c_int32), POINTER(c_int32)]
         L.wsvd_shared_workspace_bytes.argtypes = [c_int32, c_int32, c_int32, c_int32, c_int32, POINTER(c_size_t)]
         L.wsvd_decode_attn_shared.argtypes = [c_void_p, c_int32, c_int32, c_int32, c_int32, c_int32, c_float] + [c_void_p] * 9 + \
                                              [c_size_t, c_void_p, c_void_p]
@@ -341,6 +342,12 @@ def wsvd_prefill_append(ctx, desc, x, x_scale, n_tokens, seq_index, A_K, A_V, ca
 def wsvd_prefill_attn(ctx, desc, q, n_q, n_after, B_K, B_V, cache, max_seq_len, out, stream=None):
     _ck(lib().wsvd_prefill_attn(ctx, byref(desc), _ptr(q), int(n_q), int(n_after), _ptr(B_K), _ptr(B_V), byref(cache),
                                 int(max_seq_len), _ptr(out), _stream(stream)), "wsvd_prefill_attn")
+
+
+def wsvd_test_shared_plan(batch, rank, t_cap):
+    s, p = c_int32(), c_int32()
+    _ck(lib().wsvd_test_shared_plan(int(batch), int(rank), int(t_cap), byref(s), byref(p)), "wsvd_test_shared_plan")
+    return s.value, p.value
 
 
 def wsvd_shared_workspace_bytes(batch, n_heads, d_head, rank, t_cap):

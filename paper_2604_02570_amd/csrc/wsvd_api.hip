@@ -328,6 +328,14 @@ wsvd_status wsvd_shared_workspace_bytes(int32_t batch, int32_t n_heads, int32_t 
   return WSVD_OK;
 }
 
+wsvd_status wsvd_test_shared_plan(int32_t batch, int32_t rank, int32_t t_cap, int32_t* splits, int32_t* parts) {
+  if (!splits || !parts) return WSVD_E_NULL;
+  wsvd_status st = check_shared(batch, 32, 128, rank, t_cap);
+  if (st != WSVD_OK) return st;
+  wsvd_shared_plan(batch, rank, t_cap, splits, parts);
+  return WSVD_OK;
+}
+
 wsvd_status wsvd_decode_attn_shared(wsvd_ctx* ctx, int32_t batch, int32_t n_heads, int32_t d_head, int32_t rank, int32_t t_cap,
                                     float sm_scale, const void* q, const void* B_K, const void* B_V, const void* k_codes,
                                     const void* v_codes, const void* k_scale, const void* v_scale, const int32_t* seq_lens,

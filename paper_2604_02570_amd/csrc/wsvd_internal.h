@@ -89,6 +89,7 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
 // decode attention over one shared rank-R latent (32 heads, rank 256 / 512 / 1024, int8 codes, bf16 q and factors):
 // three launches (query absorption, attention with split partials, merge + output projection)
 size_t wsvd_shared_ws_bytes(int batch, int rank, int t_cap);
+void wsvd_shared_plan(int batch, int rank, int t_cap, int* splits, int* parts);
 hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, float sm_scale, const void* q, const void* B_K,
                                    const void* B_V, const void* k_codes, const void* v_codes, const void* k_scale,
                                    const void* v_scale, const int* seq_lens, void* workspace, void* out, hipStream_t s);

@@ -48,8 +48,8 @@ struct SharedParams {
   float* pu;                  //            partial U              [B, S, H, R]
   float* out;                 // fp32 [B, H, d]
   int B, d, R, t_cap, S;
-  int per;                    // ranks above 1024: chunks of 128 tokens per split (at most 4),
-  int parts;                  //                   workgroups the slabs of the value dims are divided over
+  int parts;                  // workgroups the value dims of the same tokens are divided over
+  int per;                    // ranks above 1024: chunks of 128 tokens per split (at most 4)
   float c_scale;              // sm_scale * log2(e)
 };
 
@@ -129,9 +129,9 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
   constexpr int NKK = R / VH / 128;       // 32-dim sub-blocks of the value dims one wave owns
   extern __shared__ __align__(16) uint8_t sh_lds[];
   v4i* limbs = (v4i*)sh_lds;                                            // [3][NKS][64]
-  float* hmax = (float*)(sh_lds + 3 * NKS * 1024);                      // [4][32] each
-  float* cmax = hmax + 128;
-  float* csum = cmax + 128;
+  float* resc = (float*)(sh_lds + 3 * NKS * 1024);                      // [4][32] each: a head's rescaling of U,
+  float* cmax = resc + 128;                                             // its maximum
+  float* csum = cmax + 128;                                             // and its sum over a wave's tokens
   _Float16* pt = (_Float16*)(csum + 128);                               // [4][32][40]
   uint32_t* vsl = (uint32_t*)(pt + 4 * 32 * 40);                        // [4][64] pairs of fp16
 
@@ -260,7 +260,7 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
       psum += pw[v];
     }
     psum += __shfl_xor(psum, 32);
-    if (g2 == 0) { csum[wave * 32 + n] = psum; hmax[wave * 32 + n] = alpha; }   // (the query's maxima are no longer read)
+    if (g2 == 0) { csum[wave * 32 + n] = psum; resc[wave * 32 + n] = alpha; }
     {                                     // rows never written may hold any scale: they contribute 0
       const int tl = cbase + 2 * lane;
       vsl[wave * 64 + lane] = tl + 1 < n_b ? vsr : tl < n_b ? vsr & 0xFFFFu : 0u;
@@ -282,7 +282,7 @@ __global__ __launch_bounds__(256) void k_shared_attn(SharedParams p) {
     if (rescale) {
 #pragma unroll
       for (int m4 = 0; m4 < 4; m4++) {
-        const v4f al = *(const v4f*)&hmax[wave * 32 + 8 * m4 + 4 * g2];
+        const v4f al = *(const v4f*)&resc[wave * 32 + 8 * m4 + 4 * g2];
 #pragma unroll
         for (int kk = 0; kk < NKK; kk++)
 #pragma unroll
@@ -683,10 +683,23 @@ int shared_splits(int batch, int t_cap, int rank) {
 
 }  // namespace
 
+// The launch's plan.  (The workspace is sized for shared_splits, which no plan exceeds.)  Above rank 1024 as many parts as fit the
+// chip at once: 2 sequences of 1500 rows, rank 3712, 1 / 2 / 4 parts 56.6 / 45.3 / 39.2 us; 16 of 600 rows, rank 1920 (80
+// workgroups), 33.5 / 28.1; with more than 256 workgroups there are two rounds (parts of nothing there: 49).
+void wsvd_shared_plan(int batch, int rank, int t_cap, int* splits, int* parts) {
+  const int most = shared_splits(batch, t_cap, rank), chunks = (t_cap + kSharedChunk - 1) / kSharedChunk;
+  if (rank > 1024) {
+    *splits = most;
+    *parts = max(1, min(256 / (batch * most), (rank + kBigSlab - 1) / kBigSlab));
+  } else {
+    *parts = shared_value_parts(batch, chunks, rank);
+    *splits = shared_splits_run(batch, *parts, rank, most);
+  }
+}
+
 size_t wsvd_shared_ws_bytes(int batch, int rank, int t_cap) {
   const size_t S = (size_t)shared_splits(batch, t_cap, rank);
-  const size_t floats = (size_t)batch * kSharedHeads * rank + 2 * (size_t)batch * S * kSharedHeads + (size_t)batch * S * kSharedHeads * rank +
-                        (size_t)batch * kSharedHeads;
+  const size_t floats = (size_t)batch * kSharedHeads * rank + 2 * (size_t)batch * S * kSharedHeads + (size_t)batch * S * kSharedHeads * rank;
   return floats * sizeof(float);
 }
 
@@ -698,7 +711,8 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   p.k_codes = (const uint8_t*)k_codes; p.v_codes = (const uint8_t*)v_codes;
   p.k_scale = (const uint16_t*)k_scale; p.v_scale = (const uint16_t*)v_scale;
   p.seq_lens = seq_lens;
-  p.B = batch; p.d = d_head; p.R = rank; p.t_cap = t_cap; p.S = shared_splits(batch, t_cap, rank);
+  p.B = batch; p.d = d_head; p.R = rank; p.t_cap = t_cap;
+  wsvd_shared_plan(batch, rank, t_cap, &p.S, &p.parts);
   const int chunks_cap = (t_cap + kSharedChunk - 1) / kSharedChunk;
   p.per = (chunks_cap + p.S - 1) / p.S;
   if (rank > 1024 && (p.per > kBigChunks || rank % 128 != 0 || rank > 4096)) return hipErrorNotSupported;
@@ -731,10 +745,6 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
     static LdsLimit limit_big;
     e = wsvd_raise_lds(limit_big, (const void*)k_shared_attn_big, (int)lds_big);
     if (e != hipSuccess) return e;
-    // as many parts as fit the chip at once: 2 sequences of 1500 rows, rank 3712, 1 / 2 / 4 parts 56.6 / 45.3 / 39.2 us; 16 of
-    // 600 rows, rank 1920 (80 workgroups), 33.5 / 28.1; with more than 256 workgroups there are two rounds (parts of nothing
-    // there: 49)
-    p.parts = max(1, min(256 / (batch * p.S), (rank + kBigSlab - 1) / kBigSlab));
     hipLaunchKernelGGL(k_shared_attn_big, dim3((unsigned)((batch * p.S + 7) / 8 * 8 * p.parts)), dim3(256), lds_big, s, p);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -743,8 +753,7 @@ hipError_t wsvd_launch_attn_shared(int batch, int d_head, int rank, int t_cap, f
   }
   const size_t lds_attn = (size_t)3 * (rank / 32) * 1024 + 3 * 128 * sizeof(float) +
                           4 * 32 * 40 * sizeof(_Float16) + 4 * 128 * sizeof(_Float16);
-  const int vh = shared_value_parts(batch, chunks_cap, rank);
-  p.S = shared_splits_run(batch, vh, rank, p.S);
+  const int vh = p.parts;
   void (*fn)(SharedParams) = rank == 256   ? (vh == 2 ? k_shared_attn<256, 2> : k_shared_attn<256, 1>)
                              : rank == 512 ? (vh == 4 ? k_shared_attn<512, 4> : vh == 2 ? k_shared_attn<512, 2> : k_shared_attn<512, 1>)
                                            : (vh == 4 ? k_shared_attn<1024, 4> : vh == 2 ? k_shared_attn<1024, 2> : k_shared_attn<1024, 1>);

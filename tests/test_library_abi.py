@@ -67,6 +67,24 @@ def test_host_only_validation_and_sizes():
     assert e.value.status == W.E_NULL
 
 
+def test_shared_latent_plan_fits_its_workspace():
+    """For every batch the workspace holds the query images and the partial results of the splits that are launched, no
+    workgroup above rank 1024 gets more than four chunks of 128 tokens, and up to there a round of workgroups is not exceeded
+    (two to a CU at rank 256)."""
+    for rank in (256, 512, 1024, 1152, 2560, 4096):
+        for t_cap in (128, 512, 2048, 8192, 16384):
+            for batch in (*range(1, 70), 85, 86, 127, 128, 129, 200, 255, 256, 257, 600):
+                splits, parts = W.wsvd_test_shared_plan(batch, rank, t_cap)
+                chunks = t_cap // 128
+                need = 4 * batch * 32 * (rank + splits * (rank + 2))
+                assert need <= W.wsvd_shared_workspace_bytes(batch, 32, 128, rank, t_cap), (rank, t_cap, batch)
+                assert 1 <= splits <= min(32, chunks) and parts in ((1, 2, 3, 4) if rank > 1024 else (1, 2, 4)), (rank, t_cap, batch)
+                if rank > 1024:
+                    assert -(-chunks // splits) <= 4, (rank, t_cap, batch)
+                else:
+                    assert batch * splits * parts <= max(512 if rank == 256 else 256, batch), (rank, t_cap, batch)
+
+
 def kernel_scratch_bytes():
     """Scratch memory per lane of every kernel of the built library, by (mangled) name: the notes of its gfx950 code objects."""
     data = open(W.LIB_PATH, "rb").read()
@@ -95,7 +113,7 @@ def test_row_and_prompt_kernels_use_no_scratch_memory():
     prompt projection without LDS, for sequences of 2^31 bytes and more and for rank 128, is the known exception)."""
     sizes = kernel_scratch_bytes()
     for part, least in (("k_latent_store", 3), ("k_append", 6), ("k_prefill_attn", 24), ("k_prefill_project_direct", 6),
-                        ("k_prefill_project_lds", 3), ("k_rmsnorm_quant", 8), ("k_swiglu_quant", 4), ("k_quantize_act", 9), ("k_attn_generic", 96)):
+                        ("k_prefill_project_lds", 3), ("k_shared", 14), ("k_rmsnorm_quant", 8), ("k_swiglu_quant", 4), ("k_quantize_act", 9), ("k_attn_generic", 96)):
         found = {k: v for k, v in sizes.items() if part in k}
         assert len(found) >= least, (part, sorted(found))
         assert not any(found.values()), {k: v for k, v in found.items() if v}
