@@ -29,10 +29,10 @@ HBM_PEAK_GBPS = 8000.0   # MI355X published HBM3E peak
 MEASURED_TRAFFIC_BYTES = 74_620_000   # 74.35 MB fetched + 0.26 MB written at 2073 rows (profiles/attn_mfma_int8_c3_hbm_traffic.md)
 MEASURED_TRAFFIC_APPEND = 20_040_000  # 18.66 MB fetched + 1.38 MB written (same file, section on the append)
 MEASURED_TRAFFIC_BYTES_C5 = 141_840_000   # 140.8 MB fetched + 1.03 MB written (profiles/attn_gqa_int8_c5_hbm_traffic.md)
-# prefill and shared-latent kernels (profiles/prefill_int8_c3_kernel_trace.md, profiles/attn_shared_int8_r1024_kernel_trace.md)
+# prefill and shared-latent kernels (profiles/prefill_int8_c3_kernel_trace.md, profiles/attn_shared_int8_r1024_limbs_once_kernel_trace.md)
 MEASURED_TRAFFIC_PREFILL_ATTN = 894_500_000    # 357.6 MB fetched + 536.9 MB written (the fp32 outputs)
 MEASURED_TRAFFIC_PREFILL_PROJ = 881_700_000    # 808.3 MB fetched (factors once per XCD and round of workgroups) + 73.4 MB written
-MEASURED_TRAFFIC_SHARED_STEP = 186_000_000     # three launches: 142.9 MB fetched + 43.1 MB written
+MEASURED_TRAFFIC_SHARED_STEP = 123_700_000     # three launches: 103.4 MB fetched + 20.3 MB written
 
 
 def parse():
@@ -1018,7 +1018,7 @@ def run_shared(args, np, torch, W, WI):
         assert W.wsvd_check(ctx, stream) == 0 and bool(torch.isfinite(out).all())
     cache_bytes = 2 * B * T * (R + 2)
     factor_bytes = 2 * H * R * d * 2
-    ws_floats = W.wsvd_shared_workspace_bytes(B, H, d, R, T) // 4
+    splits, parts = W.wsvd_test_shared_plan(B, R, T)
     res = {
         "metric": "decode_attn_latent_bandwidth", "value": round(cache_bytes / (us * 1e-6) / 1e9, 1), "unit": "GB/s", "n_gpus": 1,
         "steps": reps * n_sets, "warmup": warmup, "ms_per_step": round(us * 1e-3, 5), "us_per_decode_step": round(us, 3),
@@ -1027,13 +1027,13 @@ def run_shared(args, np, torch, W, WI):
                                "(B=16, T=2048, d_head=128), per-head up-projections [1024, 128]; same cache bytes as the per-head "
                                "int8 workload (32 heads x rank 32)",
                    "batch": B, "context": T, "heads": H, "rank": R, "cache_sets": n_sets, "launch": "hip_graph",
-                   "launches_per_step": 3},
+                   "launches_per_step": 3, "context_splits": splits, "value_parts": parts},
         # the step's three launches are timed together here; the kernel-trace summary under profiles/ splits them
         "roofline": {"kernel": "wsvd_decode_attn_shared (k_shared_absorb_limbs + k_shared_attn + k_shared_out)", "bound": "hbm",
                      "achieved": round(cache_bytes / (us * 1e-6) / 1e9, 1), "peak": HBM_PEAK_GBPS, "unit": "GB/s",
                      "frac": round(cache_bytes / (us * 1e-6) / 1e9 / HBM_PEAK_GBPS, 4), "traffic": MEASURED_TRAFFIC_SHARED_STEP,
                      "algorithmic_bytes_per_launch": int(cache_bytes),
-                     "other_bytes_per_step": {"up_projection_factors": int(factor_bytes), "split_partials_written_and_read": int(2 * 4 * (ws_floats - B * H * R))},
+                     "other_bytes_per_step": {"up_projection_factors": int(factor_bytes), "split_partials_written_and_read": int(2 * 4 * B * H * splits * (R + 2))},
                      "int8_score_GOP_issued": round(3 * 2.0 * B * T * R * H / 1e9, 2), "fp16_value_GFLOP": round(2.0 * B * T * R * H / 1e9, 2)},
     }
     print(json.dumps(res))
