@@ -14,9 +14,11 @@ from test_gpu_parity import check_out, layer_for
 pytestmark = pytest.mark.gpu
 
 
-def _rope(name, base, **over):
+def _rope(name, base, options=(), **over):
     c = build_case(name, **over)
     L = layer_for(c); L.upload(c.cache)
+    for option, value in options:
+        W.wsvd_ctx_set_option(L.ctx, option, value)
     qd, qs, q64 = q_to_device(c.q32[0], c.sp.q_dtype)
     BKd, BVd = as_dtype_dev(c.BK, "bf16"), as_dtype_dev(c.BV, "bf16")
     got = L.attend_rope(qd, qs, BKd, BVd, int(c.cache.seq_lens.max()), base)
@@ -34,6 +36,16 @@ def _rope(name, base, **over):
 @pytest.mark.parametrize("name", ["c3_small", "c4_small"])
 def test_rope_table(name, over):
     _rope(name, 10000.0, **{**dict(batch=9, n_q_heads=32, n_kv_heads=32, ragged=()), **over})
+
+
+# the same split over two to nine workgroups, which has to be asked for: chunks of one run for every wave and of single tiles, a
+# chunk's last run of one tile, a last chunk of few rows, sequences that end before the later chunks begin
+@pytest.mark.parametrize("min_chunk,over", [(512, dict(context=1024)), (576, dict(context=1100)), (256, dict(context=2050)), (1024, dict(context=2049, d_head=64)),
+                                            (320, dict(context=1300, ragged=(1, 1300)))], ids=["512", "576", "256", "1024-d64", "320-ragged"])
+@pytest.mark.parametrize("name", ["c3_small", "c4_small"])
+def test_rope_table_split_over_workgroups(name, min_chunk, over):
+    _rope(name, 10000.0, options=(("wg_per_cu", 64), ("min_chunk", min_chunk)),
+          **{**dict(batch=9, n_q_heads=32, n_kv_heads=32, ragged=()), **over})
 
 
 @pytest.mark.parametrize("q_dtype", ["f32", "bf16", "i8"])
