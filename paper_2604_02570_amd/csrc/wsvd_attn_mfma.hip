@@ -186,8 +186,13 @@ struct RopeShared {
 // b of the run adds is the same for every head, sequence and run: cos theta_i b, sin theta_i b, a table in LDS.  One product
 // W = N' F(b) on the matrix cores gives the latent-space query of every token of a block, and the score is W . c: 16 multiply-adds
 // per lane.  N' (at most 2^14) and F (times 2^10) are fp16 pairs, hi hi + lo hi + hi lo, all in normal range down to 2^-24 of
-// their largest.  24 products of 32 cycles per block of 32 tokens and wave bound it; for more query heads or rank 64 the form
-// above needs fewer (16 per head and 32; its rotation is shared by the heads).
+// their largest.  The scores lose nothing by it against features in fp32: emulated against 64 bits, 1.5e-7 .. 1.6e-7 relative at
+// every length, the form above 1.4e-7 .. 2.3e-7 with exact start values and 2.6e-7 .. 3.1e-7 with the hardware's sine (lo lo
+// would change nothing).  What bounds it is instruction issue, two waves per SIMD: 16 x 2048 tokens of 32 heads keep the vector
+// ALU busy 50 % of the cycles (274 instructions per block of 32 tokens and wave, the table, the rebuilding of N' once per run
+// and the merge among them) and the matrix cores 37 % (24 products of 32 cycles per block), 87 % together as the two overlap
+// little; LDS 27 %.  For more query heads or rank 64 the form above needs fewer products (16 per head and 32; its rotation is
+// shared by the heads).
 template <int D, int NT>
 struct RopeTable {
   __attribute__((aligned(16))) _Float16 feat[4][D / 16][2][512];   // [32-token block of the run][step][hi, lo][lane][8]
@@ -1052,7 +1057,11 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
       const float pw = __builtin_amdgcn_exp2f(s - m[g]);          // <= 1
       lsum[g] += pw;
       const float wt = valid ? pw * vsc : 0.f;
-      if (__builtin_amdgcn_ballot_w64(wt > wref[g]) != 0) {       // a weight beyond the fixed-point range
+      // A weight beyond the fixed-point range: the range is moved to twice the weight, so that it seldom moves again.  The table
+      // form's workgroups have half the waves, each meets twice the rows, and the range of its largest weight holds for all of
+      // them: with 2 its error against 64 bits is 1.12 times that of the features form (20 cases, 64 to 4096 rows; the part
+      // that comes from the scores is the same in both), with 1.125 it is 0.84 times, at the same speed.
+      if (__builtin_amdgcn_ballot_w64(wt > wref[g]) != 0) {
         flush(g);
         wref[g] = (TABLE ? 1.125f : 2.f) * wave_max(wt);
         winv[g] = kLimbFull * __builtin_amdgcn_rcpf(wref[g]);
