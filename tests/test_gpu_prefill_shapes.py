@@ -46,8 +46,8 @@ def test_int4_prompt_projection_shapes(shape, n):
     _prompt("c4_small", shape, n, batch=3, context=120, ragged=(60, 120))
 
 
-# (the first three take 128 x 32 tiles, the others 256 x 64, since three rounds of the small ones would be one of the large:
-# channel tiles that end inside a workgroup's group, tokens at the edges of a tile and one sequence of several)
+# (the first three take 64 x 32 tiles, the fourth and the last 128 x 32, the fifth 256 x 64: channel tiles that end inside a
+# workgroup's group, tokens at the edges of a tile and one sequence of several)
 @pytest.mark.parametrize("name,n,over", [("c3_small", 1, dict()), ("c3_small", 33, dict(n_q_heads=7, n_kv_heads=7)), ("c3_small", 64, dict(rank=64)),
                                          ("c3_small", 345, dict(n_q_heads=32, n_kv_heads=32)), ("c3_small", 321, dict(rank=64, n_q_heads=18, n_kv_heads=18)),
                                          ("c4_small", 353, dict(n_q_heads=34, n_kv_heads=34, ragged=(60, 120)))])

@@ -53,7 +53,9 @@ def test_rope_table_query_types_and_base(q_dtype):
     _rope("c3_small", 500.0, batch=9, n_q_heads=32, n_kv_heads=32, context=260, q_dtype=q_dtype)
 
 
-@pytest.mark.parametrize("over", [dict(context=1023), dict(context=1024), dict(context=1100), dict(context=2050, rank=64), dict(context=1500, n_q_heads=8)],
+# (8 units: one chunk up to 1100 rows, two to eight from 1300 on)
+@pytest.mark.parametrize("over", [dict(context=1023), dict(context=1024), dict(context=1100), dict(context=2050, rank=64), dict(context=1500, n_q_heads=8),
+                                  dict(context=1300), dict(context=2049, ragged=(3, 2049)), dict(context=4100)],
                          ids=lambda o: "-".join(f"{k}{v}" for k, v in o.items()))
 def test_rope_split_over_workgroups(over):
     _rope("c3_small", 10000.0, **{**dict(batch=2, n_q_heads=4, n_kv_heads=4), **over})

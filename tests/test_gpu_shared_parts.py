@@ -11,25 +11,28 @@ from test_gpu_shared import H, SharedCase
 
 pytestmark = pytest.mark.gpu
 
-#      rank, d, t_cap, lengths                                      parts, chunks per split
+#      rank, d, t_cap, lengths, (splits, parts)                    what a workgroup walks
 CASES = [
-    (1024, 128, 5120, [4999]),                                     # 4, two
-    (1024, 64, 1024, [1000 - 61 * b for b in range(17)]),          # 2, up to two
-    (1024, 128, 2048, [(2048 * (b % 5)) // 4 for b in range(24)]),   # 2, up to four, empty sequences
-    (512, 128, 1024, [1023, 1]),                                   # 4, one
-    (512, 64, 1280, [1280 - 100 * b for b in range(9)]),           # 2, one
-    (512, 128, 640, [640 - 16 * b for b in range(40)]),            # 1, one
-    (256, 128, 512, [129, 0, 512]),                                # 2, one
-    (3712, 128, 1280, [1280 - 97 * b for b in range(12)]),         # two workgroups for four slabs of value dims, one
-    (256, 64, 1024, [1024 - 31 * b for b in range(33)]),           # 1, two
-    (1024, 128, 768, [768 - 11 * b for b in range(66)]),           # 1 (all registers), two
-    (1024, 64, 384, [384 - 2 * b for b in range(130)]),            # 1, up to three in one split
-    (256, 128, 512, [512 - 3 * b for b in range(130)]),            # 1, two workgroups to a CU
+    (1024, 128, 5120, [4999], (32, 4)),                                      # up to two chunks
+    (1024, 64, 1024, [1000 - 61 * b for b in range(17)], (7, 2)),            # up to two
+    (1024, 128, 2048, [(2048 * (b % 5)) // 4 for b in range(24)], (10, 1)),  # up to two, all registers, empty sequences
+    (1024, 128, 2048, [(2048 * (b % 5)) // 4 for b in range(20)], (6, 2)),   # up to three, empty sequences
+    (512, 128, 1024, [1023, 1], (8, 4)),                                     # one
+    (512, 64, 1280, [1280 - 100 * b for b in range(9)], (10, 2)),            # one
+    (512, 128, 640, [640 - 16 * b for b in range(40)], (3, 2)),              # up to two
+    (512, 128, 896, [896 - 22 * b for b in range(40)], (6, 1)),              # up to two
+    (256, 128, 512, [129, 0, 512], (4, 2)),                                  # one
+    (3712, 128, 1280, [1280 - 97 * b for b in range(12)], (10, 2)),          # two workgroups for four slabs of value dims, one
+    (256, 64, 1024, [1024 - 31 * b for b in range(33)], (7, 1)),             # up to two
+    (1024, 128, 768, [768 - 11 * b for b in range(66)], (3, 1)),             # up to two
+    (1024, 64, 384, [384 - 2 * b for b in range(130)], (1, 1)),              # up to three
+    (256, 128, 512, [512 - 3 * b for b in range(130)], (2, 1)),              # up to two, two workgroups to a CU
 ]
 
 
-@pytest.mark.parametrize("rank,d,t_cap,lens", CASES, ids=[f"r{c[0]}-d{c[1]}-b{len(c[3])}" for c in CASES])
-def test_shared_latent_launch_shapes(rank, d, t_cap, lens):
+@pytest.mark.parametrize("rank,d,t_cap,lens,plan", CASES, ids=[f"r{c[0]}-d{c[1]}-b{len(c[3])}" for c in CASES])
+def test_shared_latent_launch_shapes(rank, d, t_cap, lens, plan):
+    assert W.wsvd_test_shared_plan(len(lens), rank, t_cap) == plan
     print(f"shared latent: rank {rank}, d {d}, {len(lens)} sequences, t_cap {t_cap}", flush=True)
     c = SharedCase(len(lens), rank, d, lens, t_cap)
     ctx = W.wsvd_create(0)
