@@ -2033,13 +2033,16 @@ hipError_t wsvd_launch_attn_rope(const wsvd_ctx* ctx, const wsvd_layer_desc& d, 
   // exactly that many threads (waves without a tile of their own idle through the loop).  The table kernel takes 4, and two of
   // its workgroups share a CU, so that one's table, prologue and end run beside the other's stream: it needs more (sequence, kv
   // head) units than CUs (256 units, 2048 rows: 18.4 us with features, 25.3 with the table).  Its lead over the N build and start
-  // values, which every unit pays for, shrinks with the rows, whose cost is the higher one: it is used up at 4096 rows where
-  // the features kernel would run a second, nearly empty round, at 2048 to 2600 where it fills its rounds.  us, features /
-  // table: 512 units of 64 rows 14.8 / 11.1, 2048 rows 38.0 / 38.2, 3600 rows 55.9 / 58.7; 520 of 2048 rows 52.8 / 51.3, 4096
-  // rows 82.8 / 87.8; 257 of 2048 rows 34.7 / 30.7, 4096 rows 54.5 / 49.7; 384 of 4096 rows 54.5 / 54.4.  It is not split: 288
-  // units of 2048 rows 29.7 us as one chunk, 34.9 as two.
-  const int n_units = d.batch * d.n_kv_heads;
-  const bool table = d.rank == 32 && G == 1 && n_units > ctx->n_cu && max_seq_len <= (2 * n_units <= 3 * ctx->n_cu ? 4096 : 2048);
+  // values, which every unit pays for, shrinks with the rows, whose cost is the higher one.  It lasts to 4096 rows where the
+  // features form would run a second round that is less than half full, to about 3600 where two of its rounds are one of the
+  // table form, and to 2048 where they are not (513 to 768 units: three, and two of the table form).  us, features / table, caches
+  // out of memory: 288 units of 2048 rows 35.1 / 30.6, 4096 rows 54.8 / 52.0; 512 of 2048 rows 38.9 / 35.4, 3072 rows 48.9 / 50.3,
+  // 4096 rows 61.8 / 62.4; 520 of 2048 rows 53.3 / 50.8, 2304 rows 55.4 / 58.4, 3600 rows 77.7 / 80.8; 800 of 2600 rows 83.5 / 76.1,
+  // 3600 rows 104 / 100, 1024 of 4096 rows 122 / 123; 512 of 64 rows 14.8 / 11.1.  It is not split: 288 units of 2048 rows 29.7 us
+  // as one chunk, 34.9 as two.
+  const int n_units = d.batch * d.n_kv_heads, rounds = (n_units + ctx->n_cu - 1) / ctx->n_cu;
+  const int table_rows = 2 * n_units <= 3 * ctx->n_cu ? 4096 : rounds % 2 == 0 ? 3600 : 2048;
+  const bool table = d.rank == 32 && G == 1 && n_units > ctx->n_cu && max_seq_len <= table_rows;
   wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p, grid, threads, table ? 256 : 512,
                  table ? 1 : rope_chunks(ctx->n_cu, n_units, max_seq_len));
   RopeArgs ra;
