@@ -590,7 +590,7 @@ hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
 // beside it; `fixed` (first requests, sums, last store) shows once.  The shape that costs least.  Smaller tiles read the operands
 // more often (see k_prefill_project_direct), larger ones leave CUs idle.  The constants are fitted to 840 sizes (1 to 40 heads of
 // rank 32 or 64, d_model 64 to 8192, 2 to 40000 tokens): the choice is 0.6 % slower than the best of the shapes on average, 0.2
-// from d_model 512 on.  us per call with the update of the lengths (about 6 us with the clearing before it), 32 kv heads of rank
+// from d_model 512 on (0.4 over 170 sizes with the operands out of memory).  us per call with the update of the lengths (about 6 us with the clearing before it), 32 kv heads of rank
 // 32 / 64, d_model 4096; the last column 28 x 385 tokens at d_model 192, where the store is most of the time:
 //                   1 x 200   16 x 32   1 x 400   3 x 333   4 x 500  16 x 130  2 x 2048  8 x 1024    64 x 4    28 x 385
 //    5:  64 x  32     16/23     25/42     24/40     41/77    71/147    78/156   141/288   267/553     17/24      79/189
@@ -603,7 +603,7 @@ hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
 // short (30 x 46 tokens of 8 heads, d_model 192: 10.0 us, the others 10.9 and more).
 struct ProjectShape { int code, ch, tok; float fixed[2], store[2], chain, busy; };    // fixed, store: rank 32, 64
 constexpr ProjectShape kProjectShapes[] = {
-    {5, 64, 32, {2.f, 2.6f}, {0.9f, 1.2f}, 7.5f, 0.3f},     {11, 128, 32, {1.7f, 3.1f}, {0.85f, 1.7f}, 11.2f, 1.5f},
+    {5, 64, 32, {2.f, 2.6f}, {0.9f, 1.2f}, 7.5f, 0.3f},     {11, 128, 32, {1.7f, 3.1f}, {1.05f, 1.7f}, 11.2f, 1.5f},
     {12, 128, 64, {3.1f, 3.4f}, {3.4f, 1.9f}, 17.5f, 1.7f}, {13, 256, 32, {-1.f, 2.5f}, {0.f, 1.9f}, 21.5f, 0.f},
     {22, 256, 64, {4.5f, 3.6f}, {3.3f, 2.8f}, 31.4f, 0.f},  {25, 256, 128, {5.9f, 4.7f}, {8.2f, 7.9f}, 47.5f, 7.6f},
     {2, 256, 256, {6.8f, 5.6f}, {12.7f, 11.1f}, 95.f, 11.5f}};
