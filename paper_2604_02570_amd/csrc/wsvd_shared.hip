@@ -650,16 +650,16 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8))) void k_s
 
 // Workgroups over which the value dims of the same tokens are divided (each computes the scores of all its tokens), up to
 // rank 1024.  Where (sequence, chunk) pairs are too few for the chip the parts fill it (1 sequence of 8191 rows, rank 1024:
-// 1 / 2 / 4 parts 23.7 / 17.5 / 15.6 us; 5 of 3000 rows, rank 512: 10.8 / 8.8 us).  With one to a few pairs per workgroup two
-// parts still pay where the partial results are large: they halve them, 33.6 MB at 16 sequences of 2048 rows and rank 1024, for
-// a second reading of the keys from the die's cache.  With more the second score pass costs more than that.  us per call, one
-// part / two: rank 1024, 16 x 2048 rows 42 / 40, 20 x 2048 50 / 47, 33 x 2048 64 / 71, 65 x 2048 103 / 125, 64 x 8192 213 / 297;
-// rank 512, 16 x 2048 29 / 26, 20 x 2048 29 / 31; rank 256, 9 x 2048 17.3 / 18.1.  Beyond 64 sequences two parts would leave
-// one or two splits to choose from: 129 of 300 rows, rank 1024, 103 / 120.
+// 1 / 2 / 4 parts 23.7 / 17.5 / 15.6 us; 5 of 3000 rows, rank 512: 10.8 / 8.8 us).  At rank 1024 two parts still pay with about one
+// pair per workgroup: they halve the partial results, 33.6 MB at 16 sequences of 2048 rows, for a second reading of the keys
+// from the die's cache.  With more pairs the second score pass costs more than that.  us per call, one part / two: rank 1024, 16 x
+// 2048 rows 42 / 40, 20 x 2048 50 / 47, 33 x 2048 64 / 71, 65 x 2048 103 / 125, 64 x 8192 213 / 297; rank 512, 9 x 2048 rows 21.8 / 23.2,
+// 5 x 4000 21.0 / 23.4; rank 256, 9 x 2048 17.3 / 18.1.  Beyond 64 sequences two parts would leave one or two splits to choose from:
+// 129 of 300 rows, rank 1024, 103 / 120.
 int shared_value_parts(int batch, int chunks, int rank) {
   const long pairs = (long)batch * chunks;
   if (rank >= 512 && 4L * batch * (chunks < 32 ? chunks : 32) <= 256) return 4;
-  return batch <= 64 && pairs <= (rank == 256 ? 128 : rank == 512 ? 256 : 320) ? 2 : 1;
+  return batch <= 64 && pairs <= (rank == 1024 ? 320 : 128) ? 2 : 1;
 }
 
 // Splits of a sequence then: as many as fit the CUs, one more would be a second round (65 x 2048 rows, rank 1024: three 103 us,

@@ -19,7 +19,7 @@ CASES = [
     (1024, 128, 2048, [(2048 * (b % 5)) // 4 for b in range(20)], (6, 2)),   # up to three, empty sequences
     (512, 128, 1024, [1023, 1], (8, 4)),                                     # one
     (512, 64, 1280, [1280 - 100 * b for b in range(9)], (10, 2)),            # one
-    (512, 128, 640, [640 - 16 * b for b in range(40)], (3, 2)),              # up to two
+    (512, 128, 640, [640 - 16 * b for b in range(40)], (5, 1)),              # one
     (512, 128, 896, [896 - 22 * b for b in range(40)], (6, 1)),              # up to two
     (256, 128, 512, [129, 0, 512], (4, 2)),                                  # one
     (3712, 128, 1280, [1280 - 97 * b for b in range(12)], (10, 2)),          # two workgroups for four slabs of value dims, one
