@@ -654,12 +654,12 @@ __global__ __launch_bounds__(T) __attribute__((amdgpu_waves_per_eu(8))) void k_s
 // pair per workgroup: they halve the partial results, 33.6 MB at 16 sequences of 2048 rows, for a second reading of the keys
 // from the die's cache.  With more pairs the second score pass costs more than that.  us per call, one part / two: rank 1024, 16 x
 // 2048 rows 42 / 40, 20 x 2048 50 / 47, 33 x 2048 64 / 71, 65 x 2048 103 / 125, 64 x 8192 213 / 297; rank 512, 9 x 2048 rows 21.8 / 23.2,
-// 5 x 4000 21.0 / 23.4; rank 256, 9 x 2048 17.3 / 18.1.  Beyond 64 sequences two parts would leave one or two splits to choose from:
-// 129 of 300 rows, rank 1024, 103 / 120.
+// 5 x 4000 21.0 / 23.4; rank 256, 9 x 2048 17.3 / 18.1.  Not for 65 to 85 sequences, which have three splits in one part and one
+// in two (65 of 300 rows, rank 1024, 62 / 65), nor beyond 128 (129 of 300 rows 103 / 120).
 int shared_value_parts(int batch, int chunks, int rank) {
-  const long pairs = (long)batch * chunks;
-  if (rank >= 512 && 4L * batch * (chunks < 32 ? chunks : 32) <= 256) return 4;
-  return batch <= 64 && pairs <= (rank == 1024 ? 320 : 128) ? 2 : 1;
+  const long pairs = (long)batch * chunks, splits = (long)batch * (chunks < 32 ? chunks : 32);    // (a sequence has at most 32)
+  if (rank >= 512 && 4 * splits <= 256) return 4;
+  return 2 * splits <= 256 || (rank == 1024 && pairs <= 320 && batch <= 128 && 256 / batch != 3) ? 2 : 1;
 }
 
 // Splits of a sequence then: as many as fit the CUs, one more would be a second round (65 x 2048 rows, rank 1024: three 103 us,
