@@ -589,7 +589,7 @@ hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
 // rounds once and the last one by the square of the share of the CUs that it keeps busy, because a CU has the next workgroup
 // beside it; `fixed` (first requests, sums, last store) shows once.  The shape that costs least.  Smaller tiles read the operands
 // more often (see k_prefill_project_direct), larger ones leave CUs idle.  The constants are fitted to 840 sizes (1 to 40 heads of
-// rank 32 or 64, d_model 64 to 8192, 2 to 40000 tokens): the choice is 0.6 % slower than the best of the shapes on average, 0.2
+// rank 32 or 64, d_model 64 to 8192, 2 to 40000 tokens): the choice is 0.7 % slower than the best of the shapes on average, 0.3
 // from d_model 512 on (0.4 over 170 sizes with the operands out of memory).  us per call with the update of the lengths (about 6 us with the clearing before it), 32 kv heads of rank
 // 32 / 64, d_model 4096; the last column 28 x 385 tokens at d_model 192, where the store is most of the time:
 //                   1 x 200   16 x 32   1 x 400   3 x 333   4 x 500  16 x 130  2 x 2048  8 x 1024    64 x 4    28 x 385
@@ -600,24 +600,31 @@ hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
 //   25: 256 x 128     54/55     53/59     56/55     57/56     57/69    65/122    74/135   141/267     56/57      47/79
 //    2: 256 x 256    103/103   102/109   105/104   107/105   106/106   104/121   114/134   135/261   110/109     40/66
 // 13, 256 x 32, is there for rank 64: it reads the hidden states half as often as 11 and is the best where the contraction is
-// short (30 x 46 tokens of 8 heads, d_model 192: 10.0 us, the others 10.9 and more).
-struct ProjectShape { int code, ch, tok; float fixed[2], store[2], chain, busy; };    // fixed, store: rank 32, 64
+// short (30 x 46 tokens of 8 heads, d_model 192: 10.0 us, the others 10.9 and more); its chain is priced for that, at larger
+// d_model 12 and 22 are as fast.
+// A shape that sums the contraction in one chain has to be 2 % cheaper than one that halves it over wave groups, whose sums are
+// nearer to the exact ones (scales of 10 x 1178 tokens, d_model 512, against 64 bits: 4.2e-6 and 3.3e-6).
+struct ProjectShape { int code, ch, tok; bool halves[2]; float fixed[2], store[2], chain, busy; };   // pairs: rank 32, 64
 constexpr ProjectShape kProjectShapes[] = {
-    {5, 64, 32, {2.f, 2.6f}, {0.9f, 1.2f}, 7.5f, 0.3f},     {11, 128, 32, {1.7f, 3.1f}, {1.05f, 1.7f}, 11.2f, 1.5f},
-    {12, 128, 64, {3.1f, 3.4f}, {3.4f, 1.9f}, 17.5f, 1.7f}, {13, 256, 32, {-1.f, 2.5f}, {0.f, 1.9f}, 21.5f, 0.f},
-    {22, 256, 64, {4.5f, 3.6f}, {3.3f, 2.8f}, 31.4f, 0.f},  {25, 256, 128, {5.9f, 4.7f}, {8.2f, 7.9f}, 47.5f, 7.6f},
-    {2, 256, 256, {6.8f, 5.6f}, {12.7f, 11.1f}, 95.f, 11.5f}};
+    {5, 64, 32, {true, true}, {1.7f, 2.6f}, {0.9f, 1.2f}, 7.5f, 0.3f},
+    {11, 128, 32, {false, true}, {1.7f, 3.1f}, {1.05f, 1.7f}, 11.2f, 1.5f},
+    {12, 128, 64, {true, true}, {3.1f, 3.4f}, {3.4f, 1.9f}, 17.5f, 1.7f},
+    {13, 256, 32, {false, false}, {-1.f, 2.3f}, {0.f, 1.9f}, 26.f, 0.f},
+    {22, 256, 64, {false, false}, {4.5f, 3.6f}, {3.3f, 2.8f}, 31.4f, 0.f},
+    {25, 256, 128, {true, true}, {5.9f, 4.7f}, {8.2f, 7.9f}, 47.5f, 7.6f},
+    {2, 256, 256, {false, false}, {6.8f, 5.6f}, {12.7f, 11.1f}, 95.f, 11.5f}};
 int project_shape_rule(const ProjectParams& p, int n_seq, int R, bool i4) {
   int best = 0;
   float least = 0.f;
   for (const ProjectShape& k : kProjectShapes) {
-    const float fixed = k.fixed[R == 64], store = k.store[R == 64];
-    if (fixed < 0.f) continue;                                          // not there at this rank
+    const int r = R == 64;
+    if (k.fixed[r] < 0.f) continue;                                     // not there at this rank
     ProjectParams g = p;
     project_grid(g, n_seq, k.ch, k.tok, R, i4);
     const float wgs = (float)g.n_cg * (float)g.n_tg, rounds = ceilf(wgs / 256.f), load = wgs / 256.f - (rounds - 1.f);
     const float held = rounds - 1.f + load * load;
-    const float cost = fixed + store * held + (rounds * k.chain + held * k.busy) * (float)p.E / 4096.f;
+    const float us = 6.f + k.fixed[r] + k.store[r] * held + (rounds * k.chain + held * k.busy) * (float)p.E / 4096.f;
+    const float cost = k.halves[r] ? us : 1.02f * us;
     if (!best || cost < least) { best = k.code; least = cost; }
   }
   return best;
