@@ -215,6 +215,7 @@ wsvd_status wsvd_ctx_set_option(wsvd_ctx* ctx, const char* name, int value) {
   if (!strcmp(name, "linear_direct") && value >= 0 && value <= 1) { o.linear_direct = value; return WSVD_OK; }
   if (!strcmp(name, "prefill_tiled") && value >= 0 && value <= 1) { o.prefill_tiled = value; return WSVD_OK; }
   if (!strcmp(name, "step_deferred") && value >= 0 && value <= 2) { o.step_deferred = value; return WSVD_OK; }
+  if (!strcmp(name, "step_launches") && value >= 0 && value <= 2) { o.step_launches = value; return WSVD_OK; }
   if (!strcmp(name, "timeline_kernel") && value >= 0 && value <= 1) { o.timeline_kernel = value; return WSVD_OK; }
   if (!strcmp(name, "step_slices") && value >= 0 && value <= 4) { o.step_slices = value; return WSVD_OK; }
   if (!strcmp(name, "project_shape"))
@@ -642,6 +643,10 @@ wsvd_status wsvd_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const v
   // (step_deferred 2 insists on the int8 pair)
   const bool deferred = wsvd_step_deferred_ok(*desc) || (ctx->opt.step_deferred == 1 && wsvd_step_deferred_float_ok(*desc));
   if (e == hipErrorNotSupported && ctx->opt.step_deferred && ctx->opt.append_mode == 0 && deferred) {
+    if (ctx->opt.step_deferred == 1 && ctx->opt.step_launches != 2) {
+      e = wsvd_launch_step_float(ctx, *desc, x, A_K, A_V, q, q_scale, B_K, B_V, *cache, max_seq_len, out, s);
+      if (e != hipErrorNotSupported) return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;
+    }
     // projection launch (partial sums, lengths advanced), then the attention launch that finishes the rows
     float* parts = nullptr;
     int* pending = nullptr;

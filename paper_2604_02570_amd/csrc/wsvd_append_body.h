@@ -33,6 +33,8 @@ struct AppendParams {
   // be written
   float* defer_out;
   int* pending;
+  // the decode step as one launch (kPushShares): the same sums as {value, tag} words, zero between launches
+  unsigned long long* defer_words;
 };
 
 // which sequence a row of x belongs to, and the cache row it goes to given that sequence's length

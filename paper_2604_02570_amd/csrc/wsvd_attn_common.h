@@ -55,6 +55,9 @@ struct AttnParams {
   const int* pending;
   int n_parts;
   long part_stride;
+  // the decode step as one launch: the partial sums as {value, tag} words of the same layout, [part][plane][B][new_ld], plane
+  // part_stride / 2 words apart
+  unsigned long long* new_words;
   int out_bf16;              // out holds bf16 (round to nearest even) instead of fp32; never for the latent-space output
 };
 
@@ -95,10 +98,15 @@ WSVD_DEV WorkItem decode_work(const AttnParams& p, int n_raw, int kv, int chunk,
 }
 WSVD_DEV WorkItem decode_work(const AttnParams& p, int n_raw) { return decode_work(p, n_raw, blockIdx.x, blockIdx.y, blockIdx.z); }
 
+// Threads that take part in the pieces below: NT, or the whole workgroup.
+template <int NT>
+WSVD_DEV int n_threads() { return NT ? NT : (int)blockDim.x; }
+
 // A sequence with no rows: its outputs are zeros (written by the chunk-0 workgroup).
+template <int NT = 0>
 WSVD_DEV void write_zero_outputs(const AttnParams& p, const WorkItem& w) {
   if (w.chunk != 0) return;
-  for (int i = threadIdx.x; i < p.G * p.out_dim; i += blockDim.x)
+  for (int i = threadIdx.x; i < p.G * p.out_dim; i += n_threads<NT>())
     out_put(p, ((size_t)w.b * p.Hq + first_head(p, w.kv)) * p.out_dim + i, 0.f);
 }
 
@@ -109,21 +117,21 @@ WSVD_DEV void write_zero_outputs(const AttnParams& p, const WorkItem& w) {
 template <int MAXIT>
 struct StageRegs { v4i v[MAXIT]; };
 
-template <int MAXIT>
+template <int MAXIT, int NT = 0>
 WSVD_DEV void stage_issue(StageRegs<MAXIT>& r, const void* src, int n16) {
   // Unconditional loads (index clamped): a load under a branch would force every later wait to drain the whole
   // queue, tile prefetches included, because the wait-count bookkeeping is conservative across control flow.
 #pragma unroll
   for (int it = 0; it < MAXIT; it++) {
-    const int idx = min(it * (int)blockDim.x + (int)threadIdx.x, n16 - 1);
+    const int idx = min(it * n_threads<NT>() + (int)threadIdx.x, n16 - 1);
     r.v[it] = ((const v4i*)src)[idx];
   }
 }
-template <int MAXIT>
+template <int MAXIT, int NT = 0>
 WSVD_DEV void stage_commit(const StageRegs<MAXIT>& r, void* lds, int n16) {
 #pragma unroll
   for (int it = 0; it < MAXIT; it++) {
-    const int idx = it * (int)blockDim.x + (int)threadIdx.x;
+    const int idx = it * n_threads<NT>() + (int)threadIdx.x;
     if (idx < n16) ((v4i*)lds)[idx] = r.v[it];
   }
 }
@@ -193,12 +201,12 @@ WSVD_DEV void lds_load8(const void* lds, int idx, float* f) {
 // q~[g][j] = c_scale * sum_c B_K[kv][j][c] * q[b, kv*G+g][c]   (query absorption; whole workgroup, any multiple of 64 threads).
 // bk_lds holds B_K[kv] (R x d, element size ESZ); q_lds [G][d] floats.  Work is split into chunks of 8
 // columns: chunk id -> (row j, column block); the d/8 lanes of a row are adjacent.  Ends with a barrier.
-template <int R, int ESZ>
+template <int R, int ESZ, int NT = 0>
 WSVD_DEV void compute_qtilde(const AttnParams& p, const void* bk_lds, const float* q_lds, float* qts /* LDS [G][R] */) {
   const int tid = threadIdx.x;
   const int cpr = p.d >> 3;                 // chunks per row: 16 (d = 128) or 8 (d = 64)
   const int n_chunks = R * cpr;
-  const int nt = blockDim.x;
+  const int nt = n_threads<NT>();
   for (int ch = tid; ch < (n_chunks + nt - 1) / nt * nt; ch += nt) {   // uniform trip count: DPP needs whole rows active
     const bool on = ch < n_chunks;
     const int j = on ? ch / cpr : 0, cb = on ? ch % cpr : 0;
@@ -232,7 +240,7 @@ WSVD_DEV void compute_qtilde(const AttnParams& p, const void* bk_lds, const floa
 constexpr uint32_t kSplitTag = 0x53504C54u;
 WSVD_DEV unsigned long long split_word(float v) { return ((unsigned long long)kSplitTag << 32) | (unsigned long long)__float_as_uint(v); }
 
-template <int R>
+template <int R, int NT = 0>
 WSVD_DEV bool attn_merge_splits(const AttnParams& p, const WorkItem& w, float* Msh, float* Lsh, float* Ush, int* flag_sh) {
   const int tid = threadIdx.x;
   const int G = p.G;
@@ -240,7 +248,7 @@ WSVD_DEV bool attn_merge_splits(const AttnParams& p, const WorkItem& w, float* M
   unsigned long long* const base = p.partials + (((size_t)w.b * p.Hq + (size_t)w.kv * G) * p.n_chunks) * (R + 2);
   const size_t g_stride = (size_t)p.n_chunks * (R + 2);          // words between two heads of the group
   if (w.chunk != w.n_splits - 1) {
-    for (int i = tid; i < G * (R + 2); i += blockDim.x) {
+    for (int i = tid; i < G * (R + 2); i += n_threads<NT>()) {
       const int g = i / (R + 2), k = i % (R + 2);
       const float v = k == 0 ? Msh[g] : k == 1 ? Lsh[g] : Ush[g * R + (k - 2)];
       __hip_atomic_store(base + g * g_stride + (size_t)w.chunk * (R + 2) + k, split_word(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -253,7 +261,7 @@ WSVD_DEV bool attn_merge_splits(const AttnParams& p, const WorkItem& w, float* M
   bool timed_out = false;
 #pragma unroll
   for (int it = 0; it < NI; it++) {
-    const int i = tid + it * (int)blockDim.x;
+    const int i = tid + it * n_threads<NT>();
     if (i < G * R) {
       const int g = i / R, jj = i % R;
       const unsigned long long* src = base + g * g_stride;
@@ -314,7 +322,7 @@ WSVD_DEV bool attn_merge_splits(const AttnParams& p, const WorkItem& w, float* M
   __syncthreads();                                               // every thread has read the words and the LDS values it needs
 #pragma unroll
   for (int it = 0; it < NI; it++) {
-    const int i = tid + it * (int)blockDim.x;
+    const int i = tid + it * n_threads<NT>();
     if (i < G * R) {
       const int g = i / R, jj = i % R;
       Ush[i] = Ures[it];
@@ -334,16 +342,16 @@ WSVD_DEV bool attn_merge_splits(const AttnParams& p, const WorkItem& w, float* M
   return true;
 }
 
-template <int R, int ESZ>
+template <int R, int ESZ, int NT = 0>
 WSVD_DEV void attn_tail(const AttnParams& p, const WorkItem& w, float* Msh, float* Lsh, float* Ush, int* flag_sh,
                         const void* bv_lds) {
   const int tid = threadIdx.x;
   const int G = p.G;
-  if (!attn_merge_splits<R>(p, w, Msh, Lsh, Ush, flag_sh)) return;
+  if (!attn_merge_splits<R, NT>(p, w, Msh, Lsh, Ush, flag_sh)) return;
   WSVD_STAMP(p.timeline, ((int)blockIdx.z * (int)gridDim.y + (int)blockIdx.y) * (int)gridDim.x + (int)blockIdx.x, threadIdx.x >> 6, 11);
   if (!bv_lds) {
     // latent-output variant: the normalised accumulator itself (B_V lives in the output projection)
-    for (int i = tid; i < G * R; i += blockDim.x)
+    for (int i = tid; i < G * R; i += n_threads<NT>())
       p.out[((size_t)w.b * p.Hq + first_head(p, w.kv)) * R + i] = Ush[i] / Lsh[i / R];
     return;
   }
@@ -354,7 +362,7 @@ WSVD_DEV void attn_tail(const AttnParams& p, const WorkItem& w, float* Msh, floa
     // bf16 factors: two adjacent columns per lane (one LDS dword carries both), so half as many passes
     const int half_d = p.d >> 1, n_pair = G * half_d;
     const uint32_t* bv32 = (const uint32_t*)bv_lds;
-    for (int i0 = 0; i0 < n_pair * 4; i0 += blockDim.x) {   // uniform trip count: whole quads stay active
+    for (int i0 = 0; i0 < n_pair * 4; i0 += n_threads<NT>()) {   // uniform trip count: whole quads stay active
       const int i = i0 + tid;
       const int o = min(i >> 2, n_pair - 1), part = i & 3;
       const int g = o / half_d, c2 = o % half_d;
@@ -378,7 +386,7 @@ WSVD_DEV void attn_tail(const AttnParams& p, const WorkItem& w, float* Msh, floa
     return;
   }
   const int n_out = G * p.d;
-  for (int i0 = 0; i0 < n_out * 4; i0 += blockDim.x) {     // uniform trip count: whole quads stay active
+  for (int i0 = 0; i0 < n_out * 4; i0 += n_threads<NT>()) {     // uniform trip count: whole quads stay active
     const int i = i0 + tid;
     const int o = min(i >> 2, n_out - 1), part = i & 3;
     const int g = o / p.d, c = o % p.d;

@@ -19,6 +19,7 @@ struct wsvd_options {
   int prefill_tiled = 0;    // the tiled prefill kernels also for small calls
   int project_shape = 0;    // kernel of the tiled prefill projection (0 = automatic)
   int step_deferred = 1;    // wsvd_decode_step: projection launch + attention launch that finishes the row: 1 where supported, 2 that or UNSUPPORTED
+  int step_launches = 0;    // the fp32 / bf16 step: 0 one launch or two by size, 1 one wherever it exists, 2 never one
   int timeline_kernel = 0;  // profiling build, wsvd_decode_step: whose stamps are recorded: 0 the attention launch's, 1 the projection launch's
   int step_slices = 0;      // d_model slices of that projection launch (0 = automatic)
 };
@@ -104,6 +105,11 @@ hipError_t wsvd_launch_fold_vo(const void* BV, int factor_dtype, const float* WO
 hipError_t wsvd_launch_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* x, const void* x_scale, const void* A_K,
                                    const void* A_V, const void* q, const void* q_scale, const void* B_K, const void* B_V,
                                    const wsvd_cache& cache, int max_seq_len, void* out, hipStream_t s);
+// fp32 / bf16 latents, few workgroups: projection and attention as one launch; hipErrorNotSupported otherwise
+hipError_t wsvd_launch_step_float(wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* x, const void* A_K, const void* A_V, const void* q,
+                                  const void* q_scale, const void* B_K, const void* B_V, const wsvd_cache& cache, int max_seq_len,
+                                  void* out, hipStream_t s);
+bool wsvd_append_step_shape(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int waves, int* helpers, int* xs_stride, size_t* lds);
 hipError_t wsvd_launch_linear_w4a8(const int8_t* x, const void* x_scale, const void* w_i4, const void* w_scale, int64_t M,
                                    int64_t K, int64_t N, float* out, int64_t n_first, float* out2, bool direct, hipStream_t s);
 
@@ -120,4 +126,5 @@ hipError_t wsvd_launch_append_project(const wsvd_ctx* ctx, const wsvd_layer_desc
                                       hipStream_t s);
 size_t wsvd_attn_split_bytes(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int max_seq_len);
 size_t wsvd_append_partial_floats(const wsvd_layer_desc& d);
+size_t wsvd_zero_words(const wsvd_layer_desc& d);      // 8-byte words of the workspace that are zero between launches
 int wsvd_append_esplits(const wsvd_ctx* ctx, const wsvd_layer_desc& d);
