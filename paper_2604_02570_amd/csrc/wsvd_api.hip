@@ -644,7 +644,8 @@ wsvd_status wsvd_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const v
   const bool deferred = wsvd_step_deferred_ok(*desc) || (ctx->opt.step_deferred == 1 && wsvd_step_deferred_float_ok(*desc));
   if (e == hipErrorNotSupported && ctx->opt.step_deferred && ctx->opt.append_mode == 0 && deferred) {
     if (ctx->opt.step_deferred == 1 && ctx->opt.step_launches != 2) {
-      e = wsvd_launch_step_float(ctx, *desc, x, A_K, A_V, q, q_scale, B_K, B_V, *cache, max_seq_len, out, s);
+      e = desc->latent_dtype == WSVD_I8 ? wsvd_launch_step_i8(ctx, *desc, x, A_K, A_V, q, q_scale, B_K, B_V, *cache, max_seq_len, out, s)
+                                        : wsvd_launch_step_float(ctx, *desc, x, A_K, A_V, q, q_scale, B_K, B_V, *cache, max_seq_len, out, s);
       if (e != hipErrorNotSupported) return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;
     }
     // projection launch (partial sums, lengths advanced), then the attention launch that finishes the rows

@@ -91,19 +91,27 @@ static hipError_t launch_append_split(const AppendParams& p, const wsvd_layer_de
 }
 
 static bool append_mfma_path(const wsvd_layer_desc& d);
+int wsvd_step_slices(const wsvd_ctx* ctx, const wsvd_layer_desc& d);
 // The decode step's projection launch: `ns` equal d_model slices per (plane, kv head), partial sums to p.defer_out.
-template <int R, int NT>
-static hipError_t launch_append_project(const AppendParams& p, const wsvd_layer_desc& d, int ns, hipStream_t s) {
+static void project_shape(const wsvd_layer_desc& d, int ns, int nw, int* sb, int* stride, int* groups, size_t* lds) {
   const int nks = d.d_model / 16;
   const int share = (nks + ns - 1) / ns * 16;
-  const int stride = share + 8;
-  int sb = 16;
-  while (sb > 1 && (size_t)sb * stride * 2 > (size_t)144 * 1024) sb >>= 1;
-  const int groups = (d.batch + sb - 1) / sb;
-  const int nw = NT / 64;
-  size_t lds = (size_t)sb * stride * 2;
-  const size_t red_bytes = (size_t)nw * sb * (R + 1) * 4;
-  if (red_bytes > lds) lds = red_bytes;
+  *stride = share + 8;
+  *sb = 16;
+  while (*sb > 1 && (size_t)*sb * *stride * 2 > (size_t)144 * 1024) *sb >>= 1;
+  *groups = (d.batch + *sb - 1) / *sb;
+  const size_t xs = (size_t)*sb * *stride * 2, red = (size_t)nw * *sb * (d.rank + 1) * 4;
+  *lds = xs > red ? xs : red;
+}
+void wsvd_append_project_shape(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int waves, int* slices, int* sb, int* stride, int* groups, size_t* lds) {
+  *slices = wsvd_step_slices(ctx, d);
+  project_shape(d, *slices, waves, sb, stride, groups, lds);
+}
+template <int R, int NT>
+static hipError_t launch_append_project(const AppendParams& p, const wsvd_layer_desc& d, int ns, hipStream_t s) {
+  int sb, stride, groups;
+  size_t lds;
+  project_shape(d, ns, NT / 64, &sb, &stride, &groups, &lds);
   if (lds > (size_t)150 * 1024) return hipErrorInvalidValue;
   static LdsLimit limit;
   hipError_t e = wsvd_raise_lds(limit, (const void*)k_append_split<R, NT, kDeferSlices>, 150 * 1024);

@@ -5,13 +5,15 @@
 
 // What becomes of a workgroup's sums.  kNoDefer: this launch finishes the rows.  kDeferSlices, kDeferShares: plain stores for
 // the attention launch that follows.  kPushShares: {value, tag} words for attention workgroups of the same launch, which wait
-// for them, and which advance the lengths.
-enum { kNoDefer = 0, kDeferSlices = 1, kDeferShares = 2, kPushShares = 3 };
+// for them, and which advance the lengths; kPushSlices: kDeferSlices that way.
+enum { kNoDefer = 0, kDeferSlices = 1, kDeferShares = 2, kPushShares = 3, kPushSlices = 4 };
+constexpr bool defer_pushes(int defer) { return defer == kPushShares || defer == kPushSlices; }
+constexpr bool defer_slices(int defer) { return defer == kDeferSlices || defer == kPushSlices; }
 constexpr uint32_t kLLTag = 0x4C4C5701u;      // marks a pushed word as written by the running launch's helper
 WSVD_DEV unsigned long long ll_word(float v) { return ((unsigned long long)kLLTag << 32) | (unsigned long long)__float_as_uint(v); }
 template <int DEFER>
 WSVD_DEV void append_defer_out(const AppendParams& p, size_t i, float v) {
-  if constexpr (DEFER == kPushShares) __hip_atomic_store(p.defer_words + i, ll_word(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if constexpr (defer_pushes(DEFER)) __hip_atomic_store(p.defer_words + i, ll_word(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   else p.defer_out[i] = v;
 }
 
@@ -30,8 +32,8 @@ WSVD_DEV void append_defer_bump(const AppendParams& p, int b, int n) {
 // the lengths and marks the rows as pending.  No ticket, no read-back: 9.8 -> 6.3 us for one sequence of 8 heads, rank 16,
 // d_model 512, where the ticket and the read-back were most of the launch; staging one sequence instead of eight: 5.2 us.
 // BB: sequences per pass (1 for a single sequence: an eighth of the staging and of the products).
-template <int R, int FESZ, int DEFER, int BB>
-WSVD_DEV void append_valu_body(const AppendParams& p, int wg) {
+template <int R, int FESZ, int DEFER, int BB, class Params = AppendParams>
+WSVD_DEV void append_valu_body(Params p, int wg) {
   constexpr int EL = 256 / R;                 // threads along d_model per latent channel
   constexpr int NA = kAppendMaxESL / EL;      // factor elements per thread
   __shared__ __attribute__((aligned(16))) float xs[kAppendMaxESL][BB];
@@ -124,11 +126,13 @@ WSVD_DEV void append_valu_body(const AppendParams& p, int wg) {
 // the rows are bit for bit the append's: fp32 / bf16 latents.  One sequence of 32 heads, rank 32, d_model 4096: 8.0 us
 // against 9.3 us for the launch that finishes the rows itself (four equal slices: 6.9 us, but other bits).
 // kPushShares: kDeferShares inside a launch that attends too (wsvd_step.hip): words for the attention's workgroups.
-// wg: the workgroup's place among the n_wg of its group of sequences.
+// wg: the workgroup's place among the n_wg of its group of sequences.  Params: by value in a kernel of
+// its own (by reference 8 more registers, 0.4 us for 64 sequences), by reference where they are part of a larger kernel argument
+// (a copy of that part goes through scratch memory, 16 us a step instead of 11 for one bf16 sequence).
 // VW: shares of the contraction per wave, each with accumulators of its own, where the launch has fewer waves than the append
 // (the sums are the same: share by share).  A wave asks for the first KB k-steps of all its shares at once.
-template <int R, int NT, int DEFER, int VW = 1>
-WSVD_DEV void append_split_body(const AppendParams& p, int SB, int xs_stride /* elements */, int NP,
+template <int R, int NT, int DEFER, int VW = 1, class Params = AppendParams>
+WSVD_DEV void append_split_body(Params p, int SB, int xs_stride /* elements */, int NP,
                                 unsigned long long* ll /* [units][groups][NP][SB * R] */, int wg, int n_wg, int group, int n_groups,
                                 uint8_t* app_lds) {
   __shared__ int n_loc[32];
@@ -138,9 +142,9 @@ WSVD_DEV void append_split_body(const AppendParams& p, int SB, int xs_stride /* 
   uint16_t* xs = (uint16_t*)app_lds;                            // [SB][xs_stride] hidden states (bf16)
   float (*red)[R + 1] = (float (*)[R + 1])app_lds;              // [NW * SB][R + 1] partial tiles, later [SB][R + 1] rows
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NW = (int)(blockDim.x >> 6) * VW;
-  const int n_roles = DEFER == kDeferSlices ? NP : NP + 1;
+  const int n_roles = defer_slices(DEFER) ? NP : NP + 1;
   const int unit = wg / n_roles, role = wg % n_roles;     // role < NP: helper, NP: finisher
-  const bool finisher = !DEFER && role == NP, first_share = DEFER != kDeferSlices && role == NP;
+  const bool finisher = !DEFER && role == NP, first_share = !defer_slices(DEFER) && role == NP;
   const int pl = unit / p.Hkv, kv = unit % p.Hkv;
   const int b0 = group * SB, nb = min(SB, p.B - b0);
   const int col = lane & 31, g = lane >> 5;
@@ -151,12 +155,12 @@ WSVD_DEV void append_split_body(const AppendParams& p, int SB, int xs_stride /* 
   // ... and, for the finisher that will turn out to be the last one, the lengths it advances on its way out: asked for
   // now, they cost nothing then (nobody writes them before that)
   int n_bump = (finisher && !p.fused) ? p.seq_lens[p.one_seq >= 0 ? p.one_seq : min(tid, p.B - 1)] : 0;
-  if (DEFER && DEFER != kPushShares && wg == 0) n_bump = p.seq_lens[b0 + min(tid, nb - 1)];
+  if (DEFER && !defer_pushes(DEFER) && wg == 0) n_bump = p.seq_lens[b0 + min(tid, nb - 1)];
   const uint16_t* Ap = (const uint16_t*)p.A[pl];
   const uint16_t* xp = (const uint16_t*)p.x;
   // ---- this workgroup's share of the k-steps (16 model dims each), then this wave's share of that
   const int nks = p.E >> 4;
-  const int nks_fin = DEFER == kDeferSlices ? 0 : NP ? (nks + 1) / 2 : nks;     // the finisher's share comes first
+  const int nks_fin = defer_slices(DEFER) ? 0 : NP ? (nks + 1) / 2 : nks;     // the finisher's share comes first
   const int per_helper = NP ? (nks - nks_fin + NP - 1) / NP : 0;
   const int wg_k0 = first_share ? 0 : min(nks, nks_fin + role * per_helper);
   const int wg_k1 = first_share ? nks_fin : min(nks, wg_k0 + per_helper);
@@ -206,8 +210,11 @@ WSVD_DEV void append_split_body(const AppendParams& p, int SB, int xs_stride /* 
       }
     }
     if (first) {
+      if constexpr (VW == 1) { load_a(0, ks0[0]); load_a(1, ks0[0] + KB); }
+      else {
 #pragma unroll
-      for (int v = 0; v < NB; v++) load_a(v, VW == 1 ? ks0[0] + v * KB : ks0[v]);
+        for (int v = 0; v < VW; v++) load_a(v, ks0[v]);
+      }
       first = false; WSVD_STAMP(p.timeline, tl_wg, wave, 1);
     }
 #pragma unroll
@@ -289,7 +296,7 @@ WSVD_DEV void append_split_body(const AppendParams& p, int SB, int xs_stride /* 
       float c = 0.f;
       for (int k = 0; k < NW; k++) c += red[k * SB + row][j];
       if constexpr (DEFER) {
-        const int part = DEFER == kDeferSlices ? role : first_share ? 0 : role + 1;
+        const int part = defer_slices(DEFER) ? role : first_share ? 0 : role + 1;
         append_defer_out<DEFER>(p, (((size_t)part * 2 + pl) * p.B + b0 + row) * ((size_t)p.Hkv * R) + (size_t)kv * R + j, c);
       } else if (!finisher) {
         // push: value and tag in one 8-byte store, written through; nobody waits for it
@@ -319,7 +326,7 @@ WSVD_DEV void append_split_body(const AppendParams& p, int SB, int xs_stride /* 
     }
   }
   if constexpr (DEFER) {
-    if (DEFER != kPushShares && wg == 0 && tid < nb) append_defer_bump(p, b0 + tid, n_bump);
+    if (!defer_pushes(DEFER) && wg == 0 && tid < nb) append_defer_bump(p, b0 + tid, n_bump);
     WSVD_STAMP(p.timeline, tl_wg, wave, 5);
     return;
   }

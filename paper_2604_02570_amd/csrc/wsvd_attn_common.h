@@ -55,10 +55,10 @@ struct AttnParams {
   const int* pending;
   int n_parts;
   long part_stride;
+  int out_bf16;              // out holds bf16 (round to nearest even) instead of fp32; never for the latent-space output
   // the decode step as one launch: the partial sums as {value, tag} words of the same layout, [part][plane][B][new_ld], plane
   // part_stride / 2 words apart
   unsigned long long* new_words;
-  int out_bf16;              // out holds bf16 (round to nearest even) instead of fp32; never for the latent-space output
 };
 
 // element idx (pair idx, idx + 1) of the output, in the layer's output format

@@ -19,7 +19,7 @@
 #include <type_traits>
 
 #include "wsvd_attn_common.h"
-#include "wsvd_append_body.h"
+#include "wsvd_append_split.h"
 #include "wsvd_internal.h"
 
 template <int R, bool I4>
@@ -252,7 +252,11 @@ WSVD_DEV void split_fp16_pair(float x, float scale, _Float16& hi, _Float16& lo) 
 // NEWROW: the second launch of the decode step.  The projection launch before it has advanced the lengths and left the
 // new token's latents as partial sums; the workgroup whose chunk holds a sequence's last row sums them, quantises and
 // stores the row (as the append would have) and patches it into the registers of the wave that consumes its tile.
-template <int R, int G, bool I4, int NT, bool FUSED, int ROPE_D = 0, bool LATENT = false, bool PAGED = false, bool NEWROW = false,
+// NEWROW = kRowWords: the step as one launch (k_step_i8).  The lengths are still the old ones; the partial sums arrive as
+// {value, tag} words while the chunk is streamed, the wave that makes the row takes them in the middle of its stream if they are
+// there and waits for them at its end otherwise.
+enum { kNoRow = 0, kRowPending = 1, kRowWords = 2 };
+template <int R, int G, bool I4, int NT, bool FUSED, int ROPE_D = 0, bool LATENT = false, bool PAGED = false, int NEWROW = kNoRow,
           bool TABLE = false>
 WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABLE ? 2 : ROPE_D != 0 || LATENT)>& sh, const int cx,
                              const int cy, const int cz, RopeShared<R, G, (ROPE_D ? ROPE_D : 64)>* rs = nullptr, const RopeArgs* ra = nullptr,
@@ -265,7 +269,7 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
   static_assert(!LATENT || (!ROPE && !FUSED), "latent-query variant: stand-alone launch, no rotation");
   static_assert(!I4 || R == 32, "int4 latents: rank 32 only");
   static_assert(!PAGED || (!ROPE && !LATENT && !FUSED), "paged cache: the plain decode attention");
-  static_assert(!NEWROW || (!ROPE && !LATENT && !FUSED && !PAGED && !I4), "deferred row: the plain int8 decode attention");
+  static_assert(NEWROW == kNoRow || (!ROPE && !LATENT && !FUSED && !PAGED && !I4), "deferred row: the plain int8 decode attention");
   static_assert(G >= 1 && G <= 4, "paired-block kernel handles up to 4 query heads per kv head");
   constexpr int KK = R / 32;
   constexpr int NWMAX = NT / 64;
@@ -276,8 +280,10 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
 
   // scalar loads first: issued ahead of the flood of vector loads they come back quickly, and nothing needs them
   // until the tile loop
-  const int n_raw = p.seq_lens[cz];
-  [[maybe_unused]] const int pend_raw = NEWROW ? p.pending[cz] : 0;
+  const int n_old = p.seq_lens[cz];
+  const bool fits = NEWROW == kRowWords && n_old >= 0 && n_old < p.t_cap;
+  const int n_raw = n_old + (fits ? 1 : 0);
+  [[maybe_unused]] const int pend_raw = NEWROW == kRowPending ? p.pending[cz] : fits ? 1 : 0;
   const uint32_t qs_raw = q_scale_raw(p, cz);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, NW = blockDim.x >> 6;
   // NEWROW: the row stored by this launch (K | V codes and scales): written by wave 1 or 2, read by the
@@ -353,6 +359,77 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
   // rank 32: lanes 0..31 carry the K row's dims, lanes 32..63 the V row's (np_a); rank 64: np_a = K, np_b = V
   [[maybe_unused]] float np_a[NEWROW ? MAXP : 1], np_b[NEWROW && R == 64 ? MAXP : 1];
   [[maybe_unused]] bool nr_mine = false;
+  // The wave that makes the new row: of the chunk that holds it, wave 1, or wave 2 when wave 1 is the row's tile's consumer.  The
+  // early waves of a workgroup get their tiles first and finish first, so the row's work costs the workgroup nothing there
+  // (on the last wave it made that wave the workgroup's last by 0.8 us).  (wave-uniform)
+  [[maybe_unused]] auto makes_row = [&] {
+    if (wave != 1 && wave != 2) return false;
+    const int row = max(n_raw, 1) - 1, ct = p.chunk_rows >> 6, cyo = min((min(row, p.t_cap - 1) >> 6) / ct, p.n_chunks - 1);
+    const int consumer = ((row >> 6) - cyo * ct) % NW;
+    return (NEWROW == kRowWords || (pend_raw != 0 && n_raw >= 1 && n_raw <= p.t_cap)) && (int)cy == cyo && wave == (consumer == 1 ? 2 : 1);
+  };
+  // The cache row for later launches (the rule and the layout of the append kernels' row store), and a copy in
+  // LDS for this one: the tile that holds the row is fetched like any other, possibly before these stores land;
+  // its consumer overwrites the row's bytes in registers.  One pass with both rows side by side at rank 32.
+  [[maybe_unused]] auto make_row = [&](int row) {
+    const int j = lane & (R - 1);
+#pragma unroll
+    for (int pass = 0; pass < (R == 32 ? 1 : 2); pass++) {
+      const int pl = R == 32 ? (lane >> 5) : pass;
+      float c = 0.f;
+#pragma unroll
+      for (int sidx = 0; sidx < MAXP; sidx++)                    // slice order
+        c += sidx < p.n_parts ? (pass == 0 ? np_a[sidx] : np_b[R == 64 ? sidx : 0]) : 0.f;
+      const float a = R == 64 ? wave_max(fabsf(c)) : half_max(fabsf(c), lane);
+      uint16_t sh16 = 0x3C00u;
+      if (a != 0.f) sh16 = guard_scale_f16(a / 127.0f);
+      const float sc = f16_bits_to_f32(sh16);
+      const uint8_t code = (uint8_t)(int8_t)(int)fminf(fmaxf(__builtin_rintf(c / sc), -127.f), 127.f);
+      uint8_t* plane = const_cast<uint8_t*>(pl ? p.v_codes : p.k_codes) + ph * plane_bytes;
+      plane[pl ? i8_v_offset(row, j, R) : i8_k_offset(row, j, R)] = code;
+      if (j == 0) const_cast<uint16_t*>(pl ? p.v_meta : p.k_meta)[ph * (size_t)p.t_cap + row] = sh16;
+      new_codes[pl][j] = code;
+      if (j == 0) new_scale[pl] = sh16;
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (lane == 0) __hip_atomic_store(&new_ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  };
+  // kRowWords: the words of the row's partial sums, looked at once, or until they carry the tag (a bounded wait for workgroups
+  // with lower ids); they are cleared for the next launch and, where the sequence has room, the row is made.
+  [[maybe_unused]] auto take_words = [&](bool wait) {
+    unsigned long long* const src = p.new_words + (R == 32 && lane >= 32 ? p.part_stride / 2 : 0) + (size_t)cz * p.new_ld + (size_t)cx * R + (lane & (R - 1));
+    unsigned long long wa[MAXP], wb[R == 64 ? MAXP : 1];
+    int budget = 1 << 16;
+    for (;;) {
+      bool all = true;
+#pragma unroll
+      for (int i = 0; i < MAXP; i++) {
+        const size_t po = (size_t)min(i, p.n_parts - 1) * p.part_stride;
+        wa[i] = __hip_atomic_load(src + po, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (R == 64) wb[i] = __hip_atomic_load(src + po + p.part_stride / 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+#pragma unroll
+      for (int i = 0; i < MAXP; i++) {
+        all = all && (uint32_t)(wa[i] >> 32) == kLLTag;
+        if constexpr (R == 64) all = all && (uint32_t)(wb[i] >> 32) == kLLTag;
+      }
+      if (__builtin_amdgcn_ballot_w64(!all) == 0) break;
+      if (!wait) return false;
+      if (--budget == 0) { if (lane == 0) atomicExch(p.err_word, (int)WSVD_E_HIP); break; }      // never seen; keeps the wait finite
+      __builtin_amdgcn_s_sleep(1);
+    }
+#pragma unroll
+    for (int i = 0; i < MAXP; i++) {
+      np_a[i] = __uint_as_float((uint32_t)wa[i]);
+      if constexpr (R == 64) np_b[i] = __uint_as_float((uint32_t)wb[i]);
+      if (i < p.n_parts) {
+        __hip_atomic_store(src + (size_t)i * p.part_stride, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if constexpr (R == 64) __hip_atomic_store(src + (size_t)i * p.part_stride + p.part_stride / 2, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    if (fits) make_row(n_raw - 1);
+    return true;
+  };
   if constexpr (!STAGED) {
     // Query absorption q~ = c_scale * B_K q on the matrix cores, by the workgroup's first wave alone, operands
     // straight from memory (no staging in LDS): 8-16 KB of B_K and the queries are the only small loads of the
@@ -391,7 +468,7 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
     // NEWROW: waves 1 and 2 ask for the partial sums of their (sequence, kv head) now, ahead of the tiles and
     // whether or not the row turns out to be this workgroup's (the addresses do not depend on the length).  They were
     // written by the launch before this one, on other XCDs: they come from memory, not from this XCD's L2
-    if constexpr (NEWROW) {
+    if constexpr (NEWROW == kRowPending) {
       if (wave == 1 || wave == 2) {
         const float* src = (R == 32 && lane >= 32) ? p.new_v : p.new_k;
         const size_t o = (size_t)cz * p.new_ld + (size_t)cx * R + (lane & (R - 1));
@@ -508,50 +585,26 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
     }   // leader
     __syncthreads();
     WSVD_STAMP(tl, tl_wg, wave, 3);
-    if constexpr (NEWROW) {
+    if constexpr (NEWROW == kRowPending) {
       // The row, by one wave, off everybody else's path: the other waves go on to their tiles, the wave that
       // consumes the row's tile (its last one) looks at new_ready when it gets there.
       // (A sequence longer than the caller's bound is reported by decode_work; its row is still stored, by the last chunk.)
-      // The producer is wave 1, or wave 2 when wave 1 is the tile's consumer: both have asked for the partial sums; the
-      // early waves of a workgroup get their tiles first and finish first, so the row's work costs the workgroup nothing
-      // there (on the last wave it made that wave the workgroup's last by 0.8 us).
-      if (wave == 1 || wave == 2) {
-        const int row = n_raw - 1, ct = p.chunk_rows >> 6, cyo = min((row >> 6) / ct, p.n_chunks - 1);
-        const int consumer = ((row >> 6) - cyo * ct) % NW;
-        if (pend_raw != 0 && n_raw >= 1 && n_raw <= p.t_cap && (int)cy == cyo && wave == (consumer == 1 ? 2 : 1)) {       // wave-uniform
-          // (the empty statements pin the first use of the loaded values here: hoisted to the loads, the first
-          // addition made the whole workgroup wait for them in front of the barrier above)
+      if (makes_row()) {
+        // (the empty statements pin the first use of the loaded values here: hoisted to the loads, the first
+        // addition made the whole workgroup wait for them in front of the barrier above)
 #pragma unroll
-          for (int sidx = 0; sidx < MAXP; sidx++) {
-            asm volatile("" : "+v"(np_a[sidx]));
-            if constexpr (R == 64) asm volatile("" : "+v"(np_b[sidx]));
-          }
-          // The cache row for later launches (the rule and the layout of the append kernels' row store), and a copy in
-          // LDS for this one: the tile that holds the row is fetched like any other, possibly before these stores land;
-          // its consumer overwrites the row's bytes in registers.  One pass with both rows side by side at rank 32.
-          const int j = lane & (R - 1);
-#pragma unroll
-          for (int pass = 0; pass < (R == 32 ? 1 : 2); pass++) {
-            const int pl = R == 32 ? (lane >> 5) : pass;
-            float c = 0.f;
-#pragma unroll
-            for (int sidx = 0; sidx < MAXP; sidx++)                    // slice order
-              c += sidx < p.n_parts ? (pass == 0 ? np_a[sidx] : np_b[R == 64 ? sidx : 0]) : 0.f;
-            const float a = R == 64 ? wave_max(fabsf(c)) : half_max(fabsf(c), lane);
-            uint16_t sh16 = 0x3C00u;
-            if (a != 0.f) sh16 = guard_scale_f16(a / 127.0f);
-            const float sc = f16_bits_to_f32(sh16);
-            const uint8_t code = (uint8_t)(int8_t)(int)fminf(fmaxf(__builtin_rintf(c / sc), -127.f), 127.f);
-            uint8_t* plane = const_cast<uint8_t*>(pl ? p.v_codes : p.k_codes) + ph * plane_bytes;
-            plane[pl ? i8_v_offset(row, j, R) : i8_k_offset(row, j, R)] = code;
-            if (j == 0) const_cast<uint16_t*>(pl ? p.v_meta : p.k_meta)[ph * (size_t)p.t_cap + row] = sh16;
-            new_codes[pl][j] = code;
-            if (j == 0) new_scale[pl] = sh16;
-          }
-          __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-          if (lane == 0) __hip_atomic_store(&new_ready, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        for (int sidx = 0; sidx < MAXP; sidx++) {
+          asm volatile("" : "+v"(np_a[sidx]));
+          if constexpr (R == 64) asm volatile("" : "+v"(np_b[sidx]));
         }
+        make_row(n_raw - 1);
       }
+    }
+    if constexpr (NEWROW == kRowWords) {
+      // the length is here (the barrier is behind its use): this workgroup has read it
+      int seen = n_old;
+      asm volatile("" : "+s"(seen)::"memory");
+      if (tid == 0) __hip_atomic_fetch_add(p.done + cz, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   } else {
   const int fac16 = R * p.d * 2 / 16;
@@ -769,6 +822,7 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
   const float qs = q_scale_value(p, cz, qs_raw);
   const bool has_new = FUSED && n_raw >= 0 && n_raw < p.t_cap;          // the row being appended by this launch
   const WorkItem w = decode_work(p, n_raw + (has_new ? 1 : 0), cx, cy, cz);
+  if (NEWROW == kRowWords && w.n == 0 && makes_row()) take_words(true);       // (a negative length: the words go, no row is made)
   if (w.n == 0) { write_zero_outputs(p, w); return; }
   if (!w.active) return;
   const int new_tile = n_raw >> 6;                                      // tile of the new row (its chunk's last tile)
@@ -1144,6 +1198,10 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
     }
     __builtin_amdgcn_sched_barrier(0);     // the loads are issued here, not where their values are first used
   }
+  [[maybe_unused]] bool row_open = NEWROW == kRowWords && makes_row();
+  if constexpr (NEWROW == kRowWords) {
+    if (row_open && n > DEPTH) row_open = !take_words(false);
+  }
 #pragma unroll
   for (int i = 0; i < DEPTH; i++) {
     if (done + i < n) {
@@ -1155,6 +1213,9 @@ WSVD_DEV void attn_mfma_body(const AttnParams& p, AttnMfmaShared<R, G, NT, (TABL
 #pragma unroll
   for (int i = 0; i < DEPTH; i++)
     if (done + i < n) compute(kNoRefill, buf[i], tile_at(done + i), 0);
+  if constexpr (NEWROW == kRowWords) {
+    if (row_open) take_words(true);
+  }
 
   if (FUSED) {
     // the tile with the row appended by this launch, taken by the wave whose turn it would have been
@@ -1263,7 +1324,7 @@ __global__ __launch_bounds__(NT) void k_attn_mfma(AttnParams p) {
 template <int R, int G, int NT>
 __global__ __launch_bounds__(NT) void k_attn_mfma_newrow(AttnParams p) {
   __shared__ AttnMfmaShared<R, G, NT, 0> sh;
-  attn_mfma_body<R, G, false, NT, false, 0, false, false, true>(p, sh, blockIdx.x, blockIdx.y, blockIdx.z);
+  attn_mfma_body<R, G, false, NT, false, 0, false, false, kRowPending>(p, sh, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Q latent in, latent-space output out (Section 3.4: the Q latent's up-projection B_Q meets B_K^T in one small matrix
@@ -2088,6 +2149,95 @@ hipError_t wsvd_launch_attn_rope(const wsvd_ctx* ctx, const wsvd_layer_desc& d, 
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
+}
+
+// ---------------------------------------------------------------- the int8 decode step as one launch
+// Workgroups [0, n_proj) project (slices of d_model, pushed as words), the others attend (kRowWords).  Bound: HBM where the caches
+// are large; the projection's factors and its chain of trips travel beside the cache stream instead of in front of it.  All
+// waits are for workgroups with lower ids, and bounded: a row's maker for the projection, a sequence's last workgroup for the word
+// of the others that they have read the length, which it then advances.
+struct I8StepParams {
+  AttnParams a;
+  AppendParams ap;
+  int proj_x, groups;          // projection workgroups per group of sequences; groups
+  int sb, xs_stride, slices;   // of append_split_body
+};
+template <int R, int G, int NT>
+__global__ __launch_bounds__(NT) void k_step_i8(I8StepParams p) {
+  extern __shared__ __align__(16) uint8_t app_lds[];
+  __shared__ AttnMfmaShared<R, G, NT, 0> sh;
+  const int n_proj = p.proj_x * p.groups;
+  if ((int)blockIdx.x < n_proj) {
+    append_split_body<R, NT, kPushSlices, 1, const AppendParams&>(p.ap, p.sb, p.xs_stride, p.slices, nullptr, (int)blockIdx.x % p.proj_x, p.proj_x,
+                                          (int)blockIdx.x / p.proj_x, p.groups, app_lds);
+    return;
+  }
+  const AttnParams& a = p.a;
+  const int id = (int)blockIdx.x - n_proj, kv = id % a.Hkv, chunk = id / a.Hkv % a.n_chunks, b = id / (a.Hkv * a.n_chunks);
+  attn_mfma_body<R, G, false, NT, false, 0, false, false, kRowWords>(a, sh, kv, chunk, b);
+  if (kv != a.Hkv - 1 || chunk != a.n_chunks - 1 || threadIdx.x != 0) return;
+  const int want = a.Hkv * a.n_chunks;
+  int budget = 1 << 16;
+  while (__hip_atomic_load(a.done + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != want && --budget > 0) __builtin_amdgcn_s_sleep(8);
+  if (budget == 0) atomicExch(a.err_word, (int)WSVD_E_HIP);      // never seen; keeps the wait finite
+  __hip_atomic_store(a.done + b, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int n = a.seq_lens[b];
+  if (n >= 0 && n < a.t_cap) p.ap.seq_lens[b] = n + 1;
+  else atomicExch(a.err_word, (int)WSVD_E_CAPACITY);
+}
+
+template <int R, int NT>
+static hipError_t launch_step_i8(const I8StepParams& p, size_t lds, hipStream_t s) {
+  const dim3 grid((unsigned)(p.proj_x * p.groups + p.a.Hkv * p.a.n_chunks * p.a.B));
+  switch (p.a.G) {
+    case 1: hipLaunchKernelGGL((k_step_i8<R, 1, NT>), grid, dim3(NT), lds, s, p); break;
+    case 2: hipLaunchKernelGGL((k_step_i8<R, 2, NT>), grid, dim3(NT), lds, s, p); break;
+    case 3: hipLaunchKernelGGL((k_step_i8<R, 3, NT>), grid, dim3(NT), lds, s, p); break;
+    case 4: hipLaunchKernelGGL((k_step_i8<R, 4, NT>), grid, dim3(NT), lds, s, p); break;
+    default: return hipErrorNotSupported;
+  }
+  return hipGetLastError();
+}
+
+// One launch or two.  One where all workgroups have their places from the start: two per CU at rank 32 with one query head (128
+// registers, 8 waves), of which the projection's first ones leave early, one per CU otherwise.  Beyond, attention workgroups
+// wait for the projection's to leave.  us a step, one launch / two (cold layers):
+//   1 x 2500 rows, 32 heads, rank 32, d_model 4096   12.4 / 16.2     24 x 900, the same (beyond)     28.3 / 22.3
+//   4 x 2500, the same                               14.8 / 17.3     16 x 2500                       27.5 / 27.0
+//   1 x 900, the same                                11.8 / 13.4     8 x 250                         14.1 / 13.6
+//   32 x 900, 8 heads, rank 32, d_model 512          11.8 / 12.4     1 x 250, rank 64                19.6 / 18.0
+// Over 195 sizes on this side of the lines the median is 1.22 x, the worst 1.00.
+static bool step_i8_one_launch(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int proj, int attend) {
+  const bool slim = d.rank == 32 && d.n_q_heads == d.n_kv_heads;
+  return 2 * (proj + attend) <= (slim ? 3 : 2) * ctx->n_cu;
+}
+
+hipError_t wsvd_launch_step_i8(wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* x, const void* A_K, const void* A_V, const void* q,
+                               const void* q_scale, const void* B_K, const void* B_V, const wsvd_cache& cache, int max_seq_len,
+                               void* out, hipStream_t s) {
+  constexpr int NT = 512;
+  if (!wsvd_step_deferred_ok(d)) return hipErrorNotSupported;
+  I8StepParams p = {};
+  dim3 grid;
+  int threads;
+  wsvd_attn_plan(ctx, d, q, q_scale, B_K, B_V, cache, max_seq_len, out, p.a, grid, threads, NT);
+  wsvd_append_params(ctx, d, x, nullptr, A_K, A_V, cache, p.ap);
+  if (p.a.timeline || p.ap.timeline) return hipErrorNotSupported;      // (profiling build: the stamps are the two launches')
+  size_t lds = 0;
+  wsvd_append_project_shape(ctx, d, NT / 64, &p.slices, &p.sb, &p.xs_stride, &p.groups, &lds);
+  if (lds > (size_t)48 * 1024) return hipErrorNotSupported;
+  p.proj_x = 2 * d.n_kv_heads * p.slices;
+  if (ctx->opt.step_launches == 0 && !step_i8_one_launch(ctx, d, p.proj_x * p.groups, (int)(grid.x * grid.y * grid.z))) return hipErrorNotSupported;
+  const size_t plane = (size_t)d.batch * d.n_kv_heads * d.rank, words = (size_t)p.slices * 2 * plane;
+  const size_t split = p.a.n_chunks > 1 ? (size_t)d.batch * d.n_q_heads * p.a.n_chunks * (d.rank + 2) : 0;
+  if (split + words > wsvd_zero_words(d)) return hipErrorNotSupported;
+  p.a.n_parts = p.slices;
+  p.a.new_words = p.a.partials + split;
+  p.ap.defer_words = p.a.new_words;
+  p.a.new_ld = (long)d.n_kv_heads * d.rank;
+  p.a.part_stride = (long)(2 * plane);
+  p.a.done = p.a.tickets;
+  return d.rank == 32 ? launch_step_i8<32, NT>(p, lds, s) : launch_step_i8<64, NT>(p, lds, s);
 }
 
 // ---------------------------------------------------------------- fused decode step: append + attention in one launch

@@ -19,7 +19,7 @@ struct wsvd_options {
   int prefill_tiled = 0;    // the tiled prefill kernels also for small calls
   int project_shape = 0;    // kernel of the tiled prefill projection (0 = automatic)
   int step_deferred = 1;    // wsvd_decode_step: projection launch + attention launch that finishes the row: 1 where supported, 2 that or UNSUPPORTED
-  int step_launches = 0;    // the fp32 / bf16 step: 0 one launch or two by size, 1 one wherever it exists, 2 never one
+  int step_launches = 0;    // the decode step: 0 one launch or two by size, 1 one wherever it exists, 2 never one
   int timeline_kernel = 0;  // profiling build, wsvd_decode_step: whose stamps are recorded: 0 the attention launch's, 1 the projection launch's
   int step_slices = 0;      // d_model slices of that projection launch (0 = automatic)
 };
@@ -109,6 +109,10 @@ hipError_t wsvd_launch_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc& d, cons
 hipError_t wsvd_launch_step_float(wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* x, const void* A_K, const void* A_V, const void* q,
                                   const void* q_scale, const void* B_K, const void* B_V, const wsvd_cache& cache, int max_seq_len,
                                   void* out, hipStream_t s);
+hipError_t wsvd_launch_step_i8(wsvd_ctx* ctx, const wsvd_layer_desc& d, const void* x, const void* A_K, const void* A_V, const void* q,
+                               const void* q_scale, const void* B_K, const void* B_V, const wsvd_cache& cache, int max_seq_len,
+                               void* out, hipStream_t s);
+void wsvd_append_project_shape(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int waves, int* slices, int* sb, int* stride, int* groups, size_t* lds);
 bool wsvd_append_step_shape(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int waves, int* helpers, int* xs_stride, size_t* lds);
 hipError_t wsvd_launch_linear_w4a8(const int8_t* x, const void* x_scale, const void* w_i4, const void* w_scale, int64_t M,
                                    int64_t K, int64_t N, float* out, int64_t n_first, float* out2, bool direct, hipStream_t s);

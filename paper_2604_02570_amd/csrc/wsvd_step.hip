@@ -46,12 +46,12 @@ WSVD_DEV void step_attend(const FloatStepParams& p) {
 template <int R, int G, int NT, int VW>
 __global__ __launch_bounds__(NT) void k_step_bf16(FloatStepParams p) {
   extern __shared__ __align__(16) uint8_t app_lds[];
-  if ((int)blockIdx.x < p.n_proj) append_split_body<R, NT, kPushShares, VW>(p.ap, p.ap.B, p.xs_stride, p.helpers, nullptr, (int)blockIdx.x, p.n_proj, 0, 1, app_lds);
+  if ((int)blockIdx.x < p.n_proj) append_split_body<R, NT, kPushShares, VW, const AppendParams&>(p.ap, p.ap.B, p.xs_stride, p.helpers, nullptr, (int)blockIdx.x, p.n_proj, 0, 1, app_lds);
   else step_attend<2, R, G>(p);
 }
 template <int R, int G, int BB>
 __global__ __launch_bounds__(256) void k_step_f32(FloatStepParams p) {
-  if ((int)blockIdx.x < p.n_proj) append_valu_body<R, 4, kPushShares, BB>(p.ap, (int)blockIdx.x);
+  if ((int)blockIdx.x < p.n_proj) append_valu_body<R, 4, kPushShares, BB, const AppendParams&>(p.ap, (int)blockIdx.x);
   else step_attend<4, R, G>(p);
 }
 

@@ -1,4 +1,4 @@
-"""wsvd_decode_step over fp32 and bf16 latents: the projection launch leaves partial sums, the attention launch sums them,
+"""wsvd_decode_step over fp32 and bf16 latents, and its one-launch form over int8 ones too: the projection launch leaves partial sums, the attention launch sums them,
 rounds and stores the row and attends to it.  Rows and outputs against the oracle where the row starts or ends a chunk, is
 the first one ever, or does not fit any more; more partial sums than the kernel keeps in flight; small workspaces."""
 import numpy as np
@@ -85,22 +85,32 @@ def test_step_rows_at_chunk_edges(name, over):
 
 ONE_LAUNCH = [("c1", dict()), ("c1", dict(rank=32, n_q_heads=6, n_kv_heads=2, d_head=128, d_model=1536)), ("c1", dict(rank=64, n_q_heads=7, n_kv_heads=1, d_head=128)),
               ("c2_small", dict()), ("c2_small", dict(rank=16, n_q_heads=4, n_kv_heads=1)), ("c2_small", dict(rank=64, n_q_heads=12, n_kv_heads=4, d_model=1024)),
-              ("c2_small", dict(rank=32, n_q_heads=7, n_kv_heads=1, d_model=1088)), ("c2_small", dict(d_model=4096, n_q_heads=32, n_kv_heads=32))]
+              ("c2_small", dict(rank=32, n_q_heads=7, n_kv_heads=1, d_model=1088)), ("c2_small", dict(d_model=4096, n_q_heads=32, n_kv_heads=32)),
+              ("c3_small", dict()), ("c3_small", dict(rank=64, n_q_heads=8, n_kv_heads=4)), ("c3_small", dict(n_q_heads=8, n_kv_heads=2, d_model=1088))]
 
 
 @pytest.mark.parametrize("lens", [[0], [1087], [1024, -1, 1088], [0, 1, 63, 64, 256, 1023, 1025]], ids=lambda v: "-".join(map(str, v)))
 @pytest.mark.parametrize("name,over", ONE_LAUNCH, ids=[f"{n}-{'-'.join(f'{k}{v}' for k, v in o.items())}" for n, o in ONE_LAUNCH])
 def test_one_launch_equals_two(name, over, lens):
-    """Projection and attention in one launch against the two launches, bit for bit: outputs, rows, lengths and the status word;
-    first row ever, chunk edges, a full and a negative length; three steps on, and the words are zero again after each."""
+    """Projection and attention in one launch against the two launches: rows, lengths and the status word bit for bit, the outputs
+    too over fp32 / bf16 latents; over int8 ones the waves divide the tiles differently, and either is within 4e-6 of the exact
+    result (21-bit operands).  First row ever, chunk edges, a full and a negative length; three steps on, and the words are zero
+    again after each."""
     c = build_case(name, **{**dict(batch=len(lens), context=90, steps=1, extra_cap=0), **over})
     sp, t_cap = c.sp, 1088
     L = layer_for(c, t_cap=t_cap)
     g = torch.Generator(device="cuda").manual_seed(3)
-    dt = torch.float32 if sp.latent_dtype == "f32" else torch.bfloat16
-    for t in (L.k_codes, L.v_codes):
-        t.view(dt).copy_(torch.randn(t.view(dt).shape, device="cuda", generator=g))
-    planes = [t.clone() for t in (L.k_codes, L.v_codes)]
+    cache = (L.k_codes, L.v_codes, L.k_meta, L.v_meta)
+    if sp.latent_dtype == "i8":
+        for t in cache[:2]:
+            t.view(torch.int8).copy_(torch.randint(-127, 128, t.shape, device="cuda", generator=g))
+        for t in cache[2:]:
+            t.view(torch.float16).copy_(0.01 + 0.02 * torch.rand(t.view(torch.float16).shape, device="cuda", generator=g))
+    else:
+        dt = torch.float32 if sp.latent_dtype == "f32" else torch.bfloat16
+        for t in cache[:2]:
+            t.view(dt).copy_(torch.randn(t.view(dt).shape, device="cuda", generator=g))
+    planes = [t.clone() for t in cache]
     x = WI.bf16_exact(c.x_new[0]) if sp.factor_dtype == "bf16" else c.x_new[0]
     qd, qs, _ = q_to_device(c.q32[0], sp.q_dtype)
     args = (as_dtype_dev(x, sp.factor_dtype), L.pack_A(c.AK, sp.factor_dtype), L.pack_A(c.AV, sp.factor_dtype), qd, qs,
@@ -109,7 +119,7 @@ def test_one_launch_equals_two(name, over, lens):
     for launches in (2, 1):
         W.wsvd_ctx_set_option(L.ctx, "step_launches", launches)
         W.wsvd_ctx_set_option(L.ctx, "min_chunk", 0)
-        for t, v in zip((L.k_codes, L.v_codes), planes):
+        for t, v in zip(cache, planes):
             t.copy_(v)
         L.seq_lens.copy_(torch.tensor(lens, dtype=torch.int32))
         W.wsvd_set_workspace(L.ctx, L.ws)
@@ -119,10 +129,11 @@ def test_one_launch_equals_two(name, over, lens):
             steps.append((out, st, L.seq_lens.cpu().clone()))
             if launches == 1:
                 assert not L.ws.any(), "words left behind"
-        results.append((steps, [t.clone() for t in (L.k_codes, L.v_codes)]))
+        results.append((steps, [t.clone() for t in cache]))
     (two, two_planes), (one, one_planes) = results
     for (a, sa, na), (b, sb, nb) in zip(two, one):
-        assert (a == b).all() and sa == sb and (na == nb).all()
+        assert sa == sb and (na == nb).all()
+        assert np.linalg.norm(a - b) <= 1e-5 * np.linalg.norm(a) if sp.latent_dtype == "i8" else (a == b).all()
     assert all((a.view(torch.uint8) == b.view(torch.uint8)).all() for a, b in zip(two_planes, one_planes))
     L.close()
 
