@@ -154,8 +154,9 @@ wsvd_status wsvd_create(wsvd_ctx** out, int device_ordinal) {
   c->epoch = 0;
   c->timeline = nullptr;
   c->timeline_bytes = 0;
-  if (hipMalloc((void**)&c->err_word, 4) != hipSuccess) { delete c; return WSVD_E_HIP; }
-  if (hipMemset(c->err_word, 0, 4) != hipSuccess) { (void)hipFree(c->err_word); delete c; return WSVD_E_HIP; }
+  if (hipMalloc((void**)&c->err_word, kCtxDeviceBytes) != hipSuccess) { delete c; return WSVD_E_HIP; }
+  if (hipMemset(c->err_word, 0, kCtxDeviceBytes) != hipSuccess) { (void)hipFree(c->err_word); delete c; return WSVD_E_HIP; }
+  c->readers = c->err_word + kCtxReadersInt;
   if (static_scratch_for_device(device_ordinal, &c->static_scratch) != hipSuccess) { (void)hipFree(c->err_word); delete c; return WSVD_E_HIP; }
   *out = c;
   return WSVD_OK;

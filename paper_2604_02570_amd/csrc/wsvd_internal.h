@@ -28,7 +28,8 @@ struct wsvd_ctx {
   wsvd_options opt;
   int device;
   int n_cu;
-  int* err_word;     // device, 4 bytes
+  int* err_word;     // device memory of the context: the status word ...
+  int* readers;      // ... and, kCtxReadersInt ints on, the prompt projection's counters of workgroups (zero between launches)
   void* ws;          // caller-owned workspace
   size_t ws_bytes;
   int epoch;         // number of fused decode steps launched so far (value the append workgroups publish)
@@ -36,6 +37,8 @@ struct wsvd_ctx {
   long long* timeline;    // profiling build: caller's stamp buffer (wsvd_timeline_set_buffer), else null
   size_t timeline_bytes;
 };
+
+constexpr int kCtxReadersInt = 32, kCtxDeviceBytes = 4 * (32 + 9 * 32);
 
 struct AttnParams;
 struct AppendParams;

@@ -35,7 +35,52 @@ struct ProjectParams {
   // layout of a contiguous plane; block_table [B][max_pages]
   const int* block_table;
   int page_rows, max_pages, n_pages;
+  // tile kernels: workgroups of this launch that hold the lengths they need (the context's counter, zero between launches), and
+  // what the last of them advances
+  int* readers;
+  int n_seq, even_only;
 };
+
+// The lengths move on by the rows that fitted (sequence i of the call).  int4: nothing was stored for a sequence that starts on
+// an odd row.
+WSVD_DEV void project_bump(int* seq_lens, int i, int n_tok, int t_cap, int* err_word, int even_only) {
+  const int n0 = seq_lens[i];
+  if (even_only && n0 >= 0 && (n0 & 1)) {
+    atomicExch(err_word, (int)WSVD_E_SHAPE);
+    return;
+  }
+  if (n0 >= 0) seq_lens[i] = min(n0 + n_tok, t_cap);
+  if (n0 < 0 || n0 + n_tok > t_cap) atomicExch(err_word, (int)WSVD_E_CAPACITY);
+}
+// The tile kernels advance the lengths themselves: every workgroup counts itself once all its waves hold the lengths they store
+// by (the barrier in front), asks for the count so far, and looks at the answer when its rows are stored; the last one to
+// have counted advances them.  Eight counters a line apart, and one for whoever fills one of them: on a single word 512
+// workgroups that end together waited for each other's additions, 0.7 us.  2 x 35 tokens 15.5 -> 14.5 us, 1 x 200 15.8 -> 15.1,
+// 3 x 333 30.7 -> 29.4 (32 heads of rank 32, with the clearing of the lengths before it).
+constexpr int kReaderGap = 32;                                           // ints between two counters
+template <int N>
+WSVD_DEV void project_hold(const int (&n0)[N]) {                         // the lengths are here (in front of a barrier)
+#pragma unroll
+  for (int i = 0; i < N; i++) asm volatile("" ::"v"(n0[i]) : "memory");
+}
+WSVD_DEV int project_count(const ProjectParams& p) {
+  int seen = -1;
+  if (threadIdx.x == 0) seen = __hip_atomic_fetch_add(p.readers + kReaderGap * (1 + (blockIdx.x & 7)), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return seen;
+}
+WSVD_DEV void project_advance(const ProjectParams& p, int seen) {        // seen: of the workgroup's first lane; waves 1.. hold -1
+  const int n = (int)gridDim.x, g = (int)(blockIdx.x & 7);
+  if (__builtin_amdgcn_readfirstlane(seen) != (n + 7 - g) / 8 - 1) return;
+  const int lane = lane_number();
+  int last = 0;
+  if (lane == 0) {
+    __hip_atomic_store(p.readers + kReaderGap * (1 + g), 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    last = __hip_atomic_fetch_add(p.readers, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == min(n, 8) - 1;
+    if (last) __hip_atomic_store(p.readers, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (__builtin_amdgcn_readfirstlane(last) == 0) return;
+  for (int i = lane; i < p.n_seq; i += 64) project_bump(p.seq_lens, p.seq0 + i, p.n_tok, p.t_cap, p.err_word, p.even_only);
+}
 
 // Where row t of (sequence, kv head) lives: its plane (row_bytes per row), its row inside that plane, the index of its
 // metadata entry.  Paged: a table entry outside the pools is reported and the row is not stored (ok = false).
@@ -317,6 +362,7 @@ __global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
   for (int j = 0; j < 2 * NLD; j++) fetch1(j, 0);
 #pragma unroll
   for (int j = 0; j < 2 * NLD; j++) commit1(j, 0);
+  project_hold(n0);
   __syncthreads();
   // One or two waves per SIMD: little else fills the issue slots a wave leaves empty, so the order of its instructions
   // is fixed by hand.  Per step of 16 model dims: the operand reads of the NEXT step, then 4 groups of TT products, each
@@ -356,8 +402,10 @@ __global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
     __syncthreads();
   }
   const int ct0 = (cg * 2 + wc) * CT, row0 = by * 256 + wt * 32 * TT;
-  if (ct0 >= tiles || row0 >= p.rows) return;
+  if (ct0 >= tiles || row0 >= p.rows) return;                           // (never the first wave)
+  const int seen = project_count(p);
   project_store<R, CT, TT, I4, SPAN>(p, acc, ct0, row0, seq, n0);
+  project_advance(p, seen);
 }
 
 // The projection with the hidden states staged through LDS and the factors straight from memory into the registers that
@@ -470,8 +518,14 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
   int n0[TT];                                                           // (asked for here: no registers during the products)
 #pragma unroll
   for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, (by * TT + tt) * 32 + (lane_number() & 31));
+  // (counted behind the store where no register is left to hold the answer)
+  constexpr bool LATE = R == 64 && CT * TT >= 8;
+  int seen = -1;
+  project_hold(n0);
   if constexpr (KS == 1) {
-    if (ct0 >= tiles) return;
+    __syncthreads();
+    if constexpr (!LATE) seen = project_count(p);
+    if (ct0 >= tiles) return;                                           // (never the first wave)
     project_store<R, CT, TT, I4, SPAN>(p, acc, ct0, by * 32 * TT, seq, n0);
   } else {
     // the groups' sums meet in LDS: unit u (the channels of a head x 32 rows) is added up in group order and stored by group
@@ -489,6 +543,7 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
         for (int v = 0; v < 16; v++) mine[at + (rt * 16 + v) * 64] = acc[u / TT * RT + rt][u % TT][v];
     }
     __syncthreads();
+    if constexpr (!LATE) seen = project_count(p);
     if (ct0 >= tiles) return;
 #pragma unroll
     for (int u = 0; u < NU; u++) {
@@ -508,19 +563,14 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
       project_store_tile<R, CT, TT, I4, SPAN>(p, acc, u / TT, u % TT, ct0, by * 32 * TT, seq, n0[u % TT]);
     }
   }
+  if constexpr (LATE) seen = project_count(p);
+  project_advance(p, seen);
 }
 
-// after the projection: the lengths move on by the rows that fitted (one thread per sequence)
+// the same behind k_prefill_project, one thread per sequence
 __global__ void k_prefill_bump(int* seq_lens, int seq0, int n_seq, int n_tok, int t_cap, int* err_word, int even_only) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n_seq) return;
-  const int n0 = seq_lens[seq0 + i];
-  if (even_only && n0 >= 0 && (n0 & 1)) {      // int4: nothing was stored for a sequence that starts on an odd row
-    atomicExch(err_word, (int)WSVD_E_SHAPE);
-    return;
-  }
-  if (n0 >= 0) seq_lens[seq0 + i] = min(n0 + n_tok, t_cap);
-  if (n0 < 0 || n0 + n_tok > t_cap) atomicExch(err_word, (int)WSVD_E_CAPACITY);
+  if (i < n_seq) project_bump(seq_lens, seq0 + i, n_tok, t_cap, err_word, even_only);
 }
 
 template <int R, int CT, int TT, int WC, bool I4 = false>
@@ -652,6 +702,7 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   if (paged) { p.block_table = paged->block_table; p.page_rows = paged->page_rows; p.max_pages = paged->max_pages; p.n_pages = paged->n_pages; }
   const int n_seq = seq < 0 ? d.batch : 1;
   p.seq0 = seq < 0 ? 0 : seq;
+  p.readers = ctx->readers; p.n_seq = n_seq; p.even_only = i4 ? 1 : 0;
   const bool tiles_ok = d.d_model % kProjKC == 0 && (long long)n_tok * d.d_model * 2 < (1LL << 31);
   int shape = ctx->opt.project_shape;
   if (!shape) shape = project_shape_rule(p, n_seq, d.rank, i4);
@@ -694,7 +745,7 @@ hipError_t wsvd_launch_prefill_project(const wsvd_ctx* ctx, const wsvd_layer_des
   else if (d.rank == 32) launch_project<32, 4, 4, 4>(p, n_seq, s);
   else launch_project<64, 4, 4, 4>(p, n_seq, s);
   if (e == hipSuccess) e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (e != hipSuccess || (d.rank <= 64 && shape != 44)) return e;       // (the tile kernels have advanced the lengths)
   hipLaunchKernelGGL(k_prefill_bump, dim3((n_seq + 63) / 64), dim3(64), 0, s, cache.seq_lens, p.seq0, n_seq, n_tok, d.t_cap, ctx->err_word, i4 ? 1 : 0);
   return hipGetLastError();
 }

@@ -273,3 +273,30 @@ def test_prompt_attention_short_prompts_keep_the_waves_busy(rank):
 
     t16, t64 = us(64, 16), us(16, 64)
     assert t16 <= 1.55 * t64, (t16, t64)
+
+
+@pytest.mark.parametrize("shape", [2, 5, 11, 12, 22, 25])
+@pytest.mark.parametrize("batch,n_tok,kv_heads", [(1, 1, 1), (1, 33, 4), (7, 5, 8), (130, 3, 1), (3, 300, 16)])
+def test_projection_advances_the_lengths(shape, batch, n_tok, kv_heads):
+    """The last workgroup of the tile kernels to count itself advances the lengths: launches of fewer workgroups than counters, of
+    many, more sequences than lanes, a sequence that has no room and one that is full; three calls in a row."""
+    t_cap = (3 * n_tok + 63) // 64 * 64 + 64
+    desc = W.layer_desc(batch, kv_heads, kv_heads, 128, 128, 32, t_cap, "i8", "bf16", "bf16", "bf16", "f32", 0.0)
+    ctx = W.wsvd_create(0)
+    W.wsvd_ctx_set_option(ctx, "project_shape", shape)
+    W.wsvd_ctx_set_option(ctx, "prefill_tiled", 1)
+    cb, mb = W.wsvd_cache_bytes(desc)
+    codes, meta = [torch.zeros(cb, dtype=torch.uint8, device="cuda") for _ in range(2)], [torch.zeros(mb, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    lens = torch.arange(batch, dtype=torch.int32, device="cuda") % 5
+    lens[-1] = t_cap - 2 * n_tok if batch == 1 else t_cap          # (alone: full after two calls)
+    want = lens.cpu()
+    cache = W.make_cache(*codes, *meta, lens)
+    x = torch.randn(batch, n_tok, 128, device="cuda").to(torch.bfloat16)
+    A = [torch.zeros(W.wsvd_factor_a_bytes(desc), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    for call in range(3):
+        W.wsvd_prefill_append(ctx, desc, x, None, n_tok, -1, *A, cache)
+        full = bool((want + n_tok > t_cap).any())
+        want = torch.clamp(want + n_tok, max=t_cap)
+        assert W.wsvd_check(ctx) == (W.E_CAPACITY if full else 0), call
+        assert (lens.cpu() == want).all(), call
+    W.wsvd_destroy(ctx)
