@@ -287,7 +287,19 @@ __global__ __launch_bounds__(256) void k_prefill_project(ProjectParams p) {
 // written to the other stage before the chunk's only barrier.  E must be a multiple of 64.
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int kProjKC = 64, kProjXRow = 144;
-constexpr int kProjABytes = 8 * 4 * 1024, kProjXBytes = 256 * kProjXRow, kProjStage = kProjABytes + kProjXBytes;
+constexpr int kProjABytes = 8 * 4 * 1024, kProjXBytes = 256 * 128, kProjLds = 2 * kProjABytes + 3 * kProjXBytes;
+
+// 16 bytes per lane from memory (base + lane's offset) straight to LDS, at 16 lane past the uniform byte address `lds`.  What is
+// copied may be read behind lds_copy_wait_barrier, which waits until this wave's reads are answered and all but the newest
+// LEFT of its copies have arrived, and then for the other waves; LDS may be overwritten behind it.
+WSVD_DEV void lds_copy16(uint32_t lds, const uint8_t* base, uint32_t offset) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + offset),
+                                   (__attribute__((address_space(3))) void*)(uintptr_t)lds, 16, 0, 0);
+}
+template <int LEFT>
+WSVD_DEV void lds_copy_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+}
 
 // Workgroup -> (channel group, token group).  Consecutive workgroup ids land on different XCDs (8 of them, each with
 // its own L2).  Token-affine: XCD i takes the token groups = i (mod 8), so a line of hidden states is fetched by one XCD
@@ -306,48 +318,42 @@ WSVD_DEV void project_groups(const ProjectParams& p, int& cg, int& tg) {
 }
 
 template <int R, bool I4, bool SPAN>
-__global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
-  extern __shared__ __align__(16) uint8_t proj_lds[];
-  constexpr int WAVES = 8;
-  constexpr int RT = R / 32, CT = 4, TT = 16 / WAVES;                   // 2 x (WAVES / 2) waves, each 4 x TT tiles
-  constexpr int NT = 64 * WAVES, NLD = 2048 / NT;                       // threads; 16-byte pieces of A (and of x) per thread and chunk
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = lane & 31, g2 = lane >> 5;
-  const int wc = wave & 1, wt = wave >> 1;
+__global__ __launch_bounds__(256) void k_prefill_project_lds(ProjectParams p) {
+  extern __shared__ __align__(16) uint8_t proj_lds[];                   // two stages of A, three of x
+  constexpr int RT = R / 32, CT = 4, TT = 4, NS = kProjKC / 16;         // 2 x 2 waves, each 4 x 4 tiles
+  const int lane = threadIdx.x & 63, n = lane & 31, g2 = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wc = wave & 1, wt = wave >> 1;
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
   int cg, tg;
   project_groups(p, cg, tg);
   const int sq = tg / p.tg_seq, by = tg % p.tg_seq;                     // set of rows, 256-row group in it
   const int seq = p.seq0 + sq;                                          // (its first sequence)
-  int n0[TT];
-#pragma unroll
-  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, by * 256 + (wt * TT + tt) * 32 + n);
   const int n_steps = p.E >> 4, n_chunks = p.E / kProjKC;
-  // what this thread copies per chunk: 16 bytes of each of the 8 channel tiles, 16 bytes of 8 of the 256 token rows
-  // (uniform base pointers plus 32-bit per-thread offsets: the loads address through scalar registers)
-  const uint8_t* asrc[NLD];
-  const uint8_t* xbase = (const uint8_t*)p.x + (size_t)sq * p.n_tok * p.E * 2;
-  uint32_t xoff[NLD];
-  int xdst[NLD];
-  const uint32_t aoff = (tid & 255) * 16;
+  // What this wave copies per chunk, 1 KiB per instruction: two channel tiles of A, which are in operand order, and 64 token
+  // rows, 8 of them (whole 128-byte lines) at a time.  LDS takes what the lanes bring in lane order, so a row's 16-byte
+  // pieces are swapped on the way in: piece s of row r goes to place s ^ (r & 7), and 8 neighbouring rows' pieces of one
+  // column lie in 8 different places (no bank conflicts, no padding).
+  const uint8_t* asrc[2];
 #pragma unroll
-  for (int j = 0; j < NLD; j++) {
-    const int u = tid + NT * j;                                         // piece u: tile u / 256 of A, row u / 8 of x
-    const int ct = min(cg * 8 + (u >> 8), tiles - 1);
+  for (int j = 0; j < 2; j++) {
+    const int ct = min(cg * 8 + 2 * wave + j, tiles - 1);
     asrc[j] = (const uint8_t*)p.A[ct / tiles_plane] + (size_t)(ct % tiles_plane) * n_steps * 1024;
-    const int row = u >> 3, sg = u & 7;
-    xoff[j] = (uint32_t)min(by * 256 + row, p.rows - 1) * (uint32_t)(p.E * 2) + sg * 16;   // the launcher keeps rows * E * 2 below 2^31
-    xdst[j] = kProjABytes + row * kProjXRow + sg * 16;
   }
-  v4u rg[2 * NLD];                                                      // the chunk on its way: NLD pieces of A, NLD of x
-  auto fetch1 = [&](int j, int c) {
-    c = min(c, n_chunks - 1);                     // (past the end: the last chunk again, written to the idle stage, never read)
-    if (j < NLD) rg[j] = *(const v4u*)(asrc[j] + (size_t)c * 4096 + aoff);
-    else rg[j] = *(const v4u*)(xbase + (size_t)c * (kProjKC * 2) + xoff[j - NLD]);
+  const uint8_t* const xbase = (const uint8_t*)p.x + (size_t)sq * p.n_tok * p.E * 2;
+  const uint32_t lane16 = lane * 16;
+  uint32_t xoff[8];
+#pragma unroll
+  for (int j = 0; j < 8; j++) {
+    const int row = by * 256 + 64 * wave + 8 * j + (lane >> 3);         // the launcher keeps rows * E * 2 below 2^31
+    xoff[j] = (uint32_t)min(row, p.rows - 1) * (uint32_t)(p.E * 2) + (((lane & 7) ^ (lane >> 3)) * 16);
+  }
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)proj_lds);
+  // (past the end: the last chunk again, into a stage that is not read any more)
+  auto copy_a = [&](int j, int ks, int c) {
+    lds_copy16(lds0 + (c & 1) * kProjABytes + (2 * wave + j) * 4096 + ks * 1024, asrc[j] + (size_t)min(c, n_chunks - 1) * 4096 + ks * 1024, lane16);
   };
-  auto commit1 = [&](int j, int st) {
-    uint8_t* base = proj_lds + st * kProjStage;
-    if (j < NLD) *(v4u*)(base + (tid + NT * j) * 16) = rg[j];
-    else *(v4u*)(base + xdst[j - NLD]) = rg[j];
+  auto copy_x = [&](int j, int c, int st) {
+    lds_copy16(lds0 + 2 * kProjABytes + st * kProjXBytes + (64 * wave + 8 * j) * 128, xbase + (size_t)min(c, n_chunks - 1) * (kProjKC * 2), xoff[j]);
   };
   v16f acc[CT][TT];
 #pragma unroll
@@ -356,52 +362,59 @@ __global__ __launch_bounds__(512) void k_prefill_project_lds(ProjectParams p) {
     for (int tt = 0; tt < TT; tt++)
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[c][tt][v] = 0.f;
-  const int a_off = wc * 4 * 4096 + lane * 16;                          // + c * 4096 + ks * 1024
-  const int x_off = kProjABytes + (wt * 32 * TT + n) * kProjXRow + g2 * 16; // + tt * 32 rows + ks * 32 bytes
+  const uint8_t* const a_at = proj_lds + wc * 4 * 4096 + lane16;                             // + stage + tile * 4096 + step * 1024
+  const uint8_t* const x_at = proj_lds + 2 * kProjABytes + (wt * 128 + n) * 128;             // + stage + tile * 4096 + place
+  const uint32_t place = ((uint32_t)g2 ^ (n & 7)) * 16;                                      // ^ step * 32
+  v8bf16 fa[2][CT], fb[2][TT];
+  auto read_a = [&](int b, int cc, int ks, int c) { fa[b][cc] = *(const v8bf16*)(a_at + (c & 1) * kProjABytes + cc * 4096 + ks * 1024); };
+  auto read_x = [&](int b, int tt, int ks, int st) { fb[b][tt] = *(const v8bf16*)(x_at + st * kProjXBytes + tt * 4096 + (place ^ (ks * 32))); };
 #pragma unroll
-  for (int j = 0; j < 2 * NLD; j++) fetch1(j, 0);
+  for (int ks = 0; ks < NS; ks++) { copy_a(0, ks, 0); copy_a(1, ks, 0); }
 #pragma unroll
-  for (int j = 0; j < 2 * NLD; j++) commit1(j, 0);
-  project_hold(n0);
-  __syncthreads();
-  // One or two waves per SIMD: little else fills the issue slots a wave leaves empty, so the order of its instructions
-  // is fixed by hand.  Per step of 16 model dims: the operand reads of the NEXT step, then 4 groups of TT products, each
-  // followed, in the first two steps, by its share of the 16-byte requests of the next chunk and, in the last step, by
-  // its share of the 16-byte writes of it to the idle stage: requests and writes trickle into the memory pipelines
-  // between products instead of blocking the wave in a burst.
+  for (int j = 0; j < 8; j++) copy_x(j, 0, 0);
+#pragma unroll
+  for (int j = 0; j < 8; j++) copy_x(j, 1, 1);
+  lds_copy_wait_barrier<8>();
+#pragma unroll
+  for (int i = 0; i < 4; i++) { read_a(0, i, 0, 0); read_x(0, i, 0, 0); }
+  // Per chunk four steps of 16 products.  The operands of a step are read during the step before it, those of a chunk's
+  // first step during the last step of the chunk before: the chunk's only barrier stands in front of that last step, when all
+  // reads of the chunk have been answered and (the wait) this wave's copies of the next chunk have arrived.  Behind the
+  // barrier the stages of the chunk may be overwritten: A of the next but one and x of the next but two are asked for
+  // there and in the next chunk's first step, a chunk and two chunks before they are needed.
+  int st = 0;                                                           // stage of x
   for (int c = 0; c < n_chunks; c++) {
-    const uint8_t* base = proj_lds + (c & 1) * kProjStage;
-    v8bf16 fa[2][CT], fb[2][TT];
-    auto frags = [&](int b, int ks) {
+    const int st1 = st == 2 ? 0 : st + 1, st2 = st1 == 2 ? 0 : st1 + 1;
 #pragma unroll
-      for (int cc = 0; cc < CT; cc++) fa[b][cc] = *(const v8bf16*)(base + a_off + cc * 4096 + ks * 1024);
-#pragma unroll
-      for (int tt = 0; tt < TT; tt++) fb[b][tt] = *(const v8bf16*)(base + x_off + tt * 32 * kProjXRow + ks * 32);
-    };
-    frags(0, 0);
-#pragma unroll
-    for (int ks = 0; ks < kProjKC / 16; ks++) {
-      if (ks + 1 < kProjKC / 16) frags((ks + 1) & 1, ks + 1);
-      __builtin_amdgcn_sched_barrier(0);
+    for (int ks = 0; ks < NS; ks++) {
+      const int b = ks & 1;
+      if (ks == NS - 1) {
+        __builtin_amdgcn_sched_barrier(0);
+        lds_copy_wait_barrier<8>();
+      }
 #pragma unroll
       for (int cc = 0; cc < CT; cc++) {
-#pragma unroll
-        for (int tt = 0; tt < TT; tt++) acc[cc][tt] = mfma_bf16(fa[ks & 1][cc], fb[ks & 1][tt], acc[cc][tt]);
         __builtin_amdgcn_sched_barrier(0);
-        if (ks < 2) {
-#pragma unroll
-          for (int j = 0; j < NLD / 4; j++) fetch1((NLD / 4) * (ks * 4 + cc) + j, c + 1);
-        }
-        if (ks == 3) {
-#pragma unroll
-          for (int j = 0; j < NLD / 2; j++) commit1((NLD / 2) * cc + j, (c + 1) & 1);
-        }
+        if (ks < NS - 1) { read_a(b ^ 1, cc, ks + 1, c); read_x(b ^ 1, cc, ks + 1, st); }
+        else { read_a(b ^ 1, cc, 0, c + 1); read_x(b ^ 1, cc, 0, st1); }
         __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tt = 0; tt < TT; tt++) {
+          acc[cc][tt] = mfma_bf16(fa[b][cc], fb[b][tt], acc[cc][tt]);
+          __builtin_amdgcn_sched_barrier(0);
+          if (ks == 0 && tt < 2) copy_a(tt, cc, c + 1);
+          if (ks == 1 && tt < 2) copy_x(2 * cc + tt, c + 2, st2);
+        }
       }
     }
-    __syncthreads();
+    st = st1;
   }
   const int ct0 = (cg * 2 + wc) * CT, row0 = by * 256 + wt * 32 * TT;
+  int n0[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, row0 + 32 * tt + n);
+  project_hold(n0);
+  __syncthreads();
   if (ct0 >= tiles || row0 >= p.rows) return;                           // (never the first wave)
   const int seen = project_count(p);
   project_store<R, CT, TT, I4, SPAN>(p, acc, ct0, row0, seq, n0);
@@ -622,10 +635,10 @@ hipError_t launch_project_direct(ProjectParams p, int n_seq, hipStream_t s) {
 template <int R, bool I4, bool SPAN>
 hipError_t launch_project_lds_span(const ProjectParams& p, hipStream_t s) {
   static LdsLimit limit;
-  const size_t lds = 2 * (size_t)kProjStage;
+  const size_t lds = kProjLds;
   hipError_t e = wsvd_raise_lds(limit, (const void*)k_prefill_project_lds<R, I4, SPAN>, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_prefill_project_lds<R, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(512), lds, s, p);
+  hipLaunchKernelGGL((k_prefill_project_lds<R, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(256), lds, s, p);
   return hipGetLastError();
 }
 template <int R, bool I4 = false>
