@@ -104,20 +104,42 @@ WSVD_DEV ProjRow project_row(const ProjectParams& p, int pl, int seq, int kv, in
 }
 
 // One token's row of one head and plane: the 16 channels of every 32 that this lane holds in a[], the rest in its partner
-// half.  Symmetric int8 (the latent quantiser's rule), then the stores.
+// half.  Symmetric int8 (the latent quantiser's rule), then the stores.  The codes are made without a branch, so that those of
+// several rows can overlap (4 waves of 16 such rows each: 17 us one after the other, 14 four at a time).
 template <int RT>
-WSVD_DEV void store_row_i8(const ProjectParams& p, const v16f (&a)[RT], int pl, int seq, int kv, int t, bool on) {
-  constexpr int R = 32 * RT;
-  const int g2 = lane_number() >> 5;
+struct RowI8 {
+  uint32_t codes[RT][4];                                                // channels 32 rt + 8 m4 + 4 g2 .. + 3
+  uint16_t scale;
+};
+template <int RT>
+WSVD_DEV RowI8<RT> quantise_row_i8(const v16f (&a)[RT]) {
+  RowI8<RT> r;
   float m = 0.f;
 #pragma unroll
   for (int rt = 0; rt < RT; rt++)
 #pragma unroll
     for (int v = 0; v < 16; v++) m = fmaxf(m, fabsf(a[rt][v]));
   m = fmaxf(m, __shfl_xor(m, 32));
-  uint16_t sh = 0x3C00u;
-  if (m != 0.f) sh = guard_scale_f16(m / 127.0f);
-  const float sc = f16_bits_to_f32(sh), inv = 1.0f / sc;
+  r.scale = m != 0.f ? guard_scale_f16(m / 127.0f) : (uint16_t)0x3C00u;
+  const float sc = f16_bits_to_f32(r.scale), inv = 1.0f / sc;
+#pragma unroll
+  for (int rt = 0; rt < RT; rt++)
+#pragma unroll
+    for (int m4 = 0; m4 < 4; m4++) {
+      uint32_t pk = 0;
+#pragma unroll
+      for (int jj = 0; jj < 4; jj++) {
+        const int q = (int)__builtin_amdgcn_fmed3f(__builtin_rintf(div_by_scale(a[rt][4 * m4 + jj], sc, inv)), -127.f, 127.f);
+        pk |= ((uint32_t)q & 0xFFu) << (8 * jj);
+      }
+      r.codes[rt][m4] = pk;
+    }
+  return r;
+}
+template <int RT>
+WSVD_DEV void put_row_i8(const ProjectParams& p, const RowI8<RT>& r, int pl, int seq, int kv, int t, bool on) {
+  constexpr int R = 32 * RT;
+  const int g2 = lane_number() >> 5;
   if (!on) return;
   const ProjRow pr = project_row(p, pl, seq, kv, t, R);
   if (!pr.ok) return;
@@ -125,21 +147,15 @@ WSVD_DEV void store_row_i8(const ProjectParams& p, const v16f (&a)[RT], int pl, 
   for (int rt = 0; rt < RT; rt++)
 #pragma unroll
     for (int m4 = 0; m4 < 4; m4++) {
-      uint32_t pk = 0;
-      int q[4];
-#pragma unroll
-      for (int jj = 0; jj < 4; jj++) {
-        q[jj] = (int)fminf(fmaxf(__builtin_rintf(div_by_scale(a[rt][4 * m4 + jj], sc, inv)), -127.f), 127.f);
-        pk |= ((uint32_t)q[jj] & 0xFFu) << (8 * jj);
-      }
       const int j0 = 32 * rt + 8 * m4 + 4 * g2;                         // channels j0 .. j0 + 3
+      const uint32_t pk = r.codes[rt][m4];
       if (pl == 0) *(uint32_t*)(pr.plane + i8_k_offset(pr.t, j0, R)) = pk;
       else {
 #pragma unroll
-        for (int jj = 0; jj < 4; jj++) pr.plane[i8_v_offset(pr.t, j0 + jj, R)] = (uint8_t)q[jj];
+        for (int jj = 0; jj < 4; jj++) pr.plane[i8_v_offset(pr.t, j0 + jj, R)] = (uint8_t)(pk >> (8 * jj));
       }
     }
-  if (g2 == 0) p.meta[pl][pr.meta] = sh;
+  if (g2 == 0) p.meta[pl][pr.meta] = r.scale;
 }
 
 // The same for int4 (rank 32: one channel tile per head): the rule of quantize_row_i4; K bytes pair dims (2 adjacent
@@ -194,31 +210,41 @@ template <bool SPAN>
 WSVD_DEV int row_length(const ProjectParams& p, int seq, int row) {
   return p.seq_lens[SPAN ? seq + min(row, p.rows - 1) / p.n_tok : seq];
 }
-template <int R, int CT, int TT, bool I4, bool SPAN>
-WSVD_DEV void project_store_tile(const ProjectParams& p, const v16f (&acc)[CT][TT], int h, int tt, int ct0, int row0, int seq, int n0) {
+// Tiles [tt0, tt0 + N) of head h of the wave.
+template <int R, int CT, int TT, bool I4, bool SPAN, int N>
+WSVD_DEV void project_store_tiles(const ProjectParams& p, const v16f (&acc)[CT][TT], int h, int tt0, int ct0, int row0, int seq, const int (&n0)[TT]) {
   constexpr int RT = R / 32;
   static_assert(!I4 || R == 32, "int4 latents have rank 32");
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
   const int ct = ct0 + h * RT;
   const int pl = ct / tiles_plane, kv = (ct % tiles_plane) / RT;        // (wave-uniform)
-  const int row = row0 + 32 * tt + (lane_number() & 31), sq = SPAN ? min(row, p.rows - 1) / p.n_tok : 0;
-  const int tok = row - sq * p.n_tok, t = n0 + tok;                     // this lane's token of the prompt, its cache row
-  const bool on = ct < tiles && row < p.rows && n0 >= 0 && t < p.t_cap;
-  if constexpr (I4) {
-    store_row_i4(p, acc[h][tt], pl, seq + sq, kv, t, on && (n0 & 1) == 0, tok + 1 < p.n_tok && t + 1 < p.t_cap);
-  } else {
-    v16f a[RT];
+  RowI8<RT> rows[N];
+  if constexpr (!I4) {
 #pragma unroll
-    for (int rt = 0; rt < RT; rt++) a[rt] = acc[h * RT + rt][tt];
-    store_row_i8<RT>(p, a, pl, seq + sq, kv, t, on);
+    for (int i = 0; i < N; i++) {
+      v16f a[RT];
+#pragma unroll
+      for (int rt = 0; rt < RT; rt++) a[rt] = acc[h * RT + rt][tt0 + i];
+      rows[i] = quantise_row_i8<RT>(a);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < N; i++) {
+    const int tt = tt0 + i;
+    const int row = row0 + 32 * tt + (lane_number() & 31), sq = SPAN ? min(row, p.rows - 1) / p.n_tok : 0;
+    const int tok = row - sq * p.n_tok, t = n0[tt] + tok;               // this lane's token of the prompt, its cache row
+    const bool on = ct < tiles && row < p.rows && n0[tt] >= 0 && t < p.t_cap;
+    if constexpr (I4) store_row_i4(p, acc[h][tt], pl, seq + sq, kv, t, on && (n0[tt] & 1) == 0, tok + 1 < p.n_tok && t + 1 < p.t_cap);
+    else put_row_i8<RT>(p, rows[i], pl, seq + sq, kv, t, on);
   }
 }
-template <int R, int CT, int TT, bool I4, bool SPAN>
+// AT_ONCE rows' codes side by side
+template <int R, int CT, int TT, bool I4, bool SPAN, int AT_ONCE = 1>
 WSVD_DEV void project_store(const ProjectParams& p, const v16f (&acc)[CT][TT], int ct0, int row0, int seq, const int (&n0)[TT]) {
 #pragma unroll
   for (int h = 0; h < CT / (R / 32); h++)
 #pragma unroll
-    for (int tt = 0; tt < TT; tt++) project_store_tile<R, CT, TT, I4, SPAN>(p, acc, h, tt, ct0, row0, seq, n0[tt]);
+    for (int tt = 0; tt < TT; tt += AT_ONCE) project_store_tiles<R, CT, TT, I4, SPAN, AT_ONCE>(p, acc, h, tt, ct0, row0, seq, n0);
 }
 
 template <int R, int CT, int TT, int WC, bool I4 = false, int ST = 3>
@@ -280,11 +306,13 @@ __global__ __launch_bounds__(256) void k_prefill_project(ProjectParams p) {
 }
 
 // The same projection with both operands staged through LDS: a workgroup of 8 waves (2 x 4, each 4 x 2 tiles) owns
-// 256 channels x 256 tokens (4 waves of 4 x 4 tiles: 3 % slower).  Per chunk of 64 model dims it copies 32 KiB of the factor image (already in operand order)
-// and 256 whole 128-byte lines of hidden states (rows padded to 144 bytes in LDS, which makes the operand reads free of
-// bank conflicts), so that the first-level cache sees whole lines once per workgroup instead of 32-byte pieces once per
-// wave.  Two LDS stages: the next chunk travels global -> registers during the products of the current one and is
-// written to the other stage before the chunk's only barrier.  E must be a multiple of 64.
+// 256 channels x 256 tokens.  Per chunk of 64 model dims 32 KiB of the factor image (already in operand order) and 256 whole
+// 128-byte lines of hidden states go from memory straight to LDS, two chunks of A and three of x deep (all 160 KiB), one barrier
+// per chunk, no register and no LDS write instruction in between.  E must be a multiple of 64.
+// Bound: matrix cores and LDS reads (24 KiB per wave and chunk, 1536 cycles of a CU's 128 bytes a clock beside 2048 of
+// products), at the clock the power leaves; then the store, in which the matrix cores idle.  32 heads of rank 32, 16 x 2048
+// tokens, d_model 4096 / 512 / 64: 449 / 103 / 49 us; through registers, two stages and rows padded to 144 bytes 518 / 117 / 60;
+// this copy with 4 waves of 4 x 4 tiles (a third less to read, one wave per SIMD for the store) 462 / 128 / 78.
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int kProjKC = 64, kProjXRow = 144;
 constexpr int kProjABytes = 8 * 4 * 1024, kProjXBytes = 256 * 128, kProjLds = 2 * kProjABytes + 3 * kProjXBytes;
@@ -317,10 +345,12 @@ WSVD_DEV void project_groups(const ProjectParams& p, int& cg, int& tg) {
   else { cg = L % p.n_cg; tg = L / p.n_cg; }
 }
 
+constexpr int kProjWaves = 8;
 template <int R, bool I4, bool SPAN>
-__global__ __launch_bounds__(256) void k_prefill_project_lds(ProjectParams p) {
+__global__ __launch_bounds__(64 * kProjWaves) void k_prefill_project_lds(ProjectParams p) {
   extern __shared__ __align__(16) uint8_t proj_lds[];                   // two stages of A, three of x
-  constexpr int RT = R / 32, CT = 4, TT = 4, NS = kProjKC / 16;         // 2 x 2 waves, each 4 x 4 tiles
+  constexpr int RT = R / 32, WAVES = kProjWaves, CT = 4, TT = 16 / WAVES, NS = kProjKC / 16;     // 2 x (WAVES / 2) waves, each 4 x TT tiles
+  constexpr int NA = 8 / WAVES, NX = 32 / WAVES;                        // channel tiles, groups of 8 rows a wave copies
   const int lane = threadIdx.x & 63, n = lane & 31, g2 = lane >> 5;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), wc = wave & 1, wt = wave >> 1;
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
@@ -328,32 +358,36 @@ __global__ __launch_bounds__(256) void k_prefill_project_lds(ProjectParams p) {
   project_groups(p, cg, tg);
   const int sq = tg / p.tg_seq, by = tg % p.tg_seq;                     // set of rows, 256-row group in it
   const int seq = p.seq0 + sq;                                          // (its first sequence)
+  const int ct0 = (cg * 2 + wc) * CT, row0 = by * 256 + wt * 32 * TT;
+  int n0[TT];
+#pragma unroll
+  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, row0 + 32 * tt + n);
   const int n_steps = p.E >> 4, n_chunks = p.E / kProjKC;
   // What this wave copies per chunk, 1 KiB per instruction: two channel tiles of A, which are in operand order, and 64 token
   // rows, 8 of them (whole 128-byte lines) at a time.  LDS takes what the lanes bring in lane order, so a row's 16-byte
   // pieces are swapped on the way in: piece s of row r goes to place s ^ (r & 7), and 8 neighbouring rows' pieces of one
   // column lie in 8 different places (no bank conflicts, no padding).
-  const uint8_t* asrc[2];
+  const uint8_t* asrc[NA];
 #pragma unroll
-  for (int j = 0; j < 2; j++) {
-    const int ct = min(cg * 8 + 2 * wave + j, tiles - 1);
+  for (int j = 0; j < NA; j++) {
+    const int ct = min(cg * 8 + NA * wave + j, tiles - 1);
     asrc[j] = (const uint8_t*)p.A[ct / tiles_plane] + (size_t)(ct % tiles_plane) * n_steps * 1024;
   }
   const uint8_t* const xbase = (const uint8_t*)p.x + (size_t)sq * p.n_tok * p.E * 2;
   const uint32_t lane16 = lane * 16;
-  uint32_t xoff[8];
+  uint32_t xoff[NX];
 #pragma unroll
-  for (int j = 0; j < 8; j++) {
-    const int row = by * 256 + 64 * wave + 8 * j + (lane >> 3);         // the launcher keeps rows * E * 2 below 2^31
+  for (int j = 0; j < NX; j++) {
+    const int row = by * 256 + 8 * NX * wave + 8 * j + (lane >> 3);         // the launcher keeps rows * E * 2 below 2^31
     xoff[j] = (uint32_t)min(row, p.rows - 1) * (uint32_t)(p.E * 2) + (((lane & 7) ^ (lane >> 3)) * 16);
   }
   const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)proj_lds);
   // (past the end: the last chunk again, into a stage that is not read any more)
   auto copy_a = [&](int j, int ks, int c) {
-    lds_copy16(lds0 + (c & 1) * kProjABytes + (2 * wave + j) * 4096 + ks * 1024, asrc[j] + (size_t)min(c, n_chunks - 1) * 4096 + ks * 1024, lane16);
+    lds_copy16(lds0 + (c & 1) * kProjABytes + (NA * wave + j) * 4096 + ks * 1024, asrc[j] + (size_t)min(c, n_chunks - 1) * 4096 + ks * 1024, lane16);
   };
   auto copy_x = [&](int j, int c, int st) {
-    lds_copy16(lds0 + 2 * kProjABytes + st * kProjXBytes + (64 * wave + 8 * j) * 128, xbase + (size_t)min(c, n_chunks - 1) * (kProjKC * 2), xoff[j]);
+    lds_copy16(lds0 + 2 * kProjABytes + st * kProjXBytes + (8 * NX * wave + 8 * j) * 128, xbase + (size_t)min(c, n_chunks - 1) * (kProjKC * 2), xoff[j]);
   };
   v16f acc[CT][TT];
 #pragma unroll
@@ -363,20 +397,23 @@ __global__ __launch_bounds__(256) void k_prefill_project_lds(ProjectParams p) {
 #pragma unroll
       for (int v = 0; v < 16; v++) acc[c][tt][v] = 0.f;
   const uint8_t* const a_at = proj_lds + wc * 4 * 4096 + lane16;                             // + stage + tile * 4096 + step * 1024
-  const uint8_t* const x_at = proj_lds + 2 * kProjABytes + (wt * 128 + n) * 128;             // + stage + tile * 4096 + place
+  const uint8_t* const x_at = proj_lds + 2 * kProjABytes + (wt * 32 * TT + n) * 128;             // + stage + tile * 4096 + place
   const uint32_t place = ((uint32_t)g2 ^ (n & 7)) * 16;                                      // ^ step * 32
   v8bf16 fa[2][CT], fb[2][TT];
   auto read_a = [&](int b, int cc, int ks, int c) { fa[b][cc] = *(const v8bf16*)(a_at + (c & 1) * kProjABytes + cc * 4096 + ks * 1024); };
   auto read_x = [&](int b, int tt, int ks, int st) { fb[b][tt] = *(const v8bf16*)(x_at + st * kProjXBytes + tt * 4096 + (place ^ (ks * 32))); };
 #pragma unroll
-  for (int ks = 0; ks < NS; ks++) { copy_a(0, ks, 0); copy_a(1, ks, 0); }
+  for (int ks = 0; ks < NS; ks++)
 #pragma unroll
-  for (int j = 0; j < 8; j++) copy_x(j, 0, 0);
+    for (int j = 0; j < NA; j++) copy_a(j, ks, 0);
 #pragma unroll
-  for (int j = 0; j < 8; j++) copy_x(j, 1, 1);
-  lds_copy_wait_barrier<8>();
+  for (int j = 0; j < NX; j++) copy_x(j, 0, 0);
 #pragma unroll
-  for (int i = 0; i < 4; i++) { read_a(0, i, 0, 0); read_x(0, i, 0, 0); }
+  for (int j = 0; j < NX; j++) copy_x(j, 1, 1);
+  project_hold(n0);
+  lds_copy_wait_barrier<NX>();
+#pragma unroll
+  for (int i = 0; i < 4; i++) { read_a(0, i, 0, 0); if (i < TT) read_x(0, i, 0, 0); }
   // Per chunk four steps of 16 products.  The operands of a step are read during the step before it, those of a chunk's
   // first step during the last step of the chunk before: the chunk's only barrier stands in front of that last step, when all
   // reads of the chunk have been answered and (the wait) this wave's copies of the next chunk have arrived.  Behind the
@@ -390,34 +427,28 @@ __global__ __launch_bounds__(256) void k_prefill_project_lds(ProjectParams p) {
       const int b = ks & 1;
       if (ks == NS - 1) {
         __builtin_amdgcn_sched_barrier(0);
-        lds_copy_wait_barrier<8>();
+        lds_copy_wait_barrier<NX>();
       }
 #pragma unroll
       for (int cc = 0; cc < CT; cc++) {
         __builtin_amdgcn_sched_barrier(0);
-        if (ks < NS - 1) { read_a(b ^ 1, cc, ks + 1, c); read_x(b ^ 1, cc, ks + 1, st); }
-        else { read_a(b ^ 1, cc, 0, c + 1); read_x(b ^ 1, cc, 0, st1); }
+        if (ks < NS - 1) { read_a(b ^ 1, cc, ks + 1, c); if (cc < TT) read_x(b ^ 1, cc, ks + 1, st); }
+        else { read_a(b ^ 1, cc, 0, c + 1); if (cc < TT) read_x(b ^ 1, cc, 0, st1); }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int tt = 0; tt < TT; tt++) {
           acc[cc][tt] = mfma_bf16(fa[b][cc], fb[b][tt], acc[cc][tt]);
           __builtin_amdgcn_sched_barrier(0);
-          if (ks == 0 && tt < 2) copy_a(tt, cc, c + 1);
-          if (ks == 1 && tt < 2) copy_x(2 * cc + tt, c + 2, st2);
+          if (ks == 0 && tt < NA) copy_a(tt, cc, c + 1);
+          if (ks == 1 && tt < NX / 4) copy_x(NX / 4 * cc + tt, c + 2, st2);
         }
       }
     }
     st = st1;
   }
-  const int ct0 = (cg * 2 + wc) * CT, row0 = by * 256 + wt * 32 * TT;
-  int n0[TT];
-#pragma unroll
-  for (int tt = 0; tt < TT; tt++) n0[tt] = row_length<SPAN>(p, seq, row0 + 32 * tt + n);
-  project_hold(n0);
-  __syncthreads();
   if (ct0 >= tiles || row0 >= p.rows) return;                           // (never the first wave)
   const int seen = project_count(p);
-  project_store<R, CT, TT, I4, SPAN>(p, acc, ct0, row0, seq, n0);
+  project_store<R, CT, TT, I4, SPAN, TT>(p, acc, ct0, row0, seq, n0);
   project_advance(p, seen);
 }
 
@@ -573,7 +604,7 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
           }
           acc[u / TT * RT + rt][u % TT][v] = sum;
         }
-      project_store_tile<R, CT, TT, I4, SPAN>(p, acc, u / TT, u % TT, ct0, by * 32 * TT, seq, n0[u % TT]);
+      project_store_tiles<R, CT, TT, I4, SPAN, 1>(p, acc, u / TT, u % TT, ct0, by * 32 * TT, seq, n0);
     }
   }
   if constexpr (LATE) seen = project_count(p);
@@ -638,7 +669,7 @@ hipError_t launch_project_lds_span(const ProjectParams& p, hipStream_t s) {
   const size_t lds = kProjLds;
   hipError_t e = wsvd_raise_lds(limit, (const void*)k_prefill_project_lds<R, I4, SPAN>, (int)lds);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((k_prefill_project_lds<R, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(256), lds, s, p);
+  hipLaunchKernelGGL((k_prefill_project_lds<R, I4, SPAN>), dim3((unsigned)(p.n_cg * p.n_tg)), dim3(64 * kProjWaves), lds, s, p);
   return hipGetLastError();
 }
 template <int R, bool I4 = false>
@@ -653,7 +684,10 @@ hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
 // beside it; `fixed` (first requests, sums, last store) shows once.  The shape that costs least.  Smaller tiles read the operands
 // more often (see k_prefill_project_direct), larger ones leave CUs idle.  The constants are fitted to 840 sizes (1 to 40 heads of
 // rank 32 or 64, d_model 64 to 8192, 2 to 40000 tokens): the choice is 0.7 % slower than the best of the shapes on average, 0.3
-// from d_model 512 on (0.4 over 170 sizes with the operands out of memory).  us per call with the update of the lengths (about 6 us with the clearing before it), 32 kv heads of rank
+// from d_model 512 on (0.4 over 170 sizes with the operands out of memory).  Those of 22, 25 and 2 are fitted again to 136 sizes of
+// 512 to 40000 tokens (choice 0.5 % slower than the best on average; 2.5 with the constants of the 256 x 256 tiles before they were
+// copied straight to LDS: 6 x 1000 tokens 117 us then, 96 now).  us per call with the update of the lengths and the clearing before
+// it (all but the last row measured with the update as a launch of its own, about 1 us), 32 kv heads of rank
 // 32 / 64, d_model 4096; the last column 28 x 385 tokens at d_model 192, where the store is most of the time:
 //                   1 x 200   16 x 32   1 x 400   3 x 333   4 x 500  16 x 130  2 x 2048  8 x 1024    64 x 4    28 x 385
 //    5:  64 x  32     16/23     25/42     24/40     41/77    71/147    78/156   141/288   267/553     17/24      79/189
@@ -661,36 +695,35 @@ hipError_t launch_project_lds(ProjectParams p, int n_seq, hipStream_t s) {
 //   12: 128 x  64     25/30     27/31     26/31     31/49     53/89    71/106   101/168   192/342     26/31      64/84
 //   22: 256 x  64     42/41     41/43     42/42     43/47     47/78    72/111    84/149   158/304     44/42      46/69
 //   25: 256 x 128     54/55     53/59     56/55     57/56     57/69    65/122    74/135   141/267     56/57      47/79
-//    2: 256 x 256    103/103   102/109   105/104   107/105   106/106   104/121   114/134   135/261   110/109     40/66
+//    2: 256 x 256      78/75     81/99     77/76     80/80     80/85    82/107    82/118   121/233     78/77     32/60
 // 13, 256 x 32, is there for rank 64: it reads the hidden states half as often as 11 and is the best where the contraction is
 // short (30 x 46 tokens of 8 heads, d_model 192: 10.0 us, the others 10.9 and more); its chain is priced for that, at larger
 // d_model 12 and 22 are as fast.
-// A shape that sums the contraction in one chain has to be 2 % cheaper than one that halves it over wave groups, whose sums are
-// nearer to the exact ones (scales of 10 x 1178 tokens, d_model 512, against 64 bits: 4.2e-6 and 3.3e-6).
+// A shape that sums the contraction in one chain has to be 2 % cheaper (256 x 256: 6 %) than one that halves it over wave groups, whose
+// sums are nearer to the exact ones (scales of 10 x 1178 tokens, d_model 512, against 64 bits: 4.2e-6 and 3.3e-6).
 struct ProjectShape { int code, ch, tok; bool halves[2]; float fixed[2], store[2], chain, busy; };   // pairs: rank 32, 64
 constexpr ProjectShape kProjectShapes[] = {
-    {5, 64, 32, {true, true}, {1.7f, 2.6f}, {0.9f, 1.2f}, 7.5f, 0.3f},
-    {11, 128, 32, {false, true}, {1.7f, 3.1f}, {1.05f, 1.7f}, 11.2f, 1.5f},
-    {12, 128, 64, {true, true}, {3.1f, 3.4f}, {3.4f, 1.9f}, 17.5f, 1.7f},
-    {13, 256, 32, {false, false}, {-1.f, 2.3f}, {0.f, 1.9f}, 26.f, 0.f},
-    {22, 256, 64, {false, false}, {4.5f, 3.6f}, {3.3f, 2.8f}, 31.4f, 0.f},
-    {25, 256, 128, {true, true}, {5.9f, 4.7f}, {8.2f, 7.9f}, 47.5f, 7.6f},
-    {2, 256, 256, {false, false}, {6.8f, 5.6f}, {12.7f, 11.1f}, 95.f, 11.5f}};
+    {5, 64, 32, {true, true}, {0.9f, 1.8f}, {0.9f, 1.2f}, 7.5f, 0.3f},
+    {11, 128, 32, {false, true}, {0.9f, 2.3f}, {1.05f, 1.7f}, 11.2f, 1.5f},
+    {12, 128, 64, {true, true}, {2.3f, 2.6f}, {3.4f, 1.9f}, 17.5f, 1.7f},
+    {13, 256, 32, {false, false}, {-1.f, 1.5f}, {0.f, 1.9f}, 26.f, 0.f},
+    {22, 256, 64, {false, false}, {3.9f, 2.5f}, {2.7f, 2.8f}, 31.8f, 1.6f},
+    {25, 256, 128, {true, true}, {5.0f, 0.6f}, {6.5f, 6.9f}, 47.7f, 9.8f},
+    {2, 256, 256, {false, false}, {6.5f, 4.5f}, {8.0f, 7.7f}, 64.7f, 33.3f}};
 int project_shape_rule(const ProjectParams& p, int n_seq, int R, bool i4) {
-  int best = 0;
-  float least = 0.f;
+  int best[2] = {0, 0};                                                 // of the shapes that sum in one chain, of those that halve it
+  float least[2] = {INFINITY, INFINITY};
   for (const ProjectShape& k : kProjectShapes) {
-    const int r = R == 64;
+    const int r = R == 64, halves = k.halves[r];
     if (k.fixed[r] < 0.f) continue;                                     // not there at this rank
     ProjectParams g = p;
     project_grid(g, n_seq, k.ch, k.tok, R, i4);
     const float wgs = (float)g.n_cg * (float)g.n_tg, rounds = ceilf(wgs / 256.f), load = wgs / 256.f - (rounds - 1.f);
     const float held = rounds - 1.f + load * load;
     const float us = 6.f + k.fixed[r] + k.store[r] * held + (rounds * k.chain + held * k.busy) * (float)p.E / 4096.f;
-    const float cost = k.halves[r] ? us : 1.02f * us;
-    if (!best || cost < least) { best = k.code; least = cost; }
+    if (us < least[halves]) { best[halves] = k.code; least[halves] = us; }
   }
-  return best;
+  return least[0] * (best[0] == 2 ? 1.06f : 1.02f) < least[1] ? best[0] : best[1];
 }
 
 }  // namespace
