@@ -95,6 +95,8 @@ struct OwnOperands {
   WSVD_DEV v8f16 v(int kk, int s) const { return vc[kk][s]; }
 };
 
+enum { kFirst, kWhole, kPart, kAny };      // what a wave's queries see of a key block, see there
+
 template <int R, int D, int QW, int KG>
 __global__ __launch_bounds__(64 * QW * KG) __attribute__((amdgpu_waves_per_eu(R == 32 ? 4 : 2)))
 void k_prefill_attn(PrefillParams p) {
@@ -113,7 +115,6 @@ void k_prefill_attn(PrefillParams p) {
   const size_t ph = (size_t)b * p.Hkv + kv;
   const int perm = 16 * ((n >> 2) & 1) + 4 * (n >> 3) + (n & 3);
   const int rho_c = min(qb * 32 + n, p.NR - 1);                         // this lane's query row
-  const bool row_ok = qb * 32 + n < p.NR;
   // nothing here depends on the length: queries, B_K and the length itself travel in one round trip
   v8bf16 bq[D / 16], bk[KK][D / 16];
 #pragma unroll
@@ -130,8 +131,10 @@ void k_prefill_attn(PrefillParams p) {
   const int lim_wg = sees((qb - qw) * 32 + 32 * QW - 1);
   const int n_kblocks = lim_wg > 0 ? (lim_wg + 31) >> 5 : 0;            // of the workgroup
   if (n_kblocks == 0) {                                                 // nothing visible to any row of the workgroup
-    float* orow = p.out + (ph * p.NR + rho_c) * D;
-    if (row_ok && kg == 0)
+    int row = qb * 32 + n;
+    asm volatile("" : "+v"(row));                                       // (a row's address of its own: the queries' would be held through the loop)
+    float* const orow = p.out + (ph * p.NR + min(row, p.NR - 1)) * D;
+    if (row < p.NR && kg == 0)
       for (int c = g2 * (D / 2); c < (g2 + 1) * (D / 2); c++) orow[c] = 0.f;
     return;
   }
@@ -243,8 +246,12 @@ void k_prefill_attn(PrefillParams p) {
   };
 
   // op: the block's operands, each asked for where it is used (k(s), scales ks(s), v(kk, s))
-  auto block = [&](const auto& op, int kb, auto masked_c) {
-    constexpr bool MASKED = decltype(masked_c)::value;
+  // kFirst: nothing seen yet, every query sees the whole block; kWhole: every query does; kPart: every query has a reference,
+  // some see a part; kAny: everything else.  (68, 68, 100 and 200 vector instructions; with the general form for the first and the
+  // last block of every prompt, and the output's operands from single elements of B_V: 4 x 100 tokens of rank 64 9.3 -> 8.4 us,
+  // 16 x 32 over 232 keys 11.2 -> 10.9, 2 x 700 21.2 -> 20.9, 16 x 2048 418 -> 416.)
+  auto block = [&](const auto& op, int kb, auto form_c) {
+    constexpr int FORM = decltype(form_c)::value;
     // scores: rows = the block's 32 tokens (register v of half g2 = token 16 g2 + v), columns = the 32 queries
     const v16f zero16 = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     v16f S;
@@ -261,7 +268,17 @@ void k_prefill_attn(PrefillParams p) {
 #pragma unroll
       for (int s = 0; s < 2; s++) aV[kk][s] = op.v(kk, s);
     float x[16];
-    if constexpr (MASKED) {
+    if constexpr (FORM == kFirst) {
+      float bmax = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 16; v++) {
+        x[v] = S[v] * (float)sk8[v >> 3][v & 7];
+        bmax = fmaxf(bmax, x[v]);
+      }
+      m_ref = fmaxf(bmax, __shfl_xor(bmax, 32));
+#pragma unroll
+      for (int v = 0; v < 16; v++) x[v] -= m_ref;
+    } else if constexpr (FORM == kAny) {
       float bmax = -INFINITY;
 #pragma unroll
       for (int v = 0; v < 16; v++) {
@@ -284,6 +301,7 @@ void k_prefill_attn(PrefillParams p) {
 #pragma unroll
       for (int v = 0; v < 16; v++) {
         x[v] = fmaf(S[v], (float)sk8[v >> 3][v & 7], -m_ref);           // (m_ref is finite here)
+        if constexpr (FORM == kPart) x[v] = v < lim - kb * 32 - 16 * g2 ? x[v] : -INFINITY;
         bmax = fmaxf(bmax, x[v]);
       }
       if (__builtin_amdgcn_ballot_w64(bmax > 0.f) != 0) {               // some column's maximum moves
@@ -317,23 +335,27 @@ void k_prefill_attn(PrefillParams p) {
       for (int kk = 0; kk < KK; kk++) U[kk] = mfma_f16(aV[kk][s], bp[s], U[kk]);
   };
 
-  // blocks kb, kb + STEP, .. below end in three loops: the first one (a column without a key yet has no reference, the
-  // masked form sets it), the blocks seen whole, the last ones.  (One loop with a choice inside copies the accumulators of
-  // both forms in every block.)
+  // blocks kb, kb + STEP, .. below end in loops by their form: the first one (a column without a key yet has no reference), the
+  // blocks seen whole, the last ones.  (One loop with a choice inside copies the accumulators of both forms in every block.)
+  constexpr std::integral_constant<int, kFirst> first_c{};
+  constexpr std::integral_constant<int, kWhole> whole_c{};
+  constexpr std::integral_constant<int, kPart> part_c{};
+  constexpr std::integral_constant<int, kAny> any_c{};
   auto no_reference = [&] { return __builtin_amdgcn_ballot_w64(m_ref == -INFINITY) != 0; };
   if constexpr (OWN) {
     // ---- one wave of rows per key group: its blocks go straight to registers, every KG-th one
     load_block(min(kg, n_kblocks - 1));
-    auto next = [&](int kb, auto masked_c) {
+    auto next = [&](int kb, auto form_c) {
       OwnOperands<KK> o;
       own_operands(o, kb);
       load_block(min(kb + KG, n_kblocks - 1));                          // (after the last block: the last one again, unused)
-      block(o, kb, masked_c);
+      block(o, kb, form_c);
     };
     int kb = kg;
-    for (; kb < n_kblocks && no_reference(); kb += KG) next(kb, std::true_type{});
-    for (; kb < kb_full; kb += KG) next(kb, std::false_type{});
-    for (; kb < n_kblocks; kb += KG) next(kb, std::true_type{});
+    if (kb < kb_full) { next(kb, first_c); kb += KG; }
+    else for (; kb < n_kblocks && no_reference(); kb += KG) next(kb, any_c);
+    for (; kb < kb_full; kb += KG) next(kb, whole_c);
+    for (; kb < n_kblocks; kb += KG) next(kb, part_c);
   } else {
     // ---- stages of QW blocks: every wave converts one block of the next stage, then all of them attend to the whole
     // current one; a key group takes every KG-th stage
@@ -351,11 +373,12 @@ void k_prefill_attn(PrefillParams p) {
       }
       const uint8_t* src = stage + (it & 1) * STAGE;
       const int kb0 = (it * KG + kg) * QW, j_full = min(kb_full - kb0, QW), j_end = min(kb_end - kb0, QW);
-      auto staged = [&](int j, auto masked_c) { block(StageOperands<KK>{src + j * BLK, lane, g2}, kb0 + j, masked_c); };
+      auto staged = [&](int j, auto form_c) { block(StageOperands<KK>{src + j * BLK, lane, g2}, kb0 + j, form_c); };
       int j = 0;
-      for (; j < j_end && no_reference(); j++) staged(j, std::true_type{});
-      for (; j < j_full; j++) staged(j, std::false_type{});
-      for (; j < j_end; j++) staged(j, std::true_type{});
+      if (it == 0 && j_full > 0) staged(j++, first_c);
+      else for (; j < j_end && no_reference(); j++) staged(j, any_c);
+      for (; j < j_full; j++) staged(j, whole_c);
+      for (; j < j_end; j++) staged(j, part_c);
       __syncthreads();
     }
   }
@@ -394,11 +417,15 @@ void k_prefill_attn(PrefillParams p) {
 
   // ---- O^T = B_V^T (U / l).  Register v of U[kk] in lane half g2 is latent dim 32 kk + 8 (v / 4) + 4 g2 + v % 4; the A
   // operand gathers the rows of B_V in that order (all of the wave's output channels in one round trip).
+  // (the lane's number and row anew from the hardware: no register, and no scratch memory, holds them through the loop)
+  const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), n_e = lane_e & 31, g_e = lane_e >> 5;
+  // Where a wave has two blocks of 32 channels, they are the even and the odd ones of 64: a dword holds an element of either.
   constexpr int NRB = D / 32 / KG < 1 ? 1 : D / 32 / KG;                // blocks of 32 output channels per wave
+  constexpr bool PAIRS = NRB % 2 == 0;
   v4i av[NRB][KK][2];
 #pragma unroll
-  for (int t = 0; t < NRB; t++) {
-    const int c = 32 * min(kg + t * KG, D / 32 - 1) + n;                // output channel of this lane's A row
+  for (int t = 0; t < NRB; t += PAIRS ? 2 : 1) {
+    const int c = PAIRS ? 64 * (kg + t / 2 * KG) + 2 * n_e : 32 * min(kg + t * KG, D / 32 - 1) + n_e;     // (first) output channel of this lane's A row
 #pragma unroll
     for (int kk = 0; kk < KK; kk++)
 #pragma unroll
@@ -406,9 +433,15 @@ void k_prefill_attn(PrefillParams p) {
 #pragma unroll
         for (int e = 0; e < 4; e++) {
           const int v0 = 8 * s + 2 * e, v1 = v0 + 1;
-          const int j0 = 32 * kk + 8 * (v0 >> 2) + 4 * g2 + (v0 & 3), j1 = 32 * kk + 8 * (v1 >> 2) + 4 * g2 + (v1 & 3);
-          const uint32_t e0 = p.BV[((size_t)kv * R + j0) * D + c], e1 = p.BV[((size_t)kv * R + j1) * D + c];
-          av[t][kk][s][e] = (int)(e0 | (e1 << 16));
+          const int j0 = 32 * kk + 8 * (v0 >> 2) + 4 * g_e + (v0 & 3), j1 = 32 * kk + 8 * (v1 >> 2) + 4 * g_e + (v1 & 3);
+          const uint16_t *b0 = p.BV + ((size_t)kv * R + j0) * D + c, *b1 = p.BV + ((size_t)kv * R + j1) * D + c;
+          if constexpr (PAIRS) {
+            const uint32_t e0 = *(const uint32_t*)b0, e1 = *(const uint32_t*)b1;
+            av[t][kk][s][e] = (int)__builtin_amdgcn_perm(e1, e0, 0x05040100u);
+            av[t + (PAIRS ? 1 : 0)][kk][s][e] = (int)__builtin_amdgcn_perm(e1, e0, 0x07060302u);
+          } else {
+            av[t][kk][s][e] = (int)((uint32_t)*b0 | ((uint32_t)*b1 << 16));
+          }
         }
   }
   const float inv = L > 0.f ? 1.0f / L : 0.f;
@@ -429,10 +462,7 @@ void k_prefill_attn(PrefillParams p) {
       uh[kk][s] = __builtin_bit_cast(v8bf16, hh);
       ul[kk][s] = __builtin_bit_cast(v8bf16, ll);
     }
-#pragma unroll
-  for (int t = 0; t < NRB; t++) {
-    const int rb = kg + t * KG;
-    if (rb >= D / 32) break;                                            // (wave-uniform: more groups than channel blocks)
+  auto product = [&](int t) {
     v16f O;
 #pragma unroll
     for (int v = 0; v < 16; v++) O[v] = 0.f;
@@ -444,14 +474,34 @@ void k_prefill_attn(PrefillParams p) {
         O = mfma_bf16(a, uh[kk][s], O);
         O = mfma_bf16(a, ul[kk][s], O);
       }
-    if (row_ok) {
-      float* orow = p.out + (ph * p.NR + rho_c) * D;
+    return O;
+  };
+  int row_e = qb * 32 + n_e;
+  asm volatile("" : "+v"(row_e));
+  float* const orow = p.out + (ph * p.NR + min(row_e, p.NR - 1)) * D;
+  if constexpr (PAIRS) {
 #pragma unroll
-      for (int m4 = 0; m4 < 4; m4++) {
-        v4f o4;
+    for (int t = 0; t < NRB; t += 2) {
+      const v16f O0 = product(t), O1 = product(t + 1);
+      if (row_e < p.NR) {
 #pragma unroll
-        for (int jj = 0; jj < 4; jj++) o4[jj] = O[4 * m4 + jj];
-        *(v4f*)&orow[32 * rb + 8 * m4 + 4 * g2] = o4;
+        for (int m4 = 0; m4 < 4; m4++) {
+          float* const to = orow + 64 * (kg + t / 2 * KG) + 16 * m4 + 8 * g_e;
+          *(v4f*)to = v4f{O0[4 * m4], O1[4 * m4], O0[4 * m4 + 1], O1[4 * m4 + 1]};
+          *(v4f*)(to + 4) = v4f{O0[4 * m4 + 2], O1[4 * m4 + 2], O0[4 * m4 + 3], O1[4 * m4 + 3]};
+        }
+      }
+    }
+  } else {
+#pragma unroll
+    for (int t = 0; t < NRB; t++) {
+      const int rb = kg + t * KG;
+      if (rb >= D / 32) break;                                          // (wave-uniform: more groups than channel blocks)
+      const v16f O = product(t);
+      if (row_e < p.NR) {
+#pragma unroll
+        for (int m4 = 0; m4 < 4; m4++)
+          *(v4f*)&orow[32 * rb + 8 * m4 + 4 * g_e] = v4f{O[4 * m4], O[4 * m4 + 1], O[4 * m4 + 2], O[4 * m4 + 3]};
       }
     }
   }
