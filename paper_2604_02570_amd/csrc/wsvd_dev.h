@@ -33,6 +33,18 @@ constexpr int kTimelineWaves = 16, kTimelineSlots = 16;
 #define WSVD_STAMP(buf, wg, wave, slot) do { } while (0)
 #endif
 
+// The lane's number from the hardware, for what follows a long loop: threadIdx would hold a register through it (one lane
+// register of scratch in the 256 x 128 tiles of the prompt projection).
+WSVD_DEV int lane_number() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
+
+// What lane L % 32 of the lower and of the upper half of the wave holds, in both halves: no LDS, and no register for an index.
+WSVD_DEV void both_halves(float x, float& lower, float& upper) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  lower = __uint_as_float(r[0]); upper = __uint_as_float(r[1]);
+}
+WSVD_DEV float halves_max(float x) { float a, b; both_halves(x, a, b); return fmaxf(a, b); }
+WSVD_DEV float halves_sum(float x) { float a, b; both_halves(x, a, b); return a + b; }
+
 // ---------------------------------------------------------------- matrix-core helpers
 // 32x32 products of one wavefront.  Operand lane L holds row (column) L % 32 and the 8 (int8: 16) contraction
 // indices starting at 8 (16) * (L / 32); accumulator lane L holds column L % 32, rows 8 (v / 4) + 4 (L / 32) + v % 4.

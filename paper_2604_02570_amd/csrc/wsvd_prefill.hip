@@ -31,7 +31,7 @@
 // with the weights summed as the fp16 values: the same time there, but the largest weight is then not exact (error against
 // 64 bits up to 2.14e-4 where this has 2.12e-4, and 2.5e-4 with the sum in fp32).  With scores so small that such a
 // reference never moves, the maxima that do cost 7 % (0.53 ms against 0.49 at the clock that data leaves, 0.64 with one wave
-// per 32 rows).  Tried, no gain: the lane halves' exchange by v_permlane32_swap instead of LDS.  Tried and slower: two query
+// per 32 rows).  Tried and slower: two query
 // blocks per wave without LDS (193 registers, two waves per SIMD; three waves spill), the next block's score products issued
 // under the softmax.
 //
@@ -131,11 +131,12 @@ void k_prefill_attn(PrefillParams p) {
   const int lim_wg = sees((qb - qw) * 32 + 32 * QW - 1);
   const int n_kblocks = lim_wg > 0 ? (lim_wg + 31) >> 5 : 0;            // of the workgroup
   if (n_kblocks == 0) {                                                 // nothing visible to any row of the workgroup
-    int row = qb * 32 + n;
-    asm volatile("" : "+v"(row));                                       // (a row's address of its own: the queries' would be held through the loop)
+    int lane_z = lane_number();                                         // (of its own: no register is held through the loop for it)
+    asm volatile("" : "+v"(lane_z));
+    const int row = qb * 32 + (lane_z & 31), gz = lane_z >> 5;
     float* const orow = p.out + (ph * p.NR + min(row, p.NR - 1)) * D;
     if (row < p.NR && kg == 0)
-      for (int c = g2 * (D / 2); c < (g2 + 1) * (D / 2); c++) orow[c] = 0.f;
+      for (int c = gz * (D / 2); c < (gz + 1) * (D / 2); c++) orow[c] = 0.f;
     return;
   }
   const int lim_max = qb * 32 < p.NR ? sees(qb * 32 + 31) : 0, lim_min = sees(qb * 32);
@@ -245,6 +246,9 @@ void k_prefill_attn(PrefillParams p) {
     o.sc[0] = __builtin_bit_cast(v8f16, ks16[0]); o.sc[1] = __builtin_bit_cast(v8f16, ks16[OWN ? 1 : 0]);
   };
 
+  // over a column's rows, half of which the other half of the wave holds (through LDS where a register is left for the index: the
+  // exchange of halves takes two at once)
+  auto column_max = [&](float x) { return OWN ? fmaxf(x, __shfl_xor(x, 32)) : halves_max(x); };
   // op: the block's operands, each asked for where it is used (k(s), scales ks(s), v(kk, s))
   // kFirst: nothing seen yet, every query sees the whole block; kWhole: every query does; kPart: every query has a reference,
   // some see a part; kAny: everything else.  (68, 68, 100 and 200 vector instructions; with the general form for the first and the
@@ -275,7 +279,7 @@ void k_prefill_attn(PrefillParams p) {
         x[v] = S[v] * (float)sk8[v >> 3][v & 7];
         bmax = fmaxf(bmax, x[v]);
       }
-      m_ref = fmaxf(bmax, __shfl_xor(bmax, 32));
+      m_ref = column_max(bmax);
 #pragma unroll
       for (int v = 0; v < 16; v++) x[v] -= m_ref;
     } else if constexpr (FORM == kAny) {
@@ -286,7 +290,7 @@ void k_prefill_attn(PrefillParams p) {
         x[v] = kb * 32 + 16 * g2 + v < lim ? sc : -INFINITY;
         bmax = fmaxf(bmax, x[v]);
       }
-      bmax = fmaxf(bmax, __shfl_xor(bmax, 32));                         // the other half holds the column's other rows
+      bmax = column_max(bmax);                                          // the other half holds the column's other rows
       const float m_new = fmaxf(m_ref, bmax);
       const float alpha = m_ref == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_ref - m_new);
 #pragma unroll
@@ -305,7 +309,7 @@ void k_prefill_attn(PrefillParams p) {
         bmax = fmaxf(bmax, x[v]);
       }
       if (__builtin_amdgcn_ballot_w64(bmax > 0.f) != 0) {               // some column's maximum moves
-        bmax = fmaxf(bmax, __shfl_xor(bmax, 32));
+        bmax = column_max(bmax);
         const float m_new = m_ref + fmaxf(bmax, 0.f), d = m_new - m_ref;
         const float alpha = __builtin_amdgcn_exp2f(-d);
         m_ref = m_new; l_run *= alpha;
@@ -383,7 +387,7 @@ void k_prefill_attn(PrefillParams p) {
     }
   }
 
-  float L = l_run + __shfl_xor(l_run, 32);
+  float L = OWN ? l_run + __shfl_xor(l_run, 32) : halves_sum(l_run);
   if constexpr (KG > 1) {
     // the key groups' partial results: every group's wave of the same rows folds all of them in group order, then takes its
     // share of the output channels  (LDS: U in register order, then m and l per query; the last barrier has passed)
@@ -418,7 +422,9 @@ void k_prefill_attn(PrefillParams p) {
   // ---- O^T = B_V^T (U / l).  Register v of U[kk] in lane half g2 is latent dim 32 kk + 8 (v / 4) + 4 g2 + v % 4; the A
   // operand gathers the rows of B_V in that order (all of the wave's output channels in one round trip).
   // (the lane's number and row anew from the hardware: no register, and no scratch memory, holds them through the loop)
-  const int lane_e = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)), n_e = lane_e & 31, g_e = lane_e >> 5;
+  int lane_e = lane_number();
+  asm volatile("" : "+v"(lane_e));
+  const int n_e = lane_e & 31, g_e = lane_e >> 5;
   // Where a wave has two blocks of 32 channels, they are the even and the odd ones of 64: a dword holds an element of either.
   constexpr int NRB = D / 32 / KG < 1 ? 1 : D / 32 / KG;                // blocks of 32 output channels per wave
   constexpr bool PAIRS = NRB % 2 == 0;
@@ -476,8 +482,7 @@ void k_prefill_attn(PrefillParams p) {
       }
     return O;
   };
-  int row_e = qb * 32 + n_e;
-  asm volatile("" : "+v"(row_e));
+  const int row_e = qb * 32 + n_e;
   float* const orow = p.out + (ph * p.NR + min(row_e, p.NR - 1)) * D;
   if constexpr (PAIRS) {
 #pragma unroll

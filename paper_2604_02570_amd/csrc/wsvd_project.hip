@@ -5,10 +5,6 @@
 
 namespace {
 
-// The lane's number from the hardware, for what follows the products: threadIdx would hold a register through them (one lane
-// register of scratch in the 256 x 128 tiles).
-WSVD_DEV int lane_number() { return (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u)); }
-
 // ---------------------------------------------------------------- cache build for a whole prompt (int8 latents)
 // C^T [channels x tokens] = A^T x^T on bf16 MFMA.  The channels of both planes form one axis of 2 * Hkv * r / 32 tiles
 // of 32; a wavefront owns CT channel tiles x TT token tiles (CT * TT accumulators of 32 x 32), so each 1 KiB operand it
@@ -119,7 +115,7 @@ WSVD_DEV RowI8<RT> quantise_row_i8(const v16f (&a)[RT]) {
   for (int rt = 0; rt < RT; rt++)
 #pragma unroll
     for (int v = 0; v < 16; v++) m = fmaxf(m, fabsf(a[rt][v]));
-  m = fmaxf(m, __shfl_xor(m, 32));
+  m = halves_max(m);
   r.scale = m != 0.f ? guard_scale_f16(m / 127.0f) : (uint16_t)0x3C00u;
   const float sc = f16_bits_to_f32(r.scale), inv = 1.0f / sc;
 #pragma unroll
@@ -166,7 +162,7 @@ WSVD_DEV void store_row_i4(const ProjectParams& p, const v16f& a, int pl, int se
   float lo = 0.f, hi = 0.f;
 #pragma unroll
   for (int v = 0; v < 16; v++) { lo = fminf(lo, a[v]); hi = fmaxf(hi, a[v]); }
-  lo = fminf(lo, __shfl_xor(lo, 32)); hi = fmaxf(hi, __shfl_xor(hi, 32));
+  lo = -halves_max(-lo); hi = halves_max(hi);
   uint16_t sh = 0x3C00u;
   float z = 0.f;
   const bool flat = (hi == lo);
@@ -217,7 +213,7 @@ WSVD_DEV void project_store_tiles(const ProjectParams& p, const v16f (&acc)[CT][
   static_assert(!I4 || R == 32, "int4 latents have rank 32");
   const int tiles_plane = p.Hkv * RT, tiles = 2 * tiles_plane;
   const int ct = ct0 + h * RT;
-  const int pl = ct / tiles_plane, kv = (ct % tiles_plane) / RT;        // (wave-uniform)
+  const int pl = ct >= tiles_plane, kv = (ct - (pl ? tiles_plane : 0)) / RT;   // (wave-uniform; no division: its reciprocal was kept)
   RowI8<RT> rows[N];
   if constexpr (!I4) {
 #pragma unroll
@@ -565,7 +561,7 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
   // (counted behind the store where no register is left to hold the answer)
   constexpr bool LATE = R == 64 && CT * TT >= 8;
   int seen = -1;
-  project_hold(n0);
+  if constexpr (!LATE) project_hold(n0);
   if constexpr (KS == 1) {
     __syncthreads();
     if constexpr (!LATE) seen = project_count(p);
@@ -607,7 +603,10 @@ __global__ __launch_bounds__(64 * WC * KS) void k_prefill_project_direct(Project
       project_store_tiles<R, CT, TT, I4, SPAN, 1>(p, acc, u / TT, u % TT, ct0, by * 32 * TT, seq, n0);
     }
   }
-  if constexpr (LATE) seen = project_count(p);
+  if constexpr (LATE) {
+    __syncthreads();                                                    // (every wave has used its lengths)
+    seen = project_count(p);
+  }
   project_advance(p, seen);
 }
 
