@@ -184,42 +184,63 @@ WSVD_DEV void append_split_body(Params p, int SB, int xs_stride /* elements */, 
       }
     }
   };
-  // ---- hidden states of the share -> LDS: whole 16-byte pieces, kPieces per thread and trip in flight (wave-uniform
-  // predicate per piece); the factor batches go out between the first trip's requests and its LDS writes, so that a
-  // wave's first k-steps cost one round trip.  The row of piece i is i / ppr by a reciprocal: (i + 1/2) / ppr is at least
-  // 1 / (2 ppr) away from every integer, more than the product is off (a row number below 32 times 2^-22; ppr < 2^13, or the
-  // row is 0), so its integer part is exact.  Two integer divisions per piece / one
-  // per thread and a walk from piece to piece / this, append + attention over 130 cached rows: 64 sequences of 32 heads,
-  // int8, 31.5 / 30.2 / 29.4 us, 23 paged ones 20.7 / 20.0 / 19.6, one sequence of 8 heads, d_model 512, 10.9 / 11.1 / 10.9.
-  // Eight pieces in flight: 0.5 us less for 64 sequences, but 0.5 to 4 us more for up to 32 and for the slices of the int8
-  // step (registers).
-  constexpr int kPieces = 4;
-  const int ppr = (wg_k1 - wg_k0) * 2, n_pieces = nb * ppr;     // 16-byte pieces per row (none: an empty share)
-  const float per_row = __builtin_amdgcn_rcpf((float)ppr);
-  bool first = true;
-  for (int i0 = 0; i0 < n_pieces || first; i0 += kPieces * (int)blockDim.x) {
-    v4i piece[kPieces];
-    int to[kPieces];                                            // LDS element of the piece
-#pragma unroll
-    for (int it = 0; it < kPieces; it++) {
-      if (i0 + it * (int)blockDim.x + (wave << 6) < n_pieces) { // some lane of this wave has a piece
-        const int i = min(i0 + it * (int)blockDim.x + tid, n_pieces - 1);
-        const int row = (int)(((float)i + 0.5f) * per_row), at = (i - row * ppr) * 8;
-        piece[it] = *(const v4i*)(xp + (size_t)(b0 + row) * p.E + (size_t)wg_k0 * 16 + at);
-        to[it] = row * xs_stride + at;
-      }
+  // ---- in the int8 step of one launch: the factors of the first k-steps, and behind them the share of the hidden states
+  // straight to LDS, 1 KiB of a row per instruction, dealt to the waves: all of it in flight at once, without a register.
+  // The few workgroups of that launch are bound by this round trip, which the attention's waves wait for: four layers of 16
+  // heads, one sequence of 500 rows 44.7 -> 41.7 us, three of 2048 50.4 -> 48.1.  Everywhere else it is no gain or a loss
+  // (the bf16 step 90.0 -> 90.5 us, 64 sequences of 300 rows in two launches 30.8 -> 31.9, 28 heads on 4 93.7 -> 95.7: the
+  // workgroups that share a CU hide the trip, and the registers' copies start the products earlier), so that the pieces
+  // go through registers there.
+  if constexpr (DEFER == kPushSlices) {
+    static_assert(VW == 1);
+    load_a(0, ks0[0]); load_a(1, ks0[0] + KB);
+    const int ppr = (wg_k1 - wg_k0) * 2, segs = (ppr + 63) >> 6, n_segs = nb * segs;   // pieces of 16 bytes, instructions per row
+    const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(app_lds));
+    for (int i = __builtin_amdgcn_readfirstlane(wave); i < n_segs; i += (int)(blockDim.x >> 6)) {
+      const int row = i / segs, seg = i - row * segs;
+      const uint8_t* src = (const uint8_t*)(xp + (size_t)(b0 + row) * p.E + (size_t)wg_k0 * 16) + seg * 1024;
+      if (seg * 64 + lane < ppr) lds_copy16(lds0 + row * xs_stride * 2 + seg * 1024, src, lane * 16);
     }
-    if (first) {
-      if constexpr (VW == 1) { load_a(0, ks0[0]); load_a(1, ks0[0] + KB); }
-      else {
+    WSVD_STAMP(p.timeline, tl_wg, wave, 1);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  } else {
+    // Otherwise: hidden states of the share -> LDS, whole 16-byte pieces, kPieces per thread and trip in flight (wave-uniform
+    // predicate per piece); the factor batches go out between the first trip's requests and its LDS writes, so that a
+    // wave's first k-steps cost one round trip.  The row of piece i is i / ppr by a reciprocal: (i + 1/2) / ppr is at least
+    // 1 / (2 ppr) away from every integer, more than the product is off (a row number below 32 times 2^-22; ppr < 2^13, or the
+    // row is 0), so its integer part is exact.  Two integer divisions per piece / one
+    // per thread and a walk from piece to piece / this, append + attention over 130 cached rows: 64 sequences of 32 heads,
+    // int8, 31.5 / 30.2 / 29.4 us, 23 paged ones 20.7 / 20.0 / 19.6, one sequence of 8 heads, d_model 512, 10.9 / 11.1 / 10.9.
+    // Eight pieces in flight: 0.5 us less for 64 sequences, but 0.5 to 4 us more for up to 32 and for the slices of the int8
+    // step (registers).
+    constexpr int kPieces = 4;
+    const int ppr = (wg_k1 - wg_k0) * 2, n_pieces = nb * ppr;     // 16-byte pieces per row (none: an empty share)
+    const float per_row = __builtin_amdgcn_rcpf((float)ppr);
+    bool first = true;
+    for (int i0 = 0; i0 < n_pieces || first; i0 += kPieces * (int)blockDim.x) {
+      v4i piece[kPieces];
+      int to[kPieces];                                            // LDS element of the piece
 #pragma unroll
-        for (int v = 0; v < VW; v++) load_a(v, ks0[v]);
+      for (int it = 0; it < kPieces; it++) {
+        if (i0 + it * (int)blockDim.x + (wave << 6) < n_pieces) { // some lane of this wave has a piece
+          const int i = min(i0 + it * (int)blockDim.x + tid, n_pieces - 1);
+          const int row = (int)(((float)i + 0.5f) * per_row), at = (i - row * ppr) * 8;
+          piece[it] = *(const v4i*)(xp + (size_t)(b0 + row) * p.E + (size_t)wg_k0 * 16 + at);
+          to[it] = row * xs_stride + at;
+        }
       }
-      first = false; WSVD_STAMP(p.timeline, tl_wg, wave, 1);
-    }
+      if (first) {
+        if constexpr (VW == 1) { load_a(0, ks0[0]); load_a(1, ks0[0] + KB); }
+        else {
 #pragma unroll
-    for (int it = 0; it < kPieces; it++)
-      if (i0 + it * (int)blockDim.x + tid < n_pieces) *(v4i*)&xs[to[it]] = piece[it];
+          for (int v = 0; v < VW; v++) load_a(v, ks0[v]);
+        }
+        first = false; WSVD_STAMP(p.timeline, tl_wg, wave, 1);
+      }
+#pragma unroll
+      for (int it = 0; it < kPieces; it++)
+        if (i0 + it * (int)blockDim.x + tid < n_pieces) *(v4i*)&xs[to[it]] = piece[it];
+    }
   }
   if (tid < 32) n_loc[tid] = nreg;
   __syncthreads();

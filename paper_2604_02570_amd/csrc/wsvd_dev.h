@@ -45,6 +45,20 @@ WSVD_DEV void both_halves(float x, float& lower, float& upper) {
 WSVD_DEV float halves_max(float x) { float a, b; both_halves(x, a, b); return fmaxf(a, b); }
 WSVD_DEV float halves_sum(float x) { float a, b; both_halves(x, a, b); return a + b; }
 
+// ---------------------------------------------------------------- memory straight to LDS
+// 16 bytes per lane from memory (base + lane's offset) straight to LDS, at 16 lane past the uniform byte address `lds`.  What is
+// copied may be read behind lds_copy_wait_barrier, which waits until this wave's reads are answered and all but the newest
+// LEFT of its copies have arrived, and then for the other waves; LDS may be overwritten behind it.
+WSVD_DEV void lds_copy16(uint32_t lds, const uint8_t* base, uint32_t offset) {
+  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + offset),
+                                   (__attribute__((address_space(3))) void*)(uintptr_t)lds, 16, 0, 0);
+}
+template <int LEFT>
+WSVD_DEV void lds_copy_wait_barrier() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
+}
+WSVD_DEV uint32_t lds_address(const void* shared) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint8_t*)shared; }
+
 // ---------------------------------------------------------------- matrix-core helpers
 // 32x32 products of one wavefront.  Operand lane L holds row (column) L % 32 and the 8 (int8: 16) contraction
 // indices starting at 8 (16) * (L / 32); accumulator lane L holds column L % 32, rows 8 (v / 4) + 4 (L / 32) + v % 4.

@@ -313,18 +313,6 @@ typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 constexpr int kProjKC = 64, kProjXRow = 144;
 constexpr int kProjABytes = 8 * 4 * 1024, kProjXBytes = 256 * 128, kProjLds = 2 * kProjABytes + 3 * kProjXBytes;
 
-// 16 bytes per lane from memory (base + lane's offset) straight to LDS, at 16 lane past the uniform byte address `lds`.  What is
-// copied may be read behind lds_copy_wait_barrier, which waits until this wave's reads are answered and all but the newest
-// LEFT of its copies have arrived, and then for the other waves; LDS may be overwritten behind it.
-WSVD_DEV void lds_copy16(uint32_t lds, const uint8_t* base, uint32_t offset) {
-  __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + offset),
-                                   (__attribute__((address_space(3))) void*)(uintptr_t)lds, 16, 0, 0);
-}
-template <int LEFT>
-WSVD_DEV void lds_copy_wait_barrier() {
-  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(LEFT) : "memory");
-}
-
 // Workgroup -> (channel group, token group).  Consecutive workgroup ids land on different XCDs (8 of them, each with
 // its own L2).  Token-affine: XCD i takes the token groups = i (mod 8), so a line of hidden states is fetched by one XCD
 // only and every XCD walks through all factors.  Otherwise the channel groups go round: with a number of them that shares
@@ -377,7 +365,7 @@ __global__ __launch_bounds__(64 * kProjWaves) void k_prefill_project_lds(Project
     const int row = by * 256 + 8 * NX * wave + 8 * j + (lane >> 3);         // the launcher keeps rows * E * 2 below 2^31
     xoff[j] = (uint32_t)min(row, p.rows - 1) * (uint32_t)(p.E * 2) + (((lane & 7) ^ (lane >> 3)) * 16);
   }
-  const uint32_t lds0 = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t*)proj_lds);
+  const uint32_t lds0 = __builtin_amdgcn_readfirstlane(lds_address(proj_lds));
   // (past the end: the last chunk again, into a stage that is not read any more)
   auto copy_a = [&](int j, int ks, int c) {
     lds_copy16(lds0 + (c & 1) * kProjABytes + (NA * wave + j) * 4096 + ks * 1024, asrc[j] + (size_t)min(c, n_chunks - 1) * 4096 + ks * 1024, lane16);
