@@ -2202,11 +2202,12 @@ static hipError_t launch_step_i8(const I8StepParams& p, size_t lds, hipStream_t 
 // One launch or two.  One where all workgroups have their places from the start: two per CU at rank 32 with one query head (128
 // registers, 8 waves), of which the projection's first ones leave early, one per CU otherwise.  Beyond, attention workgroups
 // wait for the projection's to leave.  us a step, one launch / two (cold layers):
-//   1 x 2500 rows, 32 heads, rank 32, d_model 4096   12.4 / 16.2     24 x 900, the same (beyond)     28.3 / 22.3
-//   4 x 2500, the same                               14.8 / 17.3     16 x 2500                       27.5 / 27.0
-//   1 x 900, the same                                11.8 / 13.4     8 x 250                         14.1 / 13.6
-//   32 x 900, 8 heads, rank 32, d_model 512          11.8 / 12.4     1 x 250, rank 64                19.6 / 18.0
-// Over 195 sizes on this side of the lines the median is 1.22 x, the worst 1.00.
+//   1 x 2500 rows, 32 heads, rank 32, d_model 4096   12.6 / 15.9     24 x 900, the same (beyond)     26.9 / 21.5
+//   4 x 2500, the same                               13.9 / 16.7     16 x 2500                       26.4 / 26.3
+//   1 x 900, the same                                11.6 / 13.4     8 x 250                         14.3 / 13.2
+//   32 x 900, 8 heads, rank 32, d_model 512          11.7 / 11.8     1 x 250, rank 64                19.3 / 17.4
+// Over 195 sizes on this side of the lines the median is 1.22 x, the worst 1.00 (taken while this launch still moved its hidden
+// states through registers, 0 to 1 us slower).
 static bool step_i8_one_launch(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int proj, int attend) {
   const bool slim = d.rank == 32 && d.n_q_heads == d.n_kv_heads;
   return 2 * (proj + attend) <= (slim ? 3 : 2) * ctx->n_cu;
