@@ -29,7 +29,8 @@ WSVD_DEV void step_attend(const FloatStepParams& p) {
   const int id = (int)blockIdx.x - p.n_proj;
   const int kv = id % a.Hkv, chunk = id / a.Hkv % a.n_chunks, b = id / (a.Hkv * a.n_chunks);
   int n = a.seq_lens[b];
-  asm volatile("" : "+s"(n)::"memory");                          // the length is here before its reader is counted
+  asm volatile("" : "+s"(n)::"memory");                          // this wave holds the length ...
+  __syncthreads();                                               // ... and so do the other three: their workgroup may be counted
   const bool fits = n >= 0 && n < a.t_cap;
   if (threadIdx.x == 0) __hip_atomic_fetch_add(p.read + b, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   attn_generic_body<ESZ, R, G, kRowWords>(a, fits ? n + 1 : n, kv, chunk, b, fits);
