@@ -155,7 +155,12 @@ wsvd_status wsvd_create(wsvd_ctx** out, int device_ordinal) {
   c->timeline = nullptr;
   c->timeline_bytes = 0;
   if (hipMalloc((void**)&c->err_word, kCtxDeviceBytes) != hipSuccess) { delete c; return WSVD_E_HIP; }
-  if (hipMemset(c->err_word, 0, kCtxDeviceBytes) != hipSuccess) { (void)hipFree(c->err_word); delete c; return WSVD_E_HIP; }
+  // (waited for: the first call may come on a stream that does not wait for the default one, and the counters have to be zero)
+  if (hipMemset(c->err_word, 0, kCtxDeviceBytes) != hipSuccess || hipStreamSynchronize(nullptr) != hipSuccess) {
+    (void)hipFree(c->err_word);
+    delete c;
+    return WSVD_E_HIP;
+  }
   c->readers = c->err_word + kCtxReadersInt;
   if (static_scratch_for_device(device_ordinal, &c->static_scratch) != hipSuccess) { (void)hipFree(c->err_word); delete c; return WSVD_E_HIP; }
   *out = c;

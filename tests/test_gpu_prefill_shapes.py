@@ -300,3 +300,31 @@ def test_projection_advances_the_lengths(shape, batch, n_tok, kv_heads):
         assert W.wsvd_check(ctx) == (W.E_CAPACITY if full else 0), call
         assert (lens.cpu() == want).all(), call
     W.wsvd_destroy(ctx)
+
+
+def test_new_context_is_ready_on_any_stream():
+    """wsvd_create clears the context's counters on the default stream; the projection that counts on them may be the very next
+    call, on a stream that does not wait for that one, with the default stream still busy.  The memory is that of contexts before."""
+    desc = W.layer_desc(3, 8, 8, 128, 128, 32, 128, "i8", "bf16", "bf16", "bf16", "f32", 0.0)
+    cb, mb = W.wsvd_cache_bytes(desc)
+    codes, meta = [torch.zeros(cb, dtype=torch.uint8, device="cuda") for _ in range(2)], [torch.zeros(mb, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    x = torch.randn(3, 33, 128, device="cuda").to(torch.bfloat16)
+    A = [torch.zeros(W.wsvd_factor_a_bytes(desc), dtype=torch.uint8, device="cuda") for _ in range(2)]
+    busy = torch.randn(4096, 4096, device="cuda")
+    side = torch.cuda.Stream()
+    for shape in (5, 11, 2, 25):
+        lens = torch.zeros(3, dtype=torch.int32, device="cuda")
+        cache = W.make_cache(*codes, *meta, lens)
+        torch.cuda.synchronize()
+        for _ in range(8):
+            busy = busy @ busy * 1e-3
+        ctx = W.wsvd_create(0)
+        W.wsvd_ctx_set_option(ctx, "project_shape", shape)
+        W.wsvd_ctx_set_option(ctx, "prefill_tiled", 1)
+        for _ in range(3):
+            W.wsvd_prefill_append(ctx, desc, x, None, 33, -1, *A, cache, stream=side.cuda_stream)
+        assert W.wsvd_check(ctx, stream=side.cuda_stream) == 0
+        side.synchronize()
+        torch.cuda.synchronize()
+        assert (lens.cpu() == 99).all(), shape
+        W.wsvd_destroy(ctx)
