@@ -221,7 +221,7 @@ wsvd_status wsvd_ctx_set_option(wsvd_ctx* ctx, const char* name, int value) {
   if (!strcmp(name, "linear_direct") && value >= 0 && value <= 1) { o.linear_direct = value; return WSVD_OK; }
   if (!strcmp(name, "prefill_tiled") && value >= 0 && value <= 1) { o.prefill_tiled = value; return WSVD_OK; }
   if (!strcmp(name, "step_deferred") && value >= 0 && value <= 2) { o.step_deferred = value; return WSVD_OK; }
-  if (!strcmp(name, "step_launches") && value >= 0 && value <= 2) { o.step_launches = value; return WSVD_OK; }
+  if (!strcmp(name, "step_launches") && value >= 0 && value <= 3) { o.step_launches = value; return WSVD_OK; }
   if (!strcmp(name, "timeline_kernel") && value >= 0 && value <= 1) { o.timeline_kernel = value; return WSVD_OK; }
   if (!strcmp(name, "step_slices") && value >= 0 && value <= 4) { o.step_slices = value; return WSVD_OK; }
   if (!strcmp(name, "project_shape"))
@@ -654,6 +654,7 @@ wsvd_status wsvd_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const v
                                         : wsvd_launch_step_float(ctx, *desc, x, A_K, A_V, q, q_scale, B_K, B_V, *cache, max_seq_len, out, s);
       if (e != hipErrorNotSupported) return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;
     }
+    if (ctx->opt.step_launches == 3) return WSVD_E_UNSUPPORTED;
     // projection launch (partial sums, lengths advanced), then the attention launch that finishes the rows
     float* parts = nullptr;
     int* pending = nullptr;
@@ -662,7 +663,7 @@ wsvd_status wsvd_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const v
     if (e == hipSuccess) e = launch_step_attention(ctx, *desc, q, q_scale, B_K, B_V, *cache, max_seq_len, out, parts, pending, n_parts, s);
     if (e != hipErrorNotSupported) return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;
   }
-  if (e == hipErrorNotSupported && ctx->opt.step_deferred == 2) return WSVD_E_UNSUPPORTED;
+  if (e == hipErrorNotSupported && (ctx->opt.step_deferred == 2 || ctx->opt.step_launches == 3)) return WSVD_E_UNSUPPORTED;
   if (e == hipErrorNotSupported) {
     // no fused kernel for this combination: the two calls back to back on the stream
     e = wsvd_launch_append(ctx, *desc, x, x_scale, A_K, A_V, *cache, s);

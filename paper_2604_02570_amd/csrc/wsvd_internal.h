@@ -19,7 +19,7 @@ struct wsvd_options {
   int prefill_tiled = 0;    // the tiled prefill kernels also for small calls
   int project_shape = 0;    // kernel of the tiled prefill projection (0 = automatic)
   int step_deferred = 1;    // wsvd_decode_step: projection launch + attention launch that finishes the row: 1 where supported, 2 that or UNSUPPORTED
-  int step_launches = 0;    // the decode step: 0 one launch or two by size, 1 one wherever it exists, 2 never one
+  int step_launches = 0;    // the decode step: 0 one launch or two by size, 1 one wherever it exists, 2 never one, 3 one or UNSUPPORTED
   int timeline_kernel = 0;  // profiling build, wsvd_decode_step: whose stamps are recorded: 0 the attention launch's, 1 the projection launch's
   int step_slices = 0;      // d_model slices of that projection launch (0 = automatic)
 };

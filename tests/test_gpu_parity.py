@@ -706,15 +706,20 @@ STEP_CASES = [
     ("c3_small", dict(context=2000, batch=2), -2),
     ("c4_small", dict(context=2000, batch=2), -2),
     ("c5_small", dict(context=2000, batch=2), -2),
+    # 4: projection launch + attention launch in every format, 5: both in one launch
+    *[(n, o, m) for n, o in [("c3_small", dict()), ("c3_small", dict(rank=64, context=700)), ("c3_small", dict(batch=21, context=130)),
+                             ("c2_small", dict()), ("c2_small", dict(rank=64, n_q_heads=12, n_kv_heads=4, d_model=1024)), ("c1", dict(batch=3, context=70))] for m in (4, 5)],
 ]
 
 
 def _set_step_mode(ctx, mode):
-    """0 two launches, 1 / 2 the single-launch kernel (where it exists / or refuse), 3 the deferred-row pair of launches."""
+    """0 two launches, 1 / 2 the single-launch kernel (where it exists / or refuse), 3 the deferred-row pair of launches
+    (int8), 4 that pair, 5 projection and attention in one launch (or refuse)."""
     if mode < 0:
         return                                          # the context's defaults
     W.wsvd_ctx_set_option(ctx, "fused_step", mode if mode in (1, 2) else 0)
-    W.wsvd_ctx_set_option(ctx, "step_deferred", 2 if mode == 3 else 0)
+    W.wsvd_ctx_set_option(ctx, "step_deferred", {3: 2, 4: 1, 5: 1}.get(mode, 0))
+    W.wsvd_ctx_set_option(ctx, "step_launches", {4: 2, 5: 3}.get(mode, 0))
 
 
 @pytest.mark.parametrize("name,over,mode", STEP_CASES, ids=[f"{n}-{'-'.join(f'{k}{v}' for k, v in o.items())}" for n, o, _ in STEP_CASES])

@@ -20,12 +20,18 @@ CASES = [("c1", dict()), ("c1", dict(rank=32, d_model=4096, context=80)), ("c1",
          ("c2_small", dict(d_model=4096, n_q_heads=32, n_kv_heads=32))]
 
 
-@pytest.mark.parametrize("name,over", CASES, ids=[f"{n}-{'-'.join(f'{k}{v}' for k, v in o.items())}" for n, o in CASES])
-def test_step_rows_at_chunk_edges(name, over):
+# Two launches (2), and one (3) where it exists: not for ten bf16 sequences at d_model 4096 (the projection's LDS), and over fp32
+# latents only where the cache is large enough that the split words' area holds the projection's too (d_model / 256 partial sums a
+# row, d_model / 64 where 256 does not divide it).
+TWO_ONLY = [dict(rank=16, d_model=4160, context=80), dict(rank=64, d_model=1600, context=80), dict(d_model=4096, n_q_heads=32, n_kv_heads=32)]
+FORMS = [(n, o, 1088, 2) for n, o in CASES] + [(n, o, 4672 if o.get("d_model") == 4096 else 1088, 3) for n, o in CASES if o not in TWO_ONLY]
+
+
+@pytest.mark.parametrize("name,over,t_cap,launches", FORMS, ids=[f"{n}-{'-'.join(f'{k}{v}' for k, v in o.items())}-{'two' if m == 2 else 'one'}" for n, o, _, m in FORMS])
+def test_step_rows_at_chunk_edges(name, over, t_cap, launches):
     lens = [0, 1, 63, 64, 255, 256, 1023, 1024, 1025, 1087]
     c = build_case(name, **{**dict(batch=len(lens), context=90, steps=1, extra_cap=0), **over})
     sp = c.sp
-    t_cap = 1088
     L = layer_for(c, t_cap=t_cap)
     full = O.LatentCache(sp.batch, sp.n_kv_heads, t_cap, sp.rank, sp.latent_dtype)
     g = np.random.default_rng(11)
@@ -34,8 +40,8 @@ def test_step_rows_at_chunk_edges(name, over):
             full.store_rows(plane, b, 0, g.standard_normal((sp.n_kv_heads, n, sp.rank)))
         full.seq_lens[b] = n
     full.seq_lens[-1] = t_cap                               # full: attended as it is, reported
-    full.store_rows("k", sp.batch - 1, 1087, g.standard_normal((sp.n_kv_heads, 1, sp.rank)))
-    full.store_rows("v", sp.batch - 1, 1087, g.standard_normal((sp.n_kv_heads, 1, sp.rank)))
+    full.store_rows("k", sp.batch - 1, 1087, g.standard_normal((sp.n_kv_heads, t_cap - 1087, sp.rank)))
+    full.store_rows("v", sp.batch - 1, 1087, g.standard_normal((sp.n_kv_heads, t_cap - 1087, sp.rank)))
     L.upload(full)
     W.wsvd_ctx_set_option(L.ctx, "min_chunk", 0)
     x = WI.bf16_exact(c.x_new[0]) if sp.factor_dtype == "bf16" else c.x_new[0]
@@ -50,6 +56,7 @@ def test_step_rows_at_chunk_edges(name, over):
     two, _ = L.step(*args)
     two_planes = [t.clone() for t in (L.k_codes, L.v_codes)]
     W.wsvd_ctx_set_option(L.ctx, "step_deferred", 1)
+    W.wsvd_ctx_set_option(L.ctx, "step_launches", launches)                  # two launches, or one or nothing
     L.upload(full)
     got, st = L.step(*args)
     assert st == W.E_CAPACITY
@@ -89,8 +96,16 @@ ONE_LAUNCH = [("c1", dict()), ("c1", dict(rank=32, n_q_heads=6, n_kv_heads=2, d_
               ("c3_small", dict()), ("c3_small", dict(rank=64, n_q_heads=8, n_kv_heads=4)), ("c3_small", dict(n_q_heads=8, n_kv_heads=2, d_model=1088))]
 
 
-@pytest.mark.parametrize("lens", [[0], [1087], [1024, -1, 1088], [0, 1, 63, 64, 256, 1023, 1025]], ids=lambda v: "-".join(map(str, v)))
-@pytest.mark.parametrize("name,over", ONE_LAUNCH, ids=[f"{n}-{'-'.join(f'{k}{v}' for k, v in o.items())}" for n, o in ONE_LAUNCH])
+# more sequences than one pass over the hidden states takes (fp32: 8) or than one group of projection workgroups (int8: 16, so that
+# the last group is a part of one)
+MANY = [1088, 5, 0, 1087, 64, 1023, 7, 1024, -1, 1088, 300, 63, 1, 255, 1025, 900, 17, 1088, 0, -1, 1087, 2, 640, 65, 31, 1024, 8, 1000, 33, 1086, 12, 512, 1088]
+GROUPS = [("c1", dict(), MANY[:9]), ("c1", dict(rank=64, d_head=128), MANY[:17]), ("c2_small", dict(), MANY[:17]), ("c2_small", dict(rank=16, n_q_heads=4, n_kv_heads=2), MANY[:32]),
+          ("c3_small", dict(), MANY[:20]), ("c3_small", dict(), MANY), ("c3_small", dict(rank=64, n_q_heads=8, n_kv_heads=4), MANY[:20]),
+          ("c3_small", dict(rank=64), MANY)]
+BOTH_FORMS = [(n, o, l) for n, o in ONE_LAUNCH for l in ([0], [1087], [1024, -1, 1088], [0, 1, 63, 64, 256, 1023, 1025])] + GROUPS
+
+
+@pytest.mark.parametrize("name,over,lens", BOTH_FORMS, ids=[f"{n}-{'-'.join(f'{k}{v}' for k, v in o.items())}-{'-'.join(map(str, l)) if len(l) < 9 else f'{len(l)}seq'}" for n, o, l in BOTH_FORMS])
 def test_one_launch_equals_two(name, over, lens):
     """Projection and attention in one launch against the two launches: rows, lengths and the status word bit for bit, the outputs
     too over fp32 / bf16 latents; over int8 ones the waves divide the tiles differently, and either is within 4e-6 of the exact
@@ -116,7 +131,7 @@ def test_one_launch_equals_two(name, over, lens):
     args = (as_dtype_dev(x, sp.factor_dtype), L.pack_A(c.AK, sp.factor_dtype), L.pack_A(c.AV, sp.factor_dtype), qd, qs,
             as_dtype_dev(c.BK, sp.factor_dtype), as_dtype_dev(c.BV, sp.factor_dtype), t_cap)
     results = []
-    for launches in (2, 1):
+    for launches in (2, 3):                                       # (3: one, or an error)
         W.wsvd_ctx_set_option(L.ctx, "step_launches", launches)
         W.wsvd_ctx_set_option(L.ctx, "min_chunk", 0)
         for t, v in zip(cache, planes):
@@ -127,7 +142,7 @@ def test_one_launch_equals_two(name, over, lens):
         for _ in range(3):
             out, st = L.step(*args)
             steps.append((out, st, L.seq_lens.cpu().clone()))
-            if launches == 1:
+            if launches == 3:
                 assert not L.ws.any(), "words left behind"
         results.append((steps, [t.clone() for t in cache]))
     (two, two_planes), (one, one_planes) = results
