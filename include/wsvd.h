@@ -291,6 +291,7 @@ wsvd_status wsvd_decode_attn_rope(wsvd_ctx *ctx, const wsvd_layer_desc *desc, co
  * the partial sums handed over as words, the same rows ("step_launches" setting).  Every other combination: the append kernel and the attention kernel back to back.  A single-launch
  * kernel also exists ("fused_step" setting); it measured no faster on MI355X, so it is not the default.
  *   max_seq_len: host upper bound on the sequence lengths AFTER the append (>= 1).
+ *   out may overlap x, as it may with the two calls (then never one launch).
  * Capacity handling as in wsvd_latent_append: a full sequence is attended as it is and reported by wsvd_check.
  */
 wsvd_status wsvd_decode_step(wsvd_ctx *ctx, const wsvd_layer_desc *desc, const void *x, const void *x_scale,

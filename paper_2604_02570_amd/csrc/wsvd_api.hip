@@ -625,6 +625,10 @@ wsvd_status wsvd_test_step_attention(wsvd_ctx* ctx, const wsvd_layer_desc* desc,
   return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;
 }
 
+static bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  return (uintptr_t)a < (uintptr_t)b + b_bytes && (uintptr_t)b < (uintptr_t)a + a_bytes;
+}
+
 wsvd_status wsvd_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const void* x, const void* x_scale, const void* A_K,
                              const void* A_V, const void* q, const void* q_scale, const void* B_K, const void* B_V,
                              wsvd_cache* cache, int32_t max_seq_len, void* out, void* hip_stream) {
@@ -649,7 +653,10 @@ wsvd_status wsvd_decode_step(wsvd_ctx* ctx, const wsvd_layer_desc* desc, const v
   // (step_deferred 2 insists on the int8 pair)
   const bool deferred = wsvd_step_deferred_ok(*desc) || (ctx->opt.step_deferred == 1 && wsvd_step_deferred_float_ok(*desc));
   if (e == hipErrorNotSupported && ctx->opt.step_deferred && ctx->opt.append_mode == 0 && deferred) {
-    if (ctx->opt.step_deferred == 1 && ctx->opt.step_launches != 2) {
+    // (output over the hidden states: two launches have read all of them before the first head is written, one has not)
+    const bool over_x = overlap(x, (size_t)desc->batch * desc->d_model * (desc->x_dtype == WSVD_F32 ? 4 : 2), out,
+                                (size_t)desc->batch * desc->n_q_heads * desc->d_head * (desc->out_dtype == WSVD_BF16 ? 2 : 4));
+    if (ctx->opt.step_deferred == 1 && ctx->opt.step_launches != 2 && !over_x) {
       e = desc->latent_dtype == WSVD_I8 ? wsvd_launch_step_i8(ctx, *desc, x, A_K, A_V, q, q_scale, B_K, B_V, *cache, max_seq_len, out, s)
                                         : wsvd_launch_step_float(ctx, *desc, x, A_K, A_V, q, q_scale, B_K, B_V, *cache, max_seq_len, out, s);
       if (e != hipErrorNotSupported) return e == hipSuccess ? WSVD_OK : WSVD_E_HIP;

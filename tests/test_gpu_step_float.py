@@ -153,6 +153,44 @@ def test_one_launch_equals_two(name, over, lens):
     L.close()
 
 
+@pytest.mark.parametrize("at", ["start", "end", "behind"])
+@pytest.mark.parametrize("name,over", [("c1", dict()), ("c2_small", dict()), ("c3_small", dict())])
+def test_output_over_the_hidden_states(name, over, at):
+    """A caller may have the output written over the hidden states, which the two launches have read by then: such a call is never
+    one launch, however little of them overlaps, and gives what it gives with buffers of their own.  Right behind is not over."""
+    c = build_case(name, **over)
+    sp = c.sp
+    L = layer_for(c); L.upload(c.cache)
+    lens = L.seq_lens.clone()
+    x = as_dtype_dev(WI.bf16_exact(c.x_new[0]) if sp.factor_dtype == "bf16" else c.x_new[0], sp.factor_dtype)
+    qd, qs, _ = q_to_device(c.q32[0], sp.q_dtype)
+    args = (L.pack_A(c.AK, sp.factor_dtype), L.pack_A(c.AV, sp.factor_dtype), qd, qs, as_dtype_dev(c.BK, sp.factor_dtype), as_dtype_dev(c.BV, sp.factor_dtype), L.t_cap)
+    x_bytes, out_bytes = x.numel() * x.element_size(), L.out.numel() * 4
+    mem = torch.zeros(x_bytes + out_bytes + 64, dtype=torch.uint8, device="cuda")
+    off = {"start": 0, "end": out_bytes - 16, "behind": out_bytes}[at]
+    xv, out = mem[off:off + x_bytes], mem[:out_bytes]
+    W.wsvd_ctx_set_option(L.ctx, "step_launches", 2)
+    want, st = L.step(x, *args)
+    assert st == 0
+    results = []
+    for launches in (0, 3):
+        W.wsvd_ctx_set_option(L.ctx, "step_launches", launches)
+        L.seq_lens.copy_(lens)
+        xv.copy_(x.view(torch.uint8).flatten())
+        call = lambda: W.wsvd_decode_step(L.ctx, L.desc, xv, None, args[0], args[1], qd, qs, args[4], args[5], L.cache, L.t_cap, out)
+        if launches == 3 and at != "behind":
+            with pytest.raises(W.WsvdError) as e:
+                call()
+            assert e.value.status == W.E_UNSUPPORTED and (L.seq_lens == lens).all()
+            continue
+        call()
+        assert W.wsvd_check(L.ctx) == 0 and (L.seq_lens == lens + 1).all()
+        results.append(out.clone().view(torch.float32).view(L.out.shape).cpu().numpy().astype(np.float64))
+    for got in results:                                            # (int8: the two forms divide the tiles differently)
+        assert np.linalg.norm(got - want) <= 1e-5 * np.linalg.norm(want) if sp.latent_dtype == "i8" and at == "behind" else (got == want).all()
+    L.close()
+
+
 @pytest.mark.parametrize("d_model,rank", [(4160, 64), (4160, 32), (4096, 32)])
 def test_many_partial_sums_cost_no_more_than_the_two_calls(d_model, rank):
     """fp32, up to d_model / 64 partial sums per row: the step with the finishing attention takes no longer than the append and
