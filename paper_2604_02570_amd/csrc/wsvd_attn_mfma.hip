@@ -2186,17 +2186,24 @@ __global__ __launch_bounds__(NT) void k_step_i8(I8StepParams p) {
   else atomicExch(a.err_word, (int)WSVD_E_CAPACITY);
 }
 
+constexpr int kStepI8Lds = 48 * 1024;      // limit of the projection's hidden states and partial sums
+template <int R, int G, int NT>
+static hipError_t launch_step_i8(const I8StepParams& p, size_t lds, hipStream_t s) {
+  static LdsLimit limit;                                         // (with the attention's arrays of rank 64 above 64 KB)
+  hipError_t e = wsvd_raise_lds(limit, (const void*)k_step_i8<R, G, NT>, kStepI8Lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL((k_step_i8<R, G, NT>), dim3((unsigned)(p.proj_x * p.groups + p.a.Hkv * p.a.n_chunks * p.a.B)), dim3(NT), lds, s, p);
+  return hipGetLastError();
+}
 template <int R, int NT>
 static hipError_t launch_step_i8(const I8StepParams& p, size_t lds, hipStream_t s) {
-  const dim3 grid((unsigned)(p.proj_x * p.groups + p.a.Hkv * p.a.n_chunks * p.a.B));
   switch (p.a.G) {
-    case 1: hipLaunchKernelGGL((k_step_i8<R, 1, NT>), grid, dim3(NT), lds, s, p); break;
-    case 2: hipLaunchKernelGGL((k_step_i8<R, 2, NT>), grid, dim3(NT), lds, s, p); break;
-    case 3: hipLaunchKernelGGL((k_step_i8<R, 3, NT>), grid, dim3(NT), lds, s, p); break;
-    case 4: hipLaunchKernelGGL((k_step_i8<R, 4, NT>), grid, dim3(NT), lds, s, p); break;
+    case 1: return launch_step_i8<R, 1, NT>(p, lds, s);
+    case 2: return launch_step_i8<R, 2, NT>(p, lds, s);
+    case 3: return launch_step_i8<R, 3, NT>(p, lds, s);
+    case 4: return launch_step_i8<R, 4, NT>(p, lds, s);
     default: return hipErrorNotSupported;
   }
-  return hipGetLastError();
 }
 
 // One launch or two.  One where all workgroups have their places from the start: two per CU at rank 32 with one query head (128
@@ -2226,9 +2233,9 @@ hipError_t wsvd_launch_step_i8(wsvd_ctx* ctx, const wsvd_layer_desc& d, const vo
   if (p.a.timeline || p.ap.timeline) return hipErrorNotSupported;      // (profiling build: the stamps are the two launches')
   size_t lds = 0;
   wsvd_append_project_shape(ctx, d, NT / 64, &p.slices, &p.sb, &p.xs_stride, &p.groups, &lds);
-  if (lds > (size_t)48 * 1024) return hipErrorNotSupported;
+  if (lds > (size_t)kStepI8Lds) return hipErrorNotSupported;
   p.proj_x = 2 * d.n_kv_heads * p.slices;
-  if (ctx->opt.step_launches == 0 && !step_i8_one_launch(ctx, d, p.proj_x * p.groups, (int)(grid.x * grid.y * grid.z))) return hipErrorNotSupported;
+  if (ctx->opt.step_launches == 0 && !step_i8_one_launch(ctx, d, p.proj_x * p.groups, (int)(grid.x * grid.y * grid.z), p.a.chunk_rows)) return hipErrorNotSupported;
   const size_t plane = (size_t)d.batch * d.n_kv_heads * d.rank, words = (size_t)p.slices * 2 * plane;
   const size_t split = p.a.n_chunks > 1 ? (size_t)d.batch * d.n_q_heads * p.a.n_chunks * (d.rank + 2) : 0;
   if (split + words > wsvd_zero_words(d)) return hipErrorNotSupported;

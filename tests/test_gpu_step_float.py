@@ -101,7 +101,9 @@ ONE_LAUNCH = [("c1", dict()), ("c1", dict(rank=32, n_q_heads=6, n_kv_heads=2, d_
 MANY = [1088, 5, 0, 1087, 64, 1023, 7, 1024, -1, 1088, 300, 63, 1, 255, 1025, 900, 17, 1088, 0, -1, 1087, 2, 640, 65, 31, 1024, 8, 1000, 33, 1086, 12, 512, 1088]
 GROUPS = [("c1", dict(), MANY[:9]), ("c1", dict(rank=64, d_head=128), MANY[:17]), ("c2_small", dict(), MANY[:17]), ("c2_small", dict(rank=16, n_q_heads=4, n_kv_heads=2), MANY[:32]),
           ("c3_small", dict(), MANY[:20]), ("c3_small", dict(), MANY), ("c3_small", dict(rank=64, n_q_heads=8, n_kv_heads=4), MANY[:20]),
-          ("c3_small", dict(rank=64), MANY)]
+          ("c3_small", dict(rank=64), MANY),
+          # hidden states and the attention's arrays together above 64 KB of LDS
+          ("c3_small", dict(rank=64, n_q_heads=32, n_kv_heads=8, d_model=6080), MANY[:16])]
 BOTH_FORMS = [(n, o, l) for n, o in ONE_LAUNCH for l in ([0], [1087], [1024, -1, 1088], [0, 1, 63, 64, 256, 1023, 1025])] + GROUPS
 
 
