@@ -2208,15 +2208,21 @@ static hipError_t launch_step_i8(const I8StepParams& p, size_t lds, hipStream_t 
 
 // One launch or two.  One where all workgroups have their places from the start: two per CU at rank 32 with one query head (128
 // registers, 8 waves), of which the projection's first ones leave early, one per CU otherwise.  Beyond, attention workgroups
-// wait for the projection's to leave.  us a step, one launch / two (cold layers):
-//   1 x 2500 rows, 32 heads, rank 32, d_model 4096   12.6 / 15.9     24 x 900, the same (beyond)     26.9 / 21.5
-//   4 x 2500, the same                               13.9 / 16.7     16 x 2500                       26.4 / 26.3
-//   1 x 900, the same                                11.6 / 13.4     8 x 250                         14.3 / 13.2
-//   32 x 900, 8 heads, rank 32, d_model 512          11.7 / 11.8     1 x 250, rank 64                19.3 / 17.4
-// Over 195 sizes on this side of the lines the median is 1.22 x, the worst 1.00 (taken while this launch still moved its hidden
-// states through registers, 0 to 1 us slower).
-static bool step_i8_one_launch(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int proj, int attend) {
+// wait for the projection's to leave.  Two per CU hold back a projection that shares the CU with them, so that beyond 5 attention
+// workgroups for 8 CUs their stream has to be long enough to hide it.  us a step, one launch / two (cold layers, replayed from a graph):
+//   1 x 2500 rows, 32 heads, rank 32, d_model 4096   12.8 / 16.3     24 x 900, the same (beyond)     27.2 / 21.8
+//   4 x 2500, the same                               14.0 / 16.8     16 x 2500                       26.2 / 26.3
+//   1 x 900, the same                                11.4 / 13.4     8 x 250                         14.4 / 13.3
+//   8 x 2449, 16 heads, d_model 2048                 11.1 / 14.6     1 x 250, rank 64                19.7 / 17.5
+//   18 x 554, 8 heads, d_model 512 (144 workgroups)  9.6 / 10.2     31 x 270, the same (248)         11.3 / 10.0
+//   4 x 219, 32 heads, d_model 512 (128)             8.9 /  9.9     16 x 377, 16 heads, d_model 1024 (256)   12.2 / 10.4
+//                                                                   11 x 278, 16 heads, d_model 2048 (176)   10.0 / 10.7
+// Over 269 sizes on this side of the lines the median is 1.13 x, the worst 0.955 (40 x 155 rows, one kv head of 4, rank 64, d_model 512:
+// 16.8 / 16.1).  Called one by one instead, two launches take at least what the host needs for them, 11.5 us, and one is no slower
+// for short streams either (31 x 270: 11.35 / 11.4, 61 x 18 of 4 heads 10.7 / 11.7).
+static bool step_i8_one_launch(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int proj, int attend, int chunk_rows) {
   const bool slim = d.rank == 32 && d.n_q_heads == d.n_kv_heads;
+  if (slim && 8 * attend > 5 * ctx->n_cu && chunk_rows < 1024) return false;
   return 2 * (proj + attend) <= (slim ? 3 : 2) * ctx->n_cu;
 }
 
