@@ -280,8 +280,9 @@ void k_prefill_attn(PrefillParams p) {
         bmax = fmaxf(bmax, x[v]);
       }
       m_ref = column_max(bmax);
+      const float m_fin = fmaxf(m_ref, -3.402823466e38f);               // (every score -inf: no reference yet, weights 0)
 #pragma unroll
-      for (int v = 0; v < 16; v++) x[v] -= m_ref;
+      for (int v = 0; v < 16; v++) x[v] -= m_fin;
     } else if constexpr (FORM == kAny) {
       float bmax = -INFINITY;
 #pragma unroll
@@ -357,7 +358,7 @@ void k_prefill_attn(PrefillParams p) {
     };
     int kb = kg;
     if (kb < kb_full) { next(kb, first_c); kb += KG; }
-    else for (; kb < n_kblocks && no_reference(); kb += KG) next(kb, any_c);
+    for (; kb < n_kblocks && no_reference(); kb += KG) next(kb, any_c);
     for (; kb < kb_full; kb += KG) next(kb, whole_c);
     for (; kb < n_kblocks; kb += KG) next(kb, part_c);
   } else {
@@ -380,7 +381,7 @@ void k_prefill_attn(PrefillParams p) {
       auto staged = [&](int j, auto form_c) { block(StageOperands<KK>{src + j * BLK, lane, g2}, kb0 + j, form_c); };
       int j = 0;
       if (it == 0 && j_full > 0) staged(j++, first_c);
-      else for (; j < j_end && no_reference(); j++) staged(j, any_c);
+      for (; j < j_end && no_reference(); j++) staged(j, any_c);
       for (; j < j_full; j++) staged(j, whole_c);
       for (; j < j_end; j++) staged(j, part_c);
       __syncthreads();

@@ -328,3 +328,38 @@ def test_new_context_is_ready_on_any_stream():
         torch.cuda.synchronize()
         assert (lens.cpu() == 99).all(), shape
         W.wsvd_destroy(ctx)
+
+
+@pytest.mark.parametrize("rank", [32, 64])
+@pytest.mark.parametrize("batch,kv_heads,n,past", [(1, 2, 32, 40), (1, 2, 33, 200), (32, 32, 32, 170), (8, 32, 64, 200), (16, 32, 128, 60), (40, 32, 64, 50), (3, 8, 70, 1000)])
+def test_prompt_attention_over_infinite_scales(rank, batch, kv_heads, n, past):
+    """Scales are the caller's (wsvd_cache_import): the first 40 keys' are infinite and their scores -inf, the first block's for every
+    query.  Such keys have weight 0, as masked ones do, whatever the workgroup's shape; everything behind them counts in full."""
+    t, dead = past + n, 40
+    desc = W.layer_desc(batch, kv_heads, kv_heads, 128, 64, rank, (t + 63) // 64 * 64, "i8", "bf16", "bf16", "bf16", "f32", 0.0)
+    ctx = W.wsvd_create(0)
+    cb, mb = W.wsvd_cache_bytes(desc)
+    planes, meta = [torch.zeros(cb, dtype=torch.uint8, device="cuda") for _ in range(2)], [torch.zeros(mb, dtype=torch.uint8, device="cuda") for _ in range(2)]
+    lens = torch.full((batch,), t, dtype=torch.int32, device="cuda")
+    cache = W.make_cache(*planes, *meta, lens)
+    g = torch.Generator(device="cuda").manual_seed(rank + t)
+    kc, vc = (torch.randint(-127, 128, (batch, kv_heads, t, rank), device="cuda", generator=g, dtype=torch.int8) for _ in range(2))
+    kc[:, :, :dead] = torch.randint(-127, 0, (batch, kv_heads, dead, rank), device="cuda", generator=g, dtype=torch.int8)
+    ks, vs = (0.001 * (1 + torch.rand(batch, kv_heads, t, device="cuda", generator=g)) for _ in range(2))
+    ks[:, :, :dead] = float("inf")
+    ks, vs = ks.half(), vs.half()
+    W.wsvd_cache_import(ctx, desc, 0, kc, ks, 0, t, cache)
+    W.wsvd_cache_import(ctx, desc, 1, vc, vs, 0, t, cache)
+    q = torch.randn(batch, kv_heads, n, 128, device="cuda", generator=g).abs().to(torch.bfloat16)
+    BK, BV = (torch.randn(kv_heads, rank, 128, device="cuda", generator=g).to(torch.bfloat16) for _ in range(2))
+    BK = BK.abs()
+    out = torch.full((batch, kv_heads, n, 1, 128), float("nan"), device="cuda")
+    W.wsvd_prefill_attn(ctx, desc, q, n, 0, BK, BV, cache, t, out)
+    assert W.wsvd_check(ctx) == 0
+    C, V = kc.double()[:, :, dead:] * ks.double()[:, :, dead:, None], vc.double()[:, :, dead:] * vs.double()[:, :, dead:, None]
+    s = (q.double() @ BK.double().transpose(1, 2)) @ C.transpose(2, 3) / 128 ** 0.5
+    late = torch.arange(t - dead, device="cuda")[None, :] + dead > torch.arange(n, device="cuda")[:, None] + past
+    ref = (torch.softmax(s.masked_fill(late, float("-inf")), -1) @ V) @ BV.double()
+    err = (out[:, :, :, 0].double() - ref).norm() / ref.norm()
+    assert err <= 2e-3, float(err)                               # (fp16 weights: 2^-12 each, seen 2e-4 with finite scales)
+    W.wsvd_destroy(ctx)
