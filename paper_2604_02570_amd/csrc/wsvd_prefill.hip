@@ -97,8 +97,10 @@ struct OwnOperands {
 
 enum { kFirst, kWhole, kPart, kAny };      // what a wave's queries see of a key block, see there
 
+// (Rank 64 in key groups: two waves per SIMD even where the registers would hold three.  The waves of such a launch are few and of
+// unequal length; with three a CU takes more of the long ones than its neighbour: 5 x 1007 tokens, 8 heads, 39.6 us, with two 36.2.)
 template <int R, int D, int QW, int KG>
-__global__ __launch_bounds__(64 * QW * KG) __attribute__((amdgpu_waves_per_eu(R == 32 ? 4 : 2)))
+__global__ __launch_bounds__(64 * QW * KG) __attribute__((amdgpu_waves_per_eu(R == 32 ? 4 : 2, R == 64 && KG > 1 ? 2 : 8)))
 void k_prefill_attn(PrefillParams p) {
   constexpr int KK = R / 32;
   constexpr bool OWN = QW == 1;
@@ -357,8 +359,10 @@ void k_prefill_attn(PrefillParams p) {
       block(o, kb, form_c);
     };
     int kb = kg;
-    if (kb < kb_full) { next(kb, first_c); kb += KG; }
-    for (; kb < n_kblocks && no_reference(); kb += KG) next(kb, any_c);
+    bool open = kb >= kb_full;                                          // some column may have no reference yet
+    if (!open) { next(kb, first_c); kb += KG; open = __builtin_expect(no_reference(), 0); }
+    if (open)
+      for (; kb < n_kblocks && no_reference(); kb += KG) next(kb, any_c);
     for (; kb < kb_full; kb += KG) next(kb, whole_c);
     for (; kb < n_kblocks; kb += KG) next(kb, part_c);
   } else {
@@ -380,8 +384,10 @@ void k_prefill_attn(PrefillParams p) {
       const int kb0 = (it * KG + kg) * QW, j_full = min(kb_full - kb0, QW), j_end = min(kb_end - kb0, QW);
       auto staged = [&](int j, auto form_c) { block(StageOperands<KK>{src + j * BLK, lane, g2}, kb0 + j, form_c); };
       int j = 0;
-      if (it == 0 && j_full > 0) staged(j++, first_c);
-      for (; j < j_end && no_reference(); j++) staged(j, any_c);
+      bool open = it != 0 || j_full <= 0;
+      if (!open) { staged(j++, first_c); open = __builtin_expect(no_reference(), 0); }
+      if (open)
+        for (; j < j_end && no_reference(); j++) staged(j, any_c);
       for (; j < j_full; j++) staged(j, whole_c);
       for (; j < j_end; j++) staged(j, part_c);
       __syncthreads();
@@ -526,21 +532,23 @@ void launch_prefill_attn(const PrefillParams& p, hipStream_t s) {
 //   * On a full chip the conversion decides: 4 waves of rows together, as long as most of the 4 have rows or the walk is long;
 //     otherwise 2 or 1.
 // us per call for 1x1 / 2x1 / 4x1 / 1x2 / 1x4 (QW x KG), and for one wave converting for itself with P through LDS (before):
-//   rank, sequences x tokens, keys      1x1    2x1    4x1    1x2    1x4   before     (32 heads, d_head 128)
-//   32,  1 x 32,   32                    4.9    5.6    6.4    5.5    6.4      6.6
-//   32,  1 x 64, 1064                   21.3   25.3   23.1   13.9   10.8     26.2
-//   32, 16 x 32,  232                   11.1   12.7   13.3   10.9   11.4     13.2
-//   32, 16 x 64, 4064                   88.3    104   92.5   66.4   66.3      111
-//   32, 64 x 16,   16                   11.6   15.3   23.0   14.5   21.5     13.0
-//   32, 64 x 32, 1032                   46.3   49.6   63.7   45.8   49.9     52.8
-//   32, 64 x 64,  264                   36.4   34.4   43.9   41.4   55.9     40.0
-//   32, 16 x 2048, 2048                  507    464    431    602    697      534
-//   64, 64 x 16,   16                   15.5   24.4   40.4   23.5   35.2     17.5
-//   64, 16 x 96, 1096                   52.1   53.3   47.5   58.9   53.9     57.2
-//   64, 64 x 96,  296                   70.2   86.2   81.5   87.0    116     73.8
-//   64, 16 x 2048, 2048                  786    750    698    889    965      735
-// Over 1108 sizes (9 .. 2048 tokens, 1 .. 128 sequences, up to 4000 keys before them, 4 .. 32 kv heads, groups of 1, 4 and 7)
-// the rule is 0.8 % above the best of the six shapes on average, at most 18 %, and at most 2 % above the last column.
+//   rank, seqs x tokens, keys  1x1    2x1    4x1    1x2    1x4   before     (32 heads, d_head 128)
+//   32,  1 x 32,      32     4.5    5.4    6.0    5.0    6.1      6.6
+//   32,  1 x 64,    1064    21.6   23.4   22.1   13.5   10.3     26.2
+//   32, 16 x 32,     232    10.3   11.4   11.7   10.0   10.6     13.2
+//   32, 16 x 64,    4064    73.9   96.4   86.7   61.7   62.6      111
+//   32, 64 x 16,      16    10.9   14.0   21.1   13.8   21.4     13.0
+//   32, 64 x 32,    1032    41.6   45.0   57.7   41.6   45.6     52.8
+//   32, 64 x 64,     264    32.5   31.3   40.5   39.8   55.4     40.0
+//   32, 16 x 2048, 2048     511    464    435    612    685      534
+//   64, 64 x 16,      16    14.1   22.8   36.7   22.6   37.3     17.5
+//   64, 16 x 96,    1096    48.9   50.7   44.8   56.4   56.3     57.2
+//   64, 64 x 96,     296    60.9   79.8   75.5   84.2    123     73.8
+//   64, 16 x 2048, 2048     711    794    708    933   1170      735
+// (the last column measured then, of a kernel that is gone).  Fitted to 1108 sizes (9 .. 2048 tokens, 1 .. 128 sequences, up to 4000
+// keys before them, 4 .. 32 kv heads, groups of 1, 4 and 7): 0.8 % above the best of the six shapes on average then.  With the
+// blocks' forms as they are now it is 2.6 % above over 600 such sizes, 19 of them by more than 18 %, at most 45 (rank 64, about 2000
+// waves that see one or two blocks: 4x1 24 us, 1x1 17).
 enum { kPa11 = 11, kPa21 = 21, kPa41 = 41, kPa12 = 12, kPa22 = 22, kPa14 = 14 };    // 10 QW + KG
 int prefill_attn_rule(int R, long long waves, int rows32, int key_blocks) {
   const int quarter = R == 32 ? 256 : 128;                              // of the waves a chip holds at 1 (rank 64: 1/2) per SIMD
