@@ -88,7 +88,7 @@ WSVD_DEV WorkItem decode_work(const AttnParams& p, int n_raw, int kv, int chunk,
   w.chunk = chunk;
   w.b = b;
   w.n = n_raw < 0 ? 0 : (n_raw > p.t_cap ? p.t_cap : n_raw);
-  w.n_splits = (w.n + p.chunk_rows - 1) / p.chunk_rows;
+  w.n_splits = min((w.n + p.chunk_rows - 1) / p.chunk_rows, p.n_chunks);       // those of the grid: the last of them merges
   w.row_begin = w.chunk * p.chunk_rows;
   w.row_end = min(w.n, w.row_begin + p.chunk_rows);
   w.active = w.chunk < w.n_splits;

@@ -268,6 +268,30 @@ def test_attention_reports_a_too_small_length_bound():
     L.close()
 
 
+@pytest.mark.parametrize("name,over", [("c3_small", dict()), ("c3_small", dict(rank=64)), ("c3_small", dict(n_q_heads=8)), ("c4_small", dict(ragged=())), ("c5_small", dict()),
+                                       ("c2_small", dict()), ("c1", dict(batch=2))], ids=["i8", "i8-r64", "i8-g2", "i4", "i8-gqa7", "bf16", "f32"])
+def test_a_too_small_length_bound_covers_its_chunks_and_leaves_nothing_behind(name, over):
+    """A sequence longer than the grid covers: reported, its output computed from the covered rows, the hand-off words zero again, so
+    that the next call is right."""
+    c = build_case(name, **{**dict(context=2300, extra_cap=0), **over})
+    L = layer_for(c); L.upload(c.cache)
+    qd, qs, _ = q_to_device(c.q32[0], c.sp.q_dtype)
+    BKd, BVd = as_dtype_dev(c.BK, c.sp.factor_dtype), as_dtype_dev(c.BV, c.sp.factor_dtype)
+    lens = L.seq_lens.clone()
+    honest = L.attend(qd, qs, BKd, BVd, 2300)
+    L.seq_lens.fill_(1024)
+    covered = L.attend(qd, qs, BKd, BVd, 1000 + 24)
+    L.seq_lens.copy_(lens)
+    assert not L.ws.any()
+    L.out.fill_(float("nan"))
+    W.wsvd_decode_attn(L.ctx, L.desc, qd, qs, BKd, BVd, L.cache, 1000, L.out)      # 2300 rows, bound 1000: 1024 covered
+    assert W.wsvd_check(L.ctx) == W.E_SHAPE
+    assert not L.ws.any(), "words left behind"
+    assert (L.out.cpu().numpy().astype(np.float64) == covered).all()
+    assert (L.attend(qd, qs, BKd, BVd, 2300) == honest).all()
+    L.close()
+
+
 @pytest.mark.parametrize("name,over", [("c3_small", dict(context=2000, batch=4)), ("c5_small", dict(context=2000)),
                                        ("c4_small", dict(batch=6, context=1800, ragged=(900, 1800)))],
                          ids=["i8", "i8-gqa7", "i4-ragged"])
