@@ -10,12 +10,13 @@
  *
  * Conventions
  *  - Every pointer named below is a DEVICE pointer unless it says HOST.  All buffers are owned
- *    by the caller; the library allocates only in wsvd_create (one error word) and never in a
+ *    by the caller; the library allocates only in wsvd_create (a status word and nine counters, 1.3 KB) and never in a
  *    hot call.  Device pointers must be 16-byte aligned.
  *  - Hot calls enqueue on the caller's HIP stream (passed as void*, NULL = default stream) and
- *    return without synchronising.  One context per stream AT A TIME: tickets, split partials and
- *    the status word live in the context's workspace, so calls on one context that overlap in time
- *    (two streams, two threads) corrupt each other.  Contexts are independent of each other.
+ *    return without synchronising.  One context per stream AT A TIME: counters, hand-off words and
+ *    the status word live in the context and its workspace, so calls on one context that overlap in time
+ *    (two streams, two threads) corrupt each other, also calls that need no workspace: the prompt projection
+ *    counts its workgroups in the context and would advance lengths wrongly.  Contexts are independent of each other.
  *  - Errors detectable on the host (NULL, unsupported shape / dtype, misalignment, workspace
  *    too small) return a non-zero status and enqueue nothing.  Conditions only the device can
  *    see (a sequence already at capacity on append) are recorded in the context's error word and
@@ -48,7 +49,7 @@
 extern "C" {
 #endif
 
-typedef struct wsvd_ctx wsvd_ctx; /* opaque: device ordinal, error word, caller-provided workspace */
+typedef struct wsvd_ctx wsvd_ctx; /* opaque: device ordinal, status word and counters, caller-provided workspace */
 
 typedef enum {
   WSVD_OK = 0,
@@ -101,7 +102,8 @@ typedef struct {
   int32_t *seq_lens; /* [B] valid rows per sequence; wsvd_latent_append increments it on the device */
 } wsvd_cache;
 
-/* Create / destroy a context bound to a device ordinal.  Allocates a 4-byte device error word. */
+/* Create / destroy a context bound to a device ordinal.  Allocates 1.3 KB of device memory (status word,
+ * counters), clears it and waits for that. */
 wsvd_status wsvd_create(wsvd_ctx **out, int device_ordinal);
 wsvd_status wsvd_destroy(wsvd_ctx *ctx);
 
@@ -288,7 +290,9 @@ wsvd_status wsvd_decode_attn_rope(wsvd_ctx *ctx, const wsvd_layer_desc *desc, co
  * differ from wsvd_latent_append's where the fp32 sums, taken in another order, fall on the other side of a rounding
  * boundary).  F32 and BF16 latents: the same two launches, the partial sums being the append's own, so rows and outputs
  * are bit for bit those of the two calls.  Either with few workgroups: projection and attention side by side in one launch,
- * the partial sums handed over as words, the same rows ("step_launches" setting).  Every other combination: the append kernel and the attention kernel back to back.  A single-launch
+ * the partial sums handed over as words, the same rows ("step_launches" setting); the words have to fit behind those of the
+ * attention's splits, in an area that grows with t_cap (F32 latents, d_model 4096, rank 32, one query head per kv head: t_cap
+ * of about 1800 at d_head 128 and 4600 at 64), otherwise two launches.  Every other combination: the append kernel and the attention kernel back to back.  A single-launch
  * kernel also exists ("fused_step" setting); it measured no faster on MI355X, so it is not the default.
  *   max_seq_len: host upper bound on the sequence lengths AFTER the append (>= 1).
  *   out may overlap x, as it may with the two calls (then never one launch).
@@ -336,7 +340,7 @@ wsvd_status wsvd_cache_export(wsvd_ctx *ctx, const wsvd_layer_desc *desc, int32_
  * advances by n_tokens.  x, x_scale, A_K, A_V as for wsvd_latent_append.  Up to 64 tokens per call for every
  * supported format (the append kernels; the workspace must be large enough for a descriptor whose batch is n_tokens,
  * WSVD_E_WORKSPACE otherwise); any number of tokens per call with I8 latents and BF16 hidden states and factors (a tiled
- * projection on the matrix cores, no workspace; WSVD_E_SHAPE for n_tokens > 64 with other formats).  With those formats
+ * projection on the matrix cores, no workspace, its counters are the context's; WSVD_E_SHAPE for n_tokens > 64 with other formats).  With those formats
  * seq_index = -1 stores n_tokens rows for EVERY sequence of the batch in one launch: x is then [batch, n_tokens, d_model]
  * and each sequence's rows start at its own length (WSVD_E_SHAPE for seq_index = -1 with other formats).  Rows beyond
  * t_cap are not stored: the sequence is left full and WSVD_E_CAPACITY is recorded in the device status word.  F32, BF16,
