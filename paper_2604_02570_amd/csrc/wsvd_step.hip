@@ -62,21 +62,40 @@ constexpr int kStepShares = 2;
 constexpr int kStepLds = 40 * 1024;      // limit of the projection's hidden states and partial sums
 
 // One launch or two.  One gains while both halves find room beside each other; beyond that the attention has fewer waves per CU
-// than in a launch of its own, and its stream is the time.  us a step, one launch / two:
+// than in a launch of its own, and its stream is the time.  us a step, one launch / two, replayed from a graph over cold layers:
 //   bf16  1 sequence x 900 rows, 32 heads, rank 32, E = d_model 4096   12.9 / 18.2
 //   bf16  4 x 900, the same                                            15.4 / 18.9
 //   bf16  8 x 900, 8 kv heads of 4, rank 32                            18.3 / 23.8
-//   bf16  8 x 8000, the same (beyond)                                  45.7 / 38.0
+//   bf16  4 x 234, 8 kv heads of 7, rank 16, E 7168                    19.1 / 20.7
+//   bf16  8 x 8000, 8 kv heads of 4, rank 32 (beyond)                  45.7 / 38.0
 //   bf16  16 x 8000, 8 heads, rank 16, E 512 (beyond)                  29.4 / 25.8
 //   fp32  1 x 250, 8 heads, rank 16, E 512                             7.4 / 9.5
 //   fp32  64 x 900, 8 heads, rank 64, E 512                            92.0 / 123.8
 //   fp32  4 x 8000, 32 heads, rank 16, E 4096 (beyond)                 54.3 / 45.8
 //   fp32  16 x 8000, 4 kv heads of 7, rank 64, E 3584 (beyond)         139 / 112
-// Over 558 bf16 and 1027 fp32 sizes on this side of the lines the median is 1.18 and 1.26 x, the worst 0.987 and 0.98.
-static bool step_one_launch(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int proj, int attend) {
-  const int G = d.n_q_heads / d.n_kv_heads;
-  if (d.latent_dtype == WSVD_BF16) return G < 8 && proj + 2 * attend <= 2 * ctx->n_cu;     // (8 query heads spill)
-  return proj <= 2 * ctx->n_cu && attend <= (d.rank == 64 && G > 4 ? 1 : 4) * ctx->n_cu;   // (72 KB of LDS and more)
+// A projection that outlasts the rows' stream is better off alone.  bf16: a wave has two of the append's shares here, and where a
+// share is more than the one batch of 8 k-steps that the wave asks for at once, the rows have to make up for it:
+//   3 x 23 rows, 8 heads, rank 16, E 7168           13.2 / 12.1     4 x 1164, the same             15.2 / 15.5
+//   8 x 3, 4 heads of 64, rank 64, E 4096           14.3 / 13.1     1 x 10, 8 kv heads of 2        11.6 / 13.8
+//   1 x 15, 1 head, rank 16, E 16384                22.8 / 14.4     1 x 490, 12 kv heads of 2, rank 32, E 5120   11.3 / 15.0
+// fp32: many partial sums are as many words for one workgroup to take, and with more than 4 query heads an attention workgroup has
+// no place until the projection's leave:
+//   2 x 4299, 1 kv head of 2, rank 16, E 8128 (127 sums)   27.6 / 20.5
+//   28 x 8, 8 kv heads of 7, rank 16, E 7168        33.0 / 30.7     4 x 96, the same               19.1 / 20.6
+// Of 9242 bf16 sizes on this side of the lines (1 to 32 kv heads, d_model 512 to 12288, 1 to 8192 rows) the median is 1.20 x, one in a
+// hundred below 0.984, the worst 0.915; of 1388 fp32 sizes 1.18, 0.961 and 0.91.  Beyond them the median is 0.96 for both.
+// Groups of 7 gain although those of ranks 16 and 32 spill 25 registers.  Groups of 8 are not chosen, only built (they would gain
+// too: 359 sizes of 2 kv heads, d_model 1024, median 1.11 x).
+static bool step_one_launch(const wsvd_ctx* ctx, const wsvd_layer_desc& d, const FloatStepParams& p, int waves, int attend, int max_seq_len) {
+  const int G = d.n_q_heads / d.n_kv_heads, rows = max_seq_len < p.a.chunk_rows ? max_seq_len : p.a.chunk_rows;
+  if (d.latent_dtype == WSVD_BF16) {
+    if (G == 8 || p.n_proj + 2 * attend > 2 * ctx->n_cu) return false;
+    const int steps = ((p.helpers ? (d.d_model / 16 + 1) / 2 : d.d_model / 16) + waves - 1) / waves, batches = (steps + 7) / 8;
+    if (d.rank < 64) return steps <= 12 || (steps <= 24 && rows * G * d.rank >= 16 * 512 * (steps - 12));
+    return batches <= 1 || (batches <= 6 && (G > 1 || rows >= 32 << batches || (batches == 2 && 2 * p.n_proj > ctx->n_cu)));
+  }
+  if (p.a.n_parts > 40 + G * d.rank / 4 || (G > 4 && p.n_proj > ctx->n_cu && p.n_proj + attend > 2 * ctx->n_cu)) return false;
+  return p.n_proj <= 2 * ctx->n_cu && attend <= (d.rank == 64 && G > 4 ? 1 : 4) * ctx->n_cu;   // (72 KB of LDS and more)
 }
 
 template <int R, int G>
@@ -125,7 +144,7 @@ hipError_t wsvd_launch_step_float(wsvd_ctx* ctx, const wsvd_layer_desc& d, const
     p.a.n_parts = p.ap.ES;
   }
   p.n_proj = p.a.n_parts * 2 * d.n_kv_heads;
-  if (ctx->opt.step_launches == 0 && !step_one_launch(ctx, d, p.n_proj, (int)(grid.x * grid.y * grid.z))) return hipErrorNotSupported;
+  if (ctx->opt.step_launches == 0 && !step_one_launch(ctx, d, p, waves, (int)(grid.x * grid.y * grid.z), max_seq_len)) return hipErrorNotSupported;
   // the words: behind those that the attention's own splits use, in the part of the workspace that is zero between launches
   const size_t plane = (size_t)d.batch * d.n_kv_heads * d.rank, words = (size_t)p.a.n_parts * 2 * plane;
   const size_t split = p.a.n_chunks > 1 ? (size_t)d.batch * d.n_q_heads * p.a.n_chunks * (d.rank + 2) : 0;

@@ -232,27 +232,29 @@ def test_many_partial_sums_cost_no_more_than_the_two_calls(d_model, rank):
     W.wsvd_destroy(ctx)
 
 
-@pytest.mark.parametrize("batch,rows,kv_heads,d_model", [(16, 377, 16, 1024), (31, 270, 8, 512), (61, 18, 4, 1024), (8, 2449, 16, 2048), (4, 1096, 32, 4096)])
-def test_int8_step_takes_the_faster_form(batch, rows, kv_heads, d_model):
-    """The library's choice between one launch and two, replayed from a graph over 40 layers, takes no longer than the faster of them (the
-    first three in one launch: 9 to 17 % longer, the other two in two: 25 to 30 %)."""
-    desc = W.layer_desc(batch, kv_heads, kv_heads, 128, d_model, 32, (rows + 64) // 64 * 64, "i8", "bf16", "bf16", "i8", "f32", 0.0)
+def faster_form_is_taken(latent, batch, rows, kv_heads, group, d_head, d_model, rank, layers_n):
+    factor = "f32" if latent == "f32" else "bf16"
+    wide = torch.float32 if latent == "f32" else torch.bfloat16
+    desc = W.layer_desc(batch, kv_heads * group, kv_heads, d_head, d_model, rank, (rows + 64) // 64 * 64, latent, factor, factor,
+                        "i8" if latent == "i8" else latent, "f32", 0.0)
     ctx = W.wsvd_create(0)
     ws = torch.empty(W.wsvd_workspace_bytes(desc), dtype=torch.uint8, device="cuda")
     W.wsvd_set_workspace(ctx, ws)
     cb, mb = W.wsvd_cache_bytes(desc)
     g = torch.Generator(device="cuda").manual_seed(2)
-    rnd = lambda n, scale: (torch.randn(n, device="cuda", generator=g) * scale).to(torch.bfloat16)
-    lens0 = torch.full((40, batch), rows, dtype=torch.int32, device="cuda")
+    rnd = lambda n, scale: (torch.randn(n, device="cuda", generator=g) * scale).to(wide)
+    planes = lambda: torch.randint(0, 256, (cb,), device="cuda", generator=g, dtype=torch.uint8) if latent == "i8" else rnd(cb // wide.itemsize, 1.0)
+    lens0 = torch.full((layers_n, batch), rows, dtype=torch.int32, device="cuda")
     lens = lens0.clone()
     layers = []
-    for i in range(40):
-        codes = [torch.randint(0, 256, (cb,), device="cuda", generator=g, dtype=torch.uint8) for _ in range(2)]
-        meta = [torch.full((mb // 2,), 0.02, dtype=torch.float16, device="cuda") for _ in range(2)]
-        A, B = [rnd(W.wsvd_factor_a_bytes(desc) // 2, 0.02) for _ in range(2)], [rnd(kv_heads * 32 * 128, 0.1) for _ in range(2)]
+    for i in range(layers_n):
+        codes = [planes() for _ in range(2)]
+        meta = [torch.full((mb // 2,), 0.02, dtype=torch.float16, device="cuda") if mb else None for _ in range(2)]
+        A, B = [rnd(W.wsvd_factor_a_bytes(desc) // wide.itemsize, 0.02) for _ in range(2)], [rnd(kv_heads * rank * d_head, 0.1) for _ in range(2)]
         layers.append((A, B, W.make_cache(*codes, *meta, lens[i]), codes, meta))
-    x, q = rnd(batch * d_model, 1.0), torch.randint(-127, 128, (batch * kv_heads * 128,), device="cuda", generator=g, dtype=torch.int8)
-    qs, out = torch.full((batch + 1,), 0.02, dtype=torch.float16, device="cuda"), torch.zeros(batch, kv_heads, 128, device="cuda")
+    n_q = batch * kv_heads * group * d_head
+    x, q = rnd(batch * d_model, 1.0), torch.randint(-127, 128, (n_q,), device="cuda", generator=g, dtype=torch.int8) if latent == "i8" else rnd(n_q, 1.0)
+    qs, out = torch.full((batch + 1,), 0.02, dtype=torch.float16, device="cuda") if latent == "i8" else None, torch.zeros(n_q, device="cuda")
     stream = torch.cuda.Stream()
     graphs = []
     for launches in (0, 2, 3):
@@ -269,7 +271,25 @@ def test_int8_step_takes_the_faster_form(batch, rows, kv_heads, d_model):
         for i, graph in enumerate(graphs):
             a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
             a.record(); graph.replay(); b.record(); torch.cuda.synchronize()
-            best[i] = min(best[i], a.elapsed_time(b) * 25)
+            best[i] = min(best[i], a.elapsed_time(b) * 1000 / layers_n)
     assert W.wsvd_check(ctx) == 0
     assert best[0] <= 1.04 * min(best), best
     W.wsvd_destroy(ctx)
+
+
+@pytest.mark.parametrize("batch,rows,kv_heads,d_model", [(16, 377, 16, 1024), (31, 270, 8, 512), (61, 18, 4, 1024), (8, 2449, 16, 2048), (4, 1096, 32, 4096)])
+def test_int8_step_takes_the_faster_form(batch, rows, kv_heads, d_model):
+    """The library's choice between one launch and two, replayed from a graph over 40 layers, takes no longer than the faster of them (the
+    first three in one launch: 9 to 17 % longer, the other two in two: 25 to 30 %)."""
+    faster_form_is_taken("i8", batch, rows, kv_heads, 1, 128, d_model, 32, 40)
+
+
+@pytest.mark.parametrize("latent,batch,rows,kv_heads,group,d_head,d_model,rank",
+                         [("bf16", 3, 23, 8, 1, 128, 7168, 16), ("bf16", 8, 3, 4, 1, 64, 4096, 64), ("bf16", 1, 15, 1, 1, 128, 16384, 16),
+                          ("bf16", 1, 1, 4, 4, 128, 12288, 16), ("f32", 28, 8, 8, 7, 128, 7168, 16), ("f32", 2, 4299, 1, 2, 128, 8128, 16),
+                          ("bf16", 1, 640, 32, 1, 128, 4096, 32), ("bf16", 1, 10, 8, 2, 64, 4096, 64), ("bf16", 1, 490, 12, 2, 128, 5120, 32),
+                          ("f32", 1, 250, 8, 1, 64, 512, 16), ("f32", 4, 96, 8, 7, 128, 7168, 16)])
+def test_float_step_takes_the_faster_form(latent, batch, rows, kv_heads, group, d_head, d_model, rank):
+    """The same over fp32 and bf16 latents: the first six, whose projection outlasts their rows, took 7 to 58 % longer in one launch; the
+    others 8 to 41 % longer in two."""
+    faster_form_is_taken(latent, batch, rows, kv_heads, group, d_head, d_model, rank, 24)
