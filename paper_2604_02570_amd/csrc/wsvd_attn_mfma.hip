@@ -2217,8 +2217,9 @@ static hipError_t launch_step_i8(const I8StepParams& p, size_t lds, hipStream_t 
 //   18 x 554, 8 heads, d_model 512 (144 workgroups)  9.6 / 10.2     31 x 270, the same (248)         11.3 / 10.0
 //   4 x 219, 32 heads, d_model 512 (128)             8.9 /  9.9     16 x 377, 16 heads, d_model 1024 (256)   12.2 / 10.4
 //                                                                   11 x 278, 16 heads, d_model 2048 (176)   10.0 / 10.7
-// Over 269 sizes on this side of the lines the median is 1.13 x, the worst 0.955 (40 x 155 rows, one kv head of 4, rank 64, d_model 512:
-// 16.8 / 16.1).  Called one by one instead, two launches take at least what the host needs for them, 11.5 us, and one is no slower
+// Over 1602 sizes on this side of the lines (1 to 32 kv heads, d_model 512 to 16384) the median is 1.16 x, the worst 0.945 (1 x 8 rows, 32
+// kv heads of 2, rank 64, d_model 5120: 21.4 / 20.2); over 673 beyond them 0.90.  Groups of 4 at rank 64 spill 8 registers (the attention
+// launch of the two: 5) and gain all the same: 167 sizes, median 1.08.  Called one by one instead, two launches take at least what the host needs for them, 11.5 us, and one is no slower
 // for short streams either (31 x 270: 11.35 / 11.4, 61 x 18 of 4 heads 10.7 / 11.7).
 static bool step_i8_one_launch(const wsvd_ctx* ctx, const wsvd_layer_desc& d, int proj, int attend, int chunk_rows) {
   const bool slim = d.rank == 32 && d.n_q_heads == d.n_kv_heads;
