@@ -289,7 +289,7 @@ wsvd_status wsvd_decode_attn_rope(wsvd_ctx *ctx, const wsvd_layer_desc *desc, co
  * append's workgroups is the kernel boundary itself ("step_deferred" setting of wsvd_test.h; the stored codes may
  * differ from wsvd_latent_append's where the fp32 sums, taken in another order, fall on the other side of a rounding
  * boundary).  F32 and BF16 latents: the same two launches, the partial sums being the append's own, so rows and outputs
- * are bit for bit those of the two calls.  Either with few workgroups: projection and attention side by side in one launch,
+ * are bit for bit those of the two calls.  Either with few workgroups and a projection that the rows' stream hides: both side by side in one launch,
  * the partial sums handed over as words, the same rows ("step_launches" setting); the words have to fit behind those of the
  * attention's splits, in an area that grows with t_cap (F32 latents, d_model 4096, rank 32, one query head per kv head: t_cap
  * of about 1800 at d_head 128 and 4600 at 64), otherwise two launches.  Every other combination: the append kernel and the attention kernel back to back.  A single-launch

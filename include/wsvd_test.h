@@ -31,8 +31,8 @@ wsvd_status wsvd_timeline_set_buffer(wsvd_ctx *ctx, void *dev_ptr, size_t bytes)
  *   "step_deferred":  which two launches: 1 = projection launch + attention launch that finishes the row where that
  *                     pair exists (default), 2 = the int8 pair or WSVD_E_UNSUPPORTED, 0 = always the append kernel + the
  *                     attention kernel
- *   "step_launches":  wsvd_decode_step ("step_deferred" 1, fp32 / bf16 / int8 latents): 0 = one launch or two by the number of
- *                     workgroups, 1 = one launch wherever it exists, 2 = two launches, 3 = one launch or WSVD_E_UNSUPPORTED
+ *   "step_launches":  wsvd_decode_step ("step_deferred" 1, fp32 / bf16 / int8 latents): 0 = one launch or two by
+ *                     size, 1 = one launch wherever it exists, 2 = two launches, 3 = one launch or WSVD_E_UNSUPPORTED
  *   "timeline_kernel": profiling build, wsvd_decode_step: 0 = the attention launch writes the stamps (default), 1 = the
  *                     projection launch does (slots: 0 entry, 1 loads issued, 2 hidden states staged, 3 products
  *                     done, 4 wave partials in LDS, 5 partial sums stored)
